@@ -312,7 +312,7 @@ fs_status fs_solve_batch(fs_context *ctx, const fs_problem *p, const float *d_ca
     st = read_flags(L, ws, stream, "fs_solve_batch");
     if (st != FS_OK) return st;
   }
-  e = fs::launch_setup(P, nullptr, 0, ws, L, stream);
+  e = fs::reg_solver_supported(P) ? hipSuccess : fs::launch_setup(P, nullptr, 0, ws, L, stream);
   if (e != hipSuccess) return hip_fail(e, "set-up launch");
   e = fs::launch_solve_batch(P, d_cap, d_tail, n_scenarios, to_out(out), ws, L, stream);
   if (e != hipSuccess) return hip_fail(e, "solve launch");

@@ -94,6 +94,8 @@ bool lane_kernel_supported(const DevProblem &P);
 int lane_kernel_options(int G);
 // Exclusion scoring supports every problem without critical floors.
 bool excl_kernel_supported(const DevProblem &P);
+// Solves by the register solver, which needs no bucket map.
+bool reg_solver_supported(const DevProblem &P);
 
 // ---- launchers (fs_kernels.hip) --------------------------------------------
 struct ScoreArgs {

@@ -140,6 +140,19 @@ __device__ __forceinline__ int wave_scan_max_nonneg(int v, int lane) {
   return max(v, before);
 }
 
+// The same by DPP alone: the row totals travel by row_bcast:15 (row 0 to 1,
+// row 2 to 3) and row_bcast:31 (rows 0-1 to 2 and 3).  Lanes without a
+// source keep their value (INT_MIN, the identity, lets each step be one
+// instruction).
+__device__ __forceinline__ int wave_scan_max_dpp(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x112, 0xF, 0xF, false));  // row_shr:2
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x114, 0xF, 0xF, false));  // row_shr:4
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x118, 0xF, 0xF, false));  // row_shr:8
+  v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+  return max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
+}
+
 // Inclusive prefix sum across the 64 lanes: the same DPP shifts within rows,
 // then the totals of the rows before.
 __device__ __forceinline__ int wave_scan_add_rows(int v, int lane) {
@@ -545,6 +558,343 @@ __global__ __launch_bounds__(64) void k_solve_dense(DevProblem P, const int8_t *
   float gp;
   const int tau = wave_solve(P, bmap, R, lds, &fm, &wa, &gp);
   write_alloc(out, j, P.K, tau, fm, gp, wa);
+}
+
+// Largest budget (one wavefront) and class count of the solvers and set-ups
+// that keep a class's table in one register per lane.
+constexpr int kPrepOrderMaxG = kWave;
+constexpr int kPrepOrderMaxK = 16;
+
+// Load level of every (class k, replica count r) for those kernels, from the
+// problem statement alone (filled on the host, passed by value): lvl[k *
+// kPrepOrderMaxG + r - 1] is the smallest level holding lambda_k / r
+// (binary32), -1 when none does.
+struct alignas(16) PrepLevels {
+  int8_t lvl[kPrepOrderMaxK * kPrepOrderMaxG];
+};
+
+// The level falls as r grows, so one pass over r per class moves it
+// downwards only.
+static PrepLevels prep_levels(const DevProblem &P) {
+  PrepLevels LV{};
+  for (int k = 0; k < P.K; ++k) {
+    int b = P.B;
+    for (int r = 1; r <= P.G; ++r) {
+      const float u = P.demand[k] / (float)r;
+      while (b > 0 && !(P.levels[b - 1] < u)) --b;
+      LV.lvl[k * kPrepOrderMaxG + r - 1] = (int8_t)(b < P.B ? b : -1);
+    }
+  }
+  return LV;
+}
+
+// ---------------------------------------------------------------------------
+// Register solver: one wavefront per realisation, for budgets of at most one
+// wavefront (G <= 64), at most 16 classes and no critical floors.
+//
+// Lane g - 1 holds budget g of every class's table.  tau* needs no
+// convolution: for nondecreasing tables the (max,min) convolution of two is
+// the first entries of their ascending merge (H[g] >= v iff the entries
+// below v, counted in both, number at most g), so tau* is the entry of rank
+// G in the union of the tables' budgets 0..G.  The K entries of budget 0 are
+// 0, the smallest there is, so it is the entry of rank G - K among budgets
+// 1..G (0 when G < K).  Each merge keeps the 64 smallest, sorted: the
+// element-wise minimum of one table and the other reversed is their lower
+// half as a bitonic sequence, which six compare-exchanges sort, each one
+// lane permutation (DPP or a row swap) and one median.
+//
+// What bounds it: instruction issue (on 4 classes and 4 TP degrees about 280
+// VALU instructions a solve, 64 of them the exact quotients) and the LDS
+// gathers of the options' cells, one per (class, TP); the options' places are
+// kept in registers over all the realisations a wavefront solves, so nothing
+// else is looked up.  The wavefront solver (wave_solve), which took a
+// dependent LDS round trip per step of every crossing search, needs 231 us
+// for 65,536 realisations of 4 classes, G = 64 (67 MB of cells: 14 us at a
+// copy's 4.85 TB/s); this one 36 us.
+// ---------------------------------------------------------------------------
+constexpr int kRegSmallCells = 2 * kWave;  // cells a wavefront keeps two per lane
+
+// LDS words of one wavefront's solver: the usable capacity of every cell (0
+// when its tail breaks the SLO) and one cell of capacity 0.
+__host__ __device__ inline int reg_cells(int N) { return (N + 1 + 3) & ~3; }
+
+// What the wavefronts of a block share in LDS: every cell's SLO, the place
+// of every option by (class, TP, cost) -- the byte offset of its cell, the
+// zero cell when there is none -- and the replicas of (TP, cost), 0 where
+// the TP does not divide the cost.
+struct RegShared {
+  float *slo;       // [N]
+  uint16_t *place;  // [K][NT][kWave]
+  uint8_t *reps;    // [NT][kWave]
+};
+// LDS of a block of nw wavefronts (N is at most 4096 cells: a place fits 16
+// bits).
+inline size_t reg_lds(const DevProblem &P, int nw) {
+  return 4 * (size_t)(nw * reg_cells(P.N) + P.N) + (size_t)kWave * P.NT * (2 * P.K + 1);
+}
+
+__device__ __forceinline__ RegShared reg_shared(const DevProblem &P, float *start) {
+  RegShared X;
+  X.slo = start;
+  X.place = reinterpret_cast<uint16_t *>(X.slo + P.N);
+  X.reps = reinterpret_cast<uint8_t *>(X.place + (size_t)kWave * P.K * P.NT);
+  return X;
+}
+
+// Fills them with the whole block (then a block barrier).
+__device__ __forceinline__ void reg_stage(const DevProblem &P, const PrepLevels &LV, const RegShared &X) {
+  const int per_class = P.NT * P.B;
+  for (int c = threadIdx.x; c < P.N; c += blockDim.x) X.slo[c] = P.slo[c / per_class];
+  for (int x = threadIdx.x; x < P.K * P.NT * kWave; x += blockDim.x) {
+    const int cost = (x & (kWave - 1)) + 1, kt = x >> 6, k = kt / P.NT, ti = kt - k * P.NT;
+    const int t = P.tp[ti], r = cost / t;
+    const bool ok = cost <= P.G && r * t == cost;
+    const int b = ok ? LV.lvl[k * kPrepOrderMaxG + r - 1] : -1;
+    X.place[x] = (uint16_t)(4 * (b >= 0 ? kt * P.B + b : P.N));
+    if (k == 0) X.reps[x] = (uint8_t)(ok ? r : 0);
+  }
+}
+
+// Lane constants of the compare-exchanges: INT_MIN where the lane keeps the
+// smaller value at that distance, INT_MAX where it keeps the larger (opaque
+// to the compiler, which would otherwise turn the median into three
+// instructions).
+struct SortSides {
+  int s[6];
+  __device__ __forceinline__ void init(int lane) {
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      s[d] = (lane >> d) & 1 ? INT_MAX : INT_MIN;
+      asm("" : "+v"(s[d]));
+    }
+  }
+};
+
+// Ascending compare-exchange at distance D = 1 << LOG: each lane takes its
+// and its partner's values, and keeps their median with its side.
+template <int LOG>
+__device__ __forceinline__ int sort_step(int v, const SortSides &T) {
+  int a = v, b;
+  if constexpr (LOG == 0) b = __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);       // quad_perm [1, 0, 3, 2]
+  else if constexpr (LOG == 1) b = __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);  // quad_perm [2, 3, 0, 1]
+  else if constexpr (LOG == 2)  // xor 3 (quads reversed), then xor 7 (half-row mirror)
+    b = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(v, 0x1B, 0xF, 0xF, true), 0x141, 0xF, 0xF, true);
+  else if constexpr (LOG == 3) b = __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // row_ror:8
+  else if constexpr (LOG == 4) {  // even rows side by side with odd rows
+    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    a = (int)r[0];
+    b = (int)r[1];
+  } else {  // lower half side by side with the upper
+    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    a = (int)r[0];
+    b = (int)r[1];
+  }
+  return max(min(a, b), min(max(a, b), T.s[LOG]));  // v_med3_i32
+}
+
+// The 64 smallest entries of two ascending sequences, ascending.
+__device__ __forceinline__ int merge_low(int x, int y, int mirror, const SortSides &T) {
+  int v = min(x, __builtin_amdgcn_ds_bpermute(mirror, y));
+  v = sort_step<5>(v, T);
+  v = sort_step<4>(v, T);
+  v = sort_step<3>(v, T);
+  v = sort_step<2>(v, T);
+  v = sort_step<1>(v, T);
+  return sort_step<0>(v, T);
+}
+
+// Allocation of a solve: lane k < K holds class k's TP index and replicas (r
+// = 0: unserved) and the rate it serves.
+struct RegAlloc {
+  int ti, r;
+  float served;
+};
+
+// KP >= K classes and NTP >= NT TP degrees, compiled in: those past K and NT
+// read the zero cell (a ratio of 0 that changes nothing), so that the code of
+// up to 4 classes has no branch; more are skipped four at a time.
+template <int KP, int NTP>
+struct RegSolver {
+  int at[KP][NTP];  // LDS byte offset of the cell of (class, TP, cost lane + 1)
+  float rf[NTP];    // replicas of that cost
+  int lane, mirror;
+  SortSides sides;
+  float my_demand;  // of class `lane`
+  double my_rcp;
+  const uint16_t *my_place;  // place row of class `lane`, TP 0
+
+  __device__ __forceinline__ void init(const DevProblem &P, const RegShared &X) {
+    lane = threadIdx.x & (kWave - 1);
+    mirror = 4 * (kWave - 1 - lane);
+    sides.init(lane);
+#pragma unroll
+    for (int ti = 0; ti < NTP; ++ti) {
+      const int t = min(ti, P.NT - 1);
+      rf[ti] = ti < P.NT ? (float)X.reps[t * kWave + lane] : 0.0f;
+#pragma unroll
+      for (int k = 0; k < KP; ++k) {
+        const int x = X.place[(min(k, P.K - 1) * P.NT + t) * kWave + lane];
+        at[k][ti] = k < P.K && ti < P.NT ? x : 4 * P.N;
+      }
+    }
+    const int k = min(lane, P.K - 1);
+    my_demand = P.demand[k];
+    my_rcp = P.rcp_demand[k];
+    my_place = X.place + (size_t)k * P.NT * kWave;
+  }
+
+  // tau* as bits, from the usable capacities in LDS; E: every class's best
+  // ratio at exactly the lane's cost (0 when no option has it).
+  __device__ __forceinline__ int solve(const DevProblem &P, const float *cells, int (&E)[KP]) const {
+    const char *base = reinterpret_cast<const char *>(cells);
+    int H = INT_MAX;
+#pragma unroll
+    for (int k0 = 0; k0 < KP; k0 += 4) {
+      constexpr int kGroup = KP < 4 ? KP : 4;
+      if (KP > 4 && k0 >= P.K) {
+#pragma unroll
+        for (int k = k0; k < k0 + kGroup; ++k) E[k] = 0;
+        continue;
+      }
+      float c[kGroup][NTP];  // the reads of a group of classes overlap
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+#pragma unroll
+        for (int ti = 0; ti < NTP; ++ti) c[k][ti] = *reinterpret_cast<const float *>(base + at[k0 + k][ti]);
+      }
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        const double rcp = P.rcp_demand[k0 + k];
+        int best = 0;
+#pragma unroll
+        for (int ti = 0; ti < NTP; ++ti)
+          best = max(best, __float_as_int((float)((double)(rf[ti] * c[k][ti]) * rcp)));
+        E[k0 + k] = min(best, __float_as_int(1.0f));
+        // best with at most lane + 1 GPUs; budgets past G are above everything
+        const int b = wave_scan_max_dpp(E[k0 + k]);
+        const int B = lane < P.G && k0 + k < P.K ? b : INT_MAX;
+        H = k0 + k == 0 ? B : merge_low(H, B, mirror, sides);
+      }
+    }
+    return P.G >= P.K ? __builtin_amdgcn_readlane(H, P.G - P.K) : 0;
+  }
+
+  // The canonical allocation at tau* (each class the fewest GPUs reaching
+  // it, then the smallest TP), lane k for class k: the cost by a ballot over
+  // the class's table, then the options of that cost.
+  __device__ __forceinline__ RegAlloc alloc(const DevProblem &P, const float *cells, const RegShared &X, int tau,
+                                            const int (&E)[KP]) const {
+    RegAlloc A{-1, 0, 0.0f};
+    if (tau <= 0) return A;
+    int at_cost = 0;  // cost - 1 (0 for the lanes past K, which take nothing)
+#pragma unroll
+    for (int k = 0; k < KP; ++k) {
+      // (a class past K has no such lane; its cost is not used)
+      const uint64_t m = __builtin_amdgcn_ballot_w64(E[k] >= tau) | (1ull << 63);
+      at_cost = lane == k ? (int)__builtin_ctzll(m) : at_cost;
+    }
+    const char *base = reinterpret_cast<const char *>(cells);
+    int place[NTP], rr[NTP];
+#pragma unroll
+    for (int ti = 0; ti < NTP; ++ti) {
+      const int t = min(ti, P.NT - 1);  // (past NT: read, not taken)
+      place[ti] = my_place[t * kWave + at_cost];
+      rr[ti] = X.reps[t * kWave + at_cost];
+    }
+    float cc[NTP];
+#pragma unroll
+    for (int ti = 0; ti < NTP; ++ti) cc[ti] = *reinterpret_cast<const float *>(base + place[ti]);
+#pragma unroll
+    for (int ti = NTP - 1; ti >= 0; --ti) {  // the smallest TP is taken last; no option has ratio 0 < tau
+      const float capacity = (float)rr[ti] * cc[ti];
+      const bool hit = __float_as_int((float)((double)capacity * my_rcp)) >= tau && ti < P.NT && lane < P.K;
+      A.ti = hit ? ti : A.ti;
+      A.r = hit ? rr[ti] : A.r;
+      A.served = hit ? capacity : A.served;
+    }
+    A.served = A.served < my_demand ? A.served : my_demand;
+    A.served = A.r > 0 ? A.served : 0.0f;
+    return A;
+  }
+
+  // The served total of an allocation: the binary32 sum in class order
+  // (unserved classes and the lanes past K add 0).
+  __device__ __forceinline__ float goodput(const RegAlloc &A) const {
+    float gp = 0.0f;
+#pragma unroll
+    for (int k = 0; k < KP; ++k) gp += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(A.served), k));
+    return gp;
+  }
+};
+
+__device__ __forceinline__ void write_reg_alloc(const AllocOut &out, int64_t j, int K, int tau, float goodput,
+                                                const RegAlloc &A, int lane) {
+  if (lane == 0) {
+    if (out.objective) out.objective[j] = __int_as_float(tau);
+    if (out.floors_met) out.floors_met[j] = 1;
+    if (out.goodput) out.goodput[j] = goodput;
+  }
+  if (lane < K) {
+    uint8_t *tp_index = out.tp_index + j * K;
+    uint16_t *replicas = out.replicas + j * K;
+    if (out.tp_index) tp_index[lane] = (uint8_t)A.ti;  // -1: 0xFF
+    if (out.replicas) replicas[lane] = (uint16_t)A.r;
+  }
+}
+
+// Dense batch: the wavefronts of a fixed grid take realisations in turn.
+// SMALL (N <= 128): the next realisation's cells, two per lane, are in
+// flight while the current one is solved.
+constexpr int kSolveThreads = 256;
+
+template <int KP, int NTP, bool SMALL>
+__global__ __launch_bounds__(kSolveThreads) void k_solve_reg(DevProblem P, const float *__restrict__ cap,
+                                                             const float *__restrict__ tail, int64_t n, AllocOut out,
+                                                             const PrepLevels LV) {
+  extern __shared__ __attribute__((aligned(16))) float reg_mem[];
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nw = blockDim.x >> 6;
+  float *cells = reg_mem + wave * reg_cells(P.N);
+  const RegShared X = reg_shared(P, reg_mem + nw * reg_cells(P.N));
+  const int64_t step = (int64_t)gridDim.x * nw;
+  int64_t j = (int64_t)blockIdx.x * nw + wave;
+  const int c0 = min(lane, P.N - 1), c1 = min(lane + kWave, P.N - 1);
+  float a0 = 0.0f, a1 = 0.0f, l0 = 0.0f, l1 = 0.0f;
+  auto request = [&](int64_t q) {
+    const float *gc = cap + q * P.N, *gt = tail + q * P.N;
+    a0 = gc[c0];
+    a1 = gc[c1];
+    l0 = gt[c0];
+    l1 = gt[c1];
+  };
+  if (SMALL && j < n) request(j);
+  reg_stage(P, LV, X);
+  if (lane == 0) cells[P.N] = 0.0f;
+  __syncthreads();
+  RegSolver<KP, NTP> S;
+  S.init(P, X);
+  const float slo0 = X.slo[c0], slo1 = X.slo[c1];
+  for (; j < n; j += step) {
+    if constexpr (SMALL) {
+      // lanes past the last cell hold copies of it
+      cells[c0] = l0 <= slo0 ? a0 : 0.0f;
+      cells[c1] = l1 <= slo1 ? a1 : 0.0f;
+      request(j + step < n ? j + step : j);
+    } else {
+      const float *gc = cap + j * P.N, *gt = tail + j * P.N;
+#pragma unroll 4
+      for (int c = lane; c < P.N; c += kWave) {
+        const float a = gc[c], l = gt[c];
+        cells[c] = l <= X.slo[c] ? a : 0.0f;
+      }
+    }
+    wave_lds_fence();
+    int E[KP];
+    const int tau = S.solve(P, cells, E);
+    const RegAlloc A = S.alloc(P, cells, X, tau, E);
+    write_reg_alloc(out, j, P.K, tau, S.goodput(A), A, lane);
+    wave_lds_fence();
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1463,17 +1813,6 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
 // ---------------------------------------------------------------------------
 // Set-up of the exclusion scorer for budgets of at most one wavefront.
 // ---------------------------------------------------------------------------
-// Largest budget and class count of the one-block-per-order set-up.
-constexpr int kPrepOrderMaxG = kWave;
-constexpr int kPrepOrderMaxK = 16;
-
-// Load level of every (class k, replica count r) for the set-up with one
-// block per order, from the problem statement alone (filled on the host,
-// passed by value): lvl[k * kPrepOrderMaxG + r - 1] is the smallest level
-// holding lambda_k / r (binary32), -1 when none does.
-struct PrepLevels {
-  int8_t lvl[kPrepOrderMaxK * kPrepOrderMaxG];
-};
 // Wavefronts per block of the per-order set-up: one per class, and one per
 // 1024 listed tiles (at most 16) so the work-list block has threads enough
 // for large lists; a class block's wavefronts beyond K only help stage the
@@ -4217,6 +4556,10 @@ int lane_kernel_options(int G) { return G + G / 2 + G / 4 + G / 8; }
 
 bool excl_kernel_supported(const DevProblem &P) { return !P.has_floor; }
 
+bool reg_solver_supported(const DevProblem &P) {
+  return !P.has_floor && P.G <= kPrepOrderMaxG && P.K <= kPrepOrderMaxK;
+}
+
 // Workspace of fs_score_candidates_noalloc, for callers that cannot
 // allocate: one copy per GPU the library runs on, held until the process
 // ends, shared by every such call on that GPU.  Host code must not pass the
@@ -4336,17 +4679,7 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
   const int dump = a.tau_dump != nullptr;
   const size_t small = prep_lds_small(P), big = small + prep_lds_tables(P);
   if (a.setup == 0 && prep_order_fits(P, a.O, a.E)) {
-    // the smallest level holding lambda / r; it falls as r grows, so one
-    // pass over r per class moves it downwards only
-    PrepLevels LV{};
-    for (int k = 0; k < P.K; ++k) {
-      int b = P.B;
-      for (int r = 1; r <= P.G; ++r) {
-        const float u = P.demand[k] / (float)r;
-        while (b > 0 && !(P.levels[b - 1] < u)) --b;
-        LV.lvl[k * kPrepOrderMaxG + r - 1] = (int8_t)(b < P.B ? b : -1);
-      }
-    }
+    const PrepLevels LV = prep_levels(P);
     // compiled for the rank step's table count rounded up to 4, 8 or 16
     // and for at most 4 or 8 TP degrees (loops over them are unrolled)
 #define FS_PREP_ORDER(KP, NTP)                                                                                    \
@@ -4538,9 +4871,41 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
   return hipGetLastError();
 }
 
+// The register solver is compiled for at most 2, 4, 8 or 16 classes and 4 or 8
+// TP degrees (its loops over them are unrolled).
+#define FS_REG_DISPATCH(LAUNCH)                \
+  if (P.NT <= 4) {                             \
+    if (P.K <= 2) { LAUNCH(2, 4) }             \
+    else if (P.K <= 4) { LAUNCH(4, 4) }        \
+    else if (P.K <= 8) { LAUNCH(8, 4) }        \
+    else { LAUNCH(16, 4) }                     \
+  } else {                                     \
+    if (P.K <= 4) { LAUNCH(4, 8) }             \
+    else if (P.K <= 8) { LAUNCH(8, 8) }        \
+    else { LAUNCH(16, 8) }                     \
+  }
+
+// Wavefronts of the dense register solver's grid: eight per SIMD.
+constexpr int kSolveWaves = 8192;
+
 hipError_t launch_solve_batch(const DevProblem &P, const float *cap, const float *tail, int64_t n,
                               AllocOut out, uint8_t *ws, const WsLayout &L, hipStream_t s) {
   if (n == 0) return hipSuccess;
+  if (reg_solver_supported(P)) {
+    // small batches: one realisation per block, spread over the GPU
+    const int threads = n < kSolveWaves / 4 ? kWave : kSolveThreads, nw = threads / kWave;
+    const int64_t blocks = (n + nw - 1) / nw;
+    const unsigned grid = (unsigned)(blocks < kSolveWaves / nw ? blocks : kSolveWaves / nw);
+    const size_t lds = reg_lds(P, nw);
+    const PrepLevels LV = prep_levels(P);
+    const bool small = P.N <= kRegSmallCells;
+#define FS_SOLVE_REG(KP, NTP)                                                                       \
+  if (small) k_solve_reg<KP, NTP, true><<<grid, threads, lds, s>>>(P, cap, tail, n, out, LV);        \
+  else k_solve_reg<KP, NTP, false><<<grid, threads, lds, s>>>(P, cap, tail, n, out, LV);
+    FS_REG_DISPATCH(FS_SOLVE_REG)
+#undef FS_SOLVE_REG
+    return hipGetLastError();
+  }
   const size_t base = lds_bytes_solver(P, 1), staged = base + stage_bytes(P);
   const int stage = stage_fits(staged) ? 1 : 0;
   if (stage)
