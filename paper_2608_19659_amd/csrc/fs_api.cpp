@@ -358,7 +358,7 @@ fs_status fs_solve_batch_lex(fs_context *ctx, const fs_problem *p, const float *
     st = read_flags(L, ws, stream, "fs_solve_batch_lex");
     if (st != FS_OK) return st;
   }
-  e = fs::launch_setup(P, nullptr, 0, ws, L, stream);
+  e = fs::reg_solver_supported(P) ? hipSuccess : fs::launch_setup(P, nullptr, 0, ws, L, stream);
   if (e != hipSuccess) return hip_fail(e, "set-up launch");
   e = fs::launch_solve_batch_lex(P, d_cap, d_tail, n_scenarios, to_out(out), d_goodput64, ws, L, stream);
   if (e != hipSuccess) return hip_fail(e, "solve launch");

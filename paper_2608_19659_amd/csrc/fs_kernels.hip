@@ -842,44 +842,52 @@ __device__ __forceinline__ void write_reg_alloc(const AllocOut &out, int64_t j, 
   }
 }
 
-// Dense batch: the wavefronts of a fixed grid take realisations in turn.
-// SMALL (N <= 128): the next realisation's cells, two per lane, are in
-// flight while the current one is solved.
+// The realisations of a dense batch, taken in turn by the wavefronts of a
+// fixed grid.  SMALL (N <= 128): the next realisation's cells, two per lane,
+// are in flight while the current one is solved.
 constexpr int kSolveThreads = 256;
 
-template <int KP, int NTP, bool SMALL>
-__global__ __launch_bounds__(kSolveThreads) void k_solve_reg(DevProblem P, const float *__restrict__ cap,
-                                                             const float *__restrict__ tail, int64_t n, AllocOut out,
-                                                             const PrepLevels LV) {
-  extern __shared__ __attribute__((aligned(16))) float reg_mem[];
-  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = blockDim.x >> 6;
-  float *cells = reg_mem + wave * reg_cells(P.N);
-  const RegShared X = reg_shared(P, reg_mem + nw * reg_cells(P.N));
-  const int64_t step = (int64_t)gridDim.x * nw;
-  int64_t j = (int64_t)blockIdx.x * nw + wave;
-  const int c0 = min(lane, P.N - 1), c1 = min(lane + kWave, P.N - 1);
-  float a0 = 0.0f, a1 = 0.0f, l0 = 0.0f, l1 = 0.0f;
-  auto request = [&](int64_t q) {
+template <bool SMALL>
+struct RegBatch {
+  const float *cap, *tail;
+  int64_t n, j, step;
+  float *cells;
+  RegShared X;
+  int lane, c0, c1;
+  float a0, a1, l0, l1, slo0, slo1;
+
+  // mem: the wavefronts' cells, then what they share
+  __device__ __forceinline__ RegBatch(const DevProblem &P, const float *cap_, const float *tail_, int64_t n_,
+                                      float *mem, int wave, int nw)
+      : cap(cap_), tail(tail_), n(n_), j((int64_t)blockIdx.x * nw + wave), step((int64_t)gridDim.x * nw),
+        cells(mem + wave * reg_cells(P.N)), X(reg_shared(P, mem + nw * reg_cells(P.N))),
+        lane(threadIdx.x & (kWave - 1)), c0(min(lane, P.N - 1)), c1(min(lane + kWave, P.N - 1)) {}
+
+  __device__ __forceinline__ void request(const DevProblem &P, int64_t q) {
     const float *gc = cap + q * P.N, *gt = tail + q * P.N;
     a0 = gc[c0];
     a1 = gc[c1];
     l0 = gt[c0];
     l1 = gt[c1];
-  };
-  if (SMALL && j < n) request(j);
-  reg_stage(P, LV, X);
-  if (lane == 0) cells[P.N] = 0.0f;
-  __syncthreads();
-  RegSolver<KP, NTP> S;
-  S.init(P, X);
-  const float slo0 = X.slo[c0], slo1 = X.slo[c1];
-  for (; j < n; j += step) {
+  }
+
+  // The first request, then what the block shares (with its barrier).
+  __device__ __forceinline__ void begin(const DevProblem &P, const PrepLevels &LV) {
+    if (SMALL && j < n) request(P, j);
+    reg_stage(P, LV, X);
+    if (lane == 0) cells[P.N] = 0.0f;
+    __syncthreads();
+    slo0 = X.slo[c0];
+    slo1 = X.slo[c1];
+  }
+
+  // Usable capacities of realisation j into LDS.
+  __device__ __forceinline__ void load(const DevProblem &P) {
     if constexpr (SMALL) {
       // lanes past the last cell hold copies of it
       cells[c0] = l0 <= slo0 ? a0 : 0.0f;
       cells[c1] = l1 <= slo1 ? a1 : 0.0f;
-      request(j + step < n ? j + step : j);
+      request(P, j + step < n ? j + step : j);
     } else {
       const float *gc = cap + j * P.N, *gt = tail + j * P.N;
 #pragma unroll 4
@@ -889,10 +897,24 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_reg(DevProblem P, const
       }
     }
     wave_lds_fence();
+  }
+};
+
+template <int KP, int NTP, bool SMALL>
+__global__ __launch_bounds__(kSolveThreads) void k_solve_reg(DevProblem P, const float *__restrict__ cap,
+                                                             const float *__restrict__ tail, int64_t n, AllocOut out,
+                                                             const PrepLevels LV) {
+  extern __shared__ __attribute__((aligned(16))) float reg_mem[];
+  RegBatch<SMALL> D(P, cap, tail, n, reg_mem, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), blockDim.x >> 6);
+  D.begin(P, LV);
+  RegSolver<KP, NTP> S;
+  S.init(P, D.X);
+  for (; D.j < n; D.j += D.step) {
+    D.load(P);
     int E[KP];
-    const int tau = S.solve(P, cells, E);
-    const RegAlloc A = S.alloc(P, cells, X, tau, E);
-    write_reg_alloc(out, j, P.K, tau, S.goodput(A), A, lane);
+    const int tau = S.solve(P, D.cells, E);
+    const RegAlloc A = S.alloc(P, D.cells, D.X, tau, E);
+    write_reg_alloc(out, D.j, P.K, tau, S.goodput(A), A, S.lane);
     wave_lds_fence();
   }
 }
@@ -3321,6 +3343,183 @@ __device__ __forceinline__ LexLds lex_lds(const DevProblem &P, void *start) {
   return X;
 }
 
+// The same stage in registers, for what the register solver takes (G <= 64,
+// K <= 16, no floors): lane g - 1 holds budget g, and the layer sits in LDS
+// between -inf entries for the budgets below 0.  Per class the options of
+// the lane's cost are merged as above, then only the costs that serve more
+// than every cheaper one are kept: any other is beaten by that cheaper
+// option at every budget (at least the goodput, fewer GPUs), and with the
+// empty option allowed one that serves nothing is.  The last class's layer is
+// the best kept cost up to each budget; the first class's is needed at the
+// full budget only, one lane per cost; the middle classes take their kept
+// costs four at a time.  Bound by instruction issue: 65,536 realisations of 4
+// classes at G = 64 take 92 us, 36 of them the max-min solve, against 458 us
+// with every allowed cost at every budget of every class (wave_lex_stage).
+// Option codes are TP index << 8 | replicas (the option order), 0 empty.
+constexpr int kRegLexCells = 2 * kWave + 1;  // budgets -64 .. 64
+
+__device__ __forceinline__ void reg_lex_init(LexCell *V, int lane) {  // V: budget 0
+  V[-1 - lane] = LexCell{-__builtin_inf(), 0, 0};
+}
+
+template <int KP, int NTP>
+__device__ __forceinline__ RegAlloc reg_lex_stage(const DevProblem &P, const RegSolver<KP, NTP> &S,
+                                                  const float *cells, const RegShared &X, LexCell *V, int tau,
+                                                  double *goodput64) {
+  const int lane = S.lane, g = lane + 1, K = P.K, G = P.G;
+  const double NEG = -__builtin_inf();
+  const bool empty_ok = tau <= 0;
+  const int none_bits = __float_as_int(-1.0f);
+  const char *base = reinterpret_cast<const char *>(cells);
+  const char *vbase = reinterpret_cast<const char *>(V);
+  int choice[KP];
+  int first = -1;  // class 0's code at the full budget (-1: none)
+  double top = NEG;
+#pragma unroll
+  for (int k = KP - 1; k >= 0; --k) {
+    choice[k] = 0;
+    if (k < K) {
+      float c[NTP];
+#pragma unroll
+      for (int ti = 0; ti < NTP; ++ti) c[ti] = *reinterpret_cast<const float *>(base + S.at[k][ti]);
+      const double rcp = P.rcp_demand[k];
+      const float dm = P.demand[k];
+      float a = -1.0f;
+      int code = 0;
+#pragma unroll
+      for (int ti = 0; ti < NTP; ++ti) {
+        const float capacity = S.rf[ti] * c[ti];
+        const float sv = capacity < dm ? capacity : dm;
+        const bool take = __float_as_int((float)((double)capacity * rcp)) >= tau && sv > a;
+        a = take ? sv : a;
+        code = take ? (ti << 8) + (int)S.rf[ti] : code;
+      }
+      const int ab = __float_as_int(a);
+      const int upto = wave_scan_max_dpp(ab);
+      const int before = __builtin_amdgcn_update_dpp(none_bits, upto, 0x138, 0xF, 0xF, false);  // wave_shr:1
+      const bool keep = ab > max(before, empty_ok ? 0 : none_bits);
+      if (k == K - 1 && k > 0) {
+        const int cost = wave_scan_max_dpp(keep ? g : 0), src = 4 * max(cost - 1, 0);
+        const float ra = __int_as_float(__builtin_amdgcn_ds_bpermute(src, ab));
+        const int rc = __builtin_amdgcn_ds_bpermute(src, code);
+        choice[k] = cost > 0 ? rc : 0;
+        V[g] = LexCell{cost > 0 ? (double)ra : empty_ok ? 0.0 : NEG, cost << 16, 0};
+        if (lane == 0) V[0] = LexCell{empty_ok ? 0.0 : NEG, 0, 0};
+      } else if (k > 0) {
+        const LexCell e0 = V[g];
+        double bgp = empty_ok ? e0.gp : NEG;
+        int bkey = empty_ok ? e0.key : INT_MAX;
+        uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+        while (m != 0) {
+          double ra[4];
+          int rk[4];
+          LexCell vv[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            // past the last kept cost: one that no budget reaches
+            const bool has = m != 0;
+            const int at = has ? (int)__builtin_ctzll(m | (1ull << 63)) : kWave;
+            m &= m - 1;
+            ra[u] = (double)__int_as_float(__builtin_amdgcn_readlane(ab, at & (kWave - 1)));
+            rk[u] = __builtin_amdgcn_readlane(code, at & (kWave - 1)) + ((at + 1) << 16);
+            vv[u] = *reinterpret_cast<const LexCell *>(vbase + 16 * (g - 1 - at));
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const double v = ra[u] + vv[u].gp;
+            const int key = rk[u] + vv[u].key;
+            const bool better = v > bgp || (v == bgp && key < bkey);
+            bgp = better ? v : bgp;
+            bkey = better ? key : bkey;
+          }
+        }
+        const bool none = bgp == NEG;
+        wave_lds_fence();
+        choice[k] = none ? 0 : bkey & 0xFFFF;
+        V[g] = LexCell{bgp, none ? 0 : bkey & ~0xFFFF, 0};
+      } else {
+        if (K == 1) {  // no other class: nothing more served, whatever is left
+          V[g] = LexCell{0.0, 0, 0};
+          if (lane == 0) V[0] = LexCell{0.0, 0, 0};
+          wave_lds_fence();
+        }
+        const LexCell vv = V[G - g];
+        const double v = keep ? (double)a + vv.gp : NEG;
+        double best = fmax(v, dpp_f64<0xB1>(v));
+        best = fmax(best, dpp_f64<0x4E>(best));
+        best = fmax(best, dpp_f64<0x141>(best));
+        best = fmax(best, dpp_f64<0x140>(best));
+        best = fmax(fmax(readlane_f64(best, 0), readlane_f64(best, 16)),
+                    fmax(readlane_f64(best, 32), readlane_f64(best, 48)));
+        const int key = wave_min_dpp(v == best && keep ? vv.key + (g << 16) + code : INT_MAX);
+        const LexCell e = V[G];
+        top = best;
+        first = best == NEG ? -1 : key & 0xFFFF;
+        if (empty_ok && (e.gp > best || (e.gp == best && e.key < key))) {
+          top = e.gp;
+          first = 0;
+        }
+      }
+      wave_lds_fence();
+    }
+  }
+  *goodput64 = top == NEG ? 0.0 : top;  // no allowed completion: 0
+  // the allocation in class order from the full budget
+  RegAlloc A{-1, 0, 0.0f};
+  int rem = G, my_cost = 1;
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    if (k < K) {
+      const int q = k == 0 ? __builtin_amdgcn_readfirstlane(first)
+                           : rem > 0 ? __builtin_amdgcn_readlane(choice[k], max(rem - 1, 0)) : 0;
+      if (q > 0) {
+        const int ti = q >> 8, r = q & 0xFF;
+        int t = P.tp[0];
+#pragma unroll
+        for (int t2 = 1; t2 < NTP; ++t2) t = ti == t2 ? P.tp[t2] : t;
+        const int cost = t * r;
+        rem -= cost;
+        A.ti = lane == k ? ti : A.ti;
+        A.r = lane == k ? r : A.r;
+        my_cost = lane == k ? cost : my_cost;
+      }
+    }
+  }
+  const int place = S.my_place[max(A.ti, 0) * kWave + my_cost - 1];
+  const float capacity = (float)A.r * *reinterpret_cast<const float *>(base + place);
+  A.served = A.r > 0 ? (capacity < S.my_demand ? capacity : S.my_demand) : 0.0f;
+  return A;
+}
+
+// Dense batch under the whole objective by the register solver and stage:
+// the wavefronts of a fixed grid take realisations in turn, the cells of the
+// next one in flight (SMALL, N <= 128).
+template <int KP, int NTP, bool SMALL>
+__global__ __launch_bounds__(kSolveThreads) void k_solve_lex_reg(DevProblem P, const float *__restrict__ cap,
+                                                                 const float *__restrict__ tail, int64_t n,
+                                                                 AllocOut out, double *__restrict__ gp64_out,
+                                                                 const PrepLevels LV) {
+  extern __shared__ __attribute__((aligned(16))) float reg_mem[];
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nw = blockDim.x >> 6;
+  LexCell *V = reinterpret_cast<LexCell *>(reg_mem) + wave * kRegLexCells + kWave;
+  RegBatch<SMALL> D(P, cap, tail, n, reg_mem + nw * 4 * kRegLexCells, wave, nw);
+  D.begin(P, LV);
+  reg_lex_init(V, lane);
+  RegSolver<KP, NTP> S;
+  S.init(P, D.X);
+  for (; D.j < n; D.j += D.step) {
+    D.load(P);
+    int E[KP];
+    const int tau = S.solve(P, D.cells, E);
+    double g64;
+    const RegAlloc A = reg_lex_stage<KP, NTP>(P, S, D.cells, D.X, V, tau, &g64);
+    write_reg_alloc(out, D.j, P.K, tau, S.goodput(A), A, lane);
+    if (gp64_out && lane == 0) gp64_out[D.j] = g64;
+    wave_lds_fence();
+  }
+}
+
 // Dense batch under the whole objective: one wavefront per scenario.
 // STAGE: inputs staged in LDS (1) or read from global memory (0), fixed at
 // compile time so that every access compiles for its own memory.
@@ -4888,15 +5087,21 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
 // Wavefronts of the dense register solver's grid: eight per SIMD.
 constexpr int kSolveWaves = 8192;
 
+// Small batches take one realisation per block, spread over the GPU.
+static int reg_solve_threads(int64_t n) { return n < kSolveWaves / 4 ? kWave : kSolveThreads; }
+static unsigned reg_solve_grid(int64_t n, int threads) {
+  const int nw = threads / kWave;
+  const int64_t blocks = (n + nw - 1) / nw;
+  return (unsigned)(blocks < kSolveWaves / nw ? blocks : kSolveWaves / nw);
+}
+
 hipError_t launch_solve_batch(const DevProblem &P, const float *cap, const float *tail, int64_t n,
                               AllocOut out, uint8_t *ws, const WsLayout &L, hipStream_t s) {
   if (n == 0) return hipSuccess;
   if (reg_solver_supported(P)) {
-    // small batches: one realisation per block, spread over the GPU
-    const int threads = n < kSolveWaves / 4 ? kWave : kSolveThreads, nw = threads / kWave;
-    const int64_t blocks = (n + nw - 1) / nw;
-    const unsigned grid = (unsigned)(blocks < kSolveWaves / nw ? blocks : kSolveWaves / nw);
-    const size_t lds = reg_lds(P, nw);
+    const int threads = reg_solve_threads(n);
+    const unsigned grid = reg_solve_grid(n, threads);
+    const size_t lds = reg_lds(P, threads / kWave);
     const PrepLevels LV = prep_levels(P);
     const bool small = P.N <= kRegSmallCells;
 #define FS_SOLVE_REG(KP, NTP)                                                                       \
@@ -4922,6 +5127,19 @@ size_t lds_bytes_lex(const DevProblem &P, int n_alloc) {
 hipError_t launch_solve_batch_lex(const DevProblem &P, const float *cap, const float *tail, int64_t n,
                                   AllocOut out, double *gp64, uint8_t *ws, const WsLayout &L, hipStream_t s) {
   if (n == 0) return hipSuccess;
+  if (reg_solver_supported(P)) {
+    const int threads = reg_solve_threads(n), nw = threads / kWave;
+    const unsigned grid = reg_solve_grid(n, threads);
+    const size_t lds = reg_lds(P, nw) + sizeof(LexCell) * (size_t)(nw * kRegLexCells);
+    const PrepLevels LV = prep_levels(P);
+    const bool small = P.N <= kRegSmallCells;
+#define FS_SOLVE_LEX_REG(KP, NTP)                                                                          \
+  if (small) k_solve_lex_reg<KP, NTP, true><<<grid, threads, lds, s>>>(P, cap, tail, n, out, gp64, LV);   \
+  else k_solve_lex_reg<KP, NTP, false><<<grid, threads, lds, s>>>(P, cap, tail, n, out, gp64, LV);
+    FS_REG_DISPATCH(FS_SOLVE_LEX_REG)
+#undef FS_SOLVE_LEX_REG
+    return hipGetLastError();
+  }
   const size_t base = lds_bytes_lex(P, 1), staged = base + stage_bytes(P);
   const int stage = stage_fits(staged) ? 1 : 0;
   if (stage)

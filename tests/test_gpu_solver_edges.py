@@ -6,21 +6,22 @@ import numpy as np
 import pytest
 
 from paper_2608_19659_amd.synth import random_point_tables, random_problem
+from test_gpu_lex import assert_lex_equal, gpu_solve_lex
 from test_gpu_parity import assert_alloc_equal, env, gpu_solve  # noqa: F401 (env is a fixture)
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("K,G,tp,levels", [
+EDGES = [
     (1, 1, [1], 1), (1, 64, [1, 2, 4, 8], 8), (2, 7, [2, 4, 8], 3), (3, 2, [1, 2], 2),  # G below K
     (4, 63, [1, 2, 4, 8], 8), (4, 64, [1, 2, 4, 8], 8), (4, 64, [3, 5, 7, 64], 9),      # N above 128: 144 cells
     (4, 65, [1, 2, 4, 8], 8), (5, 48, [1, 2, 4, 8], 7), (8, 64, [1, 2, 3, 4, 6], 5), (9, 33, [1, 2, 4, 8], 6),
     (16, 64, [1, 2, 4, 8], 8), (16, 64, [1, 2, 3, 4, 5, 6, 7, 8], 12), (16, 15, [1, 4], 4), (17, 64, [1, 2, 4, 8], 4),
-])
-def test_dense_solver_edges(env, orc, K, G, tp, levels):  # noqa: F811
-    """Both sides of every limit (budget 64, 4 / 8 / 16 classes, 4 / 8 TP
-    degrees, 128 cells), budgets below the class count, and a batch that
-    gives wavefronts a second realisation (rows repeat, so each is checked)."""
+]
+
+
+def edge_tables(K, G, tp, levels):
+    """A problem of an edge's sizes and 30 realisations of it, some extreme."""
     p = random_problem(seed=31 * K + G + len(tp), K=K, tp=tp, G=G, n_levels=levels)
     cap, tail = random_point_tables(p, 30, seed=G, cap_range=(0.0, 3.0), tail_range=(5.0, 40.0))
     cap[0], tail[1] = 0.0, 1e9          # nothing to serve with; no cell within its SLO
@@ -28,9 +29,30 @@ def test_dense_solver_edges(env, orc, K, G, tp, levels):  # noqa: F811
     cap[3] = np.float32(2.0 ** -64)
     tail[4] = np.inf
     tail[5, ::2] = np.inf
+    return p, cap, tail
+
+
+@pytest.mark.parametrize("K,G,tp,levels", EDGES)
+def test_dense_solver_edges(env, orc, K, G, tp, levels):  # noqa: F811
+    """Both sides of every limit (budget 64, 4 / 8 / 16 classes, 4 / 8 TP
+    degrees, 128 cells), budgets below the class count, and a batch that
+    gives wavefronts a second realisation (rows repeat, so each is checked)."""
+    p, cap, tail = edge_tables(K, G, tp, levels)
     print(f"[gpu] dense edges K={K} G={G} tp={tp}", file=sys.stderr, flush=True)
     want = [orc.solve(p, cap[j], tail[j]) for j in range(len(cap))]
     rows = np.arange(8192 + 61) % len(cap)
     g = gpu_solve(env, p, cap[rows], tail[rows])
     for j in list(range(len(cap))) + list(range(8180, 8192 + 61)):
         assert_alloc_equal(p, g, j, want[rows[j]], f"K={K} G={G} tp={tp} row {j}")
+
+
+@pytest.mark.parametrize("K,G,tp,levels", EDGES)
+def test_dense_lex_solver_edges(env, orc, K, G, tp, levels):  # noqa: F811
+    """The same limits under the whole objective."""
+    p, cap, tail = edge_tables(K, G, tp, levels)
+    print(f"[gpu] dense lex edges K={K} G={G} tp={tp}", file=sys.stderr, flush=True)
+    want = [orc.solve(p, cap[j], tail[j], method="lex") for j in range(len(cap))]
+    rows = np.arange(8192 + 61) % len(cap)
+    g = gpu_solve_lex(env, p, cap[rows], tail[rows])
+    for j in list(range(len(cap))) + list(range(8180, 8192 + 61)):
+        assert_lex_equal(p, g, j, want[rows[j]], f"K={K} G={G} tp={tp} row {j}")
