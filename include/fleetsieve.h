@@ -112,7 +112,9 @@ typedef struct fs_context fs_context;
 
 /* Options for fs_context_set_option. */
 typedef enum fs_option {
-  /* Scoring kernel: 0 = automatic (3 without critical floors, else 1),
+  /* Scoring kernel: 0 = automatic (3 without critical floors; with them the
+   * exclusion scorer over both variants of the objective, floors held and
+   * floors ignored, where its tables fit the LDS and the workspace, else 1),
    * 1 = one wavefront per scenario, full solves (any problem),
    * 2 = one lane per scenario, full solves (no floors, TP set {1,2,4,8},
    *     budget 16, 32 or 64),

@@ -444,9 +444,12 @@ static fs_status score_candidates_impl(fs_context *ctx, const fs_problem *p, fs_
     return fail(FS_ERR_UNSUPPORTED, "exclusion scoring needs n_orders * n_cand < 2^31");
   const int32_t S = n_cand > 0 ? n_samples : 0;
   const fs::WsLayout L = fs::ws_layout(P, n_orders, n_cand, S);
+  // the exclusion scorer with critical floors where the workspace holds its
+  // tables; a smaller one still scores by full solves
+  if (ctx->score_kernel == 0 && L.floors && workspace_bytes >= L.total) kernel = fs::kScoreFloors;
   // the scratch limit depends on the sizes alone: checked before the arrays
-  if (noalloc && L.total > workspace_bytes)
-    return fail(FS_ERR_UNSUPPORTED, "these sizes need " + std::to_string(L.total) +
+  if (noalloc && L.total_min > workspace_bytes)
+    return fail(FS_ERR_UNSUPPORTED, "these sizes need " + std::to_string(L.total_min) +
                                         " bytes of scratch; fs_score_candidates_noalloc has " +
                                         std::to_string(workspace_bytes) + " (use fs_score_candidates)");
   if (n_orders > 0 && (!iv.cap_lo || !iv.cap_hi || !iv.tail_lo || !iv.tail_hi || !iv.measured))
@@ -457,8 +460,8 @@ static fs_status score_candidates_impl(fs_context *ctx, const fs_problem *p, fs_
     if (!d_workspace) return fail(FS_ERR_INTERNAL, "the device scratch address is unknown");
   } else {
     if (!d_workspace) return fail(FS_ERR_INVALID_ARGUMENT, "workspace is NULL");
-    if (workspace_bytes < L.total)
-      return fail(FS_ERR_WORKSPACE_TOO_SMALL, "workspace needs " + std::to_string(L.total) + " bytes");
+    if (workspace_bytes < L.total_min)
+      return fail(FS_ERR_WORKSPACE_TOO_SMALL, "workspace needs " + std::to_string(L.total_min) + " bytes");
   }
   if (n_orders == 0) return FS_OK;
   DeviceGuard dg(ctx->device);
@@ -478,7 +481,7 @@ static fs_status score_candidates_impl(fs_context *ctx, const fs_problem *p, fs_
     st = read_flags(L, ws, stream, "fs_score_candidates");
     if (st != FS_OK) return st;
   }
-  if (kernel != 3) {
+  if (kernel == 1 || kernel == 2) {
     e = fs::launch_setup(P, d_cand, n_cand, ws, L, stream);
     if (e != hipSuccess) return hip_fail(e, "set-up launch");
   }
@@ -634,6 +637,7 @@ fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv,
   }
   const int32_t S = (n_cand > 0 && policy == FS_POLICY_SCORE) ? n_samples : 0;
   const fs::LoopLayout LL = fs::loop_layout(P, n_orders, n_cand, S);
+  if (ctx->score_kernel == 0 && LL.score.floors) kernel = fs::kScoreFloors;
   const bool refit = ctx->loop_refit != 0;
   const fs::RefitLayout RL = fs::refit_layout(P, n_orders, n_cand, S, LL.total);
   const size_t need = refit ? RL.total : LL.total;

@@ -77,6 +77,12 @@ struct WsLayout {
   size_t live;       // int32 [1] number of listed tiles
   size_t crec;       // [O][2] per-realisation results of the certificate under the whole objective
   size_t flag;     // int32 [4]        validation / error flags
+  // exclusion scorer with critical floors (floors != 0), per variant: B
+  // tables int32 [O][2][K][G], cheapest floor-meeting costs int32 [O][2][K],
+  // M int32 [O][2][K*P], U int2 [O][E], base tau int32 [O][2]
+  size_t f_btab, f_btab_r, f_cheap, f_mopt, f_mopt_r, f_ur, f_base_u, f_base_r;
+  int32_t floors;
+  size_t total_min;  // without those: a workspace of this size scores by full solves
   size_t total;
   int64_t n_partial;  // ceil(S / 64)
   int32_t pp;         // options per class of the lane kernel (0 if unused)
@@ -97,6 +103,10 @@ bool excl_kernel_supported(const DevProblem &P);
 // Solves by the register solver, which needs no bucket map.
 bool reg_solver_supported(const DevProblem &P);
 
+// The automatic choice for problems with critical floors, where its tables
+// fit: exclusion scoring of both variants of the objective.
+constexpr int kScoreFloors = 4;
+
 // ---- launchers (fs_kernels.hip) --------------------------------------------
 struct ScoreArgs {
   const float *cap_lo, *cap_hi, *tail_lo, *tail_hi;
@@ -109,7 +119,7 @@ struct ScoreArgs {
   float *tau_dump;
   uint8_t *ws;
   WsLayout L;
-  int kernel;  // 1 = wave per scenario, 2 = lane per scenario, 3 = exclusion
+  int kernel;  // 1 = wave per scenario, 2 = lane per scenario, 3 = exclusion, kScoreFloors
   int spl;     // exclusion scorer: samples per lane (4, 8 or 16; 0 = default)
   int waves;   // exclusion scorer: wavefronts of its grid (0 = default)
   int setup;   // exclusion scorer set-up: 0 automatic, 1 general

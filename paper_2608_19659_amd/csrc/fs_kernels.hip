@@ -1490,14 +1490,26 @@ __device__ void prep_list(const DevProblem &P, int O, const uint8_t *__restrict_
 // step 40.6 -> 37.2 us; at G = 256, 1024 threads cost 4 us).
 constexpr int kBtabThreadsSmall = 256, kBtabThreadsLarge = 1024;
 
-template <int kBtabThreads>
+//
+// kFloor (critical floors): block x = 2 R' + R with R' = 1 builds the
+// restricted table, where a critical class may only take options that meet
+// its floor (-1 at the budgets none fits), and the cost of the cheapest such
+// option (0 for a class without a floor, kNoOption when there is none).
+constexpr int kNoOption = 1 << 20;
+
+template <int kBtabThreads, bool kFloor>
 __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const float *__restrict__ cap_lo,
                                                            const float *__restrict__ cap_hi,
                                                            const float *__restrict__ tail_lo,
                                                            const float *__restrict__ tail_hi,
-                                                           int32_t *__restrict__ btab) {
+                                                           int32_t *__restrict__ btab, int32_t *__restrict__ btab_r,
+                                                           int32_t *__restrict__ cheap) {
   extern __shared__ int bt_lds[];
-  const int R = blockIdx.x, o = blockIdx.y, k = blockIdx.z;
+  const int R = blockIdx.x & 1, o = blockIdx.y, k = blockIdx.z;
+  const bool restricted = kFloor && blockIdx.x >= 2 && P.floor_rps[k] > 0.0f;
+  __shared__ int s_cheap;
+  if (kFloor && threadIdx.x == 0) s_cheap = restricted ? kNoOption : 0;
+  const int none = restricted ? -1 : 0;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int G = P.G, B = P.B, NT = P.NT, per_class = NT * B, PP = P.optoff[NT];
   int *T = bt_lds;                                         // [G]
@@ -1507,7 +1519,7 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
   const size_t off = (size_t)o * P.N + (size_t)k * per_class;
   const float *gcap = (R == 0 ? cap_lo : cap_hi) + off;
   const float *gtail = (R == 0 ? tail_hi : tail_lo) + off;
-  for (int g = tid; g < G; g += kBtabThreads) T[g] = 0;  // no option: ratio 0
+  for (int g = tid; g < G; g += kBtabThreads) T[g] = none;  // no option: ratio 0
   for (int c = tid; c < per_class; c += kBtabThreads) {
     cc[c] = gcap[c];
     ct[c] = gtail[c];
@@ -1522,7 +1534,7 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
     int ti = 0;
     while (ti + 1 < NT && q >= s_off[ti + 1]) ++ti;
     const int r = q - s_off[ti] + 1, t = s_tp[ti];
-    if (t * r >= G) continue;
+    if (t * r >= G && !restricted) continue;
     const float u = dm / (float)r;
     int lo = 0, hi = B;  // first level >= u; B = none
     while (lo < hi) {
@@ -1532,6 +1544,11 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
     }
     if (lo >= B) continue;
     const int c = ti * B + lo;
+    if (restricted) {
+      if (!floor_ok(cc[c], ct[c], r, slo, dm, P.floor_rps[k])) continue;
+      atomicMin(&s_cheap, t * r);
+      if (t * r >= G) continue;
+    }
     atomicMax(&T[t * r], ratio_bits(cc[c], ct[c], r, slo, rcp));
   }
   __syncthreads();
@@ -1541,7 +1558,7 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
   {
     __shared__ int wtot[kBtabThreads / kWave];
     const int L = (G + kBtabThreads - 1) / kBtabThreads;
-    int run = 0;
+    int run = none;
     for (int j = 0; j < L; ++j) {
       const int g = tid * L + j;
       if (g < G) {
@@ -1553,7 +1570,7 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
     if (lane == kWave - 1) wtot[tid >> 6] = incl;
     __syncthreads();
     int carry = __shfl_up(incl, 1, kWave);
-    if (lane == 0) carry = 0;
+    if (lane == 0) carry = none;
     for (int w = 0; w < (tid >> 6); ++w) carry = max(carry, wtot[w]);
     for (int j = 0; j < L; ++j) {
       const int g = tid * L + j;
@@ -1561,7 +1578,9 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
     }
   }
   __syncthreads();
-  int32_t *dst = btab + (((size_t)o * 2 + R) * P.K + k) * G;
+  const size_t row = ((size_t)o * 2 + R) * P.K + k;
+  int32_t *dst = (kFloor && blockIdx.x >= 2 ? btab_r : btab) + row * G;
+  if (kFloor && blockIdx.x >= 2 && tid == 0) cheap[row] = s_cheap;
   for (int g = tid; g < G; g += kBtabThreads) dst[g] = T[g];
 }
 
@@ -1587,7 +1606,25 @@ __device__ void prep_list_staged(const DevProblem &P, int O, const uint8_t *__re
                                  TileInfo *__restrict__ tiles, int4 *__restrict__ list,
                                  int32_t *__restrict__ n_listed, int *lds);
 
-template <bool kLds, int kThreads>
+// kFloor (critical floors; tables in LDS, no work list): block x = 2 V + R.
+// Variant V = 0 ignores the floors, as above.  Variant 1 holds them: every
+// critical class takes only options that meet its floor, and "no allowed
+// choice" is -1.  The objective is variant 1's value where that is at least
+// 0 -- the floors can then be met together -- and variant 0's otherwise;
+// with H over the other classes' restricted tables, min(f, H[G - t r]) is at
+// least 0 exactly when their cheapest floor-meeting options fit beside this
+// option, so both variants are the same maximum over the options of any one
+// class.  For a class without a floor the empty option counts when the
+// critical classes' cheapest options fit in G.  Variant 1 writes its M, U
+// (u_r) and base objective beside variant 0's.
+struct FloorOut {
+  int32_t *mopt_r;  // [O][2][n_thr]
+  int2 *u_r;        // [O][E] U of the conservative / optimistic realisation
+  int32_t *base_u, *base_r;  // [O][2]
+  const int32_t *btab_r, *cheap;  // [O][2][K][G], [O][2][K]
+};
+
+template <bool kLds, int kThreads, bool kFloor>
 __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__restrict__ cap_lo,
                                              const float *__restrict__ cap_hi,
                                              const float *__restrict__ tail_lo,
@@ -1599,11 +1636,12 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
                                              float *__restrict__ thr, int32_t n_thr,
                                              int4 *__restrict__ list, int32_t *__restrict__ n_listed,
                                              int32_t thr_mode, int32_t staged_list,
-                                             const int32_t *__restrict__ btab) {
+                                             const int32_t *__restrict__ btab, FloorOut F) {
   extern __shared__ int lds[];
   __shared__ PrepConsts C;
   __shared__ int bucket_count[32], bucket_start[32], n_live;
-  const int R = blockIdx.x, o = blockIdx.y, ci = blockIdx.z;
+  const int R = blockIdx.x & 1, o = blockIdx.y, ci = blockIdx.z;
+  const bool held = kFloor && blockIdx.x >= 2;  // variant 1
   const int tid = threadIdx.x, nth = blockDim.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & (kWave - 1);
   const int G = P.G, K = P.K, N = P.N, NT = P.NT, B = P.B, KG = K * G;
@@ -1618,7 +1656,7 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
     }
     C.optoff[NT] = at;
   }
-  if (ci == K) {  // one block builds the work list of every order
+  if (!kFloor && ci == K) {  // one block builds the work list of every order
     if (R != 0 || o != 0) return;
     if (staged_list) {
       prep_list_staged(P, (int)gridDim.y, measured, cand, E, dump, PPc, tiles, list, n_listed, lds);
@@ -1682,7 +1720,7 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
   // --- B tables of the other classes, built once per (realisation, order)
   // by k_prep_btab: copied into LDS (16-byte moves when they align), or read
   // in place when the tables live in global memory
-  const int32_t *gB = btab + ((size_t)o * 2 + R) * (size_t)KG;
+  const int32_t *gB = (held ? F.btab_r : btab) + ((size_t)o * 2 + R) * (size_t)KG;
   const int *Bsrc = gB;
   if (kLds) {
     if ((KG & 3) == 0 && (reinterpret_cast<uintptr_t>(Bt) & 15) == 0) {
@@ -1756,10 +1794,11 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
 
   // --- options of class ci: M, threshold, and w folded into the cell maximum
   {
-    int32_t *Mo = mopt + ((size_t)o * 2 + R) * n_thr + (size_t)ci * PPc;
+    int32_t *Mo = (held ? F.mopt_r : mopt) + ((size_t)o * 2 + R) * n_thr + (size_t)ci * PPc;
     float *To = thr + ((size_t)o * 2 + R) * n_thr + (size_t)ci * PPc;
     const float slo = P.slo[ci], demand = P.demand[ci];
     const double rcp = P.rcp_demand[ci];
+    const bool critical = held && P.floor_rps[ci] > 0.0f;
     // whole wavefronts per pass (the cell folds shuffle across lanes)
     for (int p0 = tid - lane; p0 < PPc; p0 += nth) {
       const int p = p0 + lane;
@@ -1772,7 +1811,7 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
         const int b = lvl[ci * G + r - 1];
         if (b < 0) {
           Mo[p] = INT_MIN;
-          To[p] = __builtin_nanf("");
+          if (!kFloor) To[p] = __builtin_nanf("");
         } else {
           const int local = ti * B + b, cell = ci * per_class + local;
           // ratios never exceed 1, so M above 1 acts as 1 (min(f, M) and the
@@ -1781,8 +1820,9 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
           const int f = ratio_bits(ccap[cell], ctail[cell], r, slo, rcp);
           key = local;
           w = min(f, M);
+          if (critical && !floor_ok(ccap[cell], ctail[cell], r, slo, demand, P.floor_rps[ci])) w = -1;
           Mo[p] = M;
-          To[p] = capacity_threshold(r, M, demand, rcp, thr_mode);
+          if (!kFloor) To[p] = capacity_threshold(r, M, demand, rcp, thr_mode);
         }
       }
       fold_cell_runs(key, w, r, mc, crlo, crhi);
@@ -1791,21 +1831,39 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
   __syncthreads();
 
   // --- tile records of class ci's candidates and U; the base objective
+  int u_min = 0;  // without any option: the empty allocation's 0
+  if (held) {
+    int need = 0;
+    for (int k = lane; k < K; k += kWave) need += k != ci ? F.cheap[((size_t)o * 2 + R) * K + k] : 0;
+    need = wave_sum_int(need);
+    u_min = P.floor_rps[ci] > 0.0f || need > G ? -1 : 0;
+  }
   for (int e = tid; e < E; e += nth) {
     const int cell = e == tid ? my_cell : cand[e];
+    if (kFloor && ci == 0 && R == 0 && !held && (cell < 0 || cell >= N)) {  // no list block writes these
+      TileInfo *tl = tiles + (size_t)o * E + e;
+      tl->state = -1; tl->cell = cell; tl->cls = 0; tl->t = 0; tl->rlo = 1; tl->rhi = 0;
+      tl->toff = 0; tl->u_m = 0; tl->u_p = 0; tl->m_m = 0; tl->m_p = 0;
+    }
     if (cell < 0 || cell >= N || cell / per_class != ci) continue;
     TileInfo *tl = tiles + (size_t)o * E + e;
     const int local = cell - ci * per_class;
-    int u0 = 0, u1 = 0, u2 = 0, u3 = 0;  // the other cells' best, 4 chains
+    // the other cells' best, 4 chains
+    int u0 = u_min, u1 = u_min, u2 = u_min, u3 = u_min;
     int c = 0;
     for (; c + 4 <= per_class; c += 4) {
-      u0 = max(u0, c + 0 != local ? mc[c + 0] : 0);
-      u1 = max(u1, c + 1 != local ? mc[c + 1] : 0);
-      u2 = max(u2, c + 2 != local ? mc[c + 2] : 0);
-      u3 = max(u3, c + 3 != local ? mc[c + 3] : 0);
+      u0 = max(u0, c + 0 != local ? mc[c + 0] : u_min);
+      u1 = max(u1, c + 1 != local ? mc[c + 1] : u_min);
+      u2 = max(u2, c + 2 != local ? mc[c + 2] : u_min);
+      u3 = max(u3, c + 3 != local ? mc[c + 3] : u_min);
     }
-    for (; c < per_class; ++c) u0 = max(u0, c != local ? mc[c] : 0);
+    for (; c < per_class; ++c) u0 = max(u0, c != local ? mc[c] : u_min);
     const int u = max(max(u0, u1), max(u2, u3));
+    if (held) {
+      if (R == 0) F.u_r[(size_t)o * E + e].x = u;
+      else F.u_r[(size_t)o * E + e].y = u;
+      continue;
+    }
     const int ti = local / B;
     const int nr = crhi[local] >= crlo[local] ? crhi[local] - crlo[local] + 1 : 0;
     // M at rlo, the same value as the option's
@@ -1825,10 +1883,10 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
     }
   }
   if (ci == 0 && wave == 0) {
-    int v = 0;  // 0: the empty allocation
+    int v = u_min;  // 0: the empty allocation
     for (int c = lane; c < per_class; c += kWave) v = max(v, mc[c]);
     v = wave_max(v);
-    if (lane == 0) base[o * 2 + R] = v;
+    if (lane == 0) (kFloor ? held ? F.base_r : F.base_u : base)[o * 2 + R] = v;
   }
 }
 
@@ -2769,6 +2827,138 @@ __global__ __launch_bounds__(64) void k_score_excl(
     if (C.ent.x < 0) break;
     stage(C, A, B);
   }
+}
+
+// Scenarios of the exclusion scorer with critical floors.  Per realisation
+// two objectives: a holding the floors (over the sampled cell's options that
+// meet them, restricted M, from U_r) and b ignoring them; tau = a where the
+// floors can be met (a >= 0), else b.  A class without a floor has a >= 0 or
+// not whatever the sample.  Block (chunk of 256 samples, candidate, order);
+// a lane owns 4 consecutive samples, the chunk's pairwise sum is one partial.
+// M falls along the range in both variants, so when its first value is at
+// most U the variant's objective is U whatever the samples; a chunk where
+// that settles both realisations reads no sample.  Replica counts are
+// scanned, M of 64 of them in a register and broadcast by readlane: about 50
+// VALU instructions per replica count and 256 samples.  5 classes at G = 48
+// over 12 orders x 140 candidates x 999 samples: 7.3 us for this kernel, 27
+// us for the call (set-up 17, finalize 4), against 6,650-7,900 us with every
+// scenario solved in full (k_score_wave).
+constexpr int kFloorSpl = 4;
+constexpr int kFloorChunk = kWave * kFloorSpl;
+
+__device__ __forceinline__ int floor_pick(int held, int ignored) { return held >= 0 ? held : ignored; }
+
+template <bool VEC>
+__global__ __launch_bounds__(64) void k_score_floor(DevProblem P, TileInfo *__restrict__ tiles,
+                                                    const int32_t *__restrict__ mopt, int32_t n_thr, FloorOut F,
+                                                    int32_t *__restrict__ base, const float *__restrict__ cap_s,
+                                                    const float *__restrict__ tail_s, int32_t E, int32_t S,
+                                                    double *__restrict__ partial, int64_t n_chunk,
+                                                    float *__restrict__ tau_dump) {
+  const int chunk = blockIdx.x, e = blockIdx.y, o = blockIdx.z, lane = threadIdx.x;
+  const size_t tile = (size_t)o * E + e;
+  const TileInfo tl = tiles[tile];
+  const int2 ur = F.u_r[tile];
+  const int base_m = floor_pick(F.base_r[o * 2 + 0], F.base_u[o * 2 + 0]);
+  const int base_p = floor_pick(F.base_r[o * 2 + 1], F.base_u[o * 2 + 1]);
+  if (chunk == 0 && e == 0 && lane < 2) base[o * 2 + lane] = lane == 0 ? base_m : base_p;
+  if (tl.state < 0) return;
+  const int s_first = chunk * kFloorChunk + lane * kFloorSpl;
+  auto dump_all = [&](int tm, int tp) {
+    for (int q = 0; q < kFloorSpl && s_first + q < S; ++q) {
+      tau_dump[(tile * S + s_first + q) * 2 + 0] = __int_as_float(tm);
+      tau_dump[(tile * S + s_first + q) * 2 + 1] = __int_as_float(tp);
+    }
+  };
+  if (tl.state != 0) {  // revealed: not solved (the finalize scores it 0)
+    if (tau_dump) dump_all(base_m, base_p);
+    return;
+  }
+  const int nr = tl.rhi >= tl.rlo ? tl.rhi - tl.rlo + 1 : 0;
+  const int um = tl.u_m, up = tl.u_p;
+  if (nr == 0) {  // no replica count reaches the cell: the finalize takes the constant gap from the record
+    const int tm = floor_pick(ur.x, um), tp = floor_pick(ur.y, up);
+    if (chunk == 0 && lane == 0) {
+      tiles[tile].u_m = tm;
+      tiles[tile].u_p = tp;
+    }
+    if (tau_dump) dump_all(tm, tp);
+    return;
+  }
+  const size_t row = (size_t)o * 2 * n_thr + tl.toff;
+  const int32_t *Um = mopt + row, *Up = Um + n_thr, *Rm = F.mopt_r + row, *Rp = Rm + n_thr;
+  // whether a sample can raise a variant above its U; the variant ignoring
+  // the floors counts only where the floors may be missed
+  const bool held = Rm[0] > ur.x || Rp[0] > ur.y;
+  const bool ignored = (ur.x < 0 && tl.m_m > um) || (ur.y < 0 && tl.m_p > up);
+  if (!held && !ignored) {
+    const int tm = floor_pick(ur.x, um), tp = floor_pick(ur.y, up);
+    if (lane == 0)
+      partial[tile * n_chunk + chunk] = pairwise_run((double)__int_as_float(tp) - (double)__int_as_float(tm),
+                                                     min(kFloorChunk, S - chunk * kFloorChunk));
+    if (tau_dump) dump_all(tm, tp);
+    return;
+  }
+  const int cls = tl.cls;
+  const double rcp = P.rcp_demand[cls];
+  const float slo = P.slo[cls], dm = P.demand[cls], fl = P.floor_rps[cls];
+  // an option meets the floor when min(lambda, r c) >= floor with the tail
+  // within the SLO (a usable capacity above 0); without a floor always
+  const float need = fl > 0.0f ? (dm >= fl ? fl : __builtin_inff()) : -1.0f;
+  float cs[kFloorSpl], ls[kFloorSpl];
+  load_chunk<kFloorSpl, VEC>(cap_s, tail_s, tile * S, s_first, S, true, cs, ls);
+  int am[kFloorSpl], ap[kFloorSpl], bm[kFloorSpl], bp[kFloorSpl];
+#pragma unroll
+  for (int q = 0; q < kFloorSpl; ++q) {
+    cs[q] = ls[q] <= slo ? cs[q] : 0.0f;
+    am[q] = ur.x;
+    ap[q] = ur.y;
+    bm[q] = um;
+    bp[q] = up;
+  }
+  for (int j0 = 0; j0 < nr; j0 += kWave) {
+    const int at = min(j0 + lane, nr - 1), nj = min(kWave, nr - j0);
+    const int vrm = Rm[at], vrp = Rp[at], vum = Um[at], vup = Up[at];
+    if (held) {
+      for (int j = 0; j < nj; ++j) {
+        const int mm = __builtin_amdgcn_readlane(vrm, j), mp = __builtin_amdgcn_readlane(vrp, j);
+        const float rf = (float)(tl.rlo + j0 + j);
+#pragma unroll
+        for (int q = 0; q < kFloorSpl; ++q) {
+          const float capacity = rf * cs[q];
+          // M is at most 1: the unclamped quotient serves
+          const int f = capacity >= need ? __float_as_int((float)((double)capacity * rcp)) : -1;
+          am[q] = max(am[q], min(f, mm));
+          ap[q] = max(ap[q], min(f, mp));
+        }
+      }
+    }
+    if (ignored) {
+      for (int j = 0; j < nj; ++j) {
+        const int mm = __builtin_amdgcn_readlane(vum, j), mp = __builtin_amdgcn_readlane(vup, j);
+        const float rf = (float)(tl.rlo + j0 + j);
+#pragma unroll
+        for (int q = 0; q < kFloorSpl; ++q) {
+          const int f = sampled_quotient(rf, cs[q], rcp);
+          bm[q] = max(bm[q], min(f, mm));
+          bp[q] = max(bp[q], min(f, mp));
+        }
+      }
+    }
+  }
+  double gq[kFloorSpl];
+#pragma unroll
+  for (int q = 0; q < kFloorSpl; ++q) {
+    const int tm = floor_pick(am[q], bm[q]), tp = floor_pick(ap[q], bp[q]);
+    const bool live = s_first + q < S;
+    gq[q] = live ? (double)__int_as_float(tp) - (double)__int_as_float(tm) : 0.0;
+    if (tau_dump && live) {
+      tau_dump[(tile * S + s_first + q) * 2 + 0] = __int_as_float(tm);
+      tau_dump[(tile * S + s_first + q) * 2 + 1] = __int_as_float(tp);
+    }
+  }
+  const double v = wave_pairwise_sum((gq[0] + gq[1]) + (gq[2] + gq[3]));
+  if (lane == 0) partial[tile * n_chunk + chunk] = v;
 }
 
 // Tile score of the exclusion scorer: Gamma_t - (sum over s of the
@@ -4822,6 +5012,11 @@ static int32_t excl_thresholds(const DevProblem &P) {
   return P.K * per_class;
 }
 
+// Exclusion scoring with critical floors: its set-up's tables in LDS.
+static bool floor_scorer_supported(const DevProblem &P) {
+  return P.has_floor && prep_lds_small(P) + prep_lds_tables(P) <= kPrepGeneralLdsLimit;
+}
+
 WsLayout ws_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S) {
   WsLayout L{};
   size_t at = 0;
@@ -4847,6 +5042,25 @@ WsLayout ws_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S) {
   L.btab = at; at = align256(at + (excl ? sizeof(int32_t) * (size_t)O * 2 * P.K * P.G : 0));
   L.live = at; at = align256(at + sizeof(int32_t));
   L.crec = at; at = align256(at + sizeof(CertRec) * 2 * (size_t)(O > 0 ? O : 1));
+  L.total_min = at;
+  // the exclusion scorer with critical floors: both variants' tables
+  L.floors = floor_scorer_supported(P) && E > 0;
+  if (L.floors) {
+    const size_t O2 = (size_t)O * 2, n_thr = (size_t)excl_thresholds(P);
+    auto take = [&](size_t bytes) {
+      const size_t here = at;
+      at = align256(at + bytes);
+      return here;
+    };
+    L.f_btab = take(sizeof(int32_t) * O2 * P.K * P.G);
+    L.f_btab_r = take(sizeof(int32_t) * O2 * P.K * P.G);
+    L.f_cheap = take(sizeof(int32_t) * O2 * P.K);
+    L.f_mopt = take(sizeof(int32_t) * O2 * n_thr);
+    L.f_mopt_r = take(sizeof(int32_t) * O2 * n_thr);
+    L.f_ur = take(sizeof(int2) * (size_t)O * (size_t)E);
+    L.f_base_u = take(sizeof(int32_t) * O2);
+    L.f_base_r = take(sizeof(int32_t) * O2);
+  }
   L.total = at;
   return L;
 }
@@ -4862,6 +5076,79 @@ hipError_t launch_setup(const DevProblem &P, const int32_t *cand, int32_t E, uin
   const int nb = setup_bucket_blocks(P), nc = setup_cand_blocks(E);
   k_setup<<<nb + nc, kLexPrepThreads, 0, s>>>(P, (int8_t *)(ws + L.bmap), nb, cand, E, (CandInfo *)(ws + L.cand), nc,
                                               nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+// The B tables of the general set-up (with floors: both variants').
+template <bool kFloor>
+static hipError_t launch_btab(const DevProblem &P, const ScoreArgs &a, int32_t *btab, const FloorOut &F,
+                              hipStream_t s) {
+  const size_t blds = sizeof(int) * (size_t)P.G + 2 * sizeof(float) * (size_t)P.NT * P.B;
+  const bool large = P.G >= kPrepWideBudget;
+  const void *fn = large ? reinterpret_cast<const void *>(&k_prep_btab<kBtabThreadsLarge, kFloor>)
+                         : reinterpret_cast<const void *>(&k_prep_btab<kBtabThreadsSmall, kFloor>);
+  if (blds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)blds);
+    if (e != hipSuccess) return e;
+  }
+  const dim3 grid(kFloor ? 4 : 2, a.O, P.K);
+  int32_t *btab_r = const_cast<int32_t *>(F.btab_r), *cheap = const_cast<int32_t *>(F.cheap);
+  if (large) {
+    k_prep_btab<kBtabThreadsLarge, kFloor><<<grid, kBtabThreadsLarge, blds, s>>>(
+        P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, btab, btab_r, cheap);
+  } else {
+    k_prep_btab<kBtabThreadsSmall, kFloor><<<grid, kBtabThreadsSmall, blds, s>>>(
+        P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, btab, btab_r, cheap);
+  }
+  return hipGetLastError();
+}
+
+// Set-up and scenarios of the exclusion scorer with critical floors.
+static hipError_t launch_floor_score(const DevProblem &P, const ScoreArgs &a, int64_t n_partial, hipStream_t s) {
+  const WsLayout &L = a.L;
+  TileInfo *tiles = (TileInfo *)(a.ws + L.tiles);
+  int32_t *base = (int32_t *)(a.ws + L.base);
+  int32_t *btab = (int32_t *)(a.ws + L.f_btab), *mopt = (int32_t *)(a.ws + L.f_mopt);
+  const FloorOut F{(int32_t *)(a.ws + L.f_mopt_r), (int2 *)(a.ws + L.f_ur),          (int32_t *)(a.ws + L.f_base_u),
+                   (int32_t *)(a.ws + L.f_base_r), (const int32_t *)(a.ws + L.f_btab_r),
+                   (const int32_t *)(a.ws + L.f_cheap)};
+  const int32_t n_thr = excl_thresholds(P);
+  hipError_t e = launch_btab<true>(P, a, btab, F, s);
+  if (e != hipSuccess) return e;
+  const size_t lds = prep_lds_small(P) + prep_lds_tables(P);
+  const dim3 grid(4, a.O, P.K);
+#define FS_PREP_FLOOR(TH)                                                                                         \
+  {                                                                                                               \
+    if (lds > 64 * 1024) {                                                                                        \
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_prep<true, TH, true>),                            \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                              \
+      if (e != hipSuccess) return e;                                                                              \
+    }                                                                                                             \
+    k_prep<true, TH, true><<<grid, TH, lds, s>>>(P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, a.measured, a.cand, \
+                                                 a.E, 0, nullptr, tiles, base, mopt, nullptr, n_thr, nullptr,     \
+                                                 nullptr, a.thr_search, 0, btab, F);                              \
+  }
+  // the block sizes of the set-up without floors, whose blocks are alike
+  if (P.G >= kPrepWideBudget) FS_PREP_FLOOR(kPrepThreadsWide)
+  else if ((int64_t)4 * a.O * P.K >= 256) FS_PREP_FLOOR(kPrepThreadsNarrow)
+  else FS_PREP_FLOOR(kPrepThreads)
+#undef FS_PREP_FLOOR
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const dim3 sgrid((unsigned)n_partial, a.E, a.O);
+  double *partial = (double *)(a.ws + L.partial);
+  const bool vec = a.S % 4 == 0 && ((uintptr_t)a.cap_s & 15) == 0 && ((uintptr_t)a.tail_s & 15) == 0;
+  const int launches = a.ev_begin ? a.timing_launches : 1;
+  if (a.ev_begin) (void)hipEventRecord(a.ev_begin, s);
+  for (int rep = 0; rep < launches; ++rep) {
+    if (vec)
+      k_score_floor<true><<<sgrid, kWave, 0, s>>>(P, tiles, mopt, n_thr, F, base, a.cap_s, a.tail_s, a.E, a.S, partial,
+                                                  n_partial, a.tau_dump);
+    else
+      k_score_floor<false><<<sgrid, kWave, 0, s>>>(P, tiles, mopt, n_thr, F, base, a.cap_s, a.tail_s, a.E, a.S,
+                                                   partial, n_partial, a.tau_dump);
+  }
+  if (a.ev_end) (void)hipEventRecord(a.ev_end, s);
   return hipGetLastError();
 }
 
@@ -4907,35 +5194,21 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
     int32_t *gtab = in_lds ? nullptr : (int32_t *)(a.ws + a.L.tabB);
     int32_t *btab = (int32_t *)(a.ws + a.L.btab);
     {
-      const size_t blds = sizeof(int) * (size_t)P.G + 2 * sizeof(float) * (size_t)P.NT * P.B;
-      const bool large = P.G >= kPrepWideBudget;
-      const void *fn = large ? reinterpret_cast<const void *>(&k_prep_btab<kBtabThreadsLarge>)
-                             : reinterpret_cast<const void *>(&k_prep_btab<kBtabThreadsSmall>);
-      if (blds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)blds);
-        if (e != hipSuccess) return e;
-      }
-      if (large) {
-        k_prep_btab<kBtabThreadsLarge><<<dim3(2, a.O, P.K), kBtabThreadsLarge, blds, s>>>(
-            P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, btab);
-      } else {
-        k_prep_btab<kBtabThreadsSmall><<<dim3(2, a.O, P.K), kBtabThreadsSmall, blds, s>>>(
-            P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, btab);
-      }
-      const hipError_t e = hipGetLastError();
+      const hipError_t e = launch_btab<false>(P, a, btab, FloorOut{}, s);
       if (e != hipSuccess) return e;
     }
     const dim3 grid(2, a.O, P.K + 1);
+    const FloorOut F{};
 #define FS_PREP_GENERAL(LDS, TH)                                                                                  \
   {                                                                                                               \
     if (lds > 64 * 1024) {                                                                                        \
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_prep<LDS, TH>),                  \
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_prep<LDS, TH, false>),           \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);             \
       if (e != hipSuccess) return e;                                                                              \
     }                                                                                                             \
-    k_prep<LDS, TH><<<grid, TH, lds, s>>>(P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, a.measured, a.cand, a.E,   \
-                                          dump, gtab, tiles, base, mopt, thr, n_thr, list, live, a.thr_search,    \
-                                          staged, btab);                                                          \
+    k_prep<LDS, TH, false><<<grid, TH, lds, s>>>(P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, a.measured, a.cand, \
+                                                 a.E, dump, gtab, tiles, base, mopt, thr, n_thr, list, live,      \
+                                                 a.thr_search, staged, btab, F);                                  \
   }
     // below a budget of 512: 256 threads per block once the class blocks
     // fill the GPU (more blocks resident at a time; 8 classes at G = 256
@@ -4952,6 +5225,24 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
       else FS_PREP_GENERAL(false, kPrepThreads)
     }
 #undef FS_PREP_GENERAL
+  }
+  return hipGetLastError();
+}
+
+// Scores and arg-max of the exclusion scorers from n_partial partials a tile.
+static hipError_t launch_finalize_excl(const ScoreArgs &a, int64_t n_partial, hipStream_t s) {
+  const TileInfo *tiles = (const TileInfo *)(a.ws + a.L.tiles);
+  const int32_t *base = (const int32_t *)(a.ws + a.L.base);
+  const double *partial = (const double *)(a.ws + a.L.partial);
+  if (n_partial <= 16) {
+    const int fw = (int)((a.E + 2 * kWave - 1) / (2 * kWave));
+    const int nwf = fw < 1 ? 1 : (fw > kFinalizeMaxWaves ? kFinalizeMaxWaves : fw);
+    k_finalize_excl<<<a.O, kWave * nwf, 0, s>>>(tiles, a.E, a.S, base, partial, n_partial, a.score,
+                                                a.gap_now, a.best);
+  } else {
+    k_tile_scores_wave<<<dim3((a.E + 3) / 4, a.O), 256, 0, s>>>(tiles, a.E, a.S, base, partial, n_partial,
+                                                               a.score);
+    k_pick_best<<<a.O, 256, 0, s>>>(tiles, a.E, base, a.score, a.gap_now, a.best);
   }
   return hipGetLastError();
 }
@@ -5016,17 +5307,12 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
 #undef FS_EXCL_LAUNCH
     }
     if (a.ev_end) (void)hipEventRecord(a.ev_end, s);
-    if (n_partial <= 16) {
-      const int fw = (int)((a.E + 2 * kWave - 1) / (2 * kWave));
-      const int nwf = fw < 1 ? 1 : (fw > kFinalizeMaxWaves ? kFinalizeMaxWaves : fw);
-      k_finalize_excl<<<a.O, kWave * nwf, 0, s>>>(tiles, a.E, a.S, base, partial, n_partial, a.score,
-                                                  a.gap_now, a.best);
-    } else {
-      k_tile_scores_wave<<<dim3((a.E + 3) / 4, a.O), 256, 0, s>>>(tiles, a.E, a.S, base, partial, n_partial,
-                                                                 a.score);
-      k_pick_best<<<a.O, 256, 0, s>>>(tiles, a.E, base, a.score, a.gap_now, a.best);
-    }
-    return hipGetLastError();
+    return launch_finalize_excl(a, n_partial, s);
+  }
+  if (a.kernel == kScoreFloors && a.E > 0) {
+    const int64_t n_partial = (a.S + kFloorChunk - 1) / kFloorChunk;
+    const hipError_t e = launch_floor_score(P, a, n_partial, s);
+    return e != hipSuccess ? e : launch_finalize_excl(a, n_partial, s);
   }
   k_base<<<dim3(2, a.O), 64, lds, s>>>(P, bmap, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, base);
   int64_t n_partial = a.L.n_partial;
