@@ -817,6 +817,14 @@ struct RegSolver {
     return A;
   }
 
+  // The cell class `lane` commits to (r > 0).
+  __device__ __forceinline__ int cell_of_alloc(const DevProblem &P, const RegAlloc &A) const {
+    int t = P.tp[0];
+#pragma unroll
+    for (int ti = 1; ti < NTP; ++ti) t = A.ti == ti ? P.tp[ti] : t;
+    return my_place[max(A.ti, 0) * kWave + max(t * A.r - 1, 0)] >> 2;
+  }
+
   // The served total of an allocation: the binary32 sum in class order
   // (unserved classes and the lanes past K add 0).
   __device__ __forceinline__ float goodput(const RegAlloc &A) const {
@@ -3019,12 +3027,13 @@ __device__ __forceinline__ uint64_t wave_ext_u64(uint64_t v) {
 // defines -- then the same over the wavefronts' results.
 constexpr int kFinalizeMaxWaves = 16;
 
-__global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_finalize_excl(
-    const TileInfo *__restrict__ tiles, int32_t E, int32_t S, const int32_t *__restrict__ base,
-    const double *__restrict__ partial, int64_t n_partial, double *__restrict__ score,
-    double *__restrict__ gap_now, int32_t *__restrict__ best) {
-  __shared__ uint64_t s_key[kFinalizeMaxWaves], s_tie[kFinalizeMaxWaves];
-  const int o = blockIdx.x, lane = threadIdx.x & (kWave - 1);
+// Returns the best candidate (thread 0; -1: none).  score and gap_now may be
+// null.  Block-synchronises once.
+__device__ __forceinline__ int finalize_order(int o, const TileInfo *__restrict__ tiles, int32_t E, int32_t S,
+                                              const int32_t *__restrict__ base, const double *__restrict__ partial,
+                                              int64_t n_partial, double *__restrict__ score,
+                                              double *__restrict__ gap_now, uint64_t *s_key, uint64_t *s_tie) {
+  const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const double gap = (double)__int_as_float(base[o * 2 + 1]) - (double)__int_as_float(base[o * 2 + 0]);
   int p2 = 1;
@@ -3072,7 +3081,7 @@ __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_finalize_excl(
           tbest = t;
         }
       }
-      score[(size_t)o * E + e] = sc;
+      if (score) score[(size_t)o * E + e] = sc;
     }
   }
   const uint64_t kmax = wave_ext_u64<true>(kbest);
@@ -3082,6 +3091,7 @@ __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_finalize_excl(
     s_tie[wave] = tmin;
   }
   __syncthreads();
+  int best = -1;
   if (threadIdx.x == 0) {
     uint64_t K = 0, T = ~0ull;
     for (int w = 0; w < nw; ++w) {
@@ -3090,9 +3100,19 @@ __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_finalize_excl(
         T = s_tie[w];
       }
     }
-    if (best) best[o] = K != 0 ? (int32_t)(uint32_t)T : -1;
+    best = K != 0 ? (int32_t)(uint32_t)T : -1;
     if (gap_now) gap_now[o] = gap;
   }
+  return best;
+}
+
+__global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_finalize_excl(
+    const TileInfo *__restrict__ tiles, int32_t E, int32_t S, const int32_t *__restrict__ base,
+    const double *__restrict__ partial, int64_t n_partial, double *__restrict__ score,
+    double *__restrict__ gap_now, int32_t *__restrict__ best) {
+  __shared__ uint64_t s_key[kFinalizeMaxWaves], s_tie[kFinalizeMaxWaves];
+  const int b = finalize_order(blockIdx.x, tiles, E, S, base, partial, n_partial, score, gap_now, s_key, s_tie);
+  if (threadIdx.x == 0 && best) best[blockIdx.x] = b;
 }
 
 // Scores and best candidate, many partials per tile: one wavefront per
@@ -3301,6 +3321,72 @@ __global__ __launch_bounds__(64) void k_certify_state(DevProblem P, const int8_t
   }
   state[o] = certificate_state(P, bmap, measured, tail_hi, off, m->floors_met, p->floors_met, m->tp_index,
                                m->replicas, ok);
+}
+
+// The certificate by the register solver, one block per order: wavefront 0
+// solves the conservative realisation, wavefront 1 the optimistic one, and
+// the state follows in the same block (three launches otherwise: the bucket
+// map, the two solves, the state).
+constexpr int kCertThreads = 2 * kWave;
+
+struct CertShared {
+  int tau[2];
+  int committed;  // every cell the conservative allocation commits to is measured, its tail within the SLO
+};
+
+// Whether the conservative allocation commits to measured cells only, with
+// their upper tails within the SLO (every lane of the wavefront returns it).
+template <int KP, int NTP>
+__device__ __forceinline__ bool reg_committed(const DevProblem &P, const RegSolver<KP, NTP> &S, const RegAlloc &A,
+                                              const float *slo, const uint8_t *measured, const float *tail_hi) {
+  const int cell = min(S.cell_of_alloc(P, A), P.N - 1);
+  const bool bad = A.r > 0 && !(measured[cell] && tail_hi[cell] <= slo[cell]);
+  return __builtin_amdgcn_ballot_w64(bad) == 0;
+}
+
+template <int KP, int NTP>
+__global__ __launch_bounds__(kCertThreads) void k_certify_reg(DevProblem P, const float *__restrict__ cap_lo,
+                                                              const float *__restrict__ cap_hi,
+                                                              const float *__restrict__ tail_lo,
+                                                              const float *__restrict__ tail_hi,
+                                                              const uint8_t *__restrict__ measured, float eps,
+                                                              int32_t *__restrict__ state, AllocOut cons, AllocOut opt,
+                                                              double *__restrict__ gap, const PrepLevels LV) {
+  extern __shared__ __attribute__((aligned(16))) float reg_mem[];
+  __shared__ CertShared C;
+  const int o = blockIdx.x, lane = threadIdx.x & (kWave - 1);
+  const int R = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t off = (size_t)o * P.N;
+  float *cells = reg_mem + R * reg_cells(P.N);
+  const RegShared X = reg_shared(P, reg_mem + 2 * reg_cells(P.N));
+  // the wavefront's first cells are read while the block stages
+  const float *gc = (R == 0 ? cap_lo : cap_hi) + off, *gt = (R == 0 ? tail_hi : tail_lo) + off;
+  const int c0 = min(lane, P.N - 1), c1 = min(lane + kWave, P.N - 1);
+  const float a0 = gc[c0], a1 = gc[c1], l0 = gt[c0], l1 = gt[c1];
+  reg_stage(P, LV, X);
+  if (lane == 0) cells[P.N] = 0.0f;
+  __syncthreads();
+  cells[c0] = l0 <= X.slo[c0] ? a0 : 0.0f;
+  cells[c1] = l1 <= X.slo[c1] ? a1 : 0.0f;
+  for (int c = lane + 2 * kWave; c < P.N; c += kWave) cells[c] = gt[c] <= X.slo[c] ? gc[c] : 0.0f;
+  RegSolver<KP, NTP> S;
+  S.init(P, X);
+  wave_lds_fence();
+  int E[KP];
+  const int tau = S.solve(P, cells, E);
+  const RegAlloc A = S.alloc(P, cells, X, tau, E);
+  write_reg_alloc(R == 0 ? cons : opt, o, P.K, tau, S.goodput(A), A, lane);
+  if (lane == 0) C.tau[R] = tau;
+  if (R == 0) {
+    const bool ok = reg_committed<KP, NTP>(P, S, A, X.slo, measured + off, tail_hi + off);
+    if (lane == 0) C.committed = ok;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double g = (double)__int_as_float(C.tau[1]) - (double)__int_as_float(C.tau[0]);
+    if (gap) gap[o] = g;
+    state[o] = C.committed && g <= (double)eps ? 1 : 0;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -4945,8 +5031,12 @@ int lane_kernel_options(int G) { return G + G / 2 + G / 4 + G / 8; }
 
 bool excl_kernel_supported(const DevProblem &P) { return !P.has_floor; }
 
+// Also, the LDS of a dense block of four wavefronts (with the
+// whole-objective layers) within what a launch may ask for by default: about
+// 2,500 cells at 16 classes.
 bool reg_solver_supported(const DevProblem &P) {
-  return !P.has_floor && P.G <= kPrepOrderMaxG && P.K <= kPrepOrderMaxK;
+  return !P.has_floor && P.G <= kPrepOrderMaxG && P.K <= kPrepOrderMaxK &&
+         reg_lds(P, kSolveThreads / kWave) + sizeof(LexCell) * (kSolveThreads / kWave) * kRegLexCells <= 64 * 1024;
 }
 
 // Workspace of fs_score_candidates_noalloc, for callers that cannot
@@ -5459,6 +5549,16 @@ hipError_t launch_certify(const DevProblem &P, const float *cap_lo, const float 
                           int32_t O, float eps, int32_t *state, AllocOut cons, AllocOut opt,
                           double *gap, uint8_t *ws, const WsLayout &L, hipStream_t s) {
   if (O == 0) return hipSuccess;
+  if (reg_solver_supported(P)) {
+    const PrepLevels LV = prep_levels(P);
+    const size_t lds = reg_lds(P, 2);
+#define FS_CERTIFY_REG(KP, NTP)                                                                                  \
+  k_certify_reg<KP, NTP><<<O, kCertThreads, lds, s>>>(P, cap_lo, cap_hi, tail_lo, tail_hi, measured, eps, state, \
+                                                      cons, opt, gap, LV);
+    FS_REG_DISPATCH(FS_CERTIFY_REG)
+#undef FS_CERTIFY_REG
+    return hipGetLastError();
+  }
   const size_t base = lds_bytes_solver(P, 1), staged = base + stage_bytes(P);
   const int stage = stage_fits(staged) ? 1 : 0;
   CertRec *rec = (CertRec *)(ws + L.crec);

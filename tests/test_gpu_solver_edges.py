@@ -5,7 +5,7 @@ import sys
 import numpy as np
 import pytest
 
-from paper_2608_19659_amd.synth import random_point_tables, random_problem
+from paper_2608_19659_amd.synth import Intervals, random_point_tables, random_problem
 from test_gpu_lex import assert_lex_equal, gpu_solve_lex
 from test_gpu_parity import assert_alloc_equal, env, gpu_solve  # noqa: F401 (env is a fixture)
 
@@ -16,7 +16,9 @@ EDGES = [
     (1, 1, [1], 1), (1, 64, [1, 2, 4, 8], 8), (2, 7, [2, 4, 8], 3), (3, 2, [1, 2], 2),  # G below K
     (4, 63, [1, 2, 4, 8], 8), (4, 64, [1, 2, 4, 8], 8), (4, 64, [3, 5, 7, 64], 9),      # N above 128: 144 cells
     (4, 65, [1, 2, 4, 8], 8), (5, 48, [1, 2, 4, 8], 7), (8, 64, [1, 2, 3, 4, 6], 5), (9, 33, [1, 2, 4, 8], 6),
-    (16, 64, [1, 2, 4, 8], 8), (16, 64, [1, 2, 3, 4, 5, 6, 7, 8], 12), (16, 15, [1, 4], 4), (17, 64, [1, 2, 4, 8], 4),
+    (16, 64, [1, 2, 4, 8], 8), (16, 64, [1, 2, 3, 4, 5, 6, 7, 8], 12), (16, 15, [1, 4], 4),
+    (16, 20, [1, 2, 3, 4, 5, 6, 7, 8], 32),             # 4096 cells: more than its LDS holds
+    (17, 64, [1, 2, 4, 8], 4),
 ]
 
 
@@ -56,3 +58,27 @@ def test_dense_lex_solver_edges(env, orc, K, G, tp, levels):  # noqa: F811
     g = gpu_solve_lex(env, p, cap[rows], tail[rows])
     for j in list(range(len(cap))) + list(range(8180, 8192 + 61)):
         assert_lex_equal(p, g, j, want[rows[j]], f"K={K} G={G} tp={tp} row {j}")
+
+
+@pytest.mark.parametrize("K,G,tp,levels", [c for c in EDGES if c[0] > 1])
+def test_certificate_edges(env, orc, K, G, tp, levels):  # noqa: F811
+    """The same limits for the certificate: states (a measured and a missing
+    committed cell among them), gaps and both allocations."""
+    torch, fs, ctx = env
+    p, cap, tail = edge_tables(K, G, tp, levels)
+    rng = np.random.default_rng(K + G)
+    hi = np.minimum(cap * rng.choice([1.0, 1.25], cap.shape), 2.0 ** 64).astype(np.float32)
+    tlo = np.where(np.isfinite(tail), tail * rng.choice([1.0, 0.5], tail.shape), tail).astype(np.float32)
+    meas = np.ones(cap.shape, np.uint8)
+    meas[::2] = rng.random(cap[::2].shape) < 0.7
+    iv = Intervals(cap, hi, tlo, tail, meas)
+    print(f"[gpu] certificate edges K={K} G={G} tp={tp}", file=sys.stderr, flush=True)
+    r = fs.certify(ctx, p, fs.DeviceIntervals.from_host(iv, "cuda:0"), eps=0.2)
+    torch.cuda.synchronize()
+    o = orc.certify(p, iv, eps=0.2)
+    np.testing.assert_array_equal(r.state.cpu().numpy(), o.state)
+    np.testing.assert_array_equal(r.gap.cpu().numpy(), o.gap)
+    cons, opt = ({k: v.cpu().numpy() for k, v in d.items()} for d in (r.cons, r.opt))
+    for j in range(len(cap)):
+        assert_alloc_equal(p, cons, j, o.cons[j], f"cons {j}")
+        assert_alloc_equal(p, opt, j, o.opt[j], f"opt {j}")
