@@ -487,7 +487,7 @@ static fs_status score_candidates_impl(fs_context *ctx, const fs_problem *p, fs_
   }
   fs::ScoreArgs a{iv.cap_lo, iv.cap_hi, iv.tail_lo, iv.tail_hi, iv.measured, d_cand, d_cap_s, d_tail_s,
                   n_orders, n_cand, S, d_score, d_gap_now, d_best, d_tau_dump, ws, L, kernel,
-                  ctx->spl, ctx->waves, ctx->setup, nullptr, nullptr, 1, ctx->thr_search};
+                  ctx->spl, ctx->waves, ctx->setup, nullptr, nullptr, 1, ctx->thr_search, nullptr, false};
   if (!noalloc && ctx->timing && n_cand > 0) {
     e = hipEventCreate(&a.ev_begin);
     if (e == hipSuccess) e = hipEventCreate(&a.ev_end);
@@ -671,6 +671,45 @@ fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv,
   D.gpu_seconds = out.gpu_seconds;
   D.reveals = out.reveals;
   D.max_rounds = max_rounds;
+  // Rounds of three launches where the register solver applies (the scorer
+  // by exclusion; the samples clamped as they are scored).
+  const bool score = policy == FS_POLICY_SCORE && n_cand > 0;
+  if (!lex && (kernel == 3 || !score) && ctx->score_kernel != 1 && fs::loop_fast_supported(P)) {
+    fs::RefitArgs R{};
+    if (refit)
+      R = fs::RefitArgs{(float *)(ws + RL.cap_lo), (float *)(ws + RL.tail_lo), (float *)(ws + RL.tail_hi),
+                        (float4 *)(ws + RL.bounds)};
+    fs::ScoreArgs iv_args{};
+    iv_args.cap_lo = iv.cap_lo; iv_args.cap_hi = iv.cap_hi; iv_args.tail_lo = iv.tail_lo;
+    iv_args.tail_hi = iv.tail_hi; iv_args.measured = iv.measured;
+    fs::ScoreArgs a{refit ? R.cap_lo : D.cap_lo, D.cap_hi, refit ? R.tail_lo : D.tail_lo,
+                    refit ? R.tail_hi : D.tail_hi, D.measured, d_cand, d_cap_s, d_tail_s,
+                    n_orders, n_cand, S, D.score, D.gap_now, D.best, nullptr, ws, LL.score, 3,
+                    ctx->spl, ctx->waves, ctx->setup, nullptr, nullptr, 1, ctx->thr_search, R.bounds, false};
+    a.no_finalize = score && fs::excl_partials(a) <= 16;
+    for (int32_t rnd = 0; rnd <= max_rounds; ++rnd) {
+      e = fs::launch_loop_round(P, D, rnd == 0 ? &iv_args : nullptr, R, a, d_truth_cap, d_truth_tail, d_order, eps,
+                                (int32_t)policy, score, stream);
+      if (e != hipSuccess) return hip_fail(e, "loop round launch");
+      if (rnd == max_rounds) break;
+      if (check_every > 0 && rnd > 0 && rnd % check_every == 0) {
+        e = fs::launch_loop_count(D, n_orders, stream);
+        if (e == hipSuccess)
+          e = hipMemcpyAsync(ctx->pinned, D.n_running, sizeof(int32_t), hipMemcpyDeviceToHost, stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) return hip_fail(e, "loop progress read-back");
+        if (*ctx->pinned == 0) break;
+      }
+      if (score) {
+        e = fs::launch_score(P, a, stream);
+        if (e != hipSuccess) return hip_fail(e, "loop score launch");
+      }
+    }
+    e = fs::launch_loop_end(P, D, d_truth_cap, d_truth_tail, n_orders, to_out(out.final_alloc), out.tau_truth,
+                            out.tau_oracle, stream);
+    if (e != hipSuccess) return hip_fail(e, "loop output launch");
+    return FS_OK;
+  }
   const size_t cells = (size_t)n_orders * P.N;
   e = hipMemcpyAsync(D.cap_lo, iv.cap_lo, 4 * cells, hipMemcpyDeviceToDevice, stream);
   if (e == hipSuccess) e = hipMemcpyAsync(D.cap_hi, iv.cap_hi, 4 * cells, hipMemcpyDeviceToDevice, stream);
@@ -733,7 +772,7 @@ fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv,
       } else {
         fs::ScoreArgs a{R_cap_lo, D.cap_hi, R_tail_lo, R_tail_hi, D.measured, d_cand, cs, ts,
                         n_orders, n_cand, S, D.score, D.gap_now, D.best, nullptr, ws, LL.score, kernel,
-                        ctx->spl, ctx->waves, ctx->setup, nullptr, nullptr, 1, ctx->thr_search};
+                        ctx->spl, ctx->waves, ctx->setup, nullptr, nullptr, 1, ctx->thr_search, nullptr, false};
         e = fs::launch_score(P, a, stream);
       }
       if (e != hipSuccess) return hip_fail(e, "loop score launch");

@@ -127,7 +127,11 @@ struct ScoreArgs {
   int timing_launches;          // back-to-back launches of the scoring kernel between the events
   int thr_search;               // exclusion set-up: where the capacity-threshold search starts
                                 // (0 window, 1 stepping, 2 bisection; identical results)
+  const float4 *bounds;         // exclusion scorer: [O][E] intervals the samples are clamped into, or null
+  bool no_finalize;             // exclusion scorer: leave the partials to the caller (at most 16 per tile)
 };
+// Partials per tile of the exclusion scorer.
+int64_t excl_partials(const ScoreArgs &a);
 
 struct AllocOut {
   float *objective;
@@ -236,12 +240,29 @@ hipError_t launch_clamp_samples(const DevProblem &P, const int32_t *cand, int32_
                                 const float *tail_s, int32_t O, int32_t S, float *cs_out, float *ts_out,
                                 hipStream_t s);
 // Extra workspace of a loop with the fit step, after LoopLayout::total:
-// refitted cap_lo, tail_lo, tail_hi [O][N] and clamped samples [O][E][S] x 2.
+// refitted cap_lo, tail_lo, tail_hi [O][N], clamped samples [O][E][S] x 2 and
+// the candidates' refitted intervals float4 [O][E].
 struct RefitLayout {
-  size_t cap_lo, tail_lo, tail_hi, cap_s, tail_s, total;
+  size_t cap_lo, tail_lo, tail_hi, cap_s, tail_s, bounds, total;
 };
 RefitLayout refit_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S, size_t start);
 LoopDev loop_dev(const LoopLayout &L, uint8_t *ws, int64_t O);
+
+// The loop with everything of a round but the scorer's set-up and the scorer
+// in one launch, and its end in another (max-min objective, no floors, the
+// register solver's sizes).  iv: the caller's intervals in the first round,
+// else null.  a: the scoring arguments of the rounds; scored: the last round
+// scored (with a.no_finalize its partials are this launch's to reduce).
+struct RefitArgs {
+  float *cap_lo, *tail_lo, *tail_hi;  // refitted intervals, or null: no refit
+  float4 *bounds;
+};
+bool loop_fast_supported(const DevProblem &P);
+hipError_t launch_loop_round(const DevProblem &P, const LoopDev &L, const ScoreArgs *iv, const RefitArgs &R,
+                             const ScoreArgs &a, const float *truth_cap, const float *truth_tail,
+                             const int32_t *order, float eps, int32_t policy, bool scored, hipStream_t s);
+hipError_t launch_loop_end(const DevProblem &P, const LoopDev &L, const float *truth_cap, const float *truth_tail,
+                           int32_t O, AllocOut out, float *tau_truth, float *tau_oracle, hipStream_t s);
 
 hipError_t launch_loop_init(const LoopDev &L, int32_t O, hipStream_t s);
 // After a certificate: trajectories that certified or have no unmeasured

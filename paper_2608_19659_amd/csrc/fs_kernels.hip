@@ -2434,6 +2434,7 @@ template <int SPL>
 struct ScoreItem {
   int4 ent;
   float cs[SPL], ls[SPL];
+  float4 bd;  // with bounds: the cell's cap_lo, cap_hi, tail_lo, tail_hi
   int u0, u1, mr0, mr1;
   int vm0, vm1;
   float vt0, vt1;
@@ -2472,13 +2473,16 @@ __device__ __forceinline__ int lane_lookup(int v, int idx) { return __builtin_am
 // while f_r < M_r and falls after; with r* the first r where f_r >= M_r --
 // the first r whose capacity threshold the sample reaches -- the maximum is
 // max(f_{r*-1}, M_{r*}).
-template <int SPL, bool VEC, bool DUMP>
+//
+// CLAMP: every sample is moved into its cell's intervals first (the refitting
+// loop: min(max(x, lo), hi) with the tile's bounds, read with its record).
+template <int SPL, bool VEC, bool DUMP, bool CLAMP>
 __global__ __launch_bounds__(64) void k_score_excl(
     DevProblem P, const TileInfo *__restrict__ tiles, const int32_t *__restrict__ mopt,
     const float *__restrict__ thr, int32_t n_thr, const int4 *__restrict__ list,
     const float *__restrict__ cap_s, const float *__restrict__ tail_s, int32_t O, int32_t E, int32_t S,
     const int32_t *__restrict__ base, double *__restrict__ partial, int32_t n_chunk,
-    float *__restrict__ tau_dump) {
+    float *__restrict__ tau_dump, const float4 *__restrict__ bounds) {
   constexpr int CHUNK = 64 * SPL;
   extern __shared__ int lds[];
   const int lane = threadIdx.x;
@@ -2535,6 +2539,7 @@ __global__ __launch_bounds__(64) void k_score_excl(
     X.u1 = h.y;
     X.mr0 = h.z;
     X.mr1 = h.w;
+    if constexpr (CLAMP) X.bd = bounds[tile + vz];
   };
   // Decides, from an item's record, whether its samples can matter, and
   // issues their loads and the range's M and thresholds if so.  The test
@@ -2600,7 +2605,14 @@ __global__ __launch_bounds__(64) void k_score_excl(
     int am[SPL], ap[SPL];
     float cs[SPL];
 #pragma unroll
-    for (int q = 0; q < SPL; ++q) cs[q] = X.ls[q] <= slo ? X.cs[q] : 0.0f;
+    for (int q = 0; q < SPL; ++q) {
+      float c = X.cs[q], l = X.ls[q];
+      if constexpr (CLAMP) {
+        c = fminf(fmaxf(c, X.bd.x), X.bd.y);
+        l = fminf(fmaxf(l, X.bd.z), X.bd.w);
+      }
+      cs[q] = l <= slo ? c : 0.0f;
+    }
     if (nr <= kScanMax) {
       // pairs of replica counts, then a single one when nr is odd
 #pragma unroll
@@ -4659,13 +4671,50 @@ __device__ __forceinline__ float round_down_f32(double x) {
   return v;
 }
 
+// The refitted bounds of unmeasured cell c of one order.
+struct RefitCell {
+  float cap_lo, tail_lo, tail_hi;
+};
+__device__ __forceinline__ RefitCell refit_cell(const DevProblem &P, int c, const float *cap_lo, const float *cap_hi,
+                                                const float *tail_lo, const float *tail_hi,
+                                                const uint8_t *measured) {
+  const int NT = P.NT, B = P.B;
+  const int b = c % B, t = (c / B) % NT, row = c - b - t * B;  // row: the class's first cell
+  RefitCell out{cap_lo[c], tail_lo[c], tail_hi[c]};
+  // capacity: best measured per-GPU value on each side of t at level b
+  double left = -1.0, right = -1.0;
+  for (int a = 0; a < NT; ++a) {
+    const int ca = row + a * B + b;
+    if (a == t || !measured[ca]) continue;
+    const double q = (double)cap_lo[ca] / (double)P.tp[a];
+    if (a < t) left = fmax(left, q);
+    else right = fmax(right, q);
+  }
+  float lo = out.cap_lo;
+  if (left >= 0.0 && right >= 0.0) lo = fmaxf(lo, round_down_f32((double)P.tp[t] * fmin(left, right)));
+  if (lo <= cap_hi[c]) out.cap_lo = lo;
+  // tail: measured loads below bound it from below, above from above
+  float tl = out.tail_lo, th = out.tail_hi;
+  for (int b2 = 0; b2 < B; ++b2) {
+    const int c2 = row + t * B + b2;
+    if (b2 == b || !measured[c2]) continue;
+    const float v = tail_lo[c2];
+    if (b2 < b) tl = fmaxf(tl, v);
+    else th = fminf(th, v);
+  }
+  if (tl <= th) {
+    out.tail_lo = tl;
+    out.tail_hi = th;
+  }
+  return out;
+}
+
 __global__ __launch_bounds__(256) void k_refit(DevProblem P, const float *__restrict__ cap_lo,
                                                const float *__restrict__ cap_hi, const float *__restrict__ tail_lo,
                                                const float *__restrict__ tail_hi,
                                                const uint8_t *__restrict__ measured, float *cap_lo_out,
                                                float *tail_lo_out, float *tail_hi_out) {
   const size_t off = (size_t)blockIdx.x * P.N;
-  const int NT = P.NT, B = P.B;
   for (int c = threadIdx.x; c < P.N; c += blockDim.x) {
     if (measured[off + c]) {  // unchanged: copied unless refitting in place
       if (cap_lo_out != cap_lo) cap_lo_out[off + c] = cap_lo[off + c];
@@ -4673,36 +4722,10 @@ __global__ __launch_bounds__(256) void k_refit(DevProblem P, const float *__rest
       if (tail_hi_out != tail_hi) tail_hi_out[off + c] = tail_hi[off + c];
       continue;
     }
-    const int b = c % B, t = (c / B) % NT, row = c - b - t * B;  // row: the class's first cell
-    // capacity: best measured per-GPU value on each side of t at level b
-    double left = -1.0, right = -1.0;
-    for (int a = 0; a < NT; ++a) {
-      const int ca = row + a * B + b;
-      if (a == t || !measured[off + ca]) continue;
-      const double q = (double)cap_lo[off + ca] / (double)P.tp[a];
-      if (a < t) left = fmax(left, q);
-      else right = fmax(right, q);
-    }
-    float lo = cap_lo[off + c];
-    if (left >= 0.0 && right >= 0.0) lo = fmaxf(lo, round_down_f32((double)P.tp[t] * fmin(left, right)));
-    if (lo <= cap_hi[off + c]) cap_lo_out[off + c] = lo;
-    else if (cap_lo_out != cap_lo) cap_lo_out[off + c] = cap_lo[off + c];
-    // tail: measured loads below bound it from below, above from above
-    float tl = tail_lo[off + c], th = tail_hi[off + c];
-    for (int b2 = 0; b2 < B; ++b2) {
-      const int c2 = row + t * B + b2;
-      if (b2 == b || !measured[off + c2]) continue;
-      const float v = tail_lo[off + c2];
-      if (b2 < b) tl = fmaxf(tl, v);
-      else th = fminf(th, v);
-    }
-    if (tl <= th) {
-      tail_lo_out[off + c] = tl;
-      tail_hi_out[off + c] = th;
-    } else {
-      if (tail_lo_out != tail_lo) tail_lo_out[off + c] = tail_lo[off + c];
-      if (tail_hi_out != tail_hi) tail_hi_out[off + c] = tail_hi[off + c];
-    }
+    const RefitCell f = refit_cell(P, c, cap_lo + off, cap_hi + off, tail_lo + off, tail_hi + off, measured + off);
+    cap_lo_out[off + c] = f.cap_lo;
+    tail_lo_out[off + c] = f.tail_lo;
+    tail_hi_out[off + c] = f.tail_hi;
   }
 }
 
@@ -4871,6 +4894,224 @@ __global__ void k_loop_output(DevProblem P, LoopDev L, AllocOut meas, const int8
                                            P.rcp_demand[k])));
   }
   if (tau_truth) tau_truth[o] = unserved ? 0.0f : v;
+}
+
+// ---------------------------------------------------------------------------
+// The loop for what the register solver takes: everything of a round that
+// concerns one trajectory alone in one block -- the last round's scores and
+// their arg-max, the reveal, the refit, the certificate and the decision --
+// so that a round is three launches (this, the scorer's set-up, the scorer)
+// where it was nine or ten, each a few us of latency for a few wavefronts.
+// FIGURES_LOOP
+// ---------------------------------------------------------------------------
+// Where a round's reveal comes from: nothing scored yet; the scores of this
+// block's tiles (at most 16 partials each); best, already found; the fixed
+// order.
+enum LoopPick { kPickNone, kPickScores, kPickBest, kPickOrder };
+
+struct LoopRoundArgs {
+  const float *cap_lo, *cap_hi, *tail_lo, *tail_hi;  // first round: the caller's intervals, else null
+  const uint8_t *measured;
+  float *r_cap_lo, *r_tail_lo, *r_tail_hi;           // refitted intervals, or null
+  float4 *bounds;                                    // [O][E] candidates' refitted intervals, or null
+  const TileInfo *tiles;
+  const int32_t *base;
+  const double *partial;
+  int64_t n_partial;
+  const float *truth_cap, *truth_tail;
+  const int32_t *cand, *order;
+  int32_t O, E, S, pick;
+  float eps;
+};
+
+// LDS of a block: two wavefronts' solvers, the intervals and revealed flags.
+static size_t loop_lds(const DevProblem &P) { return reg_lds(P, 2) + 4 + 17 * (size_t)P.N; }
+
+template <int KP, int NTP>
+__global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_loop_round(DevProblem P, LoopDev L, LoopRoundArgs A,
+                                                                       const PrepLevels LV) {
+  extern __shared__ __attribute__((aligned(16))) float reg_mem[];
+  __shared__ uint64_t s_key[kFinalizeMaxWaves], s_tie[kFinalizeMaxWaves];
+  __shared__ CertShared C;
+  const int o = blockIdx.x, tid = threadIdx.x, nth = blockDim.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = P.N, E = A.E;
+  const size_t off = (size_t)o * N;
+  const bool first = A.cap_lo != nullptr;
+  if (!first && !L.running[o]) return;
+  const RegShared X = reg_shared(P, reg_mem + 2 * reg_cells(N));
+  float *cl = reinterpret_cast<float *>(X.reps + (size_t)kWave * P.NT), *ch = cl + N, *tl = ch + N, *th = tl + N;
+  uint8_t *ms = reinterpret_cast<uint8_t *>(th + N);
+
+  // --- the trajectory's intervals (the first round copies the caller's)
+  const float *gcl = (first ? A.cap_lo : L.cap_lo) + off, *gch = (first ? A.cap_hi : L.cap_hi) + off;
+  const float *gtl = (first ? A.tail_lo : L.tail_lo) + off, *gth = (first ? A.tail_hi : L.tail_hi) + off;
+  const uint8_t *gms = (first ? A.measured : L.measured) + off;
+  for (int c = tid; c < N; c += nth) {
+    const float a = gcl[c], b = gch[c], l = gtl[c], h = gth[c];
+    const uint8_t m = gms[c];
+    cl[c] = a; ch[c] = b; tl[c] = l; th[c] = h;
+    ms[c] = m;
+    if (first) {
+      L.cap_lo[off + c] = a; L.cap_hi[off + c] = b; L.tail_lo[off + c] = l; L.tail_hi[off + c] = h;
+      L.measured[off + c] = m;
+    }
+  }
+  if (first) {
+    if (tid == 0) {
+      L.running[o] = 1;
+      L.finished[o] = 0;
+      L.rounds[o] = 0;
+      L.gpu_seconds[o] = 0.0;
+    }
+    for (int j = tid; L.reveals && j < L.max_rounds; j += nth) L.reveals[(size_t)o * L.max_rounds + j] = -1;
+  }
+  reg_stage(P, LV, X);
+  if (tid < 2) reg_mem[tid * reg_cells(N) + N] = 0.0f;
+
+  // --- this round's reveal
+  int pick = -1;
+  if (A.pick == kPickScores)
+    pick = finalize_order(o, A.tiles, E, A.S, A.base, A.partial, A.n_partial, nullptr, nullptr, s_key, s_tie);
+  __syncthreads();
+  if (A.pick == kPickBest) pick = L.best[o];
+  if (A.pick == kPickOrder && wave == 0) {
+    for (int j0 = 0; j0 < E && pick < 0; j0 += kWave) {
+      const int j = j0 + lane;
+      const int e = j < E ? A.order[(size_t)o * E + j] : -1;
+      const int c = (e >= 0 && e < E) ? A.cand[e] : -1;
+      const uint64_t m = __ballot(c >= 0 && c < N && !ms[min(max(c, 0), N - 1)]);
+      if (m) pick = __shfl(e, __builtin_ctzll(m), kWave);
+    }
+  }
+  __syncthreads();
+  if (tid == 0 && pick >= 0 && pick < E) {
+    const int cell = A.cand[pick];
+    if (cell >= 0 && cell < N) {
+      const float tc = A.truth_cap[off + cell], tt = A.truth_tail[off + cell];
+      cl[cell] = ch[cell] = tc;
+      tl[cell] = th[cell] = tt;
+      ms[cell] = 1;
+      L.cap_lo[off + cell] = L.cap_hi[off + cell] = tc;
+      L.tail_lo[off + cell] = L.tail_hi[off + cell] = tt;
+      L.measured[off + cell] = 1;
+      const int r = L.rounds[o];
+      L.gpu_seconds[o] += kCellSeconds * (double)P.tp[(cell / P.B) % P.NT];
+      if (L.reveals && r < L.max_rounds) L.reveals[(size_t)o * L.max_rounds + r] = pick;
+      L.rounds[o] = r + 1;
+    }
+  }
+  __syncthreads();
+
+  // --- the refit, in place in LDS: a thread reads measured cells, which no
+  // thread writes, and its own cell
+  if (A.r_cap_lo) {
+    for (int c = tid; c < N; c += nth) {
+      if (!ms[c]) {
+        const RefitCell f = refit_cell(P, c, cl, ch, tl, th, ms);
+        cl[c] = f.cap_lo;
+        tl[c] = f.tail_lo;
+        th[c] = f.tail_hi;
+      }
+      A.r_cap_lo[off + c] = cl[c];
+      A.r_tail_lo[off + c] = tl[c];
+      A.r_tail_hi[off + c] = th[c];
+    }
+    __syncthreads();
+    for (int e = tid; A.bounds && e < E; e += nth) {
+      const int c = A.cand[e];
+      if (c >= 0 && c < N) A.bounds[(size_t)o * E + e] = make_float4(cl[c], ch[c], tl[c], th[c]);
+    }
+  }
+
+  // --- the certificate; the conservative allocation is the one returned so far
+  bool open = false;  // an unmeasured candidate
+  for (int e = tid; e < E; e += nth) {
+    const int c = A.cand[e];
+    open |= c >= 0 && c < N && !ms[min(max(c, 0), N - 1)];
+  }
+  if (wave < 2) {
+    float *cells = reg_mem + wave * reg_cells(N);
+    for (int c = lane; c < N; c += kWave)
+      cells[c] = (wave == 0 ? th[c] : tl[c]) <= X.slo[c] ? (wave == 0 ? cl[c] : ch[c]) : 0.0f;
+    RegSolver<KP, NTP> S;
+    S.init(P, X);
+    wave_lds_fence();
+    int T[KP];
+    const int tau = S.solve(P, cells, T);
+    if (lane == 0) C.tau[wave] = tau;
+    if (wave == 0) {
+      const RegAlloc a = S.alloc(P, cells, X, tau, T);
+      write_reg_alloc(L.fin, o, P.K, tau, S.goodput(a), a, lane);
+      const bool ok = reg_committed<KP, NTP>(P, S, a, X.slo, ms, th);
+      if (lane == 0) C.committed = ok;
+    }
+  }
+  open = __syncthreads_or(open) != 0;
+  const double gap = (double)__int_as_float(C.tau[1]) - (double)__int_as_float(C.tau[0]);
+  const bool certified = C.committed && gap <= (double)A.eps;
+  if (tid == 0) L.state[o] = certified ? 1 : 0;
+  if (!certified && open) return;
+  // ended: the scorer skips its candidates from now on
+  if (tid == 0) {
+    L.finished[o] = 1;
+    L.running[o] = 0;
+  }
+  for (int e = tid; e < E; e += nth) {
+    const int c = A.cand[e];
+    if (c >= 0 && c < N) L.measured[off + c] = 1;
+  }
+}
+
+// The end of the loop, a block per trajectory: wavefront 0 solves the table
+// of measured cells alone (Algorithm 1's last line, returned by a trajectory
+// that ended undecided), wavefront 1 the true table; then the returned
+// allocation and its value on the true table.
+template <int KP, int NTP>
+__global__ __launch_bounds__(kCertThreads) void k_loop_end(DevProblem P, LoopDev L,
+                                                           const float *__restrict__ truth_cap,
+                                                           const float *__restrict__ truth_tail, AllocOut out,
+                                                           float *__restrict__ tau_truth,
+                                                           float *__restrict__ tau_oracle, const PrepLevels LV) {
+  extern __shared__ __attribute__((aligned(16))) float reg_mem[];
+  const int o = blockIdx.x, lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int N = P.N;
+  const size_t off = (size_t)o * N;
+  const RegShared X = reg_shared(P, reg_mem + 2 * reg_cells(N));
+  reg_stage(P, LV, X);
+  float *cells = reg_mem + wave * reg_cells(N);
+  if (lane == 0) cells[N] = 0.0f;
+  __syncthreads();
+  for (int c = lane; c < N; c += kWave) {
+    const bool use = wave == 0 ? L.measured[off + c] && L.tail_hi[off + c] <= X.slo[c] : truth_tail[off + c] <= X.slo[c];
+    cells[c] = use ? (wave == 0 ? L.cap_lo : truth_cap)[off + c] : 0.0f;
+  }
+  RegSolver<KP, NTP> S;
+  S.init(P, X);
+  wave_lds_fence();
+  int T[KP];
+  const int tau = S.solve(P, cells, T);
+  if (wave == 1) {
+    if (lane == 0 && tau_oracle) tau_oracle[o] = __int_as_float(tau);
+    return;
+  }
+  RegAlloc a = S.alloc(P, cells, X, tau, T);
+  float objective = __int_as_float(tau), goodput = S.goodput(a);
+  const int k = min(lane, P.K - 1);
+  if (L.state[o] != 0) {  // certified: A-
+    const uint8_t ti = L.fin.tp_index[(size_t)o * P.K + k];
+    a.ti = ti == 0xFF ? -1 : (int)ti;
+    a.r = L.fin.replicas[(size_t)o * P.K + k];
+    objective = L.fin.objective[o];
+    goodput = L.fin.goodput[o];
+  }
+  write_reg_alloc(out, o, P.K, __float_as_int(objective), goodput, a, lane);
+  // the smallest fulfillment over the classes, an unserved class counting 0
+  const int cell = min(S.cell_of_alloc(P, a), N - 1);
+  const int f = a.r > 0 ? ratio_bits(truth_cap[off + cell], truth_tail[off + cell], a.r, X.slo[cell], S.my_rcp) : 0;
+  const int v = wave_min_dpp(lane < P.K ? f : INT_MAX);
+  if (lane == 0 && tau_truth) tau_truth[o] = __int_as_float(v);
 }
 
 // ---------------------------------------------------------------------------
@@ -5319,6 +5560,21 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
   return hipGetLastError();
 }
 
+// Samples per lane of the exclusion scorer.  Chunks of 1024 samples when the
+// default grid would get more than 16 chunks of 512 per wavefront: on the
+// 8-class, G = 256 workload (43 per wavefront) the scorer ran 33.0 us against
+// 35.9 with 512; with about 5 per wavefront (the 4-class, G = 64 one) 512
+// stays faster.
+static int excl_spl(const ScoreArgs &a) {
+  const int64_t chunks512 = (int64_t)(a.S + 511) / 512 * a.O * a.E;
+  return a.spl == 4 || a.spl == 8 || a.spl == 16 ? a.spl : chunks512 > 16 * (int64_t)kScorerWaves ? 16 : 8;
+}
+
+int64_t excl_partials(const ScoreArgs &a) {
+  const int64_t chunk = kWave * excl_spl(a);
+  return (a.S + chunk - 1) / chunk;
+}
+
 // Scores and arg-max of the exclusion scorers from n_partial partials a tile.
 static hipError_t launch_finalize_excl(const ScoreArgs &a, int64_t n_partial, hipStream_t s) {
   const TileInfo *tiles = (const TileInfo *)(a.ws + a.L.tiles);
@@ -5345,7 +5601,6 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
   const size_t lds = lds_bytes_solver(P, 0);
   if (a.O == 0) return hipSuccess;
   if (a.kernel == 3) {
-    constexpr int kSpl = 8;
     TileInfo *tiles = (TileInfo *)(a.ws + a.L.tiles);
     int32_t *mopt = (int32_t *)(a.ws + a.L.mopt);
     float *thr = (float *)(a.ws + a.L.thr);
@@ -5358,15 +5613,8 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
                                     a.best);
       return hipGetLastError();
     }
-    // Chunks of 1024 samples when the default grid would get more than 16
-    // chunks of 512 per wavefront: on the 8-class, G = 256 workload (43
-    // per wavefront) the scorer ran 33.0 us against 35.9 with 512; with
-    // about 5 per wavefront (the 4-class, G = 64 one) 512 stays faster.
-    const int64_t chunks512 = (int64_t)(a.S + 511) / 512 * a.O * a.E;
-    const int spl = a.spl == 4 || a.spl == 8 || a.spl == 16 ? a.spl
-                    : chunks512 > 16 * (int64_t)kScorerWaves ? 16 : kSpl;
-    const int64_t chunk = 64 * spl;
-    const int64_t n_partial = (a.S + chunk - 1) / chunk;
+    const int spl = excl_spl(a);
+    const int64_t n_partial = excl_partials(a);
     // LDS: per-class constants, then M and thresholds of a range longer
     // than a wavefront (the longest range has G / tp[0] options)
     const int32_t range_max = P.G / P.tp[0];
@@ -5378,17 +5626,20 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
     const int launches = a.ev_begin ? a.timing_launches : 1;
     if (a.ev_begin) (void)hipEventRecord(a.ev_begin, s);
     for (int rep = 0; rep < launches; ++rep) {
-#define FS_EXCL_LAUNCH(SP, VEC, DUMP)                                                               \
-  k_score_excl<SP, VEC, DUMP><<<grid, kWave, mlds, s>>>(P, tiles, mopt, thr, n_thr, list, a.cap_s,       \
-                                                        a.tail_s, a.O, a.E, a.S, base, partial,     \
-                                                        (int32_t)n_partial, a.tau_dump)
+#define FS_EXCL_LAUNCH(SP, VEC, DUMP, CLAMP)                                                               \
+  k_score_excl<SP, VEC, DUMP, CLAMP><<<grid, kWave, mlds, s>>>(P, tiles, mopt, thr, n_thr, list, a.cap_s,  \
+                                                               a.tail_s, a.O, a.E, a.S, base, partial,     \
+                                                               (int32_t)n_partial, a.tau_dump, a.bounds)
 #define FS_EXCL_SPL(SP)                                         \
-  if (a.tau_dump) {                                             \
-    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, true);           \
-    else FS_EXCL_LAUNCH(SP, false, true);                       \
+  if (a.bounds) {                                               \
+    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, false, true);    \
+    else FS_EXCL_LAUNCH(SP, false, false, true);                \
+  } else if (a.tau_dump) {                                      \
+    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, true, false);    \
+    else FS_EXCL_LAUNCH(SP, false, true, false);                \
   } else {                                                      \
-    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, false);          \
-    else FS_EXCL_LAUNCH(SP, false, false);                      \
+    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, false, false);   \
+    else FS_EXCL_LAUNCH(SP, false, false, false);               \
   }
       if (spl == 16) { FS_EXCL_SPL(16) }
       else if (spl == 8) { FS_EXCL_SPL(8) }
@@ -5397,7 +5648,7 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
 #undef FS_EXCL_LAUNCH
     }
     if (a.ev_end) (void)hipEventRecord(a.ev_end, s);
-    return launch_finalize_excl(a, n_partial, s);
+    return a.no_finalize ? hipGetLastError() : launch_finalize_excl(a, n_partial, s);
   }
   if (a.kernel == kScoreFloors && a.E > 0) {
     const int64_t n_partial = (a.S + kFloorChunk - 1) / kFloorChunk;
@@ -5627,6 +5878,7 @@ RefitLayout refit_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S, s
   L.tail_hi = take(4 * ON);
   L.cap_s = take(4 * OES);
   L.tail_s = take(4 * OES);
+  L.bounds = take(sizeof(float4) * (size_t)O * (size_t)E);
   L.total = at;
   return L;
 }
@@ -5843,6 +6095,48 @@ hipError_t launch_score_lex(const DevProblem &P, const float *cap_lo, const floa
   // with no candidates only the gaps are written (best stays as it was)
   k_finalize_lex<<<O, 64, 0, s>>>(P, info, measured, E, S, (const CertRec *)(ws + L.score.crec), gmm, ggp, pmm,
                                   pgp, S > 0 ? n_partial : 0, score_mm, score_gp, E > 0 ? best : nullptr);
+  return hipGetLastError();
+}
+
+bool loop_fast_supported(const DevProblem &P) {
+  return reg_solver_supported(P) && loop_lds(P) <= 64 * 1024 - 1024;  // less what the kernel declares statically
+}
+
+hipError_t launch_loop_round(const DevProblem &P, const LoopDev &L, const ScoreArgs *iv, const RefitArgs &R,
+                             const ScoreArgs &a, const float *truth_cap, const float *truth_tail,
+                             const int32_t *order, float eps, int32_t policy, bool scored, hipStream_t s) {
+  LoopRoundArgs A{};
+  if (iv) {
+    A.cap_lo = iv->cap_lo; A.cap_hi = iv->cap_hi; A.tail_lo = iv->tail_lo; A.tail_hi = iv->tail_hi;
+    A.measured = iv->measured;
+  }
+  A.r_cap_lo = R.cap_lo; A.r_tail_lo = R.tail_lo; A.r_tail_hi = R.tail_hi; A.bounds = R.bounds;
+  A.tiles = (const TileInfo *)(a.ws + a.L.tiles);
+  A.base = (const int32_t *)(a.ws + a.L.base);
+  A.partial = (const double *)(a.ws + a.L.partial);
+  A.truth_cap = truth_cap; A.truth_tail = truth_tail; A.cand = a.cand; A.order = order;
+  A.O = a.O; A.E = a.E; A.S = a.S; A.eps = eps;
+  A.n_partial = a.E > 0 && a.S > 0 ? excl_partials(a) : 0;
+  A.pick = iv || a.E == 0 ? kPickNone : policy != 0 ? kPickOrder : !scored ? kPickNone : a.no_finalize ? kPickScores : kPickBest;
+  // at least the two solving wavefronts, and one per 128 candidates' scores
+  const int want = (a.E + 2 * kWave - 1) / (2 * kWave);
+  const int nw = want < 2 ? 2 : want > kFinalizeMaxWaves ? kFinalizeMaxWaves : want;
+  const PrepLevels LV = prep_levels(P);
+  const size_t lds = loop_lds(P);
+#define FS_LOOP_ROUND(KP, NTP) k_loop_round<KP, NTP><<<a.O, kWave * nw, lds, s>>>(P, L, A, LV);
+  FS_REG_DISPATCH(FS_LOOP_ROUND)
+#undef FS_LOOP_ROUND
+  return hipGetLastError();
+}
+
+hipError_t launch_loop_end(const DevProblem &P, const LoopDev &L, const float *truth_cap, const float *truth_tail,
+                           int32_t O, AllocOut out, float *tau_truth, float *tau_oracle, hipStream_t s) {
+  const PrepLevels LV = prep_levels(P);
+  const size_t lds = reg_lds(P, 2);
+#define FS_LOOP_END(KP, NTP) \
+  k_loop_end<KP, NTP><<<O, kCertThreads, lds, s>>>(P, L, truth_cap, truth_tail, out, tau_truth, tau_oracle, LV);
+  FS_REG_DISPATCH(FS_LOOP_END)
+#undef FS_LOOP_END
   return hipGetLastError();
 }
 
