@@ -574,15 +574,17 @@ struct alignas(16) PrepLevels {
 };
 
 // The level falls as r grows, so one pass over r per class moves it
-// downwards only.
+// downwards only (the divisions in a loop of their own, which vectorises).
 static PrepLevels prep_levels(const DevProblem &P) {
   PrepLevels LV{};
   for (int k = 0; k < P.K; ++k) {
+    float u[kPrepOrderMaxG];
+    for (int r = 0; r < kPrepOrderMaxG; ++r) u[r] = P.demand[k] / (float)(r + 1);
     int b = P.B;
-    for (int r = 1; r <= P.G; ++r) {
-      const float u = P.demand[k] / (float)r;
-      while (b > 0 && !(P.levels[b - 1] < u)) --b;
-      LV.lvl[k * kPrepOrderMaxG + r - 1] = (int8_t)(b < P.B ? b : -1);
+    for (int r = 0; r < P.G; ++r) {
+      while (b > 0 && !(P.levels[b - 1] < u[r])) --b;
+      if (b == 0) break;  // the lowest level from here on: lvl is 0
+      LV.lvl[k * kPrepOrderMaxG + r] = (int8_t)(b < P.B ? b : -1);
     }
   }
   return LV;
@@ -641,18 +643,35 @@ __device__ __forceinline__ RegShared reg_shared(const DevProblem &P, float *star
   return X;
 }
 
-// Fills them with the whole block (then a block barrier).
-__device__ __forceinline__ void reg_stage(const DevProblem &P, const PrepLevels &LV, const RegShared &X) {
-  const int per_class = P.NT * P.B;
-  for (int c = threadIdx.x; c < P.N; c += blockDim.x) X.slo[c] = P.slo[c / per_class];
-  for (int x = threadIdx.x; x < P.K * P.NT * kWave; x += blockDim.x) {
-    const int cost = (x & (kWave - 1)) + 1, kt = x >> 6, k = kt / P.NT, ti = kt - k * P.NT;
-    const int t = P.tp[ti], r = cost / t;
-    const bool ok = cost <= P.G && r * t == cost;
-    const int b = ok ? LV.lvl[k * kPrepOrderMaxG + r - 1] : -1;
-    X.place[x] = (uint16_t)(4 * (b >= 0 ? kt * P.B + b : P.N));
-    if (k == 0) X.reps[x] = (uint8_t)(ok ? r : 0);
+// Fills them with `nth` threads, whole wavefronts (then a block barrier).  A
+// wavefront takes one (class, TP) at a time, lanes over the costs, the level
+// reads of four of them in flight together.
+__device__ __forceinline__ void reg_stage(const DevProblem &P, const PrepLevels &LV, const RegShared &X, int tid,
+                                          int nth) {
+  const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nth >> 6;
+  const int cost = lane + 1, n = P.K * P.NT;
+  for (int kt0 = wave; kt0 < n; kt0 += 4 * nw) {
+    int r[4], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int kt = min(kt0 + u * nw, n - 1), k = kt / P.NT, t = P.tp[kt - k * P.NT];
+      // cost / t, exact whenever t divides it (the float quotient is within 1/2)
+      const int q = (int)((float)cost * __builtin_amdgcn_rcpf((float)t) + 0.5f);
+      r[u] = cost <= P.G && q * t == cost ? q : 0;
+      b[u] = LV.lvl[k * kPrepOrderMaxG + max(r[u], 1) - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int kt = kt0 + u * nw;
+      if (kt < n) {
+        X.place[kt * kWave + lane] = (uint16_t)(4 * (r[u] > 0 && b[u] >= 0 ? kt * P.B + b[u] : P.N));
+        if (kt < P.NT) X.reps[kt * kWave + lane] = (uint8_t)r[u];
+      }
+    }
   }
+  const int per_class = P.NT * P.B;
+  const float inv = 1.0f / (float)per_class;
+  for (int c = tid; c < P.N; c += nth) X.slo[c] = P.slo[(int)(((float)c + 0.5f) * inv)];  // c / per_class
 }
 
 // Lane constants of the compare-exchanges: INT_MIN where the lane keeps the
@@ -723,10 +742,17 @@ struct RegSolver {
   double my_rcp;
   const uint16_t *my_place;  // place row of class `lane`, TP 0
 
-  __device__ __forceinline__ void init(const DevProblem &P, const RegShared &X) {
+  // What needs no staged table; its loads may be in flight over the staging.
+  __device__ __forceinline__ void begin(const DevProblem &P) {
     lane = threadIdx.x & (kWave - 1);
     mirror = 4 * (kWave - 1 - lane);
     sides.init(lane);
+    const int k = min(lane, P.K - 1);
+    my_demand = P.demand[k];
+    my_rcp = P.rcp_demand[k];
+  }
+
+  __device__ __forceinline__ void init(const DevProblem &P, const RegShared &X) {
 #pragma unroll
     for (int ti = 0; ti < NTP; ++ti) {
       const int t = min(ti, P.NT - 1);
@@ -737,10 +763,7 @@ struct RegSolver {
         at[k][ti] = k < P.K && ti < P.NT ? x : 4 * P.N;
       }
     }
-    const int k = min(lane, P.K - 1);
-    my_demand = P.demand[k];
-    my_rcp = P.rcp_demand[k];
-    my_place = X.place + (size_t)k * P.NT * kWave;
+    my_place = X.place + (size_t)min(lane, P.K - 1) * P.NT * kWave;
   }
 
   // tau* as bits, from the usable capacities in LDS; E: every class's best
@@ -882,7 +905,7 @@ struct RegBatch {
   // The first request, then what the block shares (with its barrier).
   __device__ __forceinline__ void begin(const DevProblem &P, const PrepLevels &LV) {
     if (SMALL && j < n) request(P, j);
-    reg_stage(P, LV, X);
+    reg_stage(P, LV, X, threadIdx.x, blockDim.x);
     if (lane == 0) cells[P.N] = 0.0f;
     __syncthreads();
     slo0 = X.slo[c0];
@@ -914,8 +937,9 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_reg(DevProblem P, const
                                                              const PrepLevels LV) {
   extern __shared__ __attribute__((aligned(16))) float reg_mem[];
   RegBatch<SMALL> D(P, cap, tail, n, reg_mem, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), blockDim.x >> 6);
-  D.begin(P, LV);
   RegSolver<KP, NTP> S;
+  S.begin(P);
+  D.begin(P, LV);
   S.init(P, D.X);
   for (; D.j < n; D.j += D.step) {
     D.load(P);
@@ -1419,8 +1443,8 @@ __device__ __forceinline__ void setup_cand_at(const DevProblem &P, const int32_t
 // decides only which wavefront evaluates a tile).
 __device__ void prep_list(const DevProblem &P, int O, const uint8_t *__restrict__ measured,
                           const int32_t *__restrict__ cand, int E, int dump, int PPc, const PrepConsts &C,
-                          TileInfo *__restrict__ tiles, int4 *__restrict__ list, int32_t *__restrict__ n_listed,
-                          int *bucket_count, int *bucket_start, int *n_live) {
+                          TileInfo *__restrict__ tiles, int4 *__restrict__ list, int *bucket_count,
+                          int *bucket_start, int *n_live) {
   const int tid = threadIdx.x, nth = blockDim.x, lane = tid & (kWave - 1);
   const int N = P.N, per_class = P.NT * P.B;
   // Threads work candidate by candidate (the replica range is computed once
@@ -1477,10 +1501,7 @@ __device__ void prep_list(const DevProblem &P, int O, const uint8_t *__restrict_
           if (lane >= d) incl += u;
         }
         if (lane < 32) bucket_start[lane] = incl - cnt;
-        if (lane == 31) {
-          *n_listed = incl;
-          *n_live = incl;
-        }
+        if (lane == 31) *n_live = incl;
       }
       __syncthreads();
     }
@@ -1609,10 +1630,17 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
 // Dynamic LDS: all cells (cap, tail) of this realisation; the class's cell
 // maxima and replica ranges; the load-level table (K x G int8); and, when
 // kLds, the tables (B and two tree buffers, 3 x K x G ints), else in gtab.
-__device__ void prep_list_staged(const DevProblem &P, int O, const uint8_t *__restrict__ measured,
+__device__ void prep_list_staged(const DevProblem &P, int o_first, int O, const uint8_t *__restrict__ measured,
                                  const int32_t *__restrict__ cand, int E, int dump, int PPc,
-                                 TileInfo *__restrict__ tiles, int4 *__restrict__ list,
-                                 int32_t *__restrict__ n_listed, int *lds);
+                                 TileInfo *__restrict__ tiles, int4 *__restrict__ list, int *lds);
+
+// The work list in n = 1 << log runs of consecutive orders, one block each:
+// run q is orders [q per, q per + per) of O (fewer or none past the last
+// order), its entries from list[q per E].  A wavefront of the scorer takes
+// its items from one run.
+struct ListRuns {
+  int log, n, per;
+};
 
 // kFloor (critical floors; tables in LDS, no work list): block x = 2 V + R.
 // Variant V = 0 ignores the floors, as above.  Variant 1 holds them: every
@@ -1642,8 +1670,8 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
                                              int32_t *__restrict__ gtab, TileInfo *__restrict__ tiles,
                                              int32_t *__restrict__ base, int32_t *__restrict__ mopt,
                                              float *__restrict__ thr, int32_t n_thr,
-                                             int4 *__restrict__ list, int32_t *__restrict__ n_listed,
-                                             int32_t thr_mode, int32_t staged_list,
+                                             int4 *__restrict__ list,
+                                             int32_t thr_mode, int32_t staged_list, ListRuns runs,
                                              const int32_t *__restrict__ btab, FloorOut F) {
   extern __shared__ int lds[];
   __shared__ PrepConsts C;
@@ -1665,15 +1693,15 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
     C.optoff[NT] = at;
   }
   if (!kFloor && ci == K) {  // one block builds the work list of every order
-    if (R != 0 || o != 0) return;
+    if (R != 0 || o >= runs.n || o * runs.per >= (int)gridDim.y) return;
     if (staged_list) {
-      prep_list_staged(P, (int)gridDim.y, measured, cand, E, dump, PPc, tiles, list, n_listed, lds);
+      prep_list_staged(P, o * runs.per, min(runs.per, (int)gridDim.y - o * runs.per), measured, cand, E, dump, PPc,
+                       tiles, list, lds);
       return;
     }
     if (tid < 32) bucket_count[tid] = 0;
     __syncthreads();
-    prep_list(P, (int)gridDim.y, measured, cand, E, dump, PPc, C, tiles, list, n_listed, bucket_count,
-              bucket_start, &n_live);
+    prep_list(P, (int)gridDim.y, measured, cand, E, dump, PPc, C, tiles, list, bucket_count, bucket_start, &n_live);
     return;
   }
   float *ccap = (float *)lds;                // [N]
@@ -1912,9 +1940,9 @@ static int prep_order_waves(const DevProblem &P, int64_t O, int64_t E) {
   return (int)(w < 16 ? w : 16);
 }
 
-// The scorer's work list, built by one block from staged inputs: the
-// candidates' cells and every order's revealed flags are read into LDS in
-// one round trip, during which the block finds, for every (class, level),
+// The scorer's work list over the O orders from o_first on, built by one
+// block from staged inputs: the candidates' cells and the orders' revealed
+// flags are read into LDS in one round trip, during which the block finds, for every (class, level),
 // the first and last replica count r in [1, G] whose per-replica load lands
 // in that level, by two bisections (the level is nonincreasing in r, so
 // these form a range; a cell of TP t keeps the part with t r <= G).  The list holds every tile the
@@ -1925,16 +1953,23 @@ static int prep_order_waves(const DevProblem &P, int64_t O, int64_t E) {
 // of rlo, rlo | nr << 16, class | revealed << 6 | order << 8).  The order of
 // entries within a bucket is arbitrary: it decides only which wavefront
 // evaluates a tile.  Also writes the tile records of invalid candidates.
+// One run takes 1.2 us to stage, 0.5 for the ranges, 0.8 to count, 1.3 to
+// place and 0.4 for the end markers at 2,400 tiles; one block over the 9,600
+// tiles of 200 orders x 48 candidates took 8.2 us and started last, so the
+// set-up lasted 12.1 us against 8.8 with four runs, started first (the call
+// 21.4 -> 17.6 us); 64 orders x 256 candidates, 8 classes: 64.5 -> 58.9 us.
 //
 // LDS: bucket counters and starts (2 x 32 + 4), the level ranges (2 x K x B),
 // per candidate its cell and range code (2 x E), the revealed flags (O x N
 // bytes).
-__device__ void prep_list_staged(const DevProblem &P, int O, const uint8_t *__restrict__ measured,
+__device__ void prep_list_staged(const DevProblem &P, int o_first, int O, const uint8_t *__restrict__ measured,
                                  const int32_t *__restrict__ cand, int E, int dump, int PPc,
-                                 TileInfo *__restrict__ tiles, int4 *__restrict__ list,
-                                 int32_t *__restrict__ n_listed, int *lds) {
+                                 TileInfo *__restrict__ tiles, int4 *__restrict__ list, int *lds) {
   const int tid = threadIdx.x, nth = blockDim.x, lane = tid & (kWave - 1);
   const int N = P.N, G = P.G, K = P.K, B = P.B, per_class = P.NT * P.B;
+  measured += (size_t)o_first * N;
+  tiles += (size_t)o_first * E;
+  list += (size_t)o_first * E;
   int *bucket_count = lds, *bucket_start = lds + 32, *n_live = lds + 64;
   int *lv_first = lds + 68, *lv_last = lv_first + K * B;
   int *c_cell = lv_last + K * B, *c_code = c_cell + E;
@@ -2022,7 +2057,7 @@ __device__ void prep_list_staged(const DevProblem &P, int O, const uint8_t *__re
           for (int u = 0; u < 8; ++u) {
             const int o = o0 + u * g;
             const bool rev = mv[u] != 0;
-            if (o < O && (dump || !rev)) list[at++] = make_int4(e, toff, code, k | ((rev ? 1 : 0) << 6) | (o << 8));
+            if (o < O && (dump || !rev)) list[at++] = make_int4(e, toff, code, k | ((rev ? 1 : 0) << 6) | ((o_first + o) << 8));
           }
         }
       }
@@ -2035,10 +2070,7 @@ __device__ void prep_list_staged(const DevProblem &P, int O, const uint8_t *__re
         const int cnt = lane < 32 ? bucket_count[lane] : 0;
         const int incl = wave_scan_add_rows(cnt, lane);
         if (lane < 32) bucket_start[lane] = incl - cnt;
-        if (lane == 31) {
-          *n_listed = incl;
-          *n_live = incl;
-        }
+        if (lane == 31) *n_live = incl;
       }
       __syncthreads();
     }
@@ -2048,8 +2080,8 @@ __device__ void prep_list_staged(const DevProblem &P, int O, const uint8_t *__re
 
 // Set-up of the exclusion scorer when the budget fits one wavefront
 // (G <= 64) and K <= 16: one block per (order o, realisation R) --
-// block 2 o + R -- with one wavefront per class (and idle ones when the
-// list is large), and block 2 O builds the work list.  R = 0 is the
+// block n + 2 o + R -- with one wavefront per class (and idle ones when the
+// list is large), and blocks 0 to n - 1 build the work list's n runs.  R = 0 is the
 // conservative corner (low capacity, high tail), R = 1 the optimistic one
 // (Section 4.1).  The same quantities as the
 // general set-up, with fewer barriers:
@@ -2081,18 +2113,22 @@ __global__ __launch_bounds__(1024) void k_prep_order(DevProblem P, const float *
                                                      int32_t dump, TileInfo *__restrict__ tiles,
                                                      int32_t *__restrict__ base, int32_t *__restrict__ mopt,
                                                      float *__restrict__ thr, int32_t n_thr,
-                                                     int4 *__restrict__ list, int32_t *__restrict__ n_listed,
-                                                     int32_t thr_mode, const PrepLevels LV) {
+                                                     int4 *__restrict__ list, ListRuns runs, int32_t thr_mode,
+                                                     const PrepLevels LV) {
   extern __shared__ int lds[];
   const int tid = threadIdx.x, nth = blockDim.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = P.G, K = P.K, N = P.N, NT = P.NT, B = P.B, per_class = NT * B;
   const int PPc = n_thr / K;
-  if ((int)blockIdx.x == 2 * O) {
-    prep_list_staged(P, O, measured, cand, E, dump, PPc, tiles, list, n_listed, lds);
+  // the list blocks come first: blocks start over about 2 us, and a list
+  // block takes as long as a class block
+  if ((int)blockIdx.x < runs.n) {
+    const int o_first = (int)blockIdx.x * runs.per;
+    if (o_first >= O) return;
+    prep_list_staged(P, o_first, min(runs.per, O - o_first), measured, cand, E, dump, PPc, tiles, list, lds);
     return;
   }
-  const int o = blockIdx.x >> 1, R = blockIdx.x & 1;
+  const int bx = (int)blockIdx.x - runs.n, o = bx >> 1, R = bx & 1;
   float *ccap = reinterpret_cast<float *>(lds);
   float *ctail = ccap + N;
   int *Bt = reinterpret_cast<int *>(ctail + N);  // [K][G] B tables
@@ -2482,11 +2518,13 @@ __global__ __launch_bounds__(64) void k_score_excl(
     const float *__restrict__ thr, int32_t n_thr, const int4 *__restrict__ list,
     const float *__restrict__ cap_s, const float *__restrict__ tail_s, int32_t O, int32_t E, int32_t S,
     const int32_t *__restrict__ base, double *__restrict__ partial, int32_t n_chunk,
-    float *__restrict__ tau_dump, const float4 *__restrict__ bounds) {
+    float *__restrict__ tau_dump, const float4 *__restrict__ bounds, ListRuns runs) {
   constexpr int CHUNK = 64 * SPL;
   extern __shared__ int lds[];
   const int lane = threadIdx.x;
-  const int wv = (int)blockIdx.x;
+  // the wavefront's run of the list, and its place among the run's wavefronts
+  const int run = (int)blockIdx.x & (runs.n - 1), wv = (int)blockIdx.x >> runs.log;
+  list += (size_t)run * runs.per * E;
   // per-class constants in LDS; then, for ranges longer than a wavefront, M
   // and the thresholds of the range
   double *c_rcp = reinterpret_cast<double *>(lds);
@@ -2503,18 +2541,20 @@ __global__ __launch_bounds__(64) void k_score_excl(
   // next item's.)
   int vz;
   asm volatile("v_mov_b32 %0, 0" : "=v"(vz));
-  const int W = (int)gridDim.x;
+  const int W = ((int)gridDim.x - run + runs.n - 1) >> runs.log;
   // Item it = j * n_chunk + c: chunk c of the tile in place j of the work
   // list (every order's live tiles, longest replica range first).  Items go
   // to the wavefronts in serpentine order: wavefront w takes items w,
   // 2W - 1 - w, 2W + w, 4W - 1 - w, ..., so the wavefronts with the
   // heaviest first items get the lightest second ones.  Positions carry the
   // parity of their round; the two steps are kept as (places, chunks).
-  struct Pos { int64_t j; int c; int odd; };
-  const int64_t n_list = (int64_t)O * E;
-  const int64_t d_even = 2 * (int64_t)W - 1 - 2 * wv, d_odd = 2 * (int64_t)wv + 1;
-  const int64_t sj0 = d_even / n_chunk, sj1 = d_odd / n_chunk;
-  const int sc0 = (int)(d_even - sj0 * n_chunk), sc1 = (int)(d_odd - sj1 * n_chunk);
+  // Everything in 32 bits (at most 2^31 tiles, steps of at most 2^21): the
+  // 64-bit divisions were 0.3 us of every wavefront's start.
+  struct Pos { uint32_t j; int c; int odd; };
+  const uint32_t n_list = (uint32_t)max(min(runs.per, O - run * runs.per), 0) * (uint32_t)E;
+  const uint32_t d_even = 2u * (uint32_t)W - 1u - 2u * (uint32_t)wv, d_odd = 2u * (uint32_t)wv + 1u;
+  const uint32_t sj0 = d_even / (uint32_t)n_chunk, sj1 = d_odd / (uint32_t)n_chunk;
+  const int sc0 = (int)(d_even - sj0 * (uint32_t)n_chunk), sc1 = (int)(d_odd - sj1 * (uint32_t)n_chunk);
   auto advance = [&](Pos q) {
     q.j += q.odd ? sj1 : sj0;
     q.c += q.odd ? sc1 : sc0;
@@ -2803,7 +2843,7 @@ __global__ __launch_bounds__(64) void k_score_excl(
 
   // Items a (current), m (next) and n (second next).
   Pos pa;
-  pa.j = wv / n_chunk;
+  pa.j = (uint32_t)wv / (uint32_t)n_chunk;
   pa.c = wv - (int)pa.j * n_chunk;
   pa.odd = 0;
   ScoreItem<SPL> A, B, C;
@@ -3039,14 +3079,16 @@ __device__ __forceinline__ uint64_t wave_ext_u64(uint64_t v) {
 // defines -- then the same over the wavefronts' results.
 constexpr int kFinalizeMaxWaves = 16;
 
-// Returns the best candidate (thread 0; -1: none).  score and gap_now may be
-// null.  Block-synchronises once.
-__device__ __forceinline__ int finalize_order(int o, const TileInfo *__restrict__ tiles, int32_t E, int32_t S,
-                                              const int32_t *__restrict__ base, const double *__restrict__ partial,
-                                              int64_t n_partial, double *__restrict__ score,
-                                              double *__restrict__ gap_now, uint64_t *s_key, uint64_t *s_tie) {
+//
+// finalize_scan: wavefront `wave` of the nw that share an order, its best
+// keys to s_key and s_tie; score and gap_now may be null.  After a block
+// barrier finalize_pick gives the best candidate (-1: none).
+__device__ __forceinline__ void finalize_scan(int o, int wave, int nw, const TileInfo *__restrict__ tiles, int32_t E,
+                                              int32_t S, const int32_t *__restrict__ base,
+                                              const double *__restrict__ partial, int64_t n_partial,
+                                              double *__restrict__ score, double *__restrict__ gap_now,
+                                              uint64_t *s_key, uint64_t *s_tie) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const double gap = (double)__int_as_float(base[o * 2 + 1]) - (double)__int_as_float(base[o * 2 + 0]);
   int p2 = 1;
   while (p2 < n_partial) p2 <<= 1;
@@ -3102,20 +3144,18 @@ __device__ __forceinline__ int finalize_order(int o, const TileInfo *__restrict_
     s_key[wave] = kmax;
     s_tie[wave] = tmin;
   }
-  __syncthreads();
-  int best = -1;
-  if (threadIdx.x == 0) {
-    uint64_t K = 0, T = ~0ull;
-    for (int w = 0; w < nw; ++w) {
-      if (s_key[w] > K || (s_key[w] == K && s_tie[w] < T)) {
-        K = s_key[w];
-        T = s_tie[w];
-      }
+  if (gap_now && wave == 0 && lane == 0) gap_now[o] = gap;
+}
+
+__device__ __forceinline__ int finalize_pick(int nw, const uint64_t *s_key, const uint64_t *s_tie) {
+  uint64_t K = 0, T = ~0ull;
+  for (int w = 0; w < nw; ++w) {
+    if (s_key[w] > K || (s_key[w] == K && s_tie[w] < T)) {
+      K = s_key[w];
+      T = s_tie[w];
     }
-    best = K != 0 ? (int32_t)(uint32_t)T : -1;
-    if (gap_now) gap_now[o] = gap;
   }
-  return best;
+  return K != 0 ? (int32_t)(uint32_t)T : -1;
 }
 
 __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_finalize_excl(
@@ -3123,8 +3163,10 @@ __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_finalize_excl(
     const double *__restrict__ partial, int64_t n_partial, double *__restrict__ score,
     double *__restrict__ gap_now, int32_t *__restrict__ best) {
   __shared__ uint64_t s_key[kFinalizeMaxWaves], s_tie[kFinalizeMaxWaves];
-  const int b = finalize_order(blockIdx.x, tiles, E, S, base, partial, n_partial, score, gap_now, s_key, s_tie);
-  if (threadIdx.x == 0 && best) best[blockIdx.x] = b;
+  const int nw = blockDim.x >> 6;
+  finalize_scan(blockIdx.x, threadIdx.x >> 6, nw, tiles, E, S, base, partial, n_partial, score, gap_now, s_key, s_tie);
+  __syncthreads();
+  if (threadIdx.x == 0 && best) best[blockIdx.x] = finalize_pick(nw, s_key, s_tie);
 }
 
 // Scores and best candidate, many partials per tile: one wavefront per
@@ -3375,13 +3417,14 @@ __global__ __launch_bounds__(kCertThreads) void k_certify_reg(DevProblem P, cons
   const float *gc = (R == 0 ? cap_lo : cap_hi) + off, *gt = (R == 0 ? tail_hi : tail_lo) + off;
   const int c0 = min(lane, P.N - 1), c1 = min(lane + kWave, P.N - 1);
   const float a0 = gc[c0], a1 = gc[c1], l0 = gt[c0], l1 = gt[c1];
-  reg_stage(P, LV, X);
+  RegSolver<KP, NTP> S;
+  S.begin(P);
+  reg_stage(P, LV, X, threadIdx.x, kCertThreads);
   if (lane == 0) cells[P.N] = 0.0f;
   __syncthreads();
   cells[c0] = l0 <= X.slo[c0] ? a0 : 0.0f;
   cells[c1] = l1 <= X.slo[c1] ? a1 : 0.0f;
   for (int c = lane + 2 * kWave; c < P.N; c += kWave) cells[c] = gt[c] <= X.slo[c] ? gc[c] : 0.0f;
-  RegSolver<KP, NTP> S;
   S.init(P, X);
   wave_lds_fence();
   int E[KP];
@@ -3792,9 +3835,10 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lex_reg(DevProblem P, c
   const int nw = blockDim.x >> 6;
   LexCell *V = reinterpret_cast<LexCell *>(reg_mem) + wave * kRegLexCells + kWave;
   RegBatch<SMALL> D(P, cap, tail, n, reg_mem + nw * 4 * kRegLexCells, wave, nw);
+  RegSolver<KP, NTP> S;
+  S.begin(P);
   D.begin(P, LV);
   reg_lex_init(V, lane);
-  RegSolver<KP, NTP> S;
   S.init(P, D.X);
   for (; D.j < n; D.j += D.step) {
     D.load(P);
@@ -4671,50 +4715,13 @@ __device__ __forceinline__ float round_down_f32(double x) {
   return v;
 }
 
-// The refitted bounds of unmeasured cell c of one order.
-struct RefitCell {
-  float cap_lo, tail_lo, tail_hi;
-};
-__device__ __forceinline__ RefitCell refit_cell(const DevProblem &P, int c, const float *cap_lo, const float *cap_hi,
-                                                const float *tail_lo, const float *tail_hi,
-                                                const uint8_t *measured) {
-  const int NT = P.NT, B = P.B;
-  const int b = c % B, t = (c / B) % NT, row = c - b - t * B;  // row: the class's first cell
-  RefitCell out{cap_lo[c], tail_lo[c], tail_hi[c]};
-  // capacity: best measured per-GPU value on each side of t at level b
-  double left = -1.0, right = -1.0;
-  for (int a = 0; a < NT; ++a) {
-    const int ca = row + a * B + b;
-    if (a == t || !measured[ca]) continue;
-    const double q = (double)cap_lo[ca] / (double)P.tp[a];
-    if (a < t) left = fmax(left, q);
-    else right = fmax(right, q);
-  }
-  float lo = out.cap_lo;
-  if (left >= 0.0 && right >= 0.0) lo = fmaxf(lo, round_down_f32((double)P.tp[t] * fmin(left, right)));
-  if (lo <= cap_hi[c]) out.cap_lo = lo;
-  // tail: measured loads below bound it from below, above from above
-  float tl = out.tail_lo, th = out.tail_hi;
-  for (int b2 = 0; b2 < B; ++b2) {
-    const int c2 = row + t * B + b2;
-    if (b2 == b || !measured[c2]) continue;
-    const float v = tail_lo[c2];
-    if (b2 < b) tl = fmaxf(tl, v);
-    else th = fminf(th, v);
-  }
-  if (tl <= th) {
-    out.tail_lo = tl;
-    out.tail_hi = th;
-  }
-  return out;
-}
-
 __global__ __launch_bounds__(256) void k_refit(DevProblem P, const float *__restrict__ cap_lo,
                                                const float *__restrict__ cap_hi, const float *__restrict__ tail_lo,
                                                const float *__restrict__ tail_hi,
                                                const uint8_t *__restrict__ measured, float *cap_lo_out,
                                                float *tail_lo_out, float *tail_hi_out) {
   const size_t off = (size_t)blockIdx.x * P.N;
+  const int NT = P.NT, B = P.B;
   for (int c = threadIdx.x; c < P.N; c += blockDim.x) {
     if (measured[off + c]) {  // unchanged: copied unless refitting in place
       if (cap_lo_out != cap_lo) cap_lo_out[off + c] = cap_lo[off + c];
@@ -4722,10 +4729,36 @@ __global__ __launch_bounds__(256) void k_refit(DevProblem P, const float *__rest
       if (tail_hi_out != tail_hi) tail_hi_out[off + c] = tail_hi[off + c];
       continue;
     }
-    const RefitCell f = refit_cell(P, c, cap_lo + off, cap_hi + off, tail_lo + off, tail_hi + off, measured + off);
-    cap_lo_out[off + c] = f.cap_lo;
-    tail_lo_out[off + c] = f.tail_lo;
-    tail_hi_out[off + c] = f.tail_hi;
+    const int b = c % B, t = (c / B) % NT, row = c - b - t * B;  // row: the class's first cell
+    // capacity: best measured per-GPU value on each side of t at level b
+    double left = -1.0, right = -1.0;
+    for (int a = 0; a < NT; ++a) {
+      const int ca = row + a * B + b;
+      if (a == t || !measured[off + ca]) continue;
+      const double q = (double)cap_lo[off + ca] / (double)P.tp[a];
+      if (a < t) left = fmax(left, q);
+      else right = fmax(right, q);
+    }
+    float lo = cap_lo[off + c];
+    if (left >= 0.0 && right >= 0.0) lo = fmaxf(lo, round_down_f32((double)P.tp[t] * fmin(left, right)));
+    if (lo <= cap_hi[off + c]) cap_lo_out[off + c] = lo;
+    else if (cap_lo_out != cap_lo) cap_lo_out[off + c] = cap_lo[off + c];
+    // tail: measured loads below bound it from below, above from above
+    float tl = tail_lo[off + c], th = tail_hi[off + c];
+    for (int b2 = 0; b2 < B; ++b2) {
+      const int c2 = row + t * B + b2;
+      if (b2 == b || !measured[off + c2]) continue;
+      const float v = tail_lo[off + c2];
+      if (b2 < b) tl = fmaxf(tl, v);
+      else th = fminf(th, v);
+    }
+    if (tl <= th) {
+      tail_lo_out[off + c] = tl;
+      tail_hi_out[off + c] = th;
+    } else {
+      if (tail_lo_out != tail_lo) tail_lo_out[off + c] = tail_lo[off + c];
+      if (tail_hi_out != tail_hi) tail_hi_out[off + c] = tail_hi[off + c];
+    }
   }
 }
 
@@ -4902,7 +4935,11 @@ __global__ void k_loop_output(DevProblem P, LoopDev L, AllocOut meas, const int8
 // their arg-max, the reveal, the refit, the certificate and the decision --
 // so that a round is three launches (this, the scorer's set-up, the scorer)
 // where it was nine or ten, each a few us of latency for a few wavefronts.
-// FIGURES_LOOP
+// All of it is latency: staging 2.9 us (the scores beside it), reveal 0.8,
+// refit 2.0, solver tables 0.9, solve 0.8, allocation and state 0.8 on 4
+// classes at G = 64 with the fit step, 11.1 us traced; 7.5 us on 2 classes
+// without.  Refit loop of 16 trajectories, 36 rounds: 3,456 -> 1,156 us;
+// 200 trajectories of 2 classes, 16 rounds: 614 -> 310 us.
 // ---------------------------------------------------------------------------
 // Where a round's reveal comes from: nothing scored yet; the scores of this
 // block's tiles (at most 16 partials each); best, already found; the fixed
@@ -4927,11 +4964,13 @@ struct LoopRoundArgs {
 // LDS of a block: two wavefronts' solvers, the intervals and revealed flags.
 static size_t loop_lds(const DevProblem &P) { return reg_lds(P, 2) + 4 + 17 * (size_t)P.N; }
 
+constexpr int kLoopMaxWaves = 8;
+
 template <int KP, int NTP>
-__global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_loop_round(DevProblem P, LoopDev L, LoopRoundArgs A,
+__global__ __launch_bounds__(64 * kLoopMaxWaves) void k_loop_round(DevProblem P, LoopDev L, LoopRoundArgs A,
                                                                        const PrepLevels LV) {
   extern __shared__ __attribute__((aligned(16))) float reg_mem[];
-  __shared__ uint64_t s_key[kFinalizeMaxWaves], s_tie[kFinalizeMaxWaves];
+  __shared__ uint64_t s_key[kLoopMaxWaves], s_tie[kLoopMaxWaves];
   __shared__ CertShared C;
   const int o = blockIdx.x, tid = threadIdx.x, nth = blockDim.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -4943,19 +4982,30 @@ __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_loop_round(DevProble
   float *cl = reinterpret_cast<float *>(X.reps + (size_t)kWave * P.NT), *ch = cl + N, *tl = ch + N, *th = tl + N;
   uint8_t *ms = reinterpret_cast<uint8_t *>(th + N);
 
-  // --- the trajectory's intervals (the first round copies the caller's)
-  const float *gcl = (first ? A.cap_lo : L.cap_lo) + off, *gch = (first ? A.cap_hi : L.cap_hi) + off;
-  const float *gtl = (first ? A.tail_lo : L.tail_lo) + off, *gth = (first ? A.tail_hi : L.tail_hi) + off;
-  const uint8_t *gms = (first ? A.measured : L.measured) + off;
-  for (int c = tid; c < N; c += nth) {
-    const float a = gcl[c], b = gch[c], l = gtl[c], h = gth[c];
-    const uint8_t m = gms[c];
-    cl[c] = a; ch[c] = b; tl[c] = l; th[c] = h;
-    ms[c] = m;
-    if (first) {
-      L.cap_lo[off + c] = a; L.cap_hi[off + c] = b; L.tail_lo[off + c] = l; L.tail_hi[off + c] = h;
-      L.measured[off + c] = m;
+  // --- wavefronts 0 and 1: the trajectory's intervals (the first round
+  // copies the caller's) and what the solvers share; the others: the last
+  // round's scores and their arg-max
+  RegSolver<KP, NTP> S;
+  S.begin(P);
+  if (wave < 2) {
+    const float *gcl = (first ? A.cap_lo : L.cap_lo) + off, *gch = (first ? A.cap_hi : L.cap_hi) + off;
+    const float *gtl = (first ? A.tail_lo : L.tail_lo) + off, *gth = (first ? A.tail_hi : L.tail_hi) + off;
+    const uint8_t *gms = (first ? A.measured : L.measured) + off;
+    for (int c = tid; c < N; c += kCertThreads) {
+      const float a = gcl[c], b = gch[c], l = gtl[c], h = gth[c];
+      const uint8_t m = gms[c];
+      cl[c] = a; ch[c] = b; tl[c] = l; th[c] = h;
+      ms[c] = m;
+      if (first) {
+        L.cap_lo[off + c] = a; L.cap_hi[off + c] = b; L.tail_lo[off + c] = l; L.tail_hi[off + c] = h;
+        L.measured[off + c] = m;
+      }
     }
+    reg_stage(P, LV, X, tid, kCertThreads);
+    if (tid < 2) reg_mem[tid * reg_cells(N) + N] = 0.0f;
+  } else if (A.pick == kPickScores) {
+    finalize_scan(o, wave - 2, (nth >> 6) - 2, A.tiles, E, A.S, A.base, A.partial, A.n_partial, nullptr, nullptr,
+                  s_key, s_tie);
   }
   if (first) {
     if (tid == 0) {
@@ -4966,14 +5016,11 @@ __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_loop_round(DevProble
     }
     for (int j = tid; L.reveals && j < L.max_rounds; j += nth) L.reveals[(size_t)o * L.max_rounds + j] = -1;
   }
-  reg_stage(P, LV, X);
-  if (tid < 2) reg_mem[tid * reg_cells(N) + N] = 0.0f;
 
   // --- this round's reveal
   int pick = -1;
-  if (A.pick == kPickScores)
-    pick = finalize_order(o, A.tiles, E, A.S, A.base, A.partial, A.n_partial, nullptr, nullptr, s_key, s_tie);
   __syncthreads();
+  if (A.pick == kPickScores && tid == 0) pick = finalize_pick((nth >> 6) - 2, s_key, s_tie);
   if (A.pick == kPickBest) pick = L.best[o];
   if (A.pick == kPickOrder && wave == 0) {
     for (int j0 = 0; j0 < E && pick < 0; j0 += kWave) {
@@ -4984,7 +5031,6 @@ __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_loop_round(DevProble
       if (m) pick = __shfl(e, __builtin_ctzll(m), kWave);
     }
   }
-  __syncthreads();
   if (tid == 0 && pick >= 0 && pick < E) {
     const int cell = A.cand[pick];
     if (cell >= 0 && cell < N) {
@@ -5003,21 +5049,60 @@ __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_loop_round(DevProble
   }
   __syncthreads();
 
-  // --- the refit, in place in LDS: a thread reads measured cells, which no
-  // thread writes, and its own cell
+  // --- the refit, in place in LDS (measured cells are read, unmeasured ones
+  // written): a thread per (class, level) for the capacities, whose TP
+  // degrees share their quotients, and a thread per cell for the tails
   if (A.r_cap_lo) {
-    for (int c = tid; c < N; c += nth) {
-      if (!ms[c]) {
-        const RefitCell f = refit_cell(P, c, cl, ch, tl, th, ms);
-        cl[c] = f.cap_lo;
-        tl[c] = f.tail_lo;
-        th[c] = f.tail_hi;
+    const int B = P.B, NT = P.NT;
+    for (int x = tid; x < P.K * B; x += nth) {
+      const int k = x / B, b = x - k * B;
+      float lo[NTP], hi[NTP];
+      double q[NTP];
+      bool m[NTP];
+#pragma unroll
+      for (int t = 0; t < NTP; ++t) {
+        const int c = (k * NT + min(t, NT - 1)) * B + b;
+        lo[t] = cl[c];
+        hi[t] = ch[c];
+        m[t] = ms[c] && t < NT;
+        q[t] = m[t] ? (double)lo[t] / (double)P.tp[min(t, NT - 1)] : -1.0;
       }
+#pragma unroll
+      for (int t = 0; t < NTP; ++t) {
+        double left = -1.0, right = -1.0;
+#pragma unroll
+        for (int a = 0; a < NTP; ++a) {
+          if (a < t) left = fmax(left, q[a]);
+          if (a > t) right = fmax(right, q[a]);
+        }
+        if (t < NT && !m[t] && left >= 0.0 && right >= 0.0) {
+          const float v = fmaxf(lo[t], round_down_f32((double)P.tp[t] * fmin(left, right)));
+          if (v <= hi[t]) cl[(k * NT + t) * B + b] = v;
+        }
+      }
+    }
+    for (int c = tid; c < N; c += nth) {
+      const int b = c % B, row = c - b;
+      float l = tl[c], h = th[c];
+      const bool own = !ms[c];
+#pragma unroll 4
+      for (int b2 = 0; b2 < B; ++b2) {
+        const float v = tl[row + b2];
+        const bool use = ms[row + b2] != 0;
+        l = use && b2 < b ? fmaxf(l, v) : l;
+        h = use && b2 > b ? fminf(h, v) : h;
+      }
+      if (own && l <= h) {
+        tl[c] = l;
+        th[c] = h;
+      }
+    }
+    __syncthreads();
+    for (int c = tid; c < N; c += nth) {
       A.r_cap_lo[off + c] = cl[c];
       A.r_tail_lo[off + c] = tl[c];
       A.r_tail_hi[off + c] = th[c];
     }
-    __syncthreads();
     for (int e = tid; A.bounds && e < E; e += nth) {
       const int c = A.cand[e];
       if (c >= 0 && c < N) A.bounds[(size_t)o * E + e] = make_float4(cl[c], ch[c], tl[c], th[c]);
@@ -5034,7 +5119,6 @@ __global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_loop_round(DevProble
     float *cells = reg_mem + wave * reg_cells(N);
     for (int c = lane; c < N; c += kWave)
       cells[c] = (wave == 0 ? th[c] : tl[c]) <= X.slo[c] ? (wave == 0 ? cl[c] : ch[c]) : 0.0f;
-    RegSolver<KP, NTP> S;
     S.init(P, X);
     wave_lds_fence();
     int T[KP];
@@ -5079,7 +5163,9 @@ __global__ __launch_bounds__(kCertThreads) void k_loop_end(DevProblem P, LoopDev
   const int N = P.N;
   const size_t off = (size_t)o * N;
   const RegShared X = reg_shared(P, reg_mem + 2 * reg_cells(N));
-  reg_stage(P, LV, X);
+  RegSolver<KP, NTP> S;
+  S.begin(P);
+  reg_stage(P, LV, X, threadIdx.x, kCertThreads);
   float *cells = reg_mem + wave * reg_cells(N);
   if (lane == 0) cells[N] = 0.0f;
   __syncthreads();
@@ -5087,7 +5173,6 @@ __global__ __launch_bounds__(kCertThreads) void k_loop_end(DevProblem P, LoopDev
     const bool use = wave == 0 ? L.measured[off + c] && L.tail_hi[off + c] <= X.slo[c] : truth_tail[off + c] <= X.slo[c];
     cells[c] = use ? (wave == 0 ? L.cap_lo : truth_cap)[off + c] : 0.0f;
   }
-  RegSolver<KP, NTP> S;
   S.init(P, X);
   wave_lds_fence();
   int T[KP];
@@ -5324,7 +5409,7 @@ constexpr size_t kPrepGeneralLdsLimit = 156 * 1024;
 
 // LDS of the one-block-per-order set-up: the larger of a class block's and
 // the work-list block's.
-static size_t prep_order_lds(const DevProblem &P, int64_t O, int64_t E) {
+static size_t prep_order_lds(const DevProblem &P, int64_t O, int64_t E) {  // O: of the longest list run
   const size_t K = P.K, G = P.G, N = P.N, pc = (size_t)P.NT * P.B;
   const size_t nw = 2 * K <= 16 ? 2 * K : K;  // wavefronts with a per-wavefront area
   const size_t cls = 4 * (2 * N + 2 * K * G + (size_t)E + nw * 3 * pc) + ((N + 3) & ~(size_t)3) + K * G;
@@ -5334,6 +5419,22 @@ static size_t prep_order_lds(const DevProblem &P, int64_t O, int64_t E) {
 
 static bool prep_order_fits(const DevProblem &P, int64_t O, int64_t E) {
   return P.G <= kPrepOrderMaxG && P.K <= kPrepOrderMaxK && prep_order_lds(P, O, E) <= kPrepLdsLimit;
+}
+
+// Runs of the work list: one block builds about 2,400 entries while a class
+// block of the set-up runs; at most 8, no more than there are orders or
+// wavefronts of the scorer (every run has at least one).
+constexpr int kListRuns = 8, kListRunTiles = 2400;
+static ListRuns list_runs(const DevProblem &P, const ScoreArgs &a) {
+  // the unstaged list block of the general set-up takes every order
+  const bool staged = (a.setup == 0 && prep_order_fits(P, a.O, a.E)) || prep_list_lds(P, a.O, a.E) <= kPrepGeneralLdsLimit;
+  int64_t n = staged ? ((int64_t)a.O * a.E + kListRunTiles - 1) / kListRunTiles : 1;
+  if (n > kListRuns) n = kListRuns;
+  if (n > a.O) n = a.O;
+  if (a.waves > 0 && n > a.waves) n = a.waves;
+  int log = 0;
+  while ((2 << log) <= n) ++log;
+  return ListRuns{log, 1 << log, (a.O + (1 << log) - 1) >> log};
 }
 
 // Options per (order, realisation): one per (class, TP, r).
@@ -5457,7 +5558,7 @@ static hipError_t launch_floor_score(const DevProblem &P, const ScoreArgs &a, in
     }                                                                                                             \
     k_prep<true, TH, true><<<grid, TH, lds, s>>>(P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, a.measured, a.cand, \
                                                  a.E, 0, nullptr, tiles, base, mopt, nullptr, n_thr, nullptr,     \
-                                                 nullptr, a.thr_search, 0, btab, F);                              \
+                                                 a.thr_search, 0, ListRuns{0, 1, 1}, btab, F);                         \
   }
   // the block sizes of the set-up without floors, whose blocks are alike
   if (P.G >= kPrepWideBudget) FS_PREP_FLOOR(kPrepThreadsWide)
@@ -5491,7 +5592,7 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
   int32_t *mopt = (int32_t *)(a.ws + a.L.mopt);
   float *thr = (float *)(a.ws + a.L.thr);
   int4 *list = (int4 *)(a.ws + a.L.list);
-  int32_t *live = (int32_t *)(a.ws + a.L.live);
+  const ListRuns runs = list_runs(P, a);
   const int32_t n_thr = excl_thresholds(P);
   const int dump = a.tau_dump != nullptr;
   const size_t small = prep_lds_small(P), big = small + prep_lds_tables(P);
@@ -5500,9 +5601,10 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
     // compiled for the rank step's table count rounded up to 4, 8 or 16
     // and for at most 4 or 8 TP degrees (loops over them are unrolled)
 #define FS_PREP_ORDER(KP, NTP)                                                                                    \
-  k_prep_order<KP, NTP><<<2 * a.O + 1, prep_order_waves(P, a.O, a.E) * kWave, prep_order_lds(P, a.O, a.E), s>>>(    \
+  k_prep_order<KP, NTP><<<2 * a.O + runs.n, prep_order_waves(P, runs.per, a.E) * kWave,                              \
+                          prep_order_lds(P, runs.per, a.E), s>>>(                                                    \
     P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, a.measured, a.cand, a.E, a.O, dump, tiles, base, mopt, thr,  \
-    n_thr, list, live, a.thr_search, LV)
+    n_thr, list, runs, a.thr_search, LV)
 #define FS_PREP_ORDER_K(NTP)                  \
   if (P.K <= 4) FS_PREP_ORDER(4, NTP);        \
   else if (P.K <= 8) FS_PREP_ORDER(8, NTP);   \
@@ -5538,8 +5640,8 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
       if (e != hipSuccess) return e;                                                                              \
     }                                                                                                             \
     k_prep<LDS, TH, false><<<grid, TH, lds, s>>>(P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, a.measured, a.cand, \
-                                                 a.E, dump, gtab, tiles, base, mopt, thr, n_thr, list, live,      \
-                                                 a.thr_search, staged, btab, F);                                  \
+                                                 a.E, dump, gtab, tiles, base, mopt, thr, n_thr, list,            \
+                                                 a.thr_search, staged, runs, btab, F);                            \
   }
     // below a budget of 512: 256 threads per block once the class blocks
     // fill the GPU (more blocks resident at a time; 8 classes at G = 256
@@ -5606,6 +5708,7 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
     float *thr = (float *)(a.ws + a.L.thr);
     int4 *list = (int4 *)(a.ws + a.L.list);
     const int32_t n_thr = excl_thresholds(P);
+    ListRuns runs = list_runs(P, a);
     hipError_t es = launch_excl_setup(P, a, s);
     if (es != hipSuccess) return es;
     if (a.E == 0) {
@@ -5622,14 +5725,14 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
                         (range_max >= kWave ? 4 * sizeof(int) * (size_t)range_max : 0);
     const int64_t items = n_partial * a.O * a.E;  // upper bound of the live items
     const int64_t waves = a.waves > 0 ? a.waves : kScorerWaves;
-    const unsigned grid = (unsigned)(items < waves ? items : waves);
+    const unsigned grid = (unsigned)(items < waves ? items : waves);  // at least runs.n
     const int launches = a.ev_begin ? a.timing_launches : 1;
     if (a.ev_begin) (void)hipEventRecord(a.ev_begin, s);
     for (int rep = 0; rep < launches; ++rep) {
 #define FS_EXCL_LAUNCH(SP, VEC, DUMP, CLAMP)                                                               \
   k_score_excl<SP, VEC, DUMP, CLAMP><<<grid, kWave, mlds, s>>>(P, tiles, mopt, thr, n_thr, list, a.cap_s,  \
                                                                a.tail_s, a.O, a.E, a.S, base, partial,     \
-                                                               (int32_t)n_partial, a.tau_dump, a.bounds)
+                                                               (int32_t)n_partial, a.tau_dump, a.bounds, runs)
 #define FS_EXCL_SPL(SP)                                         \
   if (a.bounds) {                                               \
     if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, false, true);    \
@@ -6118,9 +6221,9 @@ hipError_t launch_loop_round(const DevProblem &P, const LoopDev &L, const ScoreA
   A.O = a.O; A.E = a.E; A.S = a.S; A.eps = eps;
   A.n_partial = a.E > 0 && a.S > 0 ? excl_partials(a) : 0;
   A.pick = iv || a.E == 0 ? kPickNone : policy != 0 ? kPickOrder : !scored ? kPickNone : a.no_finalize ? kPickScores : kPickBest;
-  // at least the two solving wavefronts, and one per 128 candidates' scores
-  const int want = (a.E + 2 * kWave - 1) / (2 * kWave);
-  const int nw = want < 2 ? 2 : want > kFinalizeMaxWaves ? kFinalizeMaxWaves : want;
+  // the two solving wavefronts, and one per 128 candidates' scores
+  const int want = 2 + (a.E + 2 * kWave - 1) / (2 * kWave);
+  const int nw = want > kLoopMaxWaves ? kLoopMaxWaves : want;
   const PrepLevels LV = prep_levels(P);
   const size_t lds = loop_lds(P);
 #define FS_LOOP_ROUND(KP, NTP) k_loop_round<KP, NTP><<<a.O, kWave * nw, lds, s>>>(P, L, A, LV);

@@ -1,0 +1,36 @@
+"""The exclusion scorer's work list in several runs of orders: the same scores
+as full re-solves (the lane kernel), whatever the runs and the grid."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2608_19659_amd.synth import make_workload
+from test_gpu_parity import env, gpu_score  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("O", [50, 51, 101, 150, 200])  # 1 (2,400 tiles), 2, 4, and runs that do not divide O
+@pytest.mark.parametrize("setup,waves", [(0, 0), (0, 1), (0, 3), (1, 0), (1, 5)])
+def test_list_runs_agree_with_full_solves(env, O, setup, waves):  # noqa: F811
+    torch, fs, ctx = env
+    w = make_workload("paper-shaped-2class-G16", orders=list(range(O)), with_samples=False)
+    S = 20
+    rng = np.random.default_rng(O)
+    lo, hi = w.intervals.cap_lo[:, w.cand, None], w.intervals.cap_hi[:, w.cand, None]
+    tl, th = w.intervals.tail_lo[:, w.cand, None], w.intervals.tail_hi[:, w.cand, None]
+    shape = (O, len(w.cand), S)
+    cs = (lo + (hi - lo) * rng.random(shape)).astype(np.float32)
+    ts = (tl + (th - tl) * rng.random(shape)).astype(np.float32)
+    print(f"[gpu] list runs O={O} setup={setup} waves={waves}", file=sys.stderr, flush=True)
+    ctx.set_option(fs.OPT_SETUP, setup)
+    ctx.set_option(fs.OPT_SCORER_WAVES, waves)
+    try:
+        g = gpu_score(env, w.problem, w.intervals, w.cand, cs, ts, kernel=3)
+    finally:
+        ctx.set_option(fs.OPT_SETUP, 0)
+        ctx.set_option(fs.OPT_SCORER_WAVES, 0)
+    full = gpu_score(env, w.problem, w.intervals, w.cand, cs, ts, kernel=2)
+    for a, b, name in zip(g, full, ("score", "gap_now", "best", "tau_dump")):
+        np.testing.assert_array_equal(a, b, err_msg=name)
