@@ -692,17 +692,25 @@ fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv,
                                 (int32_t)policy, score, stream);
       if (e != hipSuccess) return hip_fail(e, "loop round launch");
       if (rnd == max_rounds) break;
-      if (check_every > 0 && rnd > 0 && rnd % check_every == 0) {
-        e = fs::launch_loop_count(D, n_orders, stream);
-        if (e == hipSuccess)
-          e = hipMemcpyAsync(ctx->pinned, D.n_running, sizeof(int32_t), hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
-        if (e != hipSuccess) return hip_fail(e, "loop progress read-back");
-        if (*ctx->pinned == 0) break;
+      // the running trajectories are counted into the pinned word, and the
+      // round's scoring is enqueued before the host waits for the count, so
+      // that the GPU has work while the host wakes up
+      const bool check = check_every > 0 && rnd > 0 && rnd % check_every == 0;
+      if (check) {
+        fs::LoopDev Dc = D;
+        Dc.n_running = ctx->pinned;
+        e = fs::launch_loop_count(Dc, n_orders, stream);
+        if (e == hipSuccess) e = hipEventRecord(ctx->fork, stream);
+        if (e != hipSuccess) return hip_fail(e, "loop progress count");
       }
       if (score) {
         e = fs::launch_score(P, a, stream);
         if (e != hipSuccess) return hip_fail(e, "loop score launch");
+      }
+      if (check) {
+        e = hipEventSynchronize(ctx->fork);
+        if (e != hipSuccess) return hip_fail(e, "loop progress read-back");
+        if (*(volatile int32_t *)ctx->pinned == 0) break;
       }
     }
     e = fs::launch_loop_end(P, D, d_truth_cap, d_truth_tail, n_orders, to_out(out.final_alloc), out.tau_truth,
