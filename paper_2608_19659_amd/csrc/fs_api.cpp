@@ -950,7 +950,7 @@ fs_status fs_certify_lex(fs_context *ctx, const fs_problem *p, fs_intervals iv, 
     st = read_flags(L, ws, stream, "fs_certify_lex");
     if (st != FS_OK) return st;
   }
-  e = fs::launch_setup(P, nullptr, 0, ws, L, stream);
+  e = fs::reg_solver_supported(P) ? hipSuccess : fs::launch_setup(P, nullptr, 0, ws, L, stream);
   if (e != hipSuccess) return hip_fail(e, "set-up launch");
   e = fs::launch_certify_lex(P, iv.cap_lo, iv.cap_hi, iv.tail_lo, iv.tail_hi, iv.measured, n_orders, eps, d_state,
                              to_out(cons), to_out(opt), d_gap_maxmin, d_gap_goodput, ws, L, stream);

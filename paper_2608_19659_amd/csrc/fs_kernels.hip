@@ -3270,20 +3270,22 @@ __global__ __launch_bounds__(64) void k_finalize(DevProblem P, const CandInfo *_
 // allocation misses a floor; 1 when the conservative allocation meets the
 // floors, every cell it commits to is measured with its tail upper bound
 // within the SLO, and the gap is within eps; 0 otherwise.
-__device__ __forceinline__ int certificate_state(const DevProblem &P, const int8_t *__restrict__ bmap,
-                                                 const uint8_t *__restrict__ measured,
+//
+// Every lane of a wavefront calls it, lane k for class k; the cell's load
+// level comes from the problem.
+__device__ __forceinline__ int certificate_state(const DevProblem &P, const uint8_t *__restrict__ measured,
                                                  const float *__restrict__ tail_hi, size_t off, int fm_m,
                                                  int fm_p, const int *tm_index, const int *tm_rep,
                                                  bool gap_ok) {
   if (P.has_floor && !fm_p) return 2;
-  bool ok = fm_m != 0;
-  for (int k = 0; k < P.K && ok; ++k) {
-    const int r = tm_rep[k];
-    if (r == 0) continue;
-    const int cell = cell_of(P, k, tm_index[k], bmap[k * (P.G + 1) + r]);
-    if (!measured[off + cell]) ok = false;
-    else if (!(tail_hi[off + cell] <= P.slo[k])) ok = false;
+  const int k = min((int)(threadIdx.x & (kWave - 1)), P.K - 1);
+  const int r = tm_rep[k];
+  bool bad = false;
+  if (r > 0) {
+    const int cell = cell_of(P, k, tm_index[k], max(level_of(P, k, r), 0));
+    bad = !measured[off + cell] || !(tail_hi[off + cell] <= P.slo[k]);
   }
+  const bool ok = fm_m != 0 && __builtin_amdgcn_ballot_w64(bad) == 0;
   return (ok && gap_ok) ? 1 : 0;
 }
 
@@ -3353,28 +3355,27 @@ __global__ __launch_bounds__(64) void k_certify(DevProblem P, const int8_t *__re
 // Gap and state of each order from its two records: the max-min gap
 // tau+ - tau-, and with lex the goodput gap |gp+ - gp-| / max(gp+, gp-) (0
 // when both are 0) of level (3)'s totals; within eps means every stage is.
-__global__ __launch_bounds__(64) void k_certify_state(DevProblem P, const int8_t *__restrict__ bmap,
-                                                      const float *__restrict__ tail_hi,
+__global__ __launch_bounds__(64) void k_certify_state(DevProblem P, const float *__restrict__ tail_hi,
                                                       const uint8_t *__restrict__ measured, float eps,
                                                       const CertRec *__restrict__ rec, int lex,
                                                       int32_t *__restrict__ state, double *__restrict__ gap_mm_out,
                                                       double *__restrict__ gap_gp_out) {
   const int o = blockIdx.x;
-  if (threadIdx.x != 0) return;
+  const bool out = threadIdx.x == 0;
   const size_t off = (size_t)o * P.N;
   const CertRec *m = rec + (size_t)o * 2, *p = m + 1;
   const double gap_mm = (double)__int_as_float(p->tau) - (double)__int_as_float(m->tau);
   bool ok = gap_mm <= (double)eps;
-  if (gap_mm_out) gap_mm_out[o] = gap_mm;
+  if (out && gap_mm_out) gap_mm_out[o] = gap_mm;
   if (lex) {
     const double g64_m = m->goodput64, g64_p = p->goodput64;
     const double top = g64_p > g64_m ? g64_p : g64_m;
     const double gap_gp = top > 0.0 ? fabs(g64_p - g64_m) / top : 0.0;
-    if (gap_gp_out) gap_gp_out[o] = gap_gp;
+    if (out && gap_gp_out) gap_gp_out[o] = gap_gp;
     ok = ok && gap_gp <= (double)eps;
   }
-  state[o] = certificate_state(P, bmap, measured, tail_hi, off, m->floors_met, p->floors_met, m->tp_index,
-                               m->replicas, ok);
+  const int st = certificate_state(P, measured, tail_hi, off, m->floors_met, p->floors_met, m->tp_index, m->replicas, ok);
+  if (out) state[o] = st;
 }
 
 // The certificate by the register solver, one block per order: wavefront 0
@@ -3888,6 +3889,64 @@ __global__ __launch_bounds__(64) void k_solve_dense_lex(DevProblem P, const int8
   if (gp64_out && threadIdx.x == 0) gp64_out[j] = gp64;
 }
 
+// One order's two realisations under the whole objective by the register
+// solver and stage: wavefront 0 the conservative one, wavefront 1 the
+// optimistic one (any further wavefronts only help to stage), their records
+// to rec[2 o], rec[2 o + 1].  mem: two layers, two wavefronts' cells, then
+// what they share.  The allocations may be null.
+inline size_t reg_cert_lex_lds(const DevProblem &P) { return 2 * sizeof(LexCell) * kRegLexCells + reg_lds(P, 2); }
+
+template <int KP, int NTP>
+__device__ __forceinline__ void reg_certify_lex(const DevProblem &P, int o, const float *cap_lo, const float *cap_hi,
+                                                const float *tail_lo, const float *tail_hi, const AllocOut &cons,
+                                                const AllocOut &opt, CertRec *rec, const PrepLevels &LV, float *mem) {
+  const int lane = threadIdx.x & (kWave - 1), R = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t off = (size_t)o * P.N;
+  float *cells = mem + 2 * 4 * kRegLexCells + min(R, 1) * reg_cells(P.N);
+  const RegShared X = reg_shared(P, mem + 2 * 4 * kRegLexCells + 2 * reg_cells(P.N));
+  RegSolver<KP, NTP> S;
+  S.begin(P);
+  reg_stage(P, LV, X, threadIdx.x, blockDim.x);
+  __syncthreads();
+  if (R >= 2) return;
+  LexCell *V = reinterpret_cast<LexCell *>(mem) + R * kRegLexCells + kWave;
+  const float *gc = (R == 0 ? cap_lo : cap_hi) + off, *gt = (R == 0 ? tail_hi : tail_lo) + off;
+#pragma unroll 2
+  for (int c = lane; c < P.N; c += kWave) cells[c] = gt[c] <= X.slo[c] ? gc[c] : 0.0f;
+  if (lane == 0) cells[P.N] = 0.0f;
+  reg_lex_init(V, lane);
+  S.init(P, X);
+  wave_lds_fence();
+  int E[KP];
+  const int tau = S.solve(P, cells, E);
+  double g64;
+  const RegAlloc A = reg_lex_stage<KP, NTP>(P, S, cells, X, V, tau, &g64);
+  const float gp = S.goodput(A);
+  write_reg_alloc(R == 0 ? cons : opt, o, P.K, tau, gp, A, lane);
+  CertRec *me = rec + (size_t)o * 2 + R;
+  if (lane == 0) {
+    me->tau = tau;
+    me->floors_met = 1;
+    me->goodput = gp;
+    me->goodput64 = g64;
+  }
+  if (lane < P.K) {
+    me->tp_index[lane] = A.ti;
+    me->replicas[lane] = A.r;
+  }
+}
+
+template <int KP, int NTP>
+__global__ __launch_bounds__(kCertThreads) void k_certify_lex_reg(DevProblem P, const float *__restrict__ cap_lo,
+                                                                  const float *__restrict__ cap_hi,
+                                                                  const float *__restrict__ tail_lo,
+                                                                  const float *__restrict__ tail_hi, AllocOut cons,
+                                                                  AllocOut opt, CertRec *__restrict__ rec,
+                                                                  const PrepLevels LV) {
+  extern __shared__ __attribute__((aligned(16))) float reg_mem[];
+  reg_certify_lex<KP, NTP>(P, blockIdx.x, cap_lo, cap_hi, tail_lo, tail_hi, cons, opt, rec, LV, reg_mem);
+}
+
 // Certificate with the stage-wise gap: both allocations under the whole
 // objective; max-min gap tau+ - tau-, goodput gap |gp+ - gp-| / max(gp+,
 // gp-) (0 when both are 0); within eps means both stages are.  Block (R, o)
@@ -4063,6 +4122,8 @@ constexpr int kLexPrepThreads = 256;
 // 12288 and 16384).
 constexpr int kLexTableWaves = 12288;
 
+constexpr int kLexRankMax = 2 * kLexPrepThreads;  // keys the breakpoints sort by rank
+
 // Keys the breakpoint sort takes: every option's ratio and the 0, padded to
 // a power of two (at least one per thread).
 __host__ __device__ inline int lex_sort_keys(int nopt) {
@@ -4151,15 +4212,14 @@ __device__ __forceinline__ void bitonic_regs(int *keys, int n2, int tid) {
 // Per (realisation R, order o), one block of kLexPrepThreads threads: every
 // option of every class (ratio bits, -1 when no load level holds it; served
 // rate) to opt_out, and the sorted distinct ratios, 0 always among them, to
-// bp_out (nb of them to nbp).  The ratios are sorted by a bitonic network in
-// LDS, then each first occurrence is placed by a block-wide count of the
-// ones before it.  Load levels come from the problem (the bucket map's
+// bp_out (nb of them to nbp).  The ratios are sorted in LDS, then each first
+// occurrence is placed by a block-wide count of the ones before it.  Load levels come from the problem (the bucket map's
 // values), so the block does not wait for the map.
 __device__ void lex_breaks_block(const DevProblem &P, int R, int o, const float *__restrict__ cap_lo,
                                  const float *__restrict__ cap_hi, const float *__restrict__ tail_lo,
                                  const float *__restrict__ tail_hi, int32_t nbmax, int2 *__restrict__ opt_out,
                                  float *__restrict__ bp_out, int32_t *__restrict__ nbp) {
-  extern __shared__ int lex_keys[];
+  extern __shared__ __attribute__((aligned(16))) int lex_keys[];
   const int tid = threadIdx.x;
   const int K = P.K, N = P.N, B = P.B, NT = P.NT, per_class = NT * B, PP = P.optoff[NT];
   const int nopt = K * PP, n2 = lex_sort_keys(nopt);
@@ -4212,38 +4272,93 @@ __device__ void lex_breaks_block(const DevProblem &P, int R, int o, const float 
     lex_keys[q] = key;
   }
   __syncthreads();
-  if (n2 == kLexPrepThreads) {
-    bitonic_regs<1>(lex_keys, n2, tid);
-  } else if (n2 == 2 * kLexPrepThreads) {
-    bitonic_regs<2>(lex_keys, n2, tid);
+  // Only the ratios strictly between 0 and 1 need sorting: 0 is always a
+  // breakpoint, and 1 (a class served in full, the commonest ratio) is the
+  // largest.  They are compacted in place (a pass's keys are read before it
+  // writes, below where it read); up to kLexRankMax of them are sorted by
+  // rank -- a thread counts the keys below its own, four to a read, and
+  // equal keys fall on one place, the others' places staying empty -- and
+  // more by a bitonic network.
+  const int one = __float_as_int(1.0f);
+  if (tid < 2) cnt[tid] = 0;
+  __syncthreads();
+  for (int q0 = 0; q0 < n2; q0 += kLexPrepThreads) {
+    const int v = lex_keys[q0 + tid];
+    __syncthreads();
+    const bool mid = v > 0 && v < one;
+    const uint64_t b = __builtin_amdgcn_ballot_w64(mid);
+    int at = 0;
+    if ((tid & (kWave - 1)) == 0 && b != 0) at = atomicAdd(&cnt[0], __builtin_popcountll(b));
+    at = __builtin_amdgcn_readfirstlane(at) +
+         __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0));
+    if (mid) lex_keys[at] = v;
+    if (v == one) cnt[1] = 1;
+    __syncthreads();
+  }
+  const int m = cnt[0], ones = cnt[1];
+  int ns = kLexPrepThreads;  // places, a power of two: 0, the m keys, 1
+  while (ns < m + 2 && ns < n2) ns <<= 1;
+  if (m <= kLexRankMax) {
+    // (past the last key: padding that counts as larger)
+    for (int q = m + tid; q < ((m + 3) & ~3); q += kLexPrepThreads) lex_keys[q] = INT_MAX;
+    __syncthreads();
+    constexpr int kPer = kLexRankMax / kLexPrepThreads;
+    int mine_v[kPer], rank[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int q = tid + u * kLexPrepThreads;
+      mine_v[u] = q < m ? lex_keys[q] : INT_MAX;
+      rank[u] = 0;
+    }
+    for (int q = 0; q < m; q += 4) {
+      const int4 x = *reinterpret_cast<const int4 *>(lex_keys + q);
+#pragma unroll
+      for (int u = 0; u < kPer; ++u)
+        rank[u] += (x.x < mine_v[u]) + (x.y < mine_v[u]) + (x.z < mine_v[u]) + (x.w < mine_v[u]);
+    }
+    __syncthreads();
+    for (int q = tid; q < ns; q += kLexPrepThreads) lex_keys[q] = q == 0 ? 0 : q == m + 1 && ones ? one : INT_MAX;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (mine_v[u] != INT_MAX) lex_keys[1 + rank[u]] = mine_v[u];
+    __syncthreads();
   } else {
-    // Bitonic sort in LDS.  A stage of stride at most 64 pairs keys inside
-    // aligned runs of 128, and one wavefront handles every pair of a run (the
-    // 64 pair indices of a wavefront map to one run), so such a stage only
-    // waits for its own wavefront's writes, unless the stage before it
-    // crossed runs.
-    int prev = n2;
-    for (int size = 2; size <= n2; size <<= 1) {
-      for (int stride = size >> 1; stride > 0; stride >>= 1) {
-        if (stride > kWave || prev > kWave) __syncthreads();
-        else wave_lds_fence();
-        prev = stride;
-        for (int idx = tid; idx < (n2 >> 1); idx += kLexPrepThreads) {
-          const int lo = ((idx & ~(stride - 1)) << 1) | (idx & (stride - 1)), hi = lo + stride;
-          const int a = lex_keys[lo], c = lex_keys[hi];
-          const bool up = (lo & size) == 0;
-          if ((a > c) == up) {
-            lex_keys[lo] = c;
-            lex_keys[hi] = a;
+    for (int q = m + tid; q < ns; q += kLexPrepThreads) lex_keys[q] = q == m ? 0 : q == m + 1 && ones ? one : INT_MAX;
+    __syncthreads();
+    if (ns == kLexPrepThreads) {
+      bitonic_regs<1>(lex_keys, ns, tid);
+    } else if (ns == 2 * kLexPrepThreads) {
+      bitonic_regs<2>(lex_keys, ns, tid);
+    } else {
+      // Bitonic sort in LDS.  A stage of stride at most 64 pairs keys inside
+      // aligned runs of 128, and one wavefront handles every pair of a run (the
+      // 64 pair indices of a wavefront map to one run), so such a stage only
+      // waits for its own wavefront's writes, unless the stage before it
+      // crossed runs.
+      int prev = ns;
+      for (int size = 2; size <= ns; size <<= 1) {
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+          if (stride > kWave || prev > kWave) __syncthreads();
+          else wave_lds_fence();
+          prev = stride;
+          for (int idx = tid; idx < (ns >> 1); idx += kLexPrepThreads) {
+            const int lo = ((idx & ~(stride - 1)) << 1) | (idx & (stride - 1)), hi = lo + stride;
+            const int a = lex_keys[lo], c = lex_keys[hi];
+            const bool up = (lo & size) == 0;
+            if ((a > c) == up) {
+              lex_keys[lo] = c;
+              lex_keys[hi] = a;
+            }
           }
         }
       }
+      __syncthreads();
     }
-    __syncthreads();
   }
   // thread t owns keys [t seg, (t + 1) seg): count its first occurrences,
   // then an exclusive count over the threads places them
-  const int seg = n2 / kLexPrepThreads, a0 = tid * seg;
+  const int seg = ns / kLexPrepThreads, a0 = tid * seg;
   int mine = 0;
   for (int a = a0; a < a0 + seg; ++a) {
     const int v = lex_keys[a];
@@ -4272,6 +4387,26 @@ __device__ void lex_breaks_block(const DevProblem &P, int R, int o, const float 
   if (tid == 0) nbp[o * 2 + R] = total;
 }
 
+// Block b of a set-up launch (the parts are described at k_setup).
+__device__ __forceinline__ void setup_block(const DevProblem &P, int b, int8_t *__restrict__ bmap, int32_t nb,
+                                            const int32_t *__restrict__ cand, int32_t E, CandInfo *__restrict__ info,
+                                            int32_t nc, const float *__restrict__ cap_lo,
+                                            const float *__restrict__ cap_hi, const float *__restrict__ tail_lo,
+                                            const float *__restrict__ tail_hi, int32_t nbmax,
+                                            int2 *__restrict__ opt_out, float *__restrict__ bp_out,
+                                            int32_t *__restrict__ nbp) {
+  if (b < nb) {
+    setup_bucket_at(P, bmap, b * kLexPrepThreads + (int)threadIdx.x);
+    return;
+  }
+  if (b < nb + nc) {
+    setup_cand_at(P, cand, E, info, (b - nb) * kLexPrepThreads + (int)threadIdx.x);
+    return;
+  }
+  const int z = b - nb - nc;
+  lex_breaks_block(P, z & 1, z >> 1, cap_lo, cap_hi, tail_lo, tail_hi, nbmax, opt_out, bp_out, nbp);
+}
+
 // A call's set-up in one launch of kLexPrepThreads-thread blocks: blocks
 // [0, nb) the bucket map (one entry per thread), [nb, nb + nc) the candidate
 // records (one per thread), then n_br blocks of option ratios and
@@ -4286,17 +4421,30 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_setup(DevProblem P, int8_t 
                                                           const float *__restrict__ tail_hi, int32_t nbmax,
                                                           int2 *__restrict__ opt_out, float *__restrict__ bp_out,
                                                           int32_t *__restrict__ nbp) {
-  const int b = blockIdx.x;
-  if (b < nb) {
-    setup_bucket_at(P, bmap, b * kLexPrepThreads + (int)threadIdx.x);
+  setup_block(P, (int)blockIdx.x, bmap, nb, cand, E, info, nc, cap_lo, cap_hi, tail_lo, tail_hi, nbmax, opt_out, bp_out,
+              nbp);
+}
+
+// The same with the orders' own certificates, where the register solver
+// takes them: blocks [0, O) solve an order's two realisations under the
+// whole objective into records, beside the breakpoints of the other blocks
+// (which take as long).
+template <int KP, int NTP>
+__global__ __launch_bounds__(kLexPrepThreads) void k_lex_setup(
+    DevProblem P, int32_t O, CertRec *__restrict__ rec, const PrepLevels LV, int8_t *__restrict__ bmap, int32_t nb,
+    const int32_t *__restrict__ cand, int32_t E, CandInfo *__restrict__ info, int32_t nc,
+    const float *__restrict__ cap_lo, const float *__restrict__ cap_hi, const float *__restrict__ tail_lo,
+    const float *__restrict__ tail_hi, int32_t nbmax, int2 *__restrict__ opt_out, float *__restrict__ bp_out,
+    int32_t *__restrict__ nbp) {
+  if ((int)blockIdx.x < O) {
+    extern __shared__ __attribute__((aligned(16))) int lex_keys[];
+    const AllocOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
+    reg_certify_lex<KP, NTP>(P, blockIdx.x, cap_lo, cap_hi, tail_lo, tail_hi, none, none, rec, LV,
+                             reinterpret_cast<float *>(lex_keys));
     return;
   }
-  if (b < nb + nc) {
-    setup_cand_at(P, cand, E, info, (b - nb) * kLexPrepThreads + (int)threadIdx.x);
-    return;
-  }
-  const int z = b - nb - nc;
-  lex_breaks_block(P, z & 1, z >> 1, cap_lo, cap_hi, tail_lo, tail_hi, nbmax, opt_out, bp_out, nbp);
+  setup_block(P, (int)blockIdx.x - O, bmap, nb, cand, E, info, nc, cap_lo, cap_hi, tail_lo, tail_hi, nbmax, opt_out,
+              bp_out, nbp);
 }
 
 // Per (realisation R, order o, class i) and interval j of the breakpoints
@@ -4387,7 +4535,14 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
       // The options of cost c are (t, c / t) for the TP degrees t dividing
       // c; every degree's read is issued (at option 0 when t does not
       // divide c), so they overlap.
+      // Of these, only the costs that serve more than every cheaper one (and
+      // than nothing, with the empty option allowed): a term of any other is
+      // at most the term of that cheaper cost at every budget, V being
+      // nondecreasing.  For the first class taken V is 0, so its layer is
+      // the best rate up to each budget.
       int n_c = 0;
+      const bool first_class = k == (i == K - 1 ? K - 2 : K - 1);
+      int carry = empty_ok ? 0 : __float_as_int(NEGF);  // best rate of the cheaper costs (bits; -inf below every rate)
       for (int c0 = 1; c0 <= G; c0 += kWave) {
         const int c = c0 + lane;
         int2 ov[NTP];
@@ -4404,14 +4559,23 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
 #pragma unroll
         for (int ti = 0; ti < NTP; ++ti)
           a = okv[ti] && ov[ti].x >= thr ? fmaxf(a, __int_as_float(ov[ti].y)) : a;
-        const bool has = a > NEGF;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(has);
-        if (has) {
-          const int at = n_c + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-          Ad[at] = (double)a;
-          Ck[at] = 8 * c;
+        const int ab = __float_as_int(a);
+        const int upto = max(wave_scan_max_dpp(ab), carry);
+        if (first_class) {
+          if (c <= G) Vc[c] = (double)__int_as_float(upto);
+        } else {
+          const int before = __builtin_amdgcn_update_dpp(carry, upto, 0x138, 0xF, 0xF, false);  // wave_shr:1
+          const bool has = ab > before;
+          const uint64_t m = __builtin_amdgcn_ballot_w64(has);
+          if (has) {
+            const int at =
+                n_c + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            Ad[at] = (double)a;
+            Ck[at] = 8 * c;
+          }
+          n_c += __builtin_popcountll(m);
         }
-        n_c += __builtin_popcountll(m);
+        carry = __builtin_amdgcn_readlane(upto, kWave - 1);
       }
       if (lane < 8) {  // padding: a cost no budget reaches
         Ck[n_c + lane] = 8 * (G + 1);
@@ -4429,7 +4593,7 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
       // budget 0 takes no listed cost (costs are at least 1); budgets 1..G
       // in groups of 64 (one group when G is 64)
       if (lane == 0) Vc[0] = empty_ok ? Vp[0] : NEG;
-      for (int top = G; top >= 1; top -= kWave) {
+      for (int top = first_class ? 0 : G; top >= 1; top -= kWave) {
         const int g = top - lane;  // lanes past g = 1 compute nothing
         const int gs = g >= 0 ? g : 0;
         const char *vg = reinterpret_cast<const char *>(Vp + gs);
@@ -5888,13 +6052,20 @@ hipError_t launch_certify_lex(const DevProblem &P, const float *cap_lo, const fl
   const int stage = stage_fits(staged) ? 1 : 0;
   CertRec *rec = (CertRec *)(ws + L.crec);
   const int8_t *bmap = (const int8_t *)(ws + L.bmap);
-  if (stage)
+  if (reg_solver_supported(P)) {
+    const PrepLevels LV = prep_levels(P);
+    const size_t lds = reg_cert_lex_lds(P);
+#define FS_CERTIFY_LEX_REG(KP, NTP)                                                                             \
+  k_certify_lex_reg<KP, NTP><<<O, kCertThreads, lds, s>>>(P, cap_lo, cap_hi, tail_lo, tail_hi, cons, opt, rec, LV);
+    FS_REG_DISPATCH(FS_CERTIFY_LEX_REG)
+#undef FS_CERTIFY_LEX_REG
+  } else if (stage)
     k_certify_lex<1><<<dim3(2, O), 64, staged, s>>>(P, bmap, cap_lo, cap_hi, tail_lo, tail_hi, cons, opt, rec);
   else
     k_certify_lex<0><<<dim3(2, O), 64, base, s>>>(P, bmap, cap_lo, cap_hi, tail_lo, tail_hi, cons, opt, rec);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !with_state) return e;
-  k_certify_state<<<O, 64, 0, s>>>(P, bmap, tail_hi, measured, eps, rec, 1, state, gap_mm, gap_gp);
+  k_certify_state<<<O, 64, 0, s>>>(P, tail_hi, measured, eps, rec, 1, state, gap_mm, gap_gp);
   return hipGetLastError();
 }
 
@@ -5923,7 +6094,7 @@ hipError_t launch_certify(const DevProblem &P, const float *cap_lo, const float 
     k_certify<0><<<dim3(2, O), 64, base, s>>>(P, bmap, cap_lo, cap_hi, tail_lo, tail_hi, cons, opt, rec);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_certify_state<<<O, 64, 0, s>>>(P, bmap, tail_hi, measured, eps, rec, 0, state, gap, nullptr);
+  k_certify_state<<<O, 64, 0, s>>>(P, tail_hi, measured, eps, rec, 0, state, gap, nullptr);
   return hipGetLastError();
 }
 
@@ -6088,7 +6259,10 @@ hipError_t launch_score_lex(const DevProblem &P, const float *cap_lo, const floa
   // costs the host about as much as two launches.  The two chains write
   // disjoint workspace regions.  The main chain's set-up and tables are
   // enqueued first, so that they run while the host enqueues the rest.
-  const bool par = side && fork && join;
+  // Where the register solver applies, the certificates are blocks of the
+  // set-up launch, and there is one chain.
+  const bool reg = reg_solver_supported(P);
+  const bool par = side && fork && join && !reg;
   hipStream_t cs = par ? side : s;
   const bool tables = S > 0 && fast && L.fast.fast && E > 0;
   const LexExclRegions &X = L.fast;
@@ -6103,7 +6277,26 @@ hipError_t launch_score_lex(const DevProblem &P, const float *cap_lo, const floa
                               (int)lds_b);
       if (e != hipSuccess) return e;
     }
-    if (nb + nc + nbr > 0) {
+    if (reg) {
+      const size_t lds_c = reg_cert_lex_lds(P), lds = lds_b > lds_c ? lds_b : lds_c;
+      const PrepLevels LV = prep_levels(P);
+#define FS_LEX_SETUP(KP, NTP)                                                                                       \
+  {                                                                                                                 \
+    if (lds > 64 * 1024) {                                                                                          \
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_lex_setup<KP, NTP>),                                \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                                \
+      if (e != hipSuccess) return e;                                                                                \
+    }                                                                                                               \
+    k_lex_setup<KP, NTP><<<O + nb + nc + nbr, kLexPrepThreads, lds, s>>>(                                           \
+        P, O, (CertRec *)(ws + L.score.crec), LV, (int8_t *)(ws + L.score.bmap), nb, cand, E,                       \
+        (CandInfo *)(ws + L.score.cand), nc, cap_lo, cap_hi, tail_lo, tail_hi, X.nbmax, (int2 *)(ws + X.opt),       \
+        (float *)(ws + X.bp), (int32_t *)(ws + X.nbp));                                                             \
+  }
+      FS_REG_DISPATCH(FS_LEX_SETUP)
+#undef FS_LEX_SETUP
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    } else if (nb + nc + nbr > 0) {
       k_setup<<<nb + nc + nbr, kLexPrepThreads, lds_b, s>>>(
           P, (int8_t *)(ws + L.score.bmap), nb, cand, E, (CandInfo *)(ws + L.score.cand), nc, cap_lo, cap_hi,
           tail_lo, tail_hi, X.nbmax, (int2 *)(ws + X.opt), (float *)(ws + X.bp), (int32_t *)(ws + X.nbp));
@@ -6153,9 +6346,11 @@ hipError_t launch_score_lex(const DevProblem &P, const float *cap_lo, const floa
     e = hipStreamWaitEvent(side, fork, 0);
     if (e != hipSuccess) return e;
   }
-  e = launch_certify_lex(P, cap_lo, cap_hi, tail_lo, tail_hi, measured, O, 0.0f, nullptr, none,
-                         none, gmm, ggp, ws, L.score, cs, false);
-  if (e != hipSuccess) return e;
+  if (!reg) {
+    e = launch_certify_lex(P, cap_lo, cap_hi, tail_lo, tail_hi, measured, O, 0.0f, nullptr, none,
+                           none, gmm, ggp, ws, L.score, cs, false);
+    if (e != hipSuccess) return e;
+  }
   if (par) {
     e = hipEventRecord(join, side);
     if (e != hipSuccess) return e;
