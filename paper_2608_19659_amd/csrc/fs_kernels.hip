@@ -193,6 +193,15 @@ __device__ __forceinline__ double wave_pairwise_sum(double v) {
   return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
 }
 
+// Maximum over the 64 lanes (wave-uniform result; no NaN).
+__device__ __forceinline__ double wave_max_f64(double v) {
+  v = fmax(v, dpp_f64<0xB1>(v));
+  v = fmax(v, dpp_f64<0x4E>(v));
+  v = fmax(v, dpp_f64<0x141>(v));
+  v = fmax(v, dpp_f64<0x140>(v));
+  return fmax(fmax(readlane_f64(v, 0), readlane_f64(v, 16)), fmax(readlane_f64(v, 32), readlane_f64(v, 48)));
+}
+
 // Orders LDS accesses of one wavefront (its lanes' writes before their
 // reads); LDS executes one wavefront's instructions in issue order.
 __device__ __forceinline__ void wave_lds_fence() {
@@ -3777,12 +3786,7 @@ __device__ __forceinline__ RegAlloc reg_lex_stage(const DevProblem &P, const Reg
         }
         const LexCell vv = V[G - g];
         const double v = keep ? (double)a + vv.gp : NEG;
-        double best = fmax(v, dpp_f64<0xB1>(v));
-        best = fmax(best, dpp_f64<0x4E>(best));
-        best = fmax(best, dpp_f64<0x141>(best));
-        best = fmax(best, dpp_f64<0x140>(best));
-        best = fmax(fmax(readlane_f64(best, 0), readlane_f64(best, 16)),
-                    fmax(readlane_f64(best, 32), readlane_f64(best, 48)));
+        const double best = wave_max_f64(v);
         const int key = wave_min_dpp(v == best && keep ? vv.key + (g << 16) + code : INT_MAX);
         const LexCell e = V[G];
         top = best;
@@ -4114,12 +4118,11 @@ __global__ __launch_bounds__(64) void k_score_lex_wave(DevProblem P, const int8_
 // ---------------------------------------------------------------------------
 constexpr int kLexPrepThreads = 256;
 // Wavefronts of the interval tables kernel in all (blocks per realisation,
-// order and class follow from it, no more than the intervals can use): a
-// wavefront walks its intervals one after another, so more and shorter-lived
-// wavefronts shorten the kernel, until they take the SIMDs from the
-// certificate solves running beside it on the second stream (on 4 classes at
-// G = 64 the whole call took 86.1-86.2, 81.8-83.8 and 83.4 us with 8192,
-// 12288 and 16384).
+// order and class follow from it, no more than the intervals can use).  On 4
+// classes at G = 64 (16 orders, 96 candidates, 64 samples) the whole call took
+// 47.2, 47.6, 48.1 and 48.7 us with 4096, 12288, 16384 and 24576: the kernel is
+// bound by instruction issue, and many short wavefronts also balance long
+// breakpoint lists.
 constexpr int kLexTableWaves = 12288;
 
 constexpr int kLexRankMax = 2 * kLexPrepThreads;  // keys the breakpoints sort by rank
@@ -4138,14 +4141,15 @@ __host__ __device__ inline size_t lex_breaks_lds(int nopt, int N) {
   return 4 * ((size_t)lex_sort_keys(nopt) + kLexPrepThreads) + 8 * (size_t)N;
 }
 
-// LDS of a k_lex_tables block: every option's (ratio, served rate), the
+// LDS of a k_lex_tables block: every option's (ratio, served rate) and one that
+// is never allowed, the
 // candidate class's options (cost, cell), then (from a 16-byte boundary)
 // per wavefront two knapsack layers (binary64, each with G + 1 entries of
 // padding), one class's best served rates (binary64) and its listed costs,
 // G + 8 of each rounded up to a multiple of 4.
 __host__ __device__ inline int lex_list_stride(int G) { return (G + 8 + 3) & ~3; }
 __host__ __device__ inline size_t lex_tables_head(int nopt, int per_class_options) {
-  return (8 * ((size_t)nopt + per_class_options) + 15) & ~(size_t)15;
+  return (8 * ((size_t)nopt + 1 + per_class_options) + 15) & ~(size_t)15;
 }
 __host__ __device__ inline size_t lex_tables_lds(int nopt, int per_class_options, int G) {
   const size_t nw = kLexPrepThreads / kWave;
@@ -4459,7 +4463,14 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_setup(
 // lanes over g from the top down, so each chunk loops c only up to its
 // largest g.  Blocks split the intervals of one (R, o, i) four wavefronts
 // at a time.
-template <int NTP>
+//
+// Bound by instruction issue (5.4 M vector and 4.7 M scalar wavefront
+// instructions, about 10 us of each SIMD, on 4 classes at G = 64).  ONE (G <=
+// 64): a lane has one cost, so the places of its options are worked out once
+// for every class and interval, a place that holds none reads an option no
+// threshold allows, and the list of costs is walked whole instead of up to a
+// counted end: 17.0 -> 15.1 us there.
+template <int NTP, bool ONE>
 __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, const int8_t *__restrict__ bmap,
                                                                const int2 *__restrict__ opt_in,
                                                                const float *__restrict__ bp_in,
@@ -4475,8 +4486,8 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
   const int nopt = K * PP;
   const int nb = nbp[o * 2 + R];
   const int first = part * nw + wave, step = nsplit * nw;
-  int2 *oinfo = reinterpret_cast<int2 *>(lex_tab_lds);  // [nopt] ratio bits, served rate bits
-  int2 *icost = oinfo + nopt;                            // [PP] class i's options: cost, cell
+  int2 *oinfo = reinterpret_cast<int2 *>(lex_tab_lds);  // [nopt + 1] ratio bits, served rate bits; last: none
+  int2 *icost = oinfo + nopt + 1;                        // [PP] class i's options: cost, cell
   // per wavefront two knapsack layers, each with G + 1 entries of -inf
   // below index 0, so that V[g - c] for a cost above the budget reads -inf
   // (which the max ignores) instead of needing a clamp and a mask
@@ -4489,33 +4500,44 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
   double *Ad = vreg + (size_t)nw * 2 * (2 * G + 2) + (size_t)wave * LS;
   int *Ck = reinterpret_cast<int *>(vreg + (size_t)nw * 2 * (2 * G + 2) + (size_t)nw * LS) + (size_t)wave * LS;
   if (part * nw > nb) return;  // no interval for this block
-  const int2 *opt = opt_in + ((size_t)o * 2 + R) * nopt;
-  for (int q = tid; q < nopt; q += kLexPrepThreads) oinfo[q] = opt[q];
-  // class i's options: (cost, cell within the class; -1 when no level holds
-  // it); TP decode from staged constants
-  __shared__ int s_tp[kMaxTp], s_off[kMaxTp + 1];
-  if (tid < NT) s_tp[tid] = P.tp[tid];
-  if (tid <= NT) s_off[tid] = P.optoff[tid];
-  __syncthreads();
-  for (int p = tid; p < PP; p += kLexPrepThreads) {
-    int ti = 0;
-    while (ti + 1 < NT && p >= s_off[ti + 1]) ++ti;
-    const int r = p - s_off[ti] + 1;
-    const int b = bmap[i * (G + 1) + r];
-    icost[p] = make_int2(s_tp[ti] * r, b >= 0 ? ti * B + b : -1);
-  }
-  __syncthreads();
-  const double NEG = -__builtin_inf();
-  const float NEGF = -__builtin_inff();
   // the TP degrees, their reciprocals and option offsets in registers
   int tpr[NTP], ofr[NTP];
   float tpinv[NTP];
 #pragma unroll
   for (int ti = 0; ti < NTP; ++ti) {
     tpr[ti] = ti < NT ? P.tp[ti] : 0;
-    ofr[ti] = ti < NT ? P.optoff[ti] : 0;
+    ofr[ti] = ti < NT ? P.optoff[ti] : INT_MAX;
     tpinv[ti] = tpr[ti] > 0 ? 1.0f / (float)tpr[ti] : 0.0f;
   }
+  // every option's (ratio, served rate), and class i's options: (cost, cell
+  // within the class; -1 when no level holds it)
+  const int2 *opt = opt_in + ((size_t)o * 2 + R) * nopt;
+  for (int p = tid; p < PP; p += kLexPrepThreads) {
+    int ti = 0, at = 0, t = tpr[0];
+#pragma unroll
+    for (int t2 = 1; t2 < NTP; ++t2) {
+      const bool in = p >= ofr[t2];
+      ti = in ? t2 : ti;
+      at = in ? ofr[t2] : at;
+      t = in ? tpr[t2] : t;
+    }
+    const int r = p - at + 1;
+    const int b = bmap[i * (G + 1) + r];
+    icost[p] = make_int2(t * r, b >= 0 ? ti * B + b : -1);
+  }
+#pragma unroll 2
+  for (int q = tid; q < nopt; q += kLexPrepThreads) oinfo[q] = opt[q];
+  if (tid == 0) oinfo[nopt] = make_int2(-1, 0);
+  __syncthreads();
+  // ONE: option of cost lane + 1 of each TP degree within a class, -1 none
+  int place[NTP];
+#pragma unroll
+  for (int ti = 0; ti < NTP; ++ti) {
+    const int r = (int)((float)(lane + 1) * tpinv[ti] + 0.5f);
+    place[ti] = ti < NT && lane < G && r >= 1 && r * tpr[ti] == lane + 1 ? ofr[ti] + r - 1 : -1;
+  }
+  const double NEG = -__builtin_inf();
+  const float NEGF = -__builtin_inff();
   for (int g = lane; g <= G; g += kWave) {  // the padding below index 0, never written again
     Va[-1 - g] = NEG;
     Vb[-1 - g] = NEG;
@@ -4546,19 +4568,21 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
       for (int c0 = 1; c0 <= G; c0 += kWave) {
         const int c = c0 + lane;
         int2 ov[NTP];
-        bool okv[NTP];
 #pragma unroll
         for (int ti = 0; ti < NTP; ++ti) {
-          // c / t, exact whenever t divides c (the float quotient is within
-          // 1/2 of it for c <= 2^22)
-          const int r = (int)((float)c * tpinv[ti] + 0.5f);
-          okv[ti] = (ti < NT) & (c <= G) & (r >= 1) & (r * tpr[ti] == c);  // no short-circuit branches
-          ov[ti] = oinfo[okv[ti] ? k * PP + ofr[ti] + r - 1 : 0];
+          int q = place[ti];
+          if constexpr (!ONE) {
+            // c / t, exact whenever t divides c (the float quotient is within
+            // 1/2 of it for c <= 2^22)
+            const int r = (int)((float)c * tpinv[ti] + 0.5f);
+            const bool ok = (ti < NT) & (c <= G) & (r >= 1) & (r * tpr[ti] == c);  // no short-circuit branches
+            q = ok ? ofr[ti] + r - 1 : -1;
+          }
+          ov[ti] = oinfo[q >= 0 ? k * PP + q : nopt];
         }
         float a = NEGF;
 #pragma unroll
-        for (int ti = 0; ti < NTP; ++ti)
-          a = okv[ti] && ov[ti].x >= thr ? fmaxf(a, __int_as_float(ov[ti].y)) : a;
+        for (int ti = 0; ti < NTP; ++ti) a = fmaxf(a, ov[ti].x >= thr ? __int_as_float(ov[ti].y) : NEGF);
         const int ab = __float_as_int(a);
         const int upto = max(wave_scan_max_dpp(ab), carry);
         if (first_class) {
@@ -4599,20 +4623,22 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
         const char *vg = reinterpret_cast<const char *>(Vp + gs);
         double best = empty_ok ? Vp[gs] : NEG;
         // listed costs up to top: the first nuse (ascending)
-        int nuse = 0;
-        for (int xb = 0; xb < n_c; xb += kWave) {
+        int nuse = ONE ? n_c : 0;
+        for (int xb = 0; !ONE && xb < n_c; xb += kWave) {
           const int x = xb + lane;
           const int m = __builtin_popcountll(__builtin_amdgcn_ballot_w64(x < n_c && Ck[min(x, n_c)] <= 8 * top));
           nuse += m;
           if (m < kWave) break;
         }
-        // past nuse (up to 7 entries): listed costs above top or the padding
-        // (cost G + 1, at most G + 1 below index 0), both reading -inf here
-        for (int x = 0; x < nuse; x += 8) {
-          int cq[8];
-          double aq[8], vq[8];
+        // past nuse (fewer than a group's entries): listed costs above top or
+        // the padding (cost G + 1, at most G + 1 below index 0), both reading
+        // -inf here
+        constexpr int kGroup = ONE ? 4 : 8;
+        for (int x = 0; x < nuse; x += kGroup) {
+          int cq[kGroup];
+          double aq[kGroup], vq[kGroup];
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
+          for (int h = 0; h < kGroup / 4; ++h) {
             const int4 c4 = *reinterpret_cast<const int4 *>(Ck + x + 4 * h);
             const double2 a01 = *reinterpret_cast<const double2 *>(Ad + x + 4 * h);
             const double2 a23 = *reinterpret_cast<const double2 *>(Ad + x + 4 * h + 2);
@@ -4620,9 +4646,9 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
             aq[4 * h] = a01.x; aq[4 * h + 1] = a01.y; aq[4 * h + 2] = a23.x; aq[4 * h + 3] = a23.y;
           }
 #pragma unroll
-          for (int u = 0; u < 8; ++u) vq[u] = *reinterpret_cast<const double *>(vg - cq[u]);
+          for (int u = 0; u < kGroup; ++u) vq[u] = *reinterpret_cast<const double *>(vg - cq[u]);
 #pragma unroll
-          for (int u = 0; u < 8; ++u) best = fmax(best, aq[u] + vq[u]);
+          for (int u = 0; u < kGroup; ++u) best = fmax(best, aq[u] + vq[u]);
         }
         if (g >= 1) Vc[g] = best;
       }
@@ -4634,36 +4660,28 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
     double *Vg = Vout + (row0 + j) * (size_t)(G + 1);
     for (int g = lane; g <= G; g += kWave) Vg[g] = Vp[g];
     // class i's allowed options: served + V[G - cost], reduced to the
-    // largest value w1 (with a cell c1 holding it) and w2, the largest over
-    // the cells other than c1.  Merging two such summaries: same c1, the
-    // larger of each; else the larger w1 leads and the other's w1 (from
-    // another cell) competes for w2.  Lanes over the options, then a
-    // butterfly (the merge is symmetric, so every lane ends with the same).
-    double w1 = NEG, w2 = NEG;
+    // largest value w1, the last cell c1 holding it, and w2, the largest over
+    // the cells other than c1: three wave reductions (a butterfly of whole
+    // summaries took a permutation of five words per step).
+    double w1 = NEG;
     int c1 = -1;
-    auto merge = [&](double b1, int bc, double b2) {
-      if (bc == c1) {
-        w1 = fmax(w1, b1);
-        w2 = fmax(w2, b2);
-      } else if (b1 > w1 || (b1 == w1 && bc > c1)) {
-        w2 = fmax(b2, w1);
-        w1 = b1;
-        c1 = bc;
-      } else {
-        w2 = fmax(w2, b1);
-      }
-    };
     for (int p = lane; p < PP; p += kWave) {
-      const int2 ic = icost[p];
-      const int2 ov = oinfo[i * PP + p];
-      if (ic.y >= 0 && ov.x >= thr) merge((double)__int_as_float(ov.y) + Vp[G - ic.x], ic.y, NEG);
+      const int2 ic = icost[p], ov = oinfo[i * PP + p];
+      const double v = (double)__int_as_float(ov.y) + Vp[G - ic.x];
+      const bool ok = ic.y >= 0 && ov.x >= thr;
+      c1 = ok && (v > w1 || (v == w1 && ic.y > c1)) ? ic.y : c1;
+      w1 = ok ? fmax(w1, v) : w1;
     }
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) {
-      const double o1 = __shfl_xor(w1, m, kWave), o2 = __shfl_xor(w2, m, kWave);
-      const int oc = __shfl_xor(c1, m, kWave);
-      merge(o1, oc, o2);
+    const double w1_all = wave_max_f64(w1);
+    c1 = wave_max_dpp(w1 == w1_all ? c1 : -1);
+    w1 = w1_all;
+    double w2 = NEG;
+    for (int p = lane; p < PP; p += kWave) {
+      const int2 ic = icost[p], ov = oinfo[i * PP + p];
+      const double v = (double)__int_as_float(ov.y) + Vp[G - ic.x];
+      w2 = ic.y >= 0 && ov.x >= thr && ic.y != c1 ? fmax(w2, v) : w2;
     }
+    w2 = wave_max_f64(w2);
     if (lane == 0) {
       double *Wj = Wout + (row0 + j) * 4;
       Wj[0] = w1;
@@ -4682,6 +4700,9 @@ __global__ __launch_bounds__(kLexPrepThreads) void k_lex_tables(DevProblem P, co
 // gp = max(the class's best off the candidate cell, the empty option, the
 // candidate cell's allowed options at the sample: served + V[G - cost]);
 // both stages' gaps reduced by the pairwise wave tree, one partial each.
+// Bound by the chain of dependent table reads.  On 4 classes at G = 64 (16
+// orders, 96 candidates, 64 samples): 15.5 us with one read per replica count,
+// 12.7 with eight in flight, 11.2 with only the counts that can matter.
 __global__ __launch_bounds__(64) void k_score_lex_excl(DevProblem P, const TileInfo *__restrict__ tiles,
                                                        const int32_t *__restrict__ mopt, int32_t n_thr,
                                                        const float *__restrict__ cap_s,
@@ -4695,19 +4716,24 @@ __global__ __launch_bounds__(64) void k_score_lex_excl(DevProblem P, const TileI
   const int chunk = blockIdx.x, e = blockIdx.y, o = blockIdx.z, lane = threadIdx.x;
   const size_t tile = (size_t)o * E + e;
   // the loads that need nothing else come first, together: the tile
-  // record, both realisations' breakpoints (every slot; those past the
-  // count are not used), the lane's sample
+  // record, both realisations' first 128 breakpoints (those past the count
+  // are not used), the lane's sample
   const TileInfo tl = tiles[tile];
   const int nb0 = nbp[o * 2 + 0], nb1 = nbp[o * 2 + 1];
-  for (int m = lane; m < nbmax; m += kWave) {
-    lex_bp[m] = __float_as_int(bp[((size_t)o * 2 + 0) * nbmax + m]);
-    lex_bp[nbmax + m] = __float_as_int(bp[((size_t)o * 2 + 1) * nbmax + m]);
-  }
+  const float *bp0 = bp + (size_t)o * 2 * nbmax, *bp1 = bp0 + nbmax;
+  const int m0 = min(lane, nbmax - 1), m1 = min(lane + kWave, nbmax - 1);
+  const float b00 = bp0[m0], b01 = bp0[m1], b10 = bp1[m0], b11 = bp1[m1];
   const int s = chunk * kWave + lane;
   const bool live = s < S;
   const float cs = cap_s[tile * S + (live ? s : 0)];
   const float ls = tail_s[tile * S + (live ? s : 0)];
   if (tl.state != 0) return;  // measured or invalid: the finalize writes those
+  lex_bp[m0] = __float_as_int(b00);
+  lex_bp[m1] = __float_as_int(b01);
+  lex_bp[nbmax + m0] = __float_as_int(b10);
+  lex_bp[nbmax + m1] = __float_as_int(b11);
+  for (int m = lane + 2 * kWave; m < nb0; m += kWave) lex_bp[m] = __float_as_int(bp0[m]);
+  for (int m = lane + 2 * kWave; m < nb1; m += kWave) lex_bp[nbmax + m] = __float_as_int(bp1[m]);
   // M of the range's options, both realisations, into LDS
   const int nr = tl.rhi >= tl.rlo ? tl.rhi - tl.rlo + 1 : 0;
   for (int j = lane; j < nr; j += kWave) {
@@ -4719,12 +4745,25 @@ __global__ __launch_bounds__(64) void k_score_lex_excl(DevProblem P, const TileI
   const int i = tl.cls, local = tl.cell - i * per_class;
   const float slo = P.slo[i], lam = P.demand[i];
   const double rcp = P.rcp_demand[i];
+  // The replica counts of the cell that can matter to some lane: past the
+  // first that serves the whole demand (about lambda / c; the cell's first
+  // if that one does) the ratio and the served rate stay and both tables
+  // fall; below U lambda / c the ratio is at most U.
+  // Two counts of margin either way cover the approximate quotient; a lane
+  // whose tail breaks the SLO serves nothing at any count.
+  const float full = fminf(lam * __builtin_amdgcn_rcpf(fmaxf(cs, 1e-30f)), 8192.0f);
+  const bool usable = live && ls <= slo;
+  const int r_full = wave_max_dpp(usable ? (int)full + 2 : 0);
+  const int u_low = min(tl.u_m, tl.u_p);
+  const int r_low = wave_min_dpp(usable ? (int)(full * __int_as_float(u_low)) - 1 : INT_MAX);
+  const int r_first = max(tl.rlo, r_low), r_last = min(tl.rhi, max(tl.rlo, r_full));
   // tau* and its interval, both realisations
   int tau[2], row_j[2];
 #pragma unroll
   for (int R = 0; R < 2; ++R) {
     int t = R == 0 ? tl.u_m : tl.u_p;
-    for (int r = tl.rlo; r <= tl.rhi; ++r) t = max(t, min(ratio_bits(cs, ls, r, slo, rcp), Ml[R * rmax + r - tl.rlo]));
+#pragma unroll 4
+    for (int r = r_first; r <= r_last; ++r) t = max(t, min(ratio_bits(cs, ls, r, slo, rcp), Ml[R * rmax + r - tl.rlo]));
     tau[R] = t;
     // interval: the count of breakpoints below tau
     const int nb = R == 0 ? nb0 : nb1;
@@ -4755,12 +4794,24 @@ __global__ __launch_bounds__(64) void k_score_lex_excl(DevProblem P, const TileI
     double g = (int)w[R][3] == local ? w[R][1] : w[R][0];
     gp[R] = fmax(g, w[R][2]);
   }
-  for (int r = tl.rlo; r <= tl.rhi; ++r) {
-    const int f = ratio_bits(cs, ls, r, slo, rcp);
-    const float sv = ls <= slo ? served_rps(cs, r, lam) : 0.0f;
-    const double v0 = Vj[0][G - tl.t * r], v1 = Vj[1][G - tl.t * r];
-    if (f >= tau[0]) gp[0] = fmax(gp[0], (double)sv + v0);
-    if (f >= tau[1]) gp[1] = fmax(gp[1], (double)sv + v1);
+  // eight replica counts at a time, their table reads in flight together
+  // (past the range: its last count again, which changes nothing)
+  for (int r0 = r_first; r0 <= r_last; r0 += 8) {
+    double v0[8], v1[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int at = G - tl.t * min(r0 + u, r_last);
+      v0[u] = Vj[0][at];
+      v1[u] = Vj[1][at];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int r = min(r0 + u, r_last);
+      const int f = ratio_bits(cs, ls, r, slo, rcp);
+      const float sv = ls <= slo ? served_rps(cs, r, lam) : 0.0f;
+      if (f >= tau[0]) gp[0] = fmax(gp[0], (double)sv + v0[u]);
+      if (f >= tau[1]) gp[1] = fmax(gp[1], (double)sv + v1[u]);
+    }
   }
   double mm, gg;
   stage_gaps(tau[0], tau[1], gp[0], gp[1], &mm, &gg);
@@ -4789,49 +4840,39 @@ __device__ __forceinline__ double partial_tree(const double *__restrict__ x, int
   return sum;
 }
 
-struct PickLex {
-  double mm, gp;
-  int tp, cell, e;  // e < 0: nothing
-};
-
-__device__ __forceinline__ bool better_lex(const PickLex &a, const PickLex &b) {
-  if (a.e < 0) return false;
-  if (b.e < 0) return true;
-  if (a.mm != b.mm) return a.mm > b.mm;
-  if (a.gp != b.gp) return a.gp > b.gp;
-  if (a.tp != b.tp) return a.tp < b.tp;
-  if (a.cell != b.cell) return a.cell < b.cell;
-  return a.e < b.e;
-}
-
-// Scores of both stages and the lexicographic argmax: one wavefront per
-// order, lanes over the candidates, then a shuffle reduction.  First the
-// order's current gaps from its two certificate records (the max-min gap
+// Scores of both stages and the lexicographic argmax: one block per order
+// of one wavefront per 64 candidates (at most 16), then three key reductions
+// -- the largest max-min score, the largest goodput score among the lanes
+// holding it, then the smallest (TP, cell, index) -- per wavefront and over
+// the wavefronts.  First the order's current gaps from its two certificate records (the max-min gap
 // tau+ - tau-, the goodput gap |gp+ - gp-| / max(gp+, gp-), 0 when both are
-// 0), written to gap_mm_out and gap_gp_out.
-__global__ __launch_bounds__(64) void k_finalize_lex(DevProblem P, const CandInfo *__restrict__ info,
-                                                     const uint8_t *__restrict__ measured, int32_t E, int32_t S,
-                                                     const CertRec *__restrict__ rec,
-                                                     double *__restrict__ gap_mm_out,
-                                                     double *__restrict__ gap_gp_out,
-                                                     const double *__restrict__ part_mm,
-                                                     const double *__restrict__ part_gp, int64_t n_partial,
-                                                     double *__restrict__ score_mm, double *__restrict__ score_gp,
-                                                     int32_t *__restrict__ best) {
-  const int o = blockIdx.x, lane = threadIdx.x;
+// 0), written to gap_mm_out and gap_gp_out.  Bound by one chain of reads; a
+// wavefront per order that shuffled (score, score, TP, cell, index) records
+// took 6.2 us for 16 orders of 96 candidates, this 4.1.
+__global__ __launch_bounds__(64 * kFinalizeMaxWaves) void k_finalize_lex(
+    DevProblem P, const CandInfo *__restrict__ info, const uint8_t *__restrict__ measured, int32_t E, int32_t S,
+    const CertRec *__restrict__ rec, double *__restrict__ gap_mm_out, double *__restrict__ gap_gp_out,
+    const double *__restrict__ part_mm, const double *__restrict__ part_gp, int64_t n_partial,
+    double *__restrict__ score_mm, double *__restrict__ score_gp, int32_t *__restrict__ best) {
+  __shared__ uint64_t s_mm[kFinalizeMaxWaves], s_gp[kFinalizeMaxWaves], s_tie[kFinalizeMaxWaves];
+  const int o = blockIdx.x, lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const CertRec *rm = rec + (size_t)o * 2, *rp = rm + 1;
   const double g_mm = (double)__int_as_float(rp->tau) - (double)__int_as_float(rm->tau);
   const double g64_m = rm->goodput64, g64_p = rp->goodput64;
   const double g_top = g64_p > g64_m ? g64_p : g64_m;
   const double g_gp = g_top > 0.0 ? fabs(g64_p - g64_m) / g_top : 0.0;
-  if (lane == 0) {
+  if (threadIdx.x == 0) {
     gap_mm_out[o] = g_mm;
     gap_gp_out[o] = g_gp;
   }
-  PickLex mine{0.0, 0.0, 0, 0, -1};
-  for (int e = lane; e < E; e += kWave) {
+  uint64_t kmm = 0, kgp = 0, tie = ~0ull;  // 0: no candidate
+  for (int e = threadIdx.x; e < E; e += blockDim.x) {
     const CandInfo ci = info[e];
     const size_t tile = (size_t)o * E + e;
+    // the first partials are read beside the record (those of tiles that
+    // were not scored are not used)
+    const double p_mm = n_partial > 0 ? part_mm[tile * n_partial] : 0.0;
+    const double p_gp = n_partial > 0 ? part_gp[tile * n_partial] : 0.0;
     if (ci.cls < 0) {
       score_mm[tile] = score_gp[tile] = __builtin_nan("");
       continue;
@@ -4840,24 +4881,39 @@ __global__ __launch_bounds__(64) void k_finalize_lex(DevProblem P, const CandInf
       score_mm[tile] = score_gp[tile] = 0.0;
       continue;
     }
-    const double smm = g_mm - partial_tree(part_mm + tile * n_partial, n_partial) / (double)S;
-    const double sgp = g_gp - partial_tree(part_gp + tile * n_partial, n_partial) / (double)S;
+    const double smm =
+        g_mm - (n_partial == 1 ? p_mm : partial_tree(part_mm + tile * n_partial, n_partial)) / (double)S;
+    const double sgp =
+        g_gp - (n_partial == 1 ? p_gp : partial_tree(part_gp + tile * n_partial, n_partial)) / (double)S;
     score_mm[tile] = smm;
     score_gp[tile] = sgp;
-    const PickLex c{smm, sgp, ci.tp, ci.cell, e};
-    if (better_lex(c, mine)) mine = c;
+    const uint64_t a = score_key(smm), b = score_key(sgp), t = tie_key(ci.tp, ci.cell, e);
+    if (a > kmm || (a == kmm && (b > kgp || (b == kgp && t < tie)))) {
+      kmm = a;
+      kgp = b;
+      tie = t;
+    }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    PickLex q;
-    q.mm = __shfl_xor(mine.mm, off, kWave);
-    q.gp = __shfl_xor(mine.gp, off, kWave);
-    q.tp = __shfl_xor(mine.tp, off, kWave);
-    q.cell = __shfl_xor(mine.cell, off, kWave);
-    q.e = __shfl_xor(mine.e, off, kWave);
-    if (better_lex(q, mine)) mine = q;
+  const uint64_t wmm = wave_ext_u64<true>(kmm);
+  const uint64_t wgp = wave_ext_u64<true>(kmm == wmm ? kgp : 0);
+  const uint64_t wtie = wave_ext_u64<false>(kmm == wmm && kgp == wgp ? tie : ~0ull);
+  if (lane == 0) {
+    s_mm[wave] = wmm;
+    s_gp[wave] = wgp;
+    s_tie[wave] = wtie;
   }
-  if (lane == 0 && best) best[o] = mine.e;
+  __syncthreads();
+  if (threadIdx.x == 0 && best) {
+    uint64_t a = 0, b = 0, t = ~0ull;
+    for (int w = 0; w < nw; ++w) {
+      if (s_mm[w] > a || (s_mm[w] == a && (s_gp[w] > b || (s_gp[w] == b && s_tie[w] < t)))) {
+        a = s_mm[w];
+        b = s_gp[w];
+        t = s_tie[w];
+      }
+    }
+    best[o] = a != 0 ? (int32_t)(uint32_t)t : -1;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -6316,12 +6372,6 @@ hipError_t launch_score_lex(const DevProblem &P, const float *cap_lo, const floa
     e = launch_excl_setup(P, a, s);
     if (e != hipSuccess) return e;
     const size_t lds_t = lex_tables_lds(nopt, P.optoff[P.NT], P.G);
-    if (lds_t > 64 * 1024) {
-      e = hipFuncSetAttribute(P.NT <= 4 ? reinterpret_cast<const void *>(&k_lex_tables<4>)
-                                        : reinterpret_cast<const void *>(&k_lex_tables<8>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_t);
-      if (e != hipSuccess) return e;
-    }
     // blocks per (realisation, order, class): about kLexTableWaves
     // wavefronts in all, no more than the intervals can use
     const int64_t per = (int64_t)2 * O * P.K;
@@ -6329,15 +6379,23 @@ hipError_t launch_score_lex(const DevProblem &P, const float *cap_lo, const floa
     const int64_t cap_split = (X.nbmax + 1 + kLexPrepThreads / kWave - 1) / (kLexPrepThreads / kWave);
     const int nsplit = (int)(want < cap_split ? want : cap_split);
     // compiled for at most 4 or 8 TP degrees (the loop over them is unrolled)
+#define FS_LEX_TABLES(NTP, ONE)                                                                                     \
+  {                                                                                                                 \
+    if (lds_t > 64 * 1024) {                                                                                        \
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_lex_tables<NTP, ONE>),                              \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_t);                              \
+      if (e != hipSuccess) return e;                                                                                \
+    }                                                                                                               \
+    k_lex_tables<NTP, ONE><<<dim3(2 * nsplit, O, P.K), kLexPrepThreads, lds_t, s>>>(                                \
+        P, (const int8_t *)(ws + L.score.bmap), (const int2 *)(ws + X.opt), (const float *)(ws + X.bp),             \
+        (const int32_t *)(ws + X.nbp), X.nbmax, nsplit, (double *)(ws + X.V), (double *)(ws + X.W));                \
+  }
     if (P.NT <= 4) {
-      k_lex_tables<4><<<dim3(2 * nsplit, O, P.K), kLexPrepThreads, lds_t, s>>>(
-          P, (const int8_t *)(ws + L.score.bmap), (const int2 *)(ws + X.opt), (const float *)(ws + X.bp),
-          (const int32_t *)(ws + X.nbp), X.nbmax, nsplit, (double *)(ws + X.V), (double *)(ws + X.W));
+      if (P.G <= kWave) FS_LEX_TABLES(4, true) else FS_LEX_TABLES(4, false)
     } else {
-      k_lex_tables<8><<<dim3(2 * nsplit, O, P.K), kLexPrepThreads, lds_t, s>>>(
-          P, (const int8_t *)(ws + L.score.bmap), (const int2 *)(ws + X.opt), (const float *)(ws + X.bp),
-          (const int32_t *)(ws + X.nbp), X.nbmax, nsplit, (double *)(ws + X.V), (double *)(ws + X.W));
+      if (P.G <= kWave) FS_LEX_TABLES(8, true) else FS_LEX_TABLES(8, false)
     }
+#undef FS_LEX_TABLES
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -6391,7 +6449,8 @@ hipError_t launch_score_lex(const DevProblem &P, const float *cap_lo, const floa
     if (e != hipSuccess) return e;
   }
   // with no candidates only the gaps are written (best stays as it was)
-  k_finalize_lex<<<O, 64, 0, s>>>(P, info, measured, E, S, (const CertRec *)(ws + L.score.crec), gmm, ggp, pmm,
+  const int fw = (E + kWave - 1) / kWave, nwf = fw < 1 ? 1 : fw > kFinalizeMaxWaves ? kFinalizeMaxWaves : fw;
+  k_finalize_lex<<<O, kWave * nwf, 0, s>>>(P, info, measured, E, S, (const CertRec *)(ws + L.score.crec), gmm, ggp, pmm,
                                   pgp, S > 0 ? n_partial : 0, score_mm, score_gp, E > 0 ? best : nullptr);
   return hipGetLastError();
 }
