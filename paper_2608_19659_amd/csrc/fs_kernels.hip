@@ -125,25 +125,10 @@ __device__ __forceinline__ int wave_sum_int(int v) {
   return v;
 }
 
-// Inclusive prefix maximum of nonnegative values across the 64 lanes: DPP
-// shifts by 1, 2, 4, 8 within each row (a lane with no source takes 0), then
-// every row takes the totals of the rows before it (by readlane).
-__device__ __forceinline__ int wave_scan_max_nonneg(int v, int lane) {
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr:1
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));  // row_shr:2
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));  // row_shr:4
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));  // row_shr:8
-  const int r0 = __builtin_amdgcn_readlane(v, 15), r1 = __builtin_amdgcn_readlane(v, 31);
-  const int r2 = __builtin_amdgcn_readlane(v, 47);
-  const int row = lane >> 4;
-  const int before = row == 0 ? 0 : row == 1 ? r0 : row == 2 ? max(r0, r1) : max(max(r0, r1), r2);
-  return max(v, before);
-}
-
-// The same by DPP alone: the row totals travel by row_bcast:15 (row 0 to 1,
-// row 2 to 3) and row_bcast:31 (rows 0-1 to 2 and 3).  Lanes without a
-// source keep their value (INT_MIN, the identity, lets each step be one
-// instruction).
+// Inclusive prefix maximum across the 64 lanes: DPP shifts by 1, 2, 4, 8
+// within each row, then the row totals by row_bcast:15 (row 0 to 1, row 2 to
+// 3) and row_bcast:31 (rows 0-1 to 2 and 3).  Lanes without a source keep
+// their value (INT_MIN, the identity, lets each step be one instruction).
 __device__ __forceinline__ int wave_scan_max_dpp(int v) {
   v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x111, 0xF, 0xF, false));  // row_shr:1
   v = max(v, __builtin_amdgcn_update_dpp(INT_MIN, v, 0x112, 0xF, 0xF, false));  // row_shr:2
@@ -299,28 +284,34 @@ __device__ __forceinline__ int merge_split(const int *X, const int *Y, int n, in
 
 // Folds options into their cells' maxima and replica ranges.  Lanes holding
 // consecutive options of one TP degree fall on few cells (the load level
-// falls as r grows), in runs of lanes; the first lane of each run folds the
-// run's largest value and replica range in with one LDS atomic each, where
-// one per lane would queue up on the same bank.  key: the cell within the
-// class, -1 for a lane with no option.  Every lane of the wavefront calls
-// it (the shuffles read every lane); r grows along a run.
+// falls as r grows), in runs of lanes; the last lane of each run folds the
+// run's largest value in with one LDS atomic, where one per lane would queue
+// up on the same bank.  key: the cell within the class, -1 for a lane with no
+// option; lanes of equal key are consecutive.  Every lane of the wavefront
+// calls it; r grows along a run.  The running maximum within runs takes DPP
+// moves (a lane without a source sees key -2, no run's); with shuffles the
+// fold was a chain of twelve LDS round trips.
 __device__ __forceinline__ void fold_cell_runs(int key, int w, int r, int *mc, int *crlo, int *crhi) {
   const int lane = threadIdx.x & (kWave - 1);
-  int wmax = w, rmax = r;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int k2 = __shfl_down(key, d, kWave);
-    const int w2 = __shfl_down(wmax, d, kWave);
-    const int r2 = __shfl_down(rmax, d, kWave);
-    const bool in = lane + d < kWave && k2 == key;
-    wmax = in ? max(wmax, w2) : wmax;
-    rmax = in ? max(rmax, r2) : rmax;
+#define FS_FOLD_STEP(CTRL, ROWS)                                                    \
+  {                                                                                 \
+    const int k2 = __builtin_amdgcn_update_dpp(-2, key, CTRL, ROWS, 0xF, false);    \
+    const int w2 = __builtin_amdgcn_update_dpp(INT_MIN, w, CTRL, ROWS, 0xF, false); \
+    w = max(w, k2 == key ? w2 : INT_MIN);                                           \
   }
-  const int kprev = __shfl_up(key, 1, kWave);
-  if (key >= 0 && (lane == 0 || kprev != key)) {
-    atomicMax(&mc[key], wmax);
-    atomicMin(&crlo[key], r);
-    atomicMax(&crhi[key], rmax);
+  FS_FOLD_STEP(0x111, 0xF)  // row_shr:1
+  FS_FOLD_STEP(0x112, 0xF)  // row_shr:2
+  FS_FOLD_STEP(0x114, 0xF)  // row_shr:4
+  FS_FOLD_STEP(0x118, 0xF)  // row_shr:8
+  FS_FOLD_STEP(0x142, 0xA)  // row_bcast:15, rows 1 and 3
+  FS_FOLD_STEP(0x143, 0xC)  // row_bcast:31, rows 2 and 3
+#undef FS_FOLD_STEP
+  const int kprev = __builtin_amdgcn_ds_bpermute(4 * max(lane - 1, 0), key);
+  const int knext = __builtin_amdgcn_ds_bpermute(4 * min(lane + 1, kWave - 1), key);
+  if (key >= 0 && (lane == 0 || kprev != key)) atomicMin(&crlo[key], r);
+  if (key >= 0 && (lane == kWave - 1 || knext != key)) {
+    atomicMax(&mc[key], w);
+    atomicMax(&crhi[key], r);
   }
 }
 
@@ -2224,7 +2215,7 @@ __global__ __launch_bounds__(1024) void k_prep_order(DevProblem P, const float *
       const int f = ratio_bits(cc[ti], ct[ti], rr[ti], slo, rcp);
       best = max(best, ok[ti] && bb[ti] >= 0 ? f : 0);
     }
-    btab = wave_scan_max_nonneg(best, lane);
+    btab = wave_scan_max_dpp(best);
     if (lane < G) {
       Bt[k * G + lane] = btab;
       Hs[k * G + lane] = 0;  // ratio 0: the smallest value a table holds
@@ -2293,7 +2284,7 @@ __global__ __launch_bounds__(1024) void k_prep_order(DevProblem P, const float *
   const int i = thr_wave ? wave - K : wave;
   // H_i in a register (lane g: H_i[g]); with one class, the empty
   // convolution (no other class constrains the budget)
-  const int hreg = K == 1 ? INT_MAX : wave_scan_max_nonneg(lane < G ? Hs[i * G + lane] : 0, lane);
+  const int hreg = K == 1 ? INT_MAX : wave_scan_max_dpp(lane < G ? Hs[i * G + lane] : 0);
   {
     int32_t *Mo = mopt + ((size_t)o * 2 + R) * n_thr + (size_t)i * PPc;
     float *To = thr + ((size_t)o * 2 + R) * n_thr + (size_t)i * PPc;
