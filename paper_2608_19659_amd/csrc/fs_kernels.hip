@@ -71,16 +71,6 @@ __device__ __forceinline__ int wave_min(int v) {
   return v;
 }
 
-// Inclusive prefix maximum across the 64 lanes.
-__device__ __forceinline__ int wave_scan_max(int v, int lane) {
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int t = __shfl_up(v, off, kWave);
-    if (lane >= off) v = max(v, t);
-  }
-  return v;
-}
-
 // Inclusive prefix sum across the 64 lanes by DPP: shifts by 1, 2, 4, 8
 // within each row of 16 lanes (lanes with no source add 0), then the last
 // lane of row 0 is added to row 1 and of row 2 to row 3 (row_bcast:15), and
@@ -271,15 +261,45 @@ __device__ __forceinline__ int conv_mono(const int *X, const int *Y, int g, int 
 }
 
 // Entries of X among the first d entries of the ascending merge of X and Y
-// (n entries each, X first among equal values): a bisection over the split.
+// (n entries each, X first among equal values): a search over the split that
+// cuts the range in four per step, the three probes read together (half the
+// dependent reads of a bisection).
 __device__ __forceinline__ int merge_split(const int *X, const int *Y, int n, int d) {
   int lo = max(0, d - n), hi = min(d, n);
   while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (X[mid] <= Y[d - 1 - mid]) lo = mid + 1;
-    else hi = mid;
+    const int len = hi - lo, m1 = lo + (len >> 2), m2 = lo + (len >> 1), m3 = lo + ((3 * len) >> 2);
+    const bool p1 = X[m1] <= Y[d - 1 - m1], p2 = X[m2] <= Y[d - 1 - m2], p3 = X[m3] <= Y[d - 1 - m3];
+    hi = !p1 ? m1 : !p2 ? m2 : !p3 ? m3 : hi;
+    lo = p3 ? m3 + 1 : p2 ? m2 + 1 : p1 ? m1 + 1 : lo;
   }
   return lo;
+}
+
+// Outputs [c0, c0 + 8) of the ascending merge of X and Y (n entries each):
+// they are the 8 smallest of 8 entries from each side of the split, the
+// elementwise minima of one run and the other reversed, sorted by a bitonic
+// merge.
+__device__ __forceinline__ void merge8(const int *X, const int *Y, int n, int c0, int (&v)[8]) {
+  const int i = merge_split(X, Y, n, c0), j = c0 - i;
+  int x[8], y[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    x[u] = X[min(i + u, n - 1)];
+    y[u] = Y[min(j + u, n - 1)];
+  }
+#pragma unroll
+  for (int u = 0; u < 8; ++u) v[u] = min(i + u < n ? x[u] : INT_MAX, j + 7 - u < n ? y[7 - u] : INT_MAX);
+#pragma unroll
+  for (int d = 4; d >= 1; d >>= 1) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if ((u & d) == 0) {
+        const int a = v[u], b = v[u + d];
+        v[u] = min(a, b);
+        v[u + d] = max(a, b);
+      }
+    }
+  }
 }
 
 // Folds options into their cells' maxima and replica ranges.  Lanes holding
@@ -399,7 +419,7 @@ __device__ int wave_solve(const DevProblem &P, const int8_t *__restrict__ bmap,
     for (int base = 1; base <= G; base += kWave) {
       const int g = base + lane;
       int v = (g <= G) ? T[g] : INT_MIN;
-      v = max(wave_scan_max(v, lane), carry);
+      v = max(wave_scan_max_dpp(v), carry);
       if (g <= G) T[g] = v;
       carry = __shfl(v, kWave - 1, kWave);
     }
@@ -1595,7 +1615,7 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
         T[g] = run;
       }
     }
-    const int incl = wave_scan_max(run, lane);
+    const int incl = wave_scan_max_dpp(run);
     if (lane == kWave - 1) wtot[tid >> 6] = incl;
     __syncthreads();
     int carry = __shfl_up(incl, 1, kWave);
@@ -1774,10 +1794,12 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
   // j is class j, or j + 1 from ci on); later levels alternate Xa / Xb.  For
   // nondecreasing tables the (max,min) convolution of two is the first G
   // entries of their ascending merge (Z[g] >= v iff at most g entries of
-  // the two lie below v), so a pair is merged: each thread takes `cw`
-  // consecutive outputs, finds where they start by a bisection over the
-  // split and then takes them one merge step at a time (one read per step,
-  // where a bisection per output reads 2 log2 G entries).
+  // the two lie below v), so a pair is merged: each thread finds where its 8
+  // outputs start and takes them in one go.  Bound by the chain of the
+  // search's reads, about 1.6 us a level.  With one dependent read per output
+  // the tree took 10.2 of a block's 15 us with 16 classes at G = 1024 and 5.2
+  // of 9.3 with 8 at G = 256; now 8.6 and 4.4 (calls 37.9 -> 36.3 and 58.0 ->
+  // 54.6 us).
   const int n0 = K - 1;
   const int *H;
   if (K == 1) {
@@ -1791,28 +1813,18 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
     int *src = nullptr, *dst = Xa;
     while (n > 1) {
       const int pairs = n >> 1, odd = n & 1;
-      // outputs per thread: enough that the pairs fill the block, at least 4
-      int cw = (pairs * G + nth - 1) / nth;
-      cw = cw < 4 ? 4 : cw;
-      const int per = (G + cw - 1) / cw;
+      const int per = (G + 7) / 8;
       for (int item = tid; item < pairs * per; item += nth) {
-        const int p = item / per, c0 = (item - p * per) * cw;
+        const int p = item / per, c0 = (item - p * per) * 8;
         const int ja = 2 * p, jb = 2 * p + 1;
         const int *X = src ? src + ja * G : Bsrc + (ja < ci ? ja : ja + 1) * G;
         const int *Y = src ? src + jb * G : Bsrc + (jb < ci ? jb : jb + 1) * G;
-        int i = merge_split(X, Y, G, c0), j = c0 - i;
-        int xv = X[min(i, G - 1)], yv = Y[min(j, G - 1)];
-        const int c1 = min(c0 + cw, G);
-        for (int g = c0; g < c1; ++g) {
-          const bool take_x = i < G && (j >= G || xv <= yv);
-          dst[p * G + g] = take_x ? xv : yv;
-          if (take_x) {
-            ++i;
-            xv = X[min(i, G - 1)];
-          } else {
-            ++j;
-            yv = Y[min(j, G - 1)];
-          }
+        int v[8];
+        merge8(X, Y, G, c0, v);
+        int *out = dst + p * G + c0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if (c0 + u < G) out[u] = v[u];
         }
       }
       if (odd) {  // the odd table passes through
