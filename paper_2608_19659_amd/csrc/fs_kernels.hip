@@ -5644,10 +5644,12 @@ static bool prep_order_fits(const DevProblem &P, int64_t O, int64_t E) {
   return P.G <= kPrepOrderMaxG && P.K <= kPrepOrderMaxK && prep_order_lds(P, O, E) <= kPrepLdsLimit;
 }
 
-// Runs of the work list: one block builds about 2,400 entries while a class
-// block of the set-up runs; at most 8, no more than there are orders or
-// wavefronts of the scorer (every run has at least one).
-constexpr int kListRuns = 8, kListRunTiles = 2400;
+// Runs of the work list: one block builds about 1,200 entries while a class
+// block of the set-up runs (2 classes at G = 16 over 200 orders and 48
+// candidates: the call took 17.4 us, with 2,400 entries a block 18.4, with 600
+// 17.4); at most 8, no more than there are orders or wavefronts of the scorer
+// (every run has at least one).
+constexpr int kListRuns = 8, kListRunTiles = 1200;
 static ListRuns list_runs(const DevProblem &P, const ScoreArgs &a) {
   // the unstaged list block of the general set-up takes every order
   const bool staged = (a.setup == 0 && prep_order_fits(P, a.O, a.E)) || prep_list_lds(P, a.O, a.E) <= kPrepGeneralLdsLimit;

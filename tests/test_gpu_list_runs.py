@@ -11,7 +11,7 @@ from test_gpu_parity import env, gpu_score  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("O", [50, 51, 101, 150, 200])  # 1 (2,400 tiles), 2, 4, and runs that do not divide O
+@pytest.mark.parametrize("O", [25, 26, 51, 101, 150, 200])  # 1 (1,200 tiles), 2, 4, 8, and runs that do not divide O
 @pytest.mark.parametrize("setup,waves", [(0, 0), (0, 1), (0, 3), (1, 0), (1, 5)])
 def test_list_runs_agree_with_full_solves(env, O, setup, waves):  # noqa: F811
     torch, fs, ctx = env
