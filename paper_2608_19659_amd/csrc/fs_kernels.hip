@@ -2438,11 +2438,9 @@ __device__ __forceinline__ double pairwise_run(double c, int64_t n) {
 // crossing search.
 constexpr int kScanMax = 4;
 
-// Default grid of the exclusion scorer: three wavefronts per SIMD (1024
-// SIMDs).  On the 4-class, G = 64 workload (about 7,100 items) three per
-// SIMD ran the scorer in 9.0-9.1 us against 9.5 us with four, 10.0 with 2.5
-// and 10.7-11.2 with two.
-constexpr int kScorerWaves = 3072;
+// Default grid of the exclusion scorer: four wavefronts per SIMD (1024
+// SIMDs), in blocks of kExclMaxWaves, two per CU (see the launch).
+constexpr int kScorerWaves = 4096, kExclMaxWaves = 8, kExclBlocks = 512;
 
 // Samples of one chunk.  VEC (S a multiple of 4): each group of 4 samples
 // of a lane lies wholly below S or wholly past it; every group is fetched by
@@ -2473,47 +2471,46 @@ __device__ __forceinline__ void load_chunk(const float *__restrict__ cap_s, cons
   }
 }
 
-// Everything one work item reads: its work-list entry, U and M at rlo of
-// both realisations (one 16-byte load of the tile record), and -- unless no
-// sample can matter (triv) -- the lane's samples and M and the capacity
-// threshold of option rlo + min(lane, nr - 1) of both realisations (a scan
-// reads M lane by lane, the crossing search looks both up across lanes).
+// What the evaluation of one work item reads: its work-list entry, its chunk
+// of the tile's samples, U of both realisations, the lane's samples and M and
+// the capacity threshold of option rlo + min(lane, nr - 1) of both
+// realisations (a scan reads M lane by lane, the crossing search looks both up
+// across lanes).
 template <int SPL>
 struct ScoreItem {
-  int4 ent;
+  int4 ent;  // ent.x < 0: no item
+  int c, u0, u1;
   float cs[SPL], ls[SPL];
   float4 bd;  // with bounds: the cell's cap_lo, cap_hi, tail_lo, tail_hi
-  int u0, u1, mr0, mr1;
   int vm0, vm1;
   float vt0, vt1;
-  bool triv;
 };
 
 // Value of lane idx (0 <= idx < 64) of v, per lane.
 __device__ __forceinline__ int lane_lookup(int v, int idx) { return __builtin_amdgcn_ds_bpermute(idx << 2, v); }
 
 // Scenarios of the exclusion scorer.  A work item is one chunk of 64 x SPL
-// samples of one live tile; items are numbered over the live tiles only, so
-// every wavefront gets the same number of items to within one, and the
-// chunks of one tile are neighbours.  Each wavefront of the grid takes the
-// items it, it + W, it + 2W, ... (W wavefronts) and runs them as a
-// three-stage pipeline: while the current item is evaluated, the list entry
-// of the third item ahead, the tile-record words of the second (U and M at
-// rlo, both realisations) and the samples and the range's M and thresholds
-// of the next are in flight.  All of these are vector loads
+// samples of one live tile; the chunks of one tile are neighbours, and block
+// w of the W blocks has the items w, w + W, w + 2 W, ... of every run.  It
+// takes one per thread at a time: the threads read their items' list entries
+// and tile records, write the partials of the items whose samples cannot matter,
+// and collect the others in LDS; then the wavefronts evaluate those in turn,
+// the samples and the range's M and thresholds of a wavefront's next item in
+// flight while its current one is evaluated.  All of these are vector loads
 // at unconditional (clamped) addresses, so each wait covers exactly the item
-// it is for; the per-class constants sit in LDS.  Lane l owns samples
-// [c * 64 * SPL + l * SPL, + SPL) of the item's tile, and the chunk's sum
-// is written as one partial (a node of the pairwise tree over s).
+// it is for.  Lane l owns samples [c * 64 * SPL + l * SPL, + SPL) of the
+// item's tile, and the chunk's sum is written as one partial (a node of the
+// pairwise tree over s).
 //
 // An item whose M over the whole range is at most U in both realisations
 // has tau = U in every scenario, whatever its samples (every term
-// min(f_r, M_r) is at most M_r): its samples are not read (the item's loads
-// go to one line at the start of the arrays, still unconditionally) and its
-// partial is the closed-form pairwise sum of the constant gap U+ - U-.
-// M falls along a range (M_r = min(H[G - t*r], 1) with H a prefix
-// maximum, as signed integers on its bits), so M at the range's first
-// count, which the set-up puts in the tile record, is its largest.
+// min(f_r, M_r) is at most M_r): its samples are not read and its partial is
+// the closed-form pairwise sum of the constant gap U+ - U-.  M falls along a
+// range (M_r = min(H[G - t*r], 1) with H a prefix maximum, as signed integers
+// on its bits), so M at the range's first count, which the set-up puts in the
+// tile record, is its largest.  Which items these are is known only here, so
+// single wavefronts with a fixed share of all items ended far apart; a block
+// of eight evens that out (see the figures at the launch).
 //
 // Per realisation, tau = max(U, max_r min(f_r, M_r)) with M_r = H[G - t*r].
 // Ranges of at most kScanMax replica counts are scanned.  For longer ones:
@@ -2525,118 +2522,73 @@ __device__ __forceinline__ int lane_lookup(int v, int idx) { return __builtin_am
 // CLAMP: every sample is moved into its cell's intervals first (the refitting
 // loop: min(max(x, lo), hi) with the tile's bounds, read with its record).
 template <int SPL, bool VEC, bool DUMP, bool CLAMP>
-__global__ __launch_bounds__(64) void k_score_excl(
+__global__ __launch_bounds__(64 * kExclMaxWaves) void k_score_excl(
     DevProblem P, const TileInfo *__restrict__ tiles, const int32_t *__restrict__ mopt,
     const float *__restrict__ thr, int32_t n_thr, const int4 *__restrict__ list,
     const float *__restrict__ cap_s, const float *__restrict__ tail_s, int32_t O, int32_t E, int32_t S,
     const int32_t *__restrict__ base, double *__restrict__ partial, int32_t n_chunk,
-    float *__restrict__ tau_dump, const float4 *__restrict__ bounds, ListRuns runs) {
+    float *__restrict__ tau_dump, const float4 *__restrict__ bounds, ListRuns runs, int32_t range_lds) {
   constexpr int CHUNK = 64 * SPL;
-  extern __shared__ int lds[];
-  const int lane = threadIdx.x;
-  // the wavefront's run of the list, and its place among the run's wavefronts
-  const int run = (int)blockIdx.x & (runs.n - 1), wv = (int)blockIdx.x >> runs.log;
+  extern __shared__ __attribute__((aligned(16))) int lds[];
+  __shared__ int s_count[kExclMaxWaves], s_more;
+  const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1), NW = T >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Thread t has items of run t mod runs.n of the list: every block has the
+  // same share of each run.
+  const int run = tid & (runs.n - 1), W = gridDim.x;
   list += (size_t)run * runs.per * E;
-  // per-class constants in LDS; then, for ranges longer than a wavefront, M
-  // and the thresholds of the range
-  double *c_rcp = reinterpret_cast<double *>(lds);
+  // the items to evaluate; per-class constants; then, for ranges longer than
+  // a wavefront, each wavefront's M and thresholds of the range
+  int4 *items = reinterpret_cast<int4 *>(lds);  // [T][2]
+  double *c_rcp = reinterpret_cast<double *>(items + 2 * T);
   float *c_slo = reinterpret_cast<float *>(c_rcp + P.K);
-  int *Mlds = reinterpret_cast<int *>(c_slo + P.K);
-  for (int k = lane; k < P.K; k += kWave) {
+  int *Mlds = reinterpret_cast<int *>(c_slo + P.K) + wave * range_lds;
+  for (int k = tid; k < P.K; k += T) {
     c_rcp[k] = P.rcp_demand[k];
     c_slo[k] = P.slo[k];
   }
-  wave_lds_fence();
-  // An opaque zero added to every address below: the loads stay vector
-  // loads.  (Scalar loads complete out of order, so a wait for any LDS
+  // An opaque zero added to the uniform addresses below: the loads stay
+  // vector loads.  (Scalar loads complete out of order, so a wait for any LDS
   // result would also wait for every scalar load in flight, including the
   // next item's.)
   int vz;
   asm volatile("v_mov_b32 %0, 0" : "=v"(vz));
-  const int W = ((int)gridDim.x - run + runs.n - 1) >> runs.log;
-  // Item it = j * n_chunk + c: chunk c of the tile in place j of the work
-  // list (every order's live tiles, longest replica range first).  Items go
-  // to the wavefronts in serpentine order: wavefront w takes items w,
-  // 2W - 1 - w, 2W + w, 4W - 1 - w, ..., so the wavefronts with the
-  // heaviest first items get the lightest second ones.  Positions carry the
-  // parity of their round; the two steps are kept as (places, chunks).
-  // Everything in 32 bits (at most 2^31 tiles, steps of at most 2^21): the
-  // 64-bit divisions were 0.3 us of every wavefront's start.
-  struct Pos { uint32_t j; int c; int odd; };
   const uint32_t n_list = (uint32_t)max(min(runs.per, O - run * runs.per), 0) * (uint32_t)E;
-  const uint32_t d_even = 2u * (uint32_t)W - 1u - 2u * (uint32_t)wv, d_odd = 2u * (uint32_t)wv + 1u;
-  const uint32_t sj0 = d_even / (uint32_t)n_chunk, sj1 = d_odd / (uint32_t)n_chunk;
-  const int sc0 = (int)(d_even - sj0 * (uint32_t)n_chunk), sc1 = (int)(d_odd - sj1 * (uint32_t)n_chunk);
-  auto advance = [&](Pos q) {
-    q.j += q.odd ? sj1 : sj0;
-    q.c += q.odd ? sc1 : sc0;
-    if (q.c >= n_chunk) { q.c -= n_chunk; ++q.j; }
-    q.odd ^= 1;
-    return q;
-  };
-  auto uniform4 = [](int4 v) {
-    return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
-                     __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
-  };
-  auto list_at = [&](const Pos &p) { return list[(p.j < n_list ? p.j : 0) + vz]; };
-  // Issues the tile-record load of an item whose list entry is known.
-  // Items without a tile read the first record instead.
-  auto issue_head = [&](ScoreItem<SPL> &X) {
-    const int4 en = X.ent;
-    const bool live = en.x >= 0;
-    const int o = en.w >> 8;
-    const size_t tile = live ? (size_t)o * E + en.x : 0;
-    const int4 h = *reinterpret_cast<const int4 *>(&tiles[tile + vz].u_m);  // (u_m, u_p, m_m, m_p)
-    X.u0 = h.x;
-    X.u1 = h.y;
-    X.mr0 = h.z;
-    X.mr1 = h.w;
+  const uint64_t n_items = (uint64_t)n_list * (uint32_t)n_chunk;
+  // Issues the loads of place k of the n collected items (past the last:
+  // none, at the arrays' first element).
+  auto fetch = [&](ScoreItem<SPL> &X, int k, int n) {
+    const bool live = k < n;
+    const int4 a = items[2 * (live ? k : 0)], b = items[2 * (live ? k : 0) + 1];
+    X.ent = make_int4(live ? __builtin_amdgcn_readfirstlane(a.x) : -1, __builtin_amdgcn_readfirstlane(a.y),
+                      __builtin_amdgcn_readfirstlane(a.z), __builtin_amdgcn_readfirstlane(a.w));
+    X.u0 = __builtin_amdgcn_readfirstlane(b.x);
+    X.u1 = __builtin_amdgcn_readfirstlane(b.y);
+    X.c = __builtin_amdgcn_readfirstlane(b.z);
+    const int nr = X.ent.z >> 16, o = X.ent.w >> 8;
+    const size_t tile = live ? (size_t)o * E + X.ent.x : 0;
     if constexpr (CLAMP) X.bd = bounds[tile + vz];
-  };
-  // Decides, from an item's record, whether its samples can matter, and
-  // issues their loads and the range's M and thresholds if so.  The test
-  // uses the comparisons the evaluation makes (signed integers on binary32
-  // bits).
-  auto issue_samples = [&](ScoreItem<SPL> &X, const Pos &p) {
-    const int4 en = X.ent;
-    const int nr = en.z >> 16, o = en.w >> 8;
-    const int m0 = __builtin_amdgcn_readfirstlane(X.mr0), m1 = __builtin_amdgcn_readfirstlane(X.mr1);
-    const int u0 = __builtin_amdgcn_readfirstlane(X.u0), u1 = __builtin_amdgcn_readfirstlane(X.u1);
-    const bool triv = !DUMP && en.x >= 0 && m0 <= u0 && m1 <= u1;
-    X.triv = triv;
-    const bool live = en.x >= 0 && !triv;
-    const size_t tile = live ? (size_t)o * E + en.x : 0;
-    load_chunk<SPL, VEC>(cap_s, tail_s, tile * S, live ? p.c * CHUNK + lane * SPL : 0, S, live, X.cs, X.ls);
+    load_chunk<SPL, VEC>(cap_s, tail_s, tile * S, live ? X.c * CHUNK + lane * SPL : 0, S, live, X.cs, X.ls);
     const size_t row0 = live ? (size_t)o * 2 * n_thr : 0, row1 = live ? row0 + n_thr : 0;
-    const int at = (live ? en.y : 0) + (live && nr > 0 ? min(lane, nr - 1) : 0) + vz;
+    const int at = (live ? X.ent.y : 0) + (live && nr > 0 ? min(lane, nr - 1) : 0) + vz;
     X.vm0 = mopt[row0 + at];
     X.vm1 = mopt[row1 + at];
     X.vt0 = thr[row0 + at];
     X.vt1 = thr[row1 + at];
   };
   // Evaluates an item whose loads were issued.
-  auto evaluate = [&](const ScoreItem<SPL> &X, const Pos &p) {
+  auto evaluate = [&](const ScoreItem<SPL> &X) {
     const int4 en = X.ent;
-    if (en.x < 0) return;  // no tile (uniform)
     const int e = en.x, toff = en.y, rlo = en.z & 0xFFFF, nr = en.z >> 16;
     const int cls = en.w & 0x3F, state = (en.w >> 6) & 3, o = en.w >> 8;
+    const int u0 = X.u0, u1 = X.u1;
     const size_t tile = (size_t)o * E + e;
-    const int s_first = p.c * CHUNK + lane * SPL;
-    if (X.triv) {
-      // the chunk's samples past S add 0
-      if (lane == 0) {
-        const int u0 = __builtin_amdgcn_readfirstlane(X.u0), u1 = __builtin_amdgcn_readfirstlane(X.u1);
-        const int n = min(CHUNK, S - p.c * CHUNK);
-        partial[tile * n_chunk + p.c] =
-            pairwise_run((double)__int_as_float(u1) - (double)__int_as_float(u0), n);
-      }
-      return;
-    }
+    const int s_first = X.c * CHUNK + lane * SPL;
     if (DUMP && (state != 0 || nr == 0)) {
       // listed only when dumping: a revealed cell keeps the base values; a
       // cell no replica count reaches leaves tau at U
-      const int vm = state != 0 ? base[o * 2 + 0] : X.u0;
-      const int vp = state != 0 ? base[o * 2 + 1] : X.u1;
+      const int vm = state != 0 ? base[o * 2 + 0] : u0;
+      const int vp = state != 0 ? base[o * 2 + 1] : u1;
       for (int q = 0; q < SPL; ++q) {
         if (s_first + q < S) {
           tau_dump[(tile * S + s_first + q) * 2 + 0] = __int_as_float(vm);
@@ -2653,7 +2605,6 @@ __global__ __launch_bounds__(64) void k_score_excl(
     // above the SLO makes every option on the cell worth 0, leaving tau = U:
     // the sample's capacity is taken as 0 instead, whose ratios (0) and
     // crossings (M <= 0 where reached) cannot raise tau above U >= 0.
-    const int u0 = __builtin_amdgcn_readfirstlane(X.u0), u1 = __builtin_amdgcn_readfirstlane(X.u1);
     int am[SPL], ap[SPL];
     float cs[SPL];
 #pragma unroll
@@ -2820,7 +2771,7 @@ __global__ __launch_bounds__(64) void k_score_excl(
     double gq[SPL];
     // samples past S add 0 (the chunk holds none of them unless it is the
     // tile's last and S is not a multiple of its size)
-    const bool full = (p.c + 1) * CHUNK <= S;
+    const bool full = (X.c + 1) * CHUNK <= S;
     if (full) {
 #pragma unroll
       for (int q = 0; q < SPL; ++q) {
@@ -2850,54 +2801,70 @@ __global__ __launch_bounds__(64) void k_score_excl(
       for (int j = 0; j + w < SPL; j += 2 * w) gq[j] = gq[j] + gq[j + w];
     }
     const double v = wave_pairwise_sum(gq[0]);
-    if (lane == 0) partial[tile * n_chunk + p.c] = v;
+    if (lane == 0) partial[tile * n_chunk + X.c] = v;
   };
 
-  // Items a (current), m (next) and n (second next).
-  Pos pa;
-  pa.j = (uint32_t)wv / (uint32_t)n_chunk;
-  pa.c = wv - (int)pa.j * n_chunk;
-  pa.odd = 0;
-  ScoreItem<SPL> A, B, C;
-  // the first three list entries are requested together
-  const int4 raw_a = list_at(pa);
-  Pos pm = advance(pa);
-  const int4 raw_m = list_at(pm);
-  Pos pn = advance(pm);
-  int4 raw_n = list_at(pn);
-  A.ent = uniform4(raw_a);
-  if (pa.j >= n_list) A.ent.x = -1;
-  issue_head(A);
-  B.ent = uniform4(raw_m);
-  if (pm.j >= n_list) B.ent.x = -1;
-  issue_head(B);
-  issue_samples(A, pa);
-  // One pipeline stage: the list entry of the third item ahead and the
-  // constants of the second are requested, the next item's samples are
-  // issued (its constants arrived during the previous stage), the current
-  // item is evaluated.  The three item buffers rotate roles (no copies, so
-  // no early waits).  Places only grow, so the first end marker ends the
-  // wavefront's work.
-  auto stage = [&](ScoreItem<SPL> &cur, ScoreItem<SPL> &mid, ScoreItem<SPL> &nxt) {
-    nxt.ent = uniform4(raw_n);
-    if (pn.j >= n_list) nxt.ent.x = -1;
-    const Pos pq = advance(pn);
-    const int4 raw_q = list_at(pq);
-    issue_head(nxt);
-    issue_samples(mid, pm);
-    evaluate(cur, pa);
-    pa = pm;
-    pm = pn;
-    pn = pq;
-    raw_n = raw_q;
-  };
-  for (;;) {
-    if (A.ent.x < 0) break;
-    stage(A, B, C);
-    if (B.ent.x < 0) break;
-    stage(B, C, A);
-    if (C.ent.x < 0) break;
-    stage(C, A, B);
+  for (uint64_t first = 0;; first += (uint64_t)(T >> runs.log) * (uint32_t)W) {
+    // this thread's item: place j of the list, chunk c (32-bit division but
+    // for the largest lists: a 64-bit one took 0.3 us of a block's start)
+    const uint64_t it = first + (uint64_t)((uint32_t)(tid >> runs.log) * (uint32_t)W + blockIdx.x);
+    const bool in = it < n_items;
+    uint32_t j, c;
+    if (n_chunk == 1) {
+      j = (uint32_t)it;
+      c = 0;
+    } else if (n_items <= 0xFFFFFFFFull) {
+      j = (uint32_t)it / (uint32_t)n_chunk;
+      c = (uint32_t)it - j * (uint32_t)n_chunk;
+    } else {
+      j = (uint32_t)(it / (uint32_t)n_chunk);
+      c = (uint32_t)(it - (uint64_t)j * (uint32_t)n_chunk);
+    }
+    const int4 en = list[in ? j : 0];
+    const bool live = in && en.x >= 0;
+    const size_t tile = live ? (size_t)(en.w >> 8) * E + en.x : 0;
+    const int4 h = *reinterpret_cast<const int4 *>(&tiles[tile].u_m);  // (u_m, u_p, m_m, m_p)
+    // the comparisons that the evaluation makes (signed integers on binary32
+    // bits)
+    const bool triv = !DUMP && live && h.z <= h.x && h.w <= h.y;
+    const bool take = live && !triv;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(take);
+    if (lane == 0) s_count[wave] = __builtin_popcountll(m);
+    // a run ends with its first empty entry; the last wavefront has the last
+    // places of every run (at most 64 runs)
+    const bool any = __builtin_amdgcn_ballot_w64(live) != 0;
+    if (tid == T - 1) s_more = any;
+    __syncthreads();
+    const int counts = lane < NW ? s_count[lane] : 0;
+    const bool more = s_more;
+    int at = 0, n = 0;
+#pragma unroll
+    for (int w = 0; w < kExclMaxWaves; ++w) {
+      const int cw = __builtin_amdgcn_readlane(counts, w);
+      at += w < wave ? cw : 0;
+      n += cw;
+    }
+    if (take) {
+      at += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+      items[2 * at] = en;
+      items[2 * at + 1] = make_int4(h.x, h.y, (int)c, 0);
+    }
+    __syncthreads();
+    ScoreItem<SPL> A, B;
+    fetch(A, wave, n);
+    if (triv)  // the chunk's samples past S add 0
+      partial[tile * n_chunk + c] = pairwise_run((double)__int_as_float(h.y) - (double)__int_as_float(h.x),
+                                                 min(CHUNK, S - (int)c * CHUNK));
+    for (int k = wave; k < n;) {
+      fetch(B, k + NW, n);
+      evaluate(A);
+      if ((k += NW) >= n) break;
+      fetch(A, k + NW, n);
+      evaluate(B);
+      k += NW;
+    }
+    if (!more) break;
+    __syncthreads();  // the next round writes the items again
   }
 }
 
@@ -4753,8 +4720,9 @@ __global__ __launch_bounds__(64) void k_score_lex_excl(DevProblem P, const TileI
   // if that one does) the ratio and the served rate stay and both tables
   // fall; below U lambda / c the ratio is at most U.
   // Two counts of margin either way cover the approximate quotient; a lane
-  // whose tail breaks the SLO serves nothing at any count.
-  const float full = fminf(lam * __builtin_amdgcn_rcpf(fmaxf(cs, 1e-30f)), 8192.0f);
+  // whose tail breaks the SLO serves nothing at any count, and one whose
+  // capacity is not a number counts as serving everything at each.
+  const float full = cs == cs ? fminf(lam * __builtin_amdgcn_rcpf(cs), 8192.0f) : 0.0f;
   const bool usable = live && ls <= slo;
   const int r_full = wave_max_dpp(usable ? (int)full + 2 : 0);
   const int u_low = min(tl.u_m, tl.u_p);
@@ -5887,14 +5855,14 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
   return hipGetLastError();
 }
 
-// Samples per lane of the exclusion scorer.  Chunks of 1024 samples when the
-// default grid would get more than 16 chunks of 512 per wavefront: on the
-// 8-class, G = 256 workload (43 per wavefront) the scorer ran 33.0 us against
-// 35.9 with 512; with about 5 per wavefront (the 4-class, G = 64 one) 512
-// stays faster.
+// Samples per lane of the exclusion scorer: a chunk of 512 samples, or of 256
+// where that holds a tile's samples (16 classes over 4 orders with 256
+// samples: the call took 38.2 us with half of each wavefront idle, 36.1 with
+// 256).  Chunks of 1024 leave a block fewer items to share out: with 8 classes
+// at G = 256 (64 orders, 256 candidates, 4096 samples) the call took 50.8 us
+// with 512 and 52.6 with 1024, which allow three wavefronts per SIMD only.
 static int excl_spl(const ScoreArgs &a) {
-  const int64_t chunks512 = (int64_t)(a.S + 511) / 512 * a.O * a.E;
-  return a.spl == 4 || a.spl == 8 || a.spl == 16 ? a.spl : chunks512 > 16 * (int64_t)kScorerWaves ? 16 : 8;
+  return a.spl == 4 || a.spl == 8 || a.spl == 16 ? a.spl : a.S <= 4 * kWave ? 4 : 8;
 }
 
 int64_t excl_partials(const ScoreArgs &a) {
@@ -5946,28 +5914,51 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
     // LDS: per-class constants, then M and thresholds of a range longer
     // than a wavefront (the longest range has G / tp[0] options)
     const int32_t range_max = P.G / P.tp[0];
-    const size_t mlds = (size_t)P.K * (sizeof(double) + sizeof(float)) +
-                        (range_max >= kWave ? 4 * sizeof(int) * (size_t)range_max : 0);
+    const int32_t range_lds = range_max >= kWave ? 4 * range_max : 0;
     const int64_t items = n_partial * a.O * a.E;  // upper bound of the live items
-    const int64_t waves = a.waves > 0 ? a.waves : kScorerWaves;
-    const unsigned grid = (unsigned)(items < waves ? items : waves);  // at least runs.n
+    const int64_t most = a.waves > 0 ? a.waves : kScorerWaves, waves = items < most ? items : most;
+    // As many wavefronts in a block as two blocks per CU need and the LDS of
+    // three holds.  8 classes at G = 256 (64 orders, 256 candidates, 4096
+    // samples), whole call over four draws: 56.3 us with single wavefronts
+    // that each keep a fixed share of the list and pipeline it, 45.2 with
+    // blocks of 8; on one draw 52.8, 50.7 and 50.8 with 2, 4 and 8.  Where a
+    // wavefront has one or two items the block's barrier costs what the even
+    // shares give: 4 classes at G = 64 18.8 -> 18.4, 2 classes over 200 orders
+    // 17.3 -> 17.6.  16 classes at G = 1024 (18 KB of LDS a wavefront): 37.5
+    // us with 2, 38.6 with 4, 39.8 with 8.
+    const size_t lds_wave = 4 * (size_t)range_lds + kWave * 2 * sizeof(int4);
+    const size_t lds_consts = (size_t)P.K * (sizeof(double) + sizeof(float));
+    const int64_t fit = (int64_t)((kPrepGeneralLdsLimit / 3 - lds_consts) / lds_wave);
+    int64_t nw = (waves + kExclBlocks - 1) / kExclBlocks;
+    if (nw > fit) nw = fit;
+    if (nw > kExclMaxWaves) nw = kExclMaxWaves;
+    if (nw < 1) nw = 1;
+    const unsigned grid = (unsigned)((waves + nw - 1) / nw);
+    const size_t mlds = lds_consts + (size_t)nw * lds_wave;
     const int launches = a.ev_begin ? a.timing_launches : 1;
     if (a.ev_begin) (void)hipEventRecord(a.ev_begin, s);
     for (int rep = 0; rep < launches; ++rep) {
 #define FS_EXCL_LAUNCH(SP, VEC, DUMP, CLAMP)                                                               \
-  k_score_excl<SP, VEC, DUMP, CLAMP><<<grid, kWave, mlds, s>>>(P, tiles, mopt, thr, n_thr, list, a.cap_s,  \
-                                                               a.tail_s, a.O, a.E, a.S, base, partial,     \
-                                                               (int32_t)n_partial, a.tau_dump, a.bounds, runs)
+  {                                                                                                         \
+    if (mlds > 64 * 1024) {                                                                                 \
+      es = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_score_excl<SP, VEC, DUMP, CLAMP>),         \
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlds);                      \
+      if (es != hipSuccess) return es;                                                                      \
+    }                                                                                                       \
+    k_score_excl<SP, VEC, DUMP, CLAMP><<<grid, kWave * (unsigned)nw, mlds, s>>>(                            \
+        P, tiles, mopt, thr, n_thr, list, a.cap_s, a.tail_s, a.O, a.E, a.S, base, partial,                  \
+        (int32_t)n_partial, a.tau_dump, a.bounds, runs, range_lds);                                         \
+  }
 #define FS_EXCL_SPL(SP)                                         \
   if (a.bounds) {                                               \
-    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, false, true);    \
-    else FS_EXCL_LAUNCH(SP, false, false, true);                \
+    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, false, true)     \
+    else FS_EXCL_LAUNCH(SP, false, false, true)                 \
   } else if (a.tau_dump) {                                      \
-    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, true, false);    \
-    else FS_EXCL_LAUNCH(SP, false, true, false);                \
+    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, true, false)     \
+    else FS_EXCL_LAUNCH(SP, false, true, false)                 \
   } else {                                                      \
-    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, false, false);   \
-    else FS_EXCL_LAUNCH(SP, false, false, false);               \
+    if (a.S % 4 == 0) FS_EXCL_LAUNCH(SP, true, false, false)    \
+    else FS_EXCL_LAUNCH(SP, false, false, false)                \
   }
       if (spl == 16) { FS_EXCL_SPL(16) }
       else if (spl == 8) { FS_EXCL_SPL(8) }

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("O", [25, 26, 51, 101, 150, 200])  # 1 (1,200 tiles), 2, 4, 8, and runs that do not divide O
-@pytest.mark.parametrize("setup,waves", [(0, 0), (0, 1), (0, 3), (1, 0), (1, 5)])
+@pytest.mark.parametrize("setup,waves", [(0, 0), (0, 1), (0, 3), (0, 513), (0, 2500), (1, 0), (1, 5)])  # blocks of 1, 2, 5, 8 wavefronts
 def test_list_runs_agree_with_full_solves(env, O, setup, waves):  # noqa: F811
     torch, fs, ctx = env
     w = make_workload("paper-shaped-2class-G16", orders=list(range(O)), with_samples=False)
