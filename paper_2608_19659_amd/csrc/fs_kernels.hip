@@ -972,6 +972,178 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_reg(DevProblem P, const
 }
 
 // ---------------------------------------------------------------------------
+// Dense batch for budgets beyond the register solver's (no critical floors,
+// K <= 16): a team of wavefronts per realisation builds the classes'
+// best-ratio tables in LDS, T[k][g - 1] = B_k[g], the best ratio with at most
+// g GPUs.  The objective is the entry of rank G - K among all of them (the
+// (max,min) convolution of nondecreasing tables is their merge), found by
+// the team's first wavefront without merging: lane (q, k) counts the entries
+// of class k at or below pivot q, the group sums decide between which pivots
+// the rank lies, and every class keeps the window of its entries there.  The
+// canonical allocation reads the tables too, instead of going through the
+// options again.
+//
+// Bound by instruction issue where the tables are small (half of it the
+// search), by the options' chain of level and cell lookups where few teams
+// fit a CU's LDS.  Against a wavefront per realisation that convolves class
+// after class by crossing searches (k_solve_dense), measured with 4 TP
+// degrees and 8 levels: 4 classes at G = 96, 40,000 realisations 170 -> 134
+// us; 8 at G = 128, 16,384 177 -> 96; 8 at G = 256, 8,192 181 -> 80; 12 at G =
+// 500, 2,800 344 -> 67; 16 at G = 1024 (5 TP degrees, 12 levels), 1,024 498 ->
+// 94.
+// ---------------------------------------------------------------------------
+constexpr int kWideMaxK = 16;
+
+// Per team T [K][G] and cells [N], then the bucket map [K][G + 1] bytes
+__host__ __device__ inline size_t wide_lds(const DevProblem &P, int teams) {
+  return 4 * teams * ((size_t)P.K * P.G + P.N) + (((size_t)P.K * (P.G + 1) + 3) & ~(size_t)3);
+}
+
+struct WideConsts {  // indexed per lane
+  float slo[kWideMaxK], demand[kWideMaxK];
+  double rcp[kWideMaxK];
+};
+
+// Entry of rank G - K (from 0) of the union of the K tables; every lane of
+// one wavefront, G >= K.
+__device__ __forceinline__ int wide_select(const int *T, int K, int G) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int lg = 0;
+  while ((1 << lg) < K) ++lg;
+  const int KP = 1 << lg, nv = kWave >> lg, k = lane & (KP - 1), q = lane >> lg;
+  const int *Tk = T + min(k, K - 1) * G;
+  const int target = G - K + 1;  // entries at or below the result, at least
+  // count(<= lo) < target <= count(<= hi); class k's entries in (lo, hi] are
+  // Tk[a .. z)
+  int lo = -1, hi = __float_as_int(1.0f), a = 0, z = k < K ? G : 0;
+  for (;;) {
+    // the window's own smallest and largest entry bound the result
+    const int first = Tk[min(a, G - 1)], last = Tk[max(z - 1, 0)];
+    lo = max(lo, wave_min_dpp(a < z ? first : INT_MAX) - 1);
+    hi = min(hi, wave_max_dpp(a < z ? last : INT_MIN));
+    const int span = hi - lo;
+    if (span <= 1) return hi;
+    // pivots in (lo, hi), ascending with q
+    const int v = span <= nv ? min(lo + q + 1, hi - 1) : lo + (q + 1) * (span / (nv + 1));
+    int x = a, y = z;
+    while (x < y) {
+      const int mid = (x + y) >> 1;
+      if (Tk[mid] <= v) x = mid + 1;
+      else y = mid;
+    }
+    int sum = x;
+    for (int d = 1; d < KP; d <<= 1) sum += __shfl_xor(sum, d, kWave);
+    const uint64_t m = __builtin_amdgcn_ballot_w64(sum >= target);
+    const int up = m != 0 ? (int)__builtin_ctzll(m) >> lg : nv;  // first pivot at or above the result
+    const int xu = __builtin_amdgcn_ds_bpermute(4 * ((min(up, nv - 1) << lg) | k), x);
+    const int xl = __builtin_amdgcn_ds_bpermute(4 * ((max(up - 1, 0) << lg) | k), x);
+    if (up < nv) {
+      hi = __builtin_amdgcn_readlane(v, up << lg);
+      z = xu;
+    }
+    if (up > 0) {
+      lo = __builtin_amdgcn_readlane(v, (up - 1) << lg);
+      a = xl;
+    }
+  }
+}
+
+template <int kThreads, int kTeam>
+__global__ __launch_bounds__(kThreads) void k_solve_wide(DevProblem P, const int8_t *__restrict__ bmap_in,
+                                                         const float *__restrict__ cap,
+                                                         const float *__restrict__ tail, int64_t n, AllocOut out) {
+  extern __shared__ __attribute__((aligned(16))) int wide_mem[];
+  __shared__ WideConsts C;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = P.G, K = P.K, N = P.N, NT = P.NT, B = P.B, per_class = NT * B;
+  constexpr int kTeams = kThreads / kWave / kTeam, kTeamThreads = kTeam * kWave;
+  const int team = wave / kTeam, rank = wave % kTeam, ttid = tid - team * kTeamThreads;
+  int *T = wide_mem + team * (K * G + N);
+  float *cells = reinterpret_cast<float *>(T + K * G);
+  int8_t *bmap = reinterpret_cast<int8_t *>(wide_mem + kTeams * (K * G + N));
+  auto sync = [] {
+    if constexpr (kTeam == 1) wave_lds_fence();
+    else __syncthreads();
+  };
+  for (int x = tid; x < K * (G + 1); x += kThreads) bmap[x] = bmap_in[x];
+  if (tid < K) {
+    C.slo[tid] = P.slo[tid];
+    C.demand[tid] = P.demand[tid];
+    C.rcp[tid] = P.rcp_demand[tid];
+  }
+  __syncthreads();
+  const float inv = 1.0f / (float)per_class;
+  const int one = __float_as_int(1.0f);
+  for (int64_t j = (int64_t)blockIdx.x * kTeams + team; j < n; j += (int64_t)gridDim.x * kTeams) {
+    for (int c = ttid; c < N; c += kTeamThreads) {
+      const float a = cap[j * N + c], l = tail[j * N + c];
+      cells[c] = l <= C.slo[(int)(((float)c + 0.5f) * inv)] ? a : 0.0f;
+    }
+    for (int x = ttid; x < K * G; x += kTeamThreads) T[x] = 0;
+    sync();
+    // a class's table is one wavefront's work: the options max-merged into
+    // their exact cost, then the prefix maximum
+    for (int k = rank; k < K; k += kTeam) {
+      const double rcp = P.rcp_demand[k];
+      int *Tk = T + k * G;
+      for (int ti = 0; ti < NT; ++ti) {
+        const int t = P.tp[ti], nr = G / t;
+        const float *row = cells + (k * NT + ti) * B;
+#pragma unroll 2
+        for (int r = lane + 1; r <= nr; r += kWave) {
+          const int b = bmap[k * (G + 1) + r];
+          const float c = row[max(b, 0)];
+          const int f = __float_as_int((float)((double)((float)r * c) * rcp));
+          atomicMax(&Tk[t * r - 1], b >= 0 ? min(f, one) : 0);
+        }
+      }
+      wave_lds_fence();
+      int carry = 0;
+      for (int g0 = 0; g0 < G; g0 += kWave) {
+        const int g = g0 + lane;
+        const int v = max(wave_scan_max_dpp(g < G ? Tk[g] : 0), carry);
+        if (g < G) Tk[g] = v;
+        carry = __builtin_amdgcn_readlane(v, kWave - 1);
+      }
+    }
+    sync();
+    if (rank == 0) {
+      const int tau = G >= K ? wide_select(T, K, G) : 0;
+      // the canonical allocation: lane k < K, the fewest GPUs reaching tau*,
+      // then the smallest TP
+      RegAlloc A{-1, 0, 0.0f};
+      if (tau > 0) {
+        const int k = min(lane, K - 1);
+        const int *Tk = T + k * G;
+        int x = 0, y = G - 1;
+        while (x < y) {
+          const int mid = (x + y) >> 1;
+          if (Tk[mid] < tau) x = mid + 1;
+          else y = mid;
+        }
+        const int cost = x + 1;
+        for (int ti = NT - 1; ti >= 0; --ti) {
+          const int t = P.tp[ti], r = cost / t;
+          const int b = bmap[k * (G + 1) + r];
+          const float capacity = (float)r * cells[(k * NT + ti) * B + max(b, 0)];
+          const bool hit = lane < K && r > 0 && r * t == cost && b >= 0 &&
+                           __float_as_int((float)((double)capacity * C.rcp[k])) >= tau;
+          A.ti = hit ? ti : A.ti;
+          A.r = hit ? r : A.r;
+          A.served = hit ? capacity : A.served;
+        }
+        A.served = A.served < C.demand[k] ? A.served : C.demand[k];
+        A.served = A.r > 0 ? A.served : 0.0f;
+      }
+      float gp = 0.0f;  // in class order
+      for (int k = 0; k < K; ++k) gp += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(A.served), k));
+      write_reg_alloc(out, j, K, tau, gp, A, lane);
+    }
+    sync();
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Base realisations of each order: tau(conservative), tau(optimistic).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void k_base(DevProblem P, const int8_t *__restrict__ bmap,
@@ -6041,6 +6213,18 @@ static unsigned reg_solve_grid(int64_t n, int threads) {
   return (unsigned)(blocks < kSolveWaves / nw ? blocks : kSolveWaves / nw);
 }
 
+// The table solver for budgets past the register solver's.  Four wavefronts
+// of a block solve apart while that leaves three blocks a CU (8 classes at G =
+// 256: 80 us, together 96; 4 at G = 96: 134 and 266); 12 classes at G = 500
+// take 67 us together and 149 apart.  Where a CU holds a single block, it has
+// eight wavefronts.
+constexpr size_t kWideAlone = 48 * 1024;
+constexpr size_t kWideLarge = 72 * 1024;
+
+static bool wide_solver_supported(const DevProblem &P) {
+  return !P.has_floor && P.K <= kWideMaxK && wide_lds(P, 1) <= kPrepGeneralLdsLimit;
+}
+
 hipError_t launch_solve_batch(const DevProblem &P, const float *cap, const float *tail, int64_t n,
                               AllocOut out, uint8_t *ws, const WsLayout &L, hipStream_t s) {
   if (n == 0) return hipSuccess;
@@ -6055,6 +6239,28 @@ hipError_t launch_solve_batch(const DevProblem &P, const float *cap, const float
   else k_solve_reg<KP, NTP, false><<<grid, threads, lds, s>>>(P, cap, tail, n, out, LV);
     FS_REG_DISPATCH(FS_SOLVE_REG)
 #undef FS_SOLVE_REG
+    return hipGetLastError();
+  }
+  if (wide_solver_supported(P)) {
+    const int8_t *bmap = (const int8_t *)(ws + L.bmap);
+    const size_t l4 = wide_lds(P, 4), l1 = wide_lds(P, 1);
+#define FS_SOLVE_WIDE(TH, TEAM, LDS)                                                                              \
+  {                                                                                                               \
+    const int64_t fit = (int64_t)(kPrepGeneralLdsLimit / ((LDS) + 1024)), most = 2048 / (TH);                     \
+    const int64_t per_cu = fit < 1 ? 1 : fit < most ? fit : most, teams = (TH) / kWave / (TEAM);                  \
+    const int64_t want = (n + teams - 1) / teams;                                                                 \
+    const unsigned grid = (unsigned)(want < 256 * per_cu ? want : 256 * per_cu);                                  \
+    if ((LDS) > 64 * 1024) {                                                                                      \
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_solve_wide<TH, TEAM>),           \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS));           \
+      if (e != hipSuccess) return e;                                                                              \
+    }                                                                                                             \
+    k_solve_wide<TH, TEAM><<<grid, TH, (LDS), s>>>(P, bmap, cap, tail, n, out);                                   \
+  }
+    if (l4 <= kWideAlone) FS_SOLVE_WIDE(256, 1, l4)
+    else if (l1 <= kWideLarge) FS_SOLVE_WIDE(256, 4, l1)
+    else FS_SOLVE_WIDE(512, 8, l1)
+#undef FS_SOLVE_WIDE
     return hipGetLastError();
   }
   const size_t base = lds_bytes_solver(P, 1), staged = base + stage_bytes(P);
