@@ -1048,98 +1048,122 @@ __device__ __forceinline__ int wide_select(const int *T, int K, int G) {
   }
 }
 
+// One realisation by a team of kTeam wavefronts: the objective's bits, and in
+// the first wavefront the allocation (lane k < K) and its served total.  The
+// team's LDS is free for another realisation after its next barrier.
+template <int kTeam>
+__device__ __forceinline__ int wide_solve(const DevProblem &P, const WideConsts &C, const int8_t *bmap, int *T,
+                                          float *cells, const float *__restrict__ cap,
+                                          const float *__restrict__ tail, int ttid, int rank, RegAlloc &A, float &gp) {
+  constexpr int kTeamThreads = kTeam * kWave;
+  const int lane = ttid & (kWave - 1);
+  const int G = P.G, K = P.K, N = P.N, NT = P.NT, B = P.B;
+  const float inv = 1.0f / (float)(NT * B);
+  const int one = __float_as_int(1.0f);
+  auto sync = [] {
+    if constexpr (kTeam == 1) wave_lds_fence();
+    else __syncthreads();
+  };
+  int tau = 0;
+  for (int c = ttid; c < N; c += kTeamThreads) {
+    const float a = cap[c], l = tail[c];
+    cells[c] = l <= C.slo[(int)(((float)c + 0.5f) * inv)] ? a : 0.0f;
+  }
+  for (int x = ttid; x < K * G; x += kTeamThreads) T[x] = 0;
+  sync();
+  // a class's table is one wavefront's work: the options max-merged into
+  // their exact cost, then the prefix maximum
+  for (int k = rank; k < K; k += kTeam) {
+    const double rcp = P.rcp_demand[k];
+    int *Tk = T + k * G;
+    for (int ti = 0; ti < NT; ++ti) {
+      const int t = P.tp[ti], nr = G / t;
+      const float *row = cells + (k * NT + ti) * B;
+#pragma unroll 2
+      for (int r = lane + 1; r <= nr; r += kWave) {
+        const int b = bmap[k * (G + 1) + r];
+        const float c = row[max(b, 0)];
+        const int f = __float_as_int((float)((double)((float)r * c) * rcp));
+        atomicMax(&Tk[t * r - 1], b >= 0 ? min(f, one) : 0);
+      }
+    }
+    wave_lds_fence();
+    int carry = 0;
+    for (int g0 = 0; g0 < G; g0 += kWave) {
+      const int g = g0 + lane;
+      const int v = max(wave_scan_max_dpp(g < G ? Tk[g] : 0), carry);
+      if (g < G) Tk[g] = v;
+      carry = __builtin_amdgcn_readlane(v, kWave - 1);
+    }
+  }
+  sync();
+  if (rank == 0) {
+    tau = G >= K ? wide_select(T, K, G) : 0;
+    // the canonical allocation: lane k < K, the fewest GPUs reaching tau*,
+    // then the smallest TP
+    A = RegAlloc{-1, 0, 0.0f};
+    if (tau > 0) {
+      const int k = min(lane, K - 1);
+      const int *Tk = T + k * G;
+      int x = 0, y = G - 1;
+      while (x < y) {
+        const int mid = (x + y) >> 1;
+        if (Tk[mid] < tau) x = mid + 1;
+        else y = mid;
+      }
+      const int cost = x + 1;
+      for (int ti = NT - 1; ti >= 0; --ti) {
+        const int t = P.tp[ti], r = cost / t;
+        const int b = bmap[k * (G + 1) + r];
+        const float capacity = (float)r * cells[(k * NT + ti) * B + max(b, 0)];
+        const bool hit = lane < K && r > 0 && r * t == cost && b >= 0 &&
+                         __float_as_int((float)((double)capacity * C.rcp[k])) >= tau;
+        A.ti = hit ? ti : A.ti;
+        A.r = hit ? r : A.r;
+        A.served = hit ? capacity : A.served;
+      }
+      A.served = A.served < C.demand[k] ? A.served : C.demand[k];
+      A.served = A.r > 0 ? A.served : 0.0f;
+    }
+    gp = 0.0f;  // in class order
+    for (int k = 0; k < K; ++k) gp += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(A.served), k));
+  }
+  return tau;
+}
+
+// What a block's teams share, staged by all of its threads (with a barrier).
+__device__ __forceinline__ void wide_stage(const DevProblem &P, const int8_t *__restrict__ bmap_in, int8_t *bmap,
+                                           WideConsts &C) {
+  for (int x = threadIdx.x; x < P.K * (P.G + 1); x += blockDim.x) bmap[x] = bmap_in[x];
+  if ((int)threadIdx.x < P.K) {
+    C.slo[threadIdx.x] = P.slo[threadIdx.x];
+    C.demand[threadIdx.x] = P.demand[threadIdx.x];
+    C.rcp[threadIdx.x] = P.rcp_demand[threadIdx.x];
+  }
+  __syncthreads();
+}
+
 template <int kThreads, int kTeam>
 __global__ __launch_bounds__(kThreads) void k_solve_wide(DevProblem P, const int8_t *__restrict__ bmap_in,
                                                          const float *__restrict__ cap,
                                                          const float *__restrict__ tail, int64_t n, AllocOut out) {
   extern __shared__ __attribute__((aligned(16))) int wide_mem[];
   __shared__ WideConsts C;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int G = P.G, K = P.K, N = P.N, NT = P.NT, B = P.B, per_class = NT * B;
-  constexpr int kTeams = kThreads / kWave / kTeam, kTeamThreads = kTeam * kWave;
-  const int team = wave / kTeam, rank = wave % kTeam, ttid = tid - team * kTeamThreads;
-  int *T = wide_mem + team * (K * G + N);
-  float *cells = reinterpret_cast<float *>(T + K * G);
-  int8_t *bmap = reinterpret_cast<int8_t *>(wide_mem + kTeams * (K * G + N));
-  auto sync = [] {
+  constexpr int kTeams = kThreads / kWave / kTeam;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int team = wave / kTeam, rank = wave % kTeam, ttid = tid - team * kTeam * kWave;
+  const int words = P.K * P.G + P.N;
+  int *T = wide_mem + team * words;
+  float *cells = reinterpret_cast<float *>(T + P.K * P.G);
+  int8_t *bmap = reinterpret_cast<int8_t *>(wide_mem + kTeams * words);
+  wide_stage(P, bmap_in, bmap, C);
+  for (int64_t j = (int64_t)blockIdx.x * kTeams + team; j < n; j += (int64_t)gridDim.x * kTeams) {
+    RegAlloc A;
+    float gp;
+    const int tau = wide_solve<kTeam>(P, C, bmap, T, cells, cap + j * P.N, tail + j * P.N, ttid, rank, A, gp);
+    if (rank == 0) write_reg_alloc(out, j, P.K, tau, gp, A, ttid & (kWave - 1));
     if constexpr (kTeam == 1) wave_lds_fence();
     else __syncthreads();
-  };
-  for (int x = tid; x < K * (G + 1); x += kThreads) bmap[x] = bmap_in[x];
-  if (tid < K) {
-    C.slo[tid] = P.slo[tid];
-    C.demand[tid] = P.demand[tid];
-    C.rcp[tid] = P.rcp_demand[tid];
-  }
-  __syncthreads();
-  const float inv = 1.0f / (float)per_class;
-  const int one = __float_as_int(1.0f);
-  for (int64_t j = (int64_t)blockIdx.x * kTeams + team; j < n; j += (int64_t)gridDim.x * kTeams) {
-    for (int c = ttid; c < N; c += kTeamThreads) {
-      const float a = cap[j * N + c], l = tail[j * N + c];
-      cells[c] = l <= C.slo[(int)(((float)c + 0.5f) * inv)] ? a : 0.0f;
-    }
-    for (int x = ttid; x < K * G; x += kTeamThreads) T[x] = 0;
-    sync();
-    // a class's table is one wavefront's work: the options max-merged into
-    // their exact cost, then the prefix maximum
-    for (int k = rank; k < K; k += kTeam) {
-      const double rcp = P.rcp_demand[k];
-      int *Tk = T + k * G;
-      for (int ti = 0; ti < NT; ++ti) {
-        const int t = P.tp[ti], nr = G / t;
-        const float *row = cells + (k * NT + ti) * B;
-#pragma unroll 2
-        for (int r = lane + 1; r <= nr; r += kWave) {
-          const int b = bmap[k * (G + 1) + r];
-          const float c = row[max(b, 0)];
-          const int f = __float_as_int((float)((double)((float)r * c) * rcp));
-          atomicMax(&Tk[t * r - 1], b >= 0 ? min(f, one) : 0);
-        }
-      }
-      wave_lds_fence();
-      int carry = 0;
-      for (int g0 = 0; g0 < G; g0 += kWave) {
-        const int g = g0 + lane;
-        const int v = max(wave_scan_max_dpp(g < G ? Tk[g] : 0), carry);
-        if (g < G) Tk[g] = v;
-        carry = __builtin_amdgcn_readlane(v, kWave - 1);
-      }
-    }
-    sync();
-    if (rank == 0) {
-      const int tau = G >= K ? wide_select(T, K, G) : 0;
-      // the canonical allocation: lane k < K, the fewest GPUs reaching tau*,
-      // then the smallest TP
-      RegAlloc A{-1, 0, 0.0f};
-      if (tau > 0) {
-        const int k = min(lane, K - 1);
-        const int *Tk = T + k * G;
-        int x = 0, y = G - 1;
-        while (x < y) {
-          const int mid = (x + y) >> 1;
-          if (Tk[mid] < tau) x = mid + 1;
-          else y = mid;
-        }
-        const int cost = x + 1;
-        for (int ti = NT - 1; ti >= 0; --ti) {
-          const int t = P.tp[ti], r = cost / t;
-          const int b = bmap[k * (G + 1) + r];
-          const float capacity = (float)r * cells[(k * NT + ti) * B + max(b, 0)];
-          const bool hit = lane < K && r > 0 && r * t == cost && b >= 0 &&
-                           __float_as_int((float)((double)capacity * C.rcp[k])) >= tau;
-          A.ti = hit ? ti : A.ti;
-          A.r = hit ? r : A.r;
-          A.served = hit ? capacity : A.served;
-        }
-        A.served = A.served < C.demand[k] ? A.served : C.demand[k];
-        A.served = A.r > 0 ? A.served : 0.0f;
-      }
-      float gp = 0.0f;  // in class order
-      for (int k = 0; k < K; ++k) gp += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(A.served), k));
-      write_reg_alloc(out, j, K, tau, gp, A, lane);
-    }
-    sync();
   }
 }
 
@@ -3501,6 +3525,46 @@ __global__ __launch_bounds__(64) void k_certify(DevProblem P, const int8_t *__re
   const int tau = wave_solve(P, bm, rz, lds, &fm, &wa, &gp);
   write_alloc(R == 0 ? cons : opt, o, P.K, tau, fm, gp, wa);
   write_cert_rec(rec + (size_t)o * 2 + R, P.K, tau, fm, gp, 0.0, wa);
+}
+
+// The same by the table solver (no critical floors, K <= 16), a block of four
+// wavefronts per realisation.  The call's kernels (bucket map, this, state):
+// 12.3 us against 26.4 for 2 orders of 4 classes at G = 96, 19.3 against 71.7
+// for 64 orders of 8 at G = 256, 51 against 493 for 4 orders of 16 at G = 1024.
+constexpr int kCertWideThreads = 4 * kWave;
+
+__global__ __launch_bounds__(kCertWideThreads) void k_certify_wide(DevProblem P, const int8_t *__restrict__ bmap_in,
+                                                                   const float *__restrict__ cap_lo,
+                                                                   const float *__restrict__ cap_hi,
+                                                                   const float *__restrict__ tail_lo,
+                                                                   const float *__restrict__ tail_hi, AllocOut cons,
+                                                                   AllocOut opt, CertRec *__restrict__ rec) {
+  extern __shared__ __attribute__((aligned(16))) int wide_mem[];
+  __shared__ WideConsts C;
+  const int R = blockIdx.x, o = blockIdx.y, lane = threadIdx.x & (kWave - 1);
+  const int rank = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t off = (size_t)o * P.N;
+  int *T = wide_mem;
+  float *cells = reinterpret_cast<float *>(T + P.K * P.G);
+  int8_t *bmap = reinterpret_cast<int8_t *>(cells + P.N);
+  wide_stage(P, bmap_in, bmap, C);
+  RegAlloc A;
+  float gp;
+  const int tau = wide_solve<kCertWideThreads / kWave>(P, C, bmap, T, cells, (R == 0 ? cap_lo : cap_hi) + off,
+                                                       (R == 0 ? tail_hi : tail_lo) + off, threadIdx.x, rank, A, gp);
+  if (rank != 0) return;
+  write_reg_alloc(R == 0 ? cons : opt, o, P.K, tau, gp, A, lane);
+  CertRec *me = rec + (size_t)o * 2 + R;
+  if (lane == 0) {
+    me->tau = tau;
+    me->floors_met = 1;
+    me->goodput = gp;
+    me->goodput64 = 0.0;
+  }
+  if (lane < P.K) {
+    me->tp_index[lane] = A.ti;
+    me->replicas[lane] = A.r;
+  }
 }
 
 // Gap and state of each order from its two records: the max-min gap
@@ -6346,7 +6410,15 @@ hipError_t launch_certify(const DevProblem &P, const float *cap_lo, const float 
   const int stage = stage_fits(staged) ? 1 : 0;
   CertRec *rec = (CertRec *)(ws + L.crec);
   const int8_t *bmap = (const int8_t *)(ws + L.bmap);
-  if (stage)
+  if (wide_solver_supported(P)) {
+    const size_t lds = wide_lds(P, 1);
+    if (lds > 64 * 1024) {
+      const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_certify_wide),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (ea != hipSuccess) return ea;
+    }
+    k_certify_wide<<<dim3(2, O), kCertWideThreads, lds, s>>>(P, bmap, cap_lo, cap_hi, tail_lo, tail_hi, cons, opt, rec);
+  } else if (stage)
     k_certify<1><<<dim3(2, O), 64, staged, s>>>(P, bmap, cap_lo, cap_hi, tail_lo, tail_hi, cons, opt, rec);
   else
     k_certify<0><<<dim3(2, O), 64, base, s>>>(P, bmap, cap_lo, cap_hi, tail_lo, tail_hi, cons, opt, rec);

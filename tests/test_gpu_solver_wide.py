@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from test_gpu_parity import assert_alloc_equal, env, gpu_solve  # noqa: F401 (env is a fixture)
-from test_gpu_solver_edges import edge_tables
+from test_gpu_solver_edges import edge_tables, test_certificate_edges as certificate_edges
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +27,9 @@ def test_wide_solver_edges(env, orc, K, G, tp, levels):  # noqa: F811
     g = gpu_solve(env, p, cap[rows], tail[rows])
     for j in list(range(n)) + list(range(2040, 2048 + 61)):
         assert_alloc_equal(p, g, j, want[rows[j]], f"K={K} G={G} tp={tp} row {j}")
+
+
+@pytest.mark.parametrize("K,G,tp,levels", [(2, 300, [7], 1), (4, 96, [1, 2, 4, 8], 8), (8, 256, [1, 2, 4, 8], 8),
+                                           (16, 512, [1, 2, 4, 8, 16], 12), (16, 2400, [2, 8], 3)])
+def test_wide_certificate_edges(env, orc, K, G, tp, levels):  # noqa: F811
+    certificate_edges(env, orc, K, G, tp, levels)
