@@ -3675,12 +3675,17 @@ __global__ __launch_bounds__(kCertThreads) void k_certify_reg(DevProblem P, cons
 // completion, so each class first merges its allowed options per cost c into
 // the largest served rate (the earliest option among equal ones) -- no other
 // option of that cost can be the best at any budget -- and the layer update
-// runs over costs, lanes over the budgets g:
+// runs over the costs that serve more than every cheaper one, lanes over the
+// budgets g:
 //   V_k[g] = best of (V_{k+1}[g] if empty allowed) and, for c = 1..g,
 //            (A_k[c] + V_{k+1}[g - c], c + GPUs of it),
 // equal (goodput, GPUs) going to the earlier option (the empty one first).
 // The choice of every (class, budget) is kept, and the allocation is read
 // in class order from the full budget.
+// Bound by instruction issue, costs times budgets.  Listing only the costs
+// that serve more than every cheaper one, dense batches: 4 classes at G = 96
+// 365 -> 171 us (20,000 realisations), 8 at G = 256 484 -> 131 (2,048), 12 at
+// G = 500 1,932 -> 343 (350).
 // ---------------------------------------------------------------------------
 // A budget's entry of the layer: its best goodput (-inf: no allowed
 // completion) and key = GPUs << 16 (the low 16 bits zero).
@@ -3745,15 +3750,18 @@ __device__ void wave_lex_stage(const DevProblem &P, const int8_t *__restrict__ b
     const float slo = P.slo[k], demand = P.demand[k], fl = P.floor_rps[k];
     const double rcp = P.rcp_demand[k];
     // per cost the best allowed option (served rate, then the first in
-    // (TP, replicas) order), listed for the costs that have one (a ballot per
-    // 64 costs)
-    int n_c = 0;
+    // (TP, replicas) order), listed for the costs that serve more than every
+    // cheaper one (a ballot per 64 costs): any other is beaten by that cheaper
+    // option at every budget (at least the goodput, fewer GPUs), and with the
+    // empty option allowed one that serves nothing is.  (Without it the rates
+    // are above 0, so their bits order them.)
+    int n_c = 0, carry = empty_ok ? 0 : -1;
     for (int c0 = 1; c0 <= G; c0 += kWave) {
       const int c = c0 + lane;
       float best = 0.0f;
       int bq = -1;
       for (int ti = 0; ti < NT && c <= G; ++ti) {  // options of cost c in (TP, replicas) order
-        const int t = P.tp[ti], r = c / t;
+        const int t = P.tp[ti], r = (int)((float)c * (1.0f / (float)t) + 0.5f);  // c / t where t divides c
         if (r * t != c) continue;
         const int b = bmap[k * (G + 1) + r];
         if (b < 0) continue;
@@ -3768,8 +3776,12 @@ __device__ void wave_lex_stage(const DevProblem &P, const int8_t *__restrict__ b
           bq = P.optoff[ti] + r - 1;
         }
       }
-      const uint64_t m = __builtin_amdgcn_ballot_w64(bq >= 0);
-      if (bq >= 0) {
+      const int ab = bq >= 0 ? __float_as_int(best) : -1;
+      const int upto = wave_scan_max_dpp(ab);
+      const bool keep = ab > max(__builtin_amdgcn_update_dpp(-1, upto, 0x138, 0xF, 0xF, false), carry);  // wave_shr:1
+      carry = max(carry, __builtin_amdgcn_readlane(upto, kWave - 1));
+      const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+      if (keep) {
         const int at = n_c + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
         X.arate[at] = best;
         X.akey[at] = (c << 16) | (bq + 1);

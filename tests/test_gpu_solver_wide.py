@@ -6,7 +6,9 @@ import numpy as np
 import pytest
 
 from test_gpu_parity import assert_alloc_equal, env, gpu_solve  # noqa: F401 (env is a fixture)
-from test_gpu_solver_edges import edge_tables, test_certificate_edges as certificate_edges
+from test_gpu_solver_edges import edge_tables
+from test_gpu_solver_edges import test_certificate_edges as certificate_edges
+from test_gpu_solver_edges import test_dense_lex_solver_edges as lex_edges
 
 pytestmark = pytest.mark.gpu
 
@@ -33,3 +35,11 @@ def test_wide_solver_edges(env, orc, K, G, tp, levels):  # noqa: F811
                                            (16, 512, [1, 2, 4, 8, 16], 12), (16, 2400, [2, 8], 3)])
 def test_wide_certificate_edges(env, orc, K, G, tp, levels):  # noqa: F811
     certificate_edges(env, orc, K, G, tp, levels)
+
+
+@pytest.mark.parametrize("K,G,tp,levels", [(1, 200, [1, 3], 2), (3, 257, [1, 2], 2), (4, 100, [3, 5, 7, 64], 9),
+                                           (6, 128, [1, 2, 4, 8], 8), (17, 70, [1, 2], 4)])
+def test_wide_lex_edges(env, orc, K, G, tp, levels):  # noqa: F811
+    """The whole objective past 64 GPUs (undominated costs over several groups
+    of 64 budgets)."""
+    lex_edges(env, orc, K, G, tp, levels)
