@@ -306,10 +306,11 @@ fs_status fs_certify_lex(fs_context *ctx, const fs_problem *p, fs_intervals iv, 
  * call) plus the candidate cell's options at the sample; with
  * FS_OPT_SCORE_KERNEL set to 1, or where those tables do not fit, every scenario
  * is solved in full (two max-min solves and two knapsacks, one wavefront:
- * far slower).  Both give the same bits.  The orders' own stages are solved
- * on a second stream of the context, forked from and joined back into
- * `stream` within the call, so every output is ordered before later work on
- * `stream`.  Workspace: fs_score_lex_workspace_size; sizes as in
+ * far slower).  Both give the same bits.  Where the budget is past 64 GPUs,
+ * there are critical floors or more than 16 classes, the orders' own stages
+ * are solved on a second stream of the context, forked from and joined back
+ * into `stream` within the call, so every output is ordered before later work
+ * on `stream`.  Workspace: fs_score_lex_workspace_size; sizes as in
  * fs_score_candidates; FS_ERR_UNSUPPORTED where the whole objective does not
  * fit (see fs_solve_batch_lex). */
 fs_status fs_score_lex_workspace_size(const fs_problem *p, int32_t n_orders, int32_t n_cand, int32_t n_samples,
@@ -454,8 +455,7 @@ fs_status fs_loop_workspace_size(const fs_problem *p, int32_t n_orders, int32_t 
  * and returns early once no trajectory is running (the call then returns
  * with the stream idle); check_every = 0: exactly max_rounds rounds are
  * enqueued without waiting.  Limits as fs_score_candidates; max_rounds in
- * [0, 65535]; critical floors are supported (the scorer then solves every
- * scenario in full). */
+ * [0, 65535]; critical floors are supported. */
 fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv, int32_t n_orders,
                           const float *d_truth_cap, const float *d_truth_tail,
                           const int32_t *d_cand, int32_t n_cand, const float *d_cap_s,

@@ -29,7 +29,7 @@ struct fs_context {
   int32_t *pinned;   // pinned host word: running trajectories read back by fs_profile_loop
   void *scratch;     // this device's address of the static scratch of fs_score_candidates_noalloc
   // a second stream (default priority) and the fork / join events of the
-  // stage-wise score
+  // stage-wise score; the profiling loop waits on the fork event for its count
   hipStream_t side;
   hipEvent_t fork, join;
   struct Timed {

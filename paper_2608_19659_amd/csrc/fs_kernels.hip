@@ -5913,7 +5913,6 @@ WsLayout ws_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S) {
   L.list = at; at = align256(at + sizeof(int4) * (size_t)O * (size_t)E);
   // B tables of the general set-up, one per (order, realisation, class)
   L.btab = at; at = align256(at + (excl ? sizeof(int32_t) * (size_t)O * 2 * P.K * P.G : 0));
-  L.live = at; at = align256(at + sizeof(int32_t));
   L.crec = at; at = align256(at + sizeof(CertRec) * 2 * (size_t)(O > 0 ? O : 1));
   L.total_min = at;
   // the exclusion scorer with critical floors: both variants' tables
