@@ -520,40 +520,58 @@ def policy_bench(args):
     ctx.close()
 
 
-def lex_work_per_scenario(problem) -> float:
+def lex_work_per_scenario(problem, cap, tail, tau) -> float:
     """Algorithmic work of one solve under the whole objective, in VALU
-    lane-slots, for the algorithm k_solve_dense_lex runs: per existing option
-    its ratio (multiply, quotient, min with 1, tail compare, select, max into
-    its budget slot: 5 + DIV_OPS); per class the prefix maximum (G - 1);
-    each (max,min) target a crossing search (per step a compare and a
-    select, then two selects and a max) -- every budget of the K - 2 middle
-    classes and budget G of the last; then level (3)'s knapsack: per class
-    and cost c the options of that cost merged (per existing option its
-    ratio test and served rate, 5 + DIV_OPS, and a compare and two selects),
-    and per class and budget g one candidate per cost c <= g (a conversion,
-    a binary64 add, the (goodput, GPUs, option) order in four compares and
-    two logic ops, and four selects: 12; binary64 adds issue at the full
-    rate on gfx950)."""
+    lane-slots, for the algorithm k_solve_lex_reg runs (budgets of at most 64
+    GPUs), averaged over the given realisations and their objectives: per
+    existing option its ratio (multiply, quotient, min with 1, max into its
+    cost: 3 + DIV_OPS); per class the prefix maximum (G - 1) and its place in
+    the merge of the classes' tables (K - 1 merges of the G smallest: a min
+    and six compare-exchanges of 2 per entry); then level (3)'s knapsack: per
+    class the options merged per cost (per option its ratio test and served
+    rate, 5 + DIV_OPS, and a compare and two selects) and the prefix maximum
+    that keeps the costs serving more than every cheaper one; and per middle
+    class one candidate per budget g and kept cost c <= g (a conversion, a
+    binary64 add, the (goodput, GPUs, option) order in four compares and two
+    logic ops, and four selects: 12), for the last class per budget and the
+    first per kept cost."""
+    import numpy as np
     G, K = problem.budget, problem.n_classes
-    ex = existing_options(problem)
-    n_ex = int(ex.sum())
-    per = n_ex * (5 + DIV_OPS) + K * (G - 1)
-    if K >= 2:
-        top = 1
-        while 2 * top <= G + 1:
-            top *= 2
-        steps = int(math.log2(top)) + 1
-        per += ((K - 2) * (G + 1) + 1) * (2 * steps + 3)
-    per += n_ex * (5 + DIV_OPS + 3)
-    return float(per) + 12.0 * K * G * (G + 1) / 2
+    tp = [int(t) for t in problem.tp]
+    B = len(problem.levels)
+    n_ex = int(existing_options(problem).sum())
+    per = n_ex * (3 + DIV_OPS) + K * (G - 1) + (K - 1) * 13 * G
+    per += n_ex * (5 + DIV_OPS + 3) + K * (G - 1)
+    options = []  # per class: (cost, cell, r) of the existing options
+    for k in range(K):
+        rows = []
+        for ti, t in enumerate(tp):
+            for r in range(1, G // t + 1):
+                fit = np.nonzero(np.float32(problem.demand[k]) / np.float32(r) <= problem.levels)[0]
+                if len(fit):
+                    rows.append((t * r, (k * len(tp) + ti) * B + int(fit[0]), r))
+        options.append(np.array(rows, np.int64).reshape(-1, 3))
+    extra = 0.0
+    for c, l, v in zip(cap, tail, tau):
+        for k in range(K):
+            cost, cell, r = options[k].T
+            ok = l[cell] <= problem.slo[k]
+            rate = np.where(ok, np.minimum(r * c[cell].astype(np.float64), problem.demand[k]), 0.0)
+            allowed = np.where(ok, np.minimum(rate / problem.demand[k], 1.0), 0.0) >= v * (1 - 1e-7)
+            best = np.full(G + 1, -1.0)
+            np.maximum.at(best, cost[allowed], rate[allowed])
+            floor = np.maximum(np.maximum.accumulate(np.concatenate(([-1.0], best[:-1]))), 0.0 if v <= 0 else -1.0)
+            kept = np.nonzero(best > floor)[0]
+            extra += G if k == K - 1 and k > 0 else 12.0 * len(kept) if k == 0 else 12.0 * float((G + 1 - kept).sum())
+    return float(per) + extra / max(len(cap), 1)
 
 
 def lex_bench(args):
     """Dense solves under the whole lexicographic objective (fs_solve_batch_lex)
     on point realisations drawn inside the workload's intervals, against the
     max-min solve (fs_solve_batch) on the same inputs.  The roofline object
-    reports k_solve_dense_lex against the VALU peak (the call's launch pair
-    also holds a set-up kernel of a few microseconds).  The CPU baseline is
+    reports k_solve_lex_reg against the VALU peak (the call is that one
+    launch), its work counted on the first 64 realisations.  The CPU baseline is
     the oracle's knapsack on a bounded sample of the same realisations."""
     import numpy as np
     import torch
@@ -613,7 +631,7 @@ def lex_bench(args):
     mm_plan = fs.ScorePlan(ctx, p, div, cand_d, cs_d, ts_d, stream=stream)
     _, ms_sm = timed(mm_plan.run, n_short)
     live = int((~ws_full.intervals.measured[:, ws_full.cand].astype(bool)).sum()) * Sx
-    slots = lex_work_per_scenario(p)
+    slots = lex_work_per_scenario(p, cap_h[:64], tail_h[:64], r_lex["objective"][:64].cpu().numpy())
     achieved = slots * n / (ms_lex / 1e3)
     cpu = None
     if not args.no_cpu_baseline:
@@ -643,7 +661,8 @@ def lex_bench(args):
                             "value": live / (ms_sl / 1e3), "unit": "scenarios/s",
                             "full_solves_ms_per_call": ms_full, "maxmin_score_ms_per_call": ms_sm},
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12, "unit": "TOP/s",
-                     "frac": achieved / VALU_PEAK_OPS, "traffic": None, "kernel": "k_solve_dense_lex",
+                     "frac": achieved / VALU_PEAK_OPS, "traffic": None,
+                     "kernel": "k_solve_lex_reg" if p.budget <= 64 else "k_solve_dense_lex",
                      "op": "VALU lane-slot", "slots_per_scenario": slots, "scenarios_per_launch": n,
                      "kernel_ms_avg": ms_lex},
         "cpu_baseline": cpu,
