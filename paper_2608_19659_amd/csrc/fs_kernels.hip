@@ -13,7 +13,11 @@
 // resolved after tau* is known: each class takes the fewest GPUs reaching
 // tau* and, among those options, the smallest TP.
 //
-// Two kernel families:
+// Kernel families that solve a scenario in full:
+//  * register solver (no floors, G <= 64, K <= 16): one wavefront owns a
+//    scenario, a lane per budget, every class's table in a register.
+//  * table solver (no floors, K <= 16): the classes' tables in LDS, tau* by a
+//    rank selection over them.
 //  * wave-per-scenario (any problem): one wavefront owns a scenario; per-class
 //    tables live in LDS; options are spread over lanes and merged with LDS
 //    atomic max; prefix maxima use a wave scan; the DP spreads budgets over
@@ -23,6 +27,8 @@
 //    same (order, candidate), so the order's option values are wave-uniform
 //    scalar loads and only the candidate's own cell differs per lane.  All
 //    tables are register-resident and the DP is fully unrolled.
+// The exclusion scorer and the interval tables solve none in full: they
+// combine one cell's options with what the other classes allow.
 //
 // Fulfillment values are compared as int32 bit patterns: for binary32 values
 // >= +0 the integer order is the float order, -1 marks "no allowed choice"
@@ -37,7 +43,7 @@ namespace fs {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Scalar helpers shared by both kernel families.
+// Scalar helpers shared by the kernel families.
 // ---------------------------------------------------------------------------
 
 // Ratio of r replicas of a cell (cap, tail) for a class with SLO `slo` and
