@@ -1054,6 +1054,35 @@ __device__ __forceinline__ int wide_select(const int *T, int K, int G) {
   }
 }
 
+// T[g - 1] = B_k[g] of class k by one wavefront: the options max-merged into
+// their exact cost, then the prefix maximum.  usable(cell): its capacity, 0
+// when its tail breaks the SLO.
+template <class F>
+__device__ __forceinline__ void wide_table(const DevProblem &P, int k, const int8_t *bmap, int *T, F usable) {
+  const int lane = threadIdx.x & (kWave - 1), G = P.G, one = __float_as_int(1.0f);
+  const double rcp = P.rcp_demand[k];
+  for (int g = lane; g < G; g += kWave) T[g] = 0;
+  wave_lds_fence();
+  for (int ti = 0; ti < P.NT; ++ti) {
+    const int t = P.tp[ti], nr = G / t, row = (k * P.NT + ti) * P.B;
+#pragma unroll 2
+    for (int r = lane + 1; r <= nr; r += kWave) {
+      const int b = bmap[k * (G + 1) + r];
+      const float c = usable(row + max(b, 0));
+      const int f = __float_as_int((float)((double)((float)r * c) * rcp));
+      atomicMax(&T[t * r - 1], b >= 0 ? min(f, one) : 0);
+    }
+  }
+  wave_lds_fence();
+  int carry = 0;
+  for (int g0 = 0; g0 < G; g0 += kWave) {
+    const int g = g0 + lane;
+    const int v = max(wave_scan_max_dpp(g < G ? T[g] : 0), carry);
+    if (g < G) T[g] = v;
+    carry = __builtin_amdgcn_readlane(v, kWave - 1);
+  }
+}
+
 // One realisation by a team of kTeam wavefronts: the objective's bits, and in
 // the first wavefront the allocation (lane k < K) and its served total.  The
 // team's LDS is free for another realisation after its next barrier.
@@ -1065,7 +1094,6 @@ __device__ __forceinline__ int wide_solve(const DevProblem &P, const WideConsts 
   const int lane = ttid & (kWave - 1);
   const int G = P.G, K = P.K, N = P.N, NT = P.NT, B = P.B;
   const float inv = 1.0f / (float)(NT * B);
-  const int one = __float_as_int(1.0f);
   auto sync = [] {
     if constexpr (kTeam == 1) wave_lds_fence();
     else __syncthreads();
@@ -1075,33 +1103,9 @@ __device__ __forceinline__ int wide_solve(const DevProblem &P, const WideConsts 
     const float a = cap[c], l = tail[c];
     cells[c] = l <= C.slo[(int)(((float)c + 0.5f) * inv)] ? a : 0.0f;
   }
-  for (int x = ttid; x < K * G; x += kTeamThreads) T[x] = 0;
   sync();
-  // a class's table is one wavefront's work: the options max-merged into
-  // their exact cost, then the prefix maximum
-  for (int k = rank; k < K; k += kTeam) {
-    const double rcp = P.rcp_demand[k];
-    int *Tk = T + k * G;
-    for (int ti = 0; ti < NT; ++ti) {
-      const int t = P.tp[ti], nr = G / t;
-      const float *row = cells + (k * NT + ti) * B;
-#pragma unroll 2
-      for (int r = lane + 1; r <= nr; r += kWave) {
-        const int b = bmap[k * (G + 1) + r];
-        const float c = row[max(b, 0)];
-        const int f = __float_as_int((float)((double)((float)r * c) * rcp));
-        atomicMax(&Tk[t * r - 1], b >= 0 ? min(f, one) : 0);
-      }
-    }
-    wave_lds_fence();
-    int carry = 0;
-    for (int g0 = 0; g0 < G; g0 += kWave) {
-      const int g = g0 + lane;
-      const int v = max(wave_scan_max_dpp(g < G ? Tk[g] : 0), carry);
-      if (g < G) Tk[g] = v;
-      carry = __builtin_amdgcn_readlane(v, kWave - 1);
-    }
-  }
+  for (int k = rank; k < K; k += kTeam)  // a class's table is one wavefront's work
+    wide_table(P, k, bmap, T + k * G, [&](int cell) { return cells[cell]; });
   sync();
   if (rank == 0) {
     tau = G >= K ? wide_select(T, K, G) : 0;
@@ -3691,7 +3695,7 @@ __global__ __launch_bounds__(kCertThreads) void k_certify_reg(DevProblem P, cons
 // Bound by instruction issue, costs times budgets.  Listing only the costs
 // that serve more than every cheaper one, dense batches: 4 classes at G = 96
 // 365 -> 171 us (20,000 realisations), 8 at G = 256 484 -> 131 (2,048), 12 at
-// G = 500 1,932 -> 343 (350).
+// G = 500 1,932 -> 343 (350), the max-min part as it was.
 // ---------------------------------------------------------------------------
 // A budget's entry of the layer: its best goodput (-inf: no allowed
 // completion) and key = GPUs << 16 (the low 16 bits zero).
@@ -3893,6 +3897,27 @@ __device__ __host__ inline size_t lex_work_bytes(int K, int G) {
   const size_t b = 16 * (g1 + 1) + 12 * (size_t)lex_cost_stride(G) + (size_t)K * g1 * sizeof(int16_t);
   const size_t solver = 3 * g1 * sizeof(int);
   return 16 + (b > solver ? b : solver);  // 16: aligning the start
+}
+
+// Max-min objective of one wavefront's realisation in a whole-objective work
+// area: by the tables and the rank selection where they fit it, otherwise
+// class after class (wave_solve).  Whole dense solves: 8 classes at G = 256
+// 130.5 -> 114.5 us (2,048), 12 at G = 500 342 -> 286 (350); with 4 classes at
+// G = 96 level (169.1, 170.7 us for 20,000).
+__device__ __forceinline__ int wave_tau(const DevProblem &P, const int8_t *__restrict__ bmap, const Realisation &R,
+                                        int *work, int *floors_met) {
+  const int K = P.K, G = P.G;
+  if (P.has_floor || K > kWideMaxK || G < K || 4 * (size_t)K * G + 16 > lex_work_bytes(K, G))
+    return wave_solve(P, bmap, R, work, floors_met, nullptr, nullptr);
+  *floors_met = 1;
+  for (int k = 0; k < K; ++k) {
+    const float slo = P.slo[k];
+    wide_table(P, k, bmap, work + k * G, [&](int cell) { return R.l(cell) <= slo ? R.c(cell) : 0.0f; });
+  }
+  wave_lds_fence();
+  const int tau = wide_select(work, K, G);
+  wave_lds_fence();  // the work area is written next
+  return tau;
 }
 
 __device__ __forceinline__ LexLds lex_lds(const DevProblem &P, void *start) {
@@ -4111,7 +4136,7 @@ __global__ __launch_bounds__(64) void k_solve_dense_lex(DevProblem P, const int8
   int fm;
   float gp;
   double gp64;
-  const int tau = wave_solve(P, bmap, R, work, &fm, nullptr, nullptr);
+  const int tau = wave_tau(P, bmap, R, work, &fm);
   wave_lex_stage(P, bmap, R, tau, fm, X, wa, &gp, &gp64);
   write_alloc(out, j, P.K, tau, fm, gp, wa);
   if (gp64_out && threadIdx.x == 0) gp64_out[j] = gp64;
@@ -4213,7 +4238,7 @@ __global__ __launch_bounds__(64) void k_certify_lex(DevProblem P, const int8_t *
   int fm;
   float gp;
   double g64;
-  const int tau = wave_solve(P, bm, rz, work, &fm, nullptr, nullptr);
+  const int tau = wave_tau(P, bm, rz, work, &fm);
   wave_lex_stage(P, bm, rz, tau, fm, X, wa, &gp, &g64);
   write_alloc(R == 0 ? cons : opt, o, P.K, tau, fm, gp, wa);
   write_cert_rec(rec + (size_t)o * 2 + R, P.K, tau, fm, gp, g64, wa);
@@ -4292,10 +4317,10 @@ __global__ __launch_bounds__(64) void k_score_lex_wave(DevProblem P, const int8_
     float g32;
     double gm, gp;
     Realisation rm{cm, lm, ci.cell, cs, ts};
-    const int tm = wave_solve(P, bm, rm, work, &fm, nullptr, nullptr);
+    const int tm = wave_tau(P, bm, rm, work, &fm);
     wave_lex_stage(P, bm, rm, tm, fm, X, wa, &g32, &gm);
     Realisation rp{cp, lp, ci.cell, cs, ts};
-    const int tp = wave_solve(P, bm, rp, work, &fm, nullptr, nullptr);
+    const int tp = wave_tau(P, bm, rp, work, &fm);
     wave_lex_stage(P, bm, rp, tp, fm, X, wa, &g32, &gp);
     // the binary64 totals are in lane 0
     gm = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(gm)),
