@@ -147,7 +147,7 @@ def host_info() -> dict:
 
 def baseline_threads() -> int:
     """Oracle threads: the CPUs this process may use, at most 16 (a GPU's
-    share of the host on the GPU pool, whatever the host's CPU count)."""
+    share of the host, whatever the host's CPU count)."""
     return max(1, min(host_info()["cpus_allowed"] or 1, 16))
 
 
