@@ -77,21 +77,6 @@ __device__ __forceinline__ int wave_min(int v) {
   return v;
 }
 
-// Inclusive prefix sum across the 64 lanes by DPP: shifts by 1, 2, 4, 8
-// within each row of 16 lanes (lanes with no source add 0), then the last
-// lane of row 0 is added to row 1 and of row 2 to row 3 (row_bcast:15), and
-// the last lane of row 1 (the total of rows 0-1) to rows 2 and 3
-// (row_bcast:31).
-__device__ __forceinline__ int wave_scan_add(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
-  return v;
-}
-
 // Maximum / minimum over the 64 lanes: DPP permutations within each row of
 // 16 lanes (quad xor 1, quad xor 2, half-row mirror, row mirror), then the
 // four row results by readlane.  Wave-uniform result; every lane must be
@@ -213,17 +198,6 @@ __device__ __forceinline__ int level_from(const DevProblem &P, float per_replica
 
 __device__ __forceinline__ int level_of(const DevProblem &P, int k, int r) {
   return level_from(P, P.demand[k] / (float)r);
-}
-
-// Number of load levels below a per-replica load: the index of the smallest
-// level that holds it, B when none does.  The loop runs over the largest
-// level count, so the level values (kernel arguments) are fetched by a few
-// wide scalar loads ahead of the compares instead of one load per level.
-__device__ __forceinline__ int levels_below(const DevProblem &P, float per_replica) {
-  int b = 0;
-#pragma unroll
-  for (int j = 0; j < kMaxLevels; ++j) b += (j < P.B && P.levels[j] < per_replica) ? 1 : 0;
-  return b;
 }
 
 // Copies n bytes to LDS with all of a thread's loads (up to 8) issued before
@@ -1484,28 +1458,6 @@ __device__ __forceinline__ Pick wave_best(Pick p) {
   return best;
 }
 
-// Z[g] = max_{a <= g} min(X[g - a], Y[a]) for one target g.
-__device__ __forceinline__ int conv_at(const int *X, const int *Y, int g) {
-  int best = INT_MIN;
-  for (int a = 0; a <= g; ++a) best = max(best, min(X[g - a], Y[a]));
-  return best;
-}
-
-// The same target split over 4 consecutive lanes (lane j of the group takes
-// a = j, j + 4, ...); every lane of the group returns the full maximum.
-// All 64 lanes of the wavefront must call it.
-__device__ __forceinline__ int conv_at4(const int *X, const int *Y, int g, bool active) {
-  const int j = threadIdx.x & 3;
-  int best = INT_MIN;
-  if (active) {
-#pragma unroll 4
-    for (int a = j; a <= g; a += 4) best = max(best, min(X[g - a], Y[a]));
-  }
-  best = max(best, __shfl_xor(best, 1, kWave));
-  best = max(best, __shfl_xor(best, 2, kWave));
-  return best;
-}
-
 __device__ __forceinline__ double load_acquire(const double *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1533,19 +1485,6 @@ __device__ double wave_tree_sum(const double *x, int64_t n) {
     }
   }
   return wave_pairwise_sum(v[0]);
-}
-
-// Decodes a flattened option index p (0 <= p < P = sum_t floor(G / t)) of
-// one class into (TP index, replicas); options are ordered by TP, then r.
-__device__ __forceinline__ void option_of(const DevProblem &P, int p, int *ti, int *r) {
-  int t = 0;
-  for (; t < P.NT - 1; ++t) {
-    const int n = P.G / P.tp[t];
-    if (p < n) break;
-    p -= n;
-  }
-  *ti = t;
-  *r = p + 1;
 }
 
 // Smallest binary32 capacity x >= 0 at which r replicas reach ratio bits M,
@@ -2691,9 +2630,6 @@ struct ScoreItem {
   int vm0, vm1;
   float vt0, vt1;
 };
-
-// Value of lane idx (0 <= idx < 64) of v, per lane.
-__device__ __forceinline__ int lane_lookup(int v, int idx) { return __builtin_amdgcn_ds_bpermute(idx << 2, v); }
 
 // Scenarios of the exclusion scorer.  A work item is one chunk of 64 x SPL
 // samples of one live tile; the chunks of one tile are neighbours, and block
