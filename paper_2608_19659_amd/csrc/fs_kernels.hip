@@ -35,6 +35,7 @@
 // (critical floors) and a -0 ratio (from a -0 capacity) sorts below every
 // usable value, which is how a zero ratio behaves in the max.
 #include "fs_internal.h"
+#include "fs_list.h"
 
 #include <limits.h>
 
@@ -1779,10 +1780,10 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
 }
 
 // Set-up of the exclusion scorer, one block per (realisation R, order o,
-// class i), plus blocks with i = K of which (R = 0, o = 0) builds the work
-// list of every order and the others return at once; R = 0 is the
-// conservative corner (low capacity, high tail) and R = 1 the optimistic one
-// (Section 4.1).  Tables over g in [0, G) (G itself is never read):
+// class i), plus blocks with i = K of which (R = 0, o = q) builds run q of the
+// work list and the others return at once; R = 0 is the conservative corner
+// (low capacity, high tail) and R = 1 the optimistic one (Section 4.1).
+// Tables over g in [0, G) (G itself is never read):
 //   B_k[g]  best ratio of class k with at most g GPUs (nondecreasing)
 //   H_i     the (max,min) convolution of B_k over every k != i, by a tree
 // Every (max,min) target of nondecreasing tables is a crossing search.  Then,
@@ -1798,14 +1799,6 @@ __global__ __launch_bounds__(kBtabThreads) void k_prep_btab(DevProblem P, const 
 __device__ void prep_list_staged(const DevProblem &P, int o_first, int O, const uint8_t *__restrict__ measured,
                                  const int32_t *__restrict__ cand, int E, int dump, int PPc,
                                  TileInfo *__restrict__ tiles, int4 *__restrict__ list, int *lds);
-
-// The work list in n = 1 << log runs of consecutive orders, one block each:
-// run q is orders [q per, q per + per) of O (fewer or none past the last
-// order), its entries from list[q per E].  A wavefront of the scorer takes
-// its items from one run.
-struct ListRuns {
-  int log, n, per;
-};
 
 // kFloor (critical floors; tables in LDS, no work list): block x = 2 V + R.
 // Variant V = 0 ignores the floors, as above.  Variant 1 holds them: every
@@ -1857,11 +1850,11 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
     }
     C.optoff[NT] = at;
   }
-  if (!kFloor && ci == K) {  // one block builds the work list of every order
-    if (R != 0 || o >= runs.n || o * runs.per >= (int)gridDim.y) return;
+  if (!kFloor && ci == K) {  // a block builds a run of the work list (unstaged: one builds all of it)
+    if (R != 0 || o >= runs.n) return;
     if (staged_list) {
-      prep_list_staged(P, o * runs.per, min(runs.per, (int)gridDim.y - o * runs.per), measured, cand, E, dump, PPc,
-                       tiles, list, lds);
+      prep_list_staged(P, runs.first(o), runs.first(o + 1) - runs.first(o), measured, cand, E, dump, PPc, tiles, list,
+                       lds);
       return;
     }
     if (tid < 32) bucket_count[tid] = 0;
@@ -2266,8 +2259,8 @@ __global__ __launch_bounds__(1024) void k_prep_order(DevProblem P, const float *
                                                      const float *__restrict__ tail_lo,
                                                      const float *__restrict__ tail_hi,
                                                      const uint8_t *__restrict__ measured,
-                                                     const int32_t *__restrict__ cand, int32_t E, int32_t O,
-                                                     int32_t dump, TileInfo *__restrict__ tiles,
+                                                     const int32_t *__restrict__ cand, int32_t E, int32_t dump,
+                                                     TileInfo *__restrict__ tiles,
                                                      int32_t *__restrict__ base, int32_t *__restrict__ mopt,
                                                      float *__restrict__ thr, int32_t n_thr,
                                                      int4 *__restrict__ list, ListRuns runs, int32_t thr_mode,
@@ -2280,9 +2273,8 @@ __global__ __launch_bounds__(1024) void k_prep_order(DevProblem P, const float *
   // the list blocks come first: blocks start over about 2 us, and a list
   // block takes as long as a class block
   if ((int)blockIdx.x < runs.n) {
-    const int o_first = (int)blockIdx.x * runs.per;
-    if (o_first >= O) return;
-    prep_list_staged(P, o_first, min(runs.per, O - o_first), measured, cand, E, dump, PPc, tiles, list, lds);
+    const int o_first = runs.first(blockIdx.x);
+    prep_list_staged(P, o_first, runs.first(blockIdx.x + 1) - o_first, measured, cand, E, dump, PPc, tiles, list, lds);
     return;
   }
   const int bx = (int)blockIdx.x - runs.n, o = bx >> 1, R = bx & 1;
@@ -2667,7 +2659,7 @@ template <int SPL, bool VEC, bool DUMP, bool CLAMP>
 __global__ __launch_bounds__(64 * kExclMaxWaves) void k_score_excl(
     DevProblem P, const TileInfo *__restrict__ tiles, const int32_t *__restrict__ mopt,
     const float *__restrict__ thr, int32_t n_thr, const int4 *__restrict__ list,
-    const float *__restrict__ cap_s, const float *__restrict__ tail_s, int32_t O, int32_t E, int32_t S,
+    const float *__restrict__ cap_s, const float *__restrict__ tail_s, int32_t E, int32_t S,
     const int32_t *__restrict__ base, double *__restrict__ partial, int32_t n_chunk,
     float *__restrict__ tau_dump, const float4 *__restrict__ bounds, ListRuns runs, int32_t range_lds) {
   constexpr int CHUNK = 64 * SPL;
@@ -2677,8 +2669,8 @@ __global__ __launch_bounds__(64 * kExclMaxWaves) void k_score_excl(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Thread t has items of run t mod runs.n of the list: every block has the
   // same share of each run.
-  const int run = tid & (runs.n - 1), W = gridDim.x;
-  list += (size_t)run * runs.per * E;
+  const int run = tid & (runs.n - 1), W = gridDim.x, run_first = runs.first(run);
+  list += (size_t)run_first * E;
   // the items to evaluate; per-class constants; then, for ranges longer than
   // a wavefront, each wavefront's M and thresholds of the range
   int4 *items = reinterpret_cast<int4 *>(lds);  // [T][2]
@@ -2695,7 +2687,7 @@ __global__ __launch_bounds__(64 * kExclMaxWaves) void k_score_excl(
   // next item's.)
   int vz;
   asm volatile("v_mov_b32 %0, 0" : "=v"(vz));
-  const uint32_t n_list = (uint32_t)max(min(runs.per, O - run * runs.per), 0) * (uint32_t)E;
+  const uint32_t n_list = (uint32_t)(runs.first(run + 1) - run_first) * (uint32_t)E;
   const uint64_t n_items = (uint64_t)n_list * (uint32_t)n_chunk;
   // Issues the loads of place k of the n collected items (past the last:
   // none, at the arrays' first element).
@@ -5830,19 +5822,16 @@ static bool prep_order_fits(const DevProblem &P, int64_t O, int64_t E) {
 // Runs of the work list: one block builds about 1,200 entries while a class
 // block of the set-up runs (2 classes at G = 16 over 200 orders and 48
 // candidates: the call took 17.4 us, with 2,400 entries a block 18.4, with 600
-// 17.4); at most 8, no more than there are orders or wavefronts of the scorer
-// (every run has at least one).
+// 17.4); at most 8, no more than there are orders (every run has at least one)
+// or wavefronts of the scorer's grid.
 constexpr int kListRuns = 8, kListRunTiles = 1200;
 static ListRuns list_runs(const DevProblem &P, const ScoreArgs &a) {
   // the unstaged list block of the general set-up takes every order
   const bool staged = (a.setup == 0 && prep_order_fits(P, a.O, a.E)) || prep_list_lds(P, a.O, a.E) <= kPrepGeneralLdsLimit;
   int64_t n = staged ? ((int64_t)a.O * a.E + kListRunTiles - 1) / kListRunTiles : 1;
   if (n > kListRuns) n = kListRuns;
-  if (n > a.O) n = a.O;
   if (a.waves > 0 && n > a.waves) n = a.waves;
-  int log = 0;
-  while ((2 << log) <= n) ++log;
-  return ListRuns{log, 1 << log, (a.O + (1 << log) - 1) >> log};
+  return list_runs_of(a.O, n);
 }
 
 // Options per (order, realisation): one per (class, TP, r).
@@ -5965,7 +5954,7 @@ static hipError_t launch_floor_score(const DevProblem &P, const ScoreArgs &a, in
     }                                                                                                             \
     k_prep<true, TH, true><<<grid, TH, lds, s>>>(P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, a.measured, a.cand, \
                                                  a.E, 0, nullptr, tiles, base, mopt, nullptr, n_thr, nullptr,     \
-                                                 a.thr_search, 0, ListRuns{0, 1, 1}, btab, F);                         \
+                                                 a.thr_search, 0, list_runs_of(a.O, 1), btab, F);                      \
   }
   // the block sizes of the set-up without floors, whose blocks are alike
   if (P.G >= kPrepWideBudget) FS_PREP_FLOOR(kPrepThreadsWide)
@@ -6010,7 +5999,7 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
 #define FS_PREP_ORDER(KP, NTP)                                                                                    \
   k_prep_order<KP, NTP><<<2 * a.O + runs.n, prep_order_waves(P, runs.per, a.E) * kWave,                              \
                           prep_order_lds(P, runs.per, a.E), s>>>(                                                    \
-    P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, a.measured, a.cand, a.E, a.O, dump, tiles, base, mopt, thr,  \
+    P, a.cap_lo, a.cap_hi, a.tail_lo, a.tail_hi, a.measured, a.cand, a.E, dump, tiles, base, mopt, thr,       \
     n_thr, list, runs, a.thr_search, LV)
 #define FS_PREP_ORDER_K(NTP)                  \
   if (P.K <= 4) FS_PREP_ORDER(4, NTP);        \
@@ -6160,7 +6149,7 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
       if (es != hipSuccess) return es;                                                                      \
     }                                                                                                       \
     k_score_excl<SP, VEC, DUMP, CLAMP><<<grid, kWave * (unsigned)nw, mlds, s>>>(                            \
-        P, tiles, mopt, thr, n_thr, list, a.cap_s, a.tail_s, a.O, a.E, a.S, base, partial,                  \
+        P, tiles, mopt, thr, n_thr, list, a.cap_s, a.tail_s, a.E, a.S, base, partial,                       \
         (int32_t)n_partial, a.tau_dump, a.bounds, runs, range_lds);                                         \
   }
 #define FS_EXCL_SPL(SP)                                         \
