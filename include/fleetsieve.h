@@ -252,7 +252,10 @@ fs_status fs_score_candidates_noalloc(fs_context *ctx, const fs_problem *p, fs_i
  *     and the gap is at most eps;
  *   UNDECIDED otherwise.
  * Writes state [n_orders], the conservative (cons) and optimistic (opt)
- * allocations [n_orders] and the gap [n_orders] (binary64, may be NULL). */
+ * allocations [n_orders] and the gap [n_orders] (binary64, may be NULL).
+ * A workspace smaller than fs_workspace_size for n_orders orders (at least
+ * its size for none) is used too, by groups of as many orders as it has
+ * records for, one after another; so in fs_certify_lex. */
 fs_status fs_certify(fs_context *ctx, const fs_problem *p, fs_intervals iv, int32_t n_orders,
                      float eps, int32_t *d_state, fs_alloc cons, fs_alloc opt, double *d_gap,
                      void *d_workspace, size_t workspace_bytes, hipStream_t stream);

@@ -744,9 +744,9 @@ fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv,
       if (e != hipSuccess) return hip_fail(e, "loop refit launch");
     }
     e = lex ? fs::launch_certify_lex(P, R_cap_lo, D.cap_hi, R_tail_lo, R_tail_hi, D.measured, n_orders, eps,
-                                     D.cert_state, D.cons, none, nullptr, nullptr, ws, LL.score, stream)
+                                     D.cert_state, D.cons, none, nullptr, nullptr, ws, LL.score, n_orders, stream)
             : fs::launch_certify(P, R_cap_lo, D.cap_hi, R_tail_lo, R_tail_hi, D.measured, n_orders, eps,
-                                 D.cert_state, D.cons, none, nullptr, ws, LL.score, stream);
+                                 D.cert_state, D.cons, none, nullptr, ws, LL.score, n_orders, stream);
     if (e == hipSuccess) e = fs::launch_loop_decide(P, D, d_cand, n_cand, n_orders, stream);
     if (e != hipSuccess) return hip_fail(e, "loop certificate launch");
     if (rnd == max_rounds) break;
@@ -913,7 +913,8 @@ fs_status fs_certify(fs_context *ctx, const fs_problem *p, fs_intervals iv, int3
   e = fs::reg_solver_supported(P) ? hipSuccess : fs::launch_setup(P, nullptr, 0, ws, L, stream);
   if (e != hipSuccess) return hip_fail(e, "set-up launch");
   e = fs::launch_certify(P, iv.cap_lo, iv.cap_hi, iv.tail_lo, iv.tail_hi, iv.measured, n_orders, eps,
-                         d_state, to_out(cons), to_out(opt), d_gap, ws, L, stream);
+                         d_state, to_out(cons), to_out(opt), d_gap, ws, L,
+                         fs::cert_record_orders(L, workspace_bytes), stream);
   if (e != hipSuccess) return hip_fail(e, "certify launch");
   return FS_OK;
 }
@@ -953,7 +954,8 @@ fs_status fs_certify_lex(fs_context *ctx, const fs_problem *p, fs_intervals iv, 
   e = fs::reg_solver_supported(P) ? hipSuccess : fs::launch_setup(P, nullptr, 0, ws, L, stream);
   if (e != hipSuccess) return hip_fail(e, "set-up launch");
   e = fs::launch_certify_lex(P, iv.cap_lo, iv.cap_hi, iv.tail_lo, iv.tail_hi, iv.measured, n_orders, eps, d_state,
-                             to_out(cons), to_out(opt), d_gap_maxmin, d_gap_goodput, ws, L, stream);
+                             to_out(cons), to_out(opt), d_gap_maxmin, d_gap_goodput, ws, L,
+                             fs::cert_record_orders(L, workspace_bytes), stream);
   if (e != hipSuccess) return hip_fail(e, "certify launch");
   return FS_OK;
 }

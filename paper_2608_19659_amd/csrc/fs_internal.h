@@ -74,7 +74,7 @@ struct WsLayout {
   size_t thr;        // float [O][2][K*P] capacity threshold of every option
   size_t list;       // int4 [O * E] live tiles of every order, longest replica range first
   size_t btab;       // int32 [O][2][K][G] B tables of the general set-up
-  size_t crec;       // [O][2] per-realisation results of the certificate under the whole objective
+  size_t crec;       // [O][2] per-realisation results of the certificate
   size_t flag;     // int32 [4]        validation / error flags
   // exclusion scorer with critical floors (floors != 0), per variant: B
   // tables int32 [O][2][K][G], cheapest floor-meeting costs int32 [O][2][K],
@@ -151,16 +151,20 @@ size_t lds_bytes_lex(const DevProblem &P, int n_alloc);
 constexpr size_t kLexLdsLimit = 64 * 1024;
 hipError_t launch_solve_batch_lex(const DevProblem &P, const float *cap, const float *tail, int64_t n,
                                   AllocOut out, double *gp64, uint8_t *ws, const WsLayout &L, hipStream_t s);
-// with_state false: only the orders' two records (for a caller that forms
-// the gaps itself; state, gap_mm and gap_gp are then not written).
+// Orders whose certificate records a workspace of `bytes` holds (at least one
+// if it holds the layout).  The certificates take that many at a time.
+int64_t cert_record_orders(const WsLayout &L, size_t bytes);
+// rec_orders: as above.  with_state false: only the orders' two records (for a
+// caller that forms the gaps itself; state, gap_mm and gap_gp are then not
+// written), which the workspace must hold for all of them.
 hipError_t launch_certify_lex(const DevProblem &P, const float *cap_lo, const float *cap_hi, const float *tail_lo,
                               const float *tail_hi, const uint8_t *measured, int32_t O, float eps, int32_t *state,
                               AllocOut cons, AllocOut opt, double *gap_mm, double *gap_gp, uint8_t *ws,
-                              const WsLayout &L, hipStream_t s, bool with_state = true);
+                              const WsLayout &L, int64_t rec_orders, hipStream_t s, bool with_state = true);
 hipError_t launch_certify(const DevProblem &P, const float *cap_lo, const float *cap_hi,
                           const float *tail_lo, const float *tail_hi, const uint8_t *measured,
                           int32_t O, float eps, int32_t *state, AllocOut cons, AllocOut opt,
-                          double *gap, uint8_t *ws, const WsLayout &L, hipStream_t s);
+                          double *gap, uint8_t *ws, const WsLayout &L, int64_t rec_orders, hipStream_t s);
 // ---- profiling loop (Algorithm 1) -------------------------------------------
 // Device state of fs_profile_loop: a working copy of the intervals, this
 // round's certificate and scores, the allocation each trajectory returns so

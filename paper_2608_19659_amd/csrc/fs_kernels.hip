@@ -6332,11 +6332,35 @@ hipError_t launch_solve_batch_lex(const DevProblem &P, const float *cap, const f
   return hipGetLastError();
 }
 
-hipError_t launch_certify_lex(const DevProblem &P, const float *cap_lo, const float *cap_hi, const float *tail_lo,
-                              const float *tail_hi, const uint8_t *measured, int32_t O, float eps, int32_t *state,
-                              AllocOut cons, AllocOut opt, double *gap_mm, double *gap_gp, uint8_t *ws,
-                              const WsLayout &L, hipStream_t s, bool with_state) {
-  if (O == 0) return hipSuccess;
+int64_t cert_record_orders(const WsLayout &L, size_t bytes) {
+  return bytes > L.crec ? (int64_t)((bytes - L.crec) / (2 * sizeof(CertRec))) : 0;
+}
+
+// The outputs of the orders from o on.
+static AllocOut alloc_from(const AllocOut &a, int64_t o, int K) {
+  return AllocOut{a.objective ? a.objective + o : nullptr, a.tp_index ? a.tp_index + o * K : nullptr,
+                  a.replicas ? a.replicas + o * K : nullptr, a.floors_met ? a.floors_met + o : nullptr,
+                  a.goodput ? a.goodput + o : nullptr};
+}
+
+// Runs launch(first order, orders) over O orders, as many at a time as the
+// workspace has records for (a workspace sized for the call: all of them).
+template <class F>
+static hipError_t by_record_orders(int32_t O, int64_t rec_orders, F launch) {
+  const int32_t step = (int32_t)(rec_orders < 1 ? 1 : rec_orders < O ? rec_orders : O);
+  for (int32_t o = 0; o < O;) {
+    const int32_t n = O - o < step ? O - o : step;
+    const hipError_t e = launch(o, n);
+    if (e != hipSuccess) return e;
+    o += n;
+  }
+  return hipSuccess;
+}
+
+static hipError_t certify_lex_orders(const DevProblem &P, const float *cap_lo, const float *cap_hi, const float *tail_lo,
+                                     const float *tail_hi, const uint8_t *measured, int32_t O, float eps,
+                                     int32_t *state, AllocOut cons, AllocOut opt, double *gap_mm, double *gap_gp,
+                                     uint8_t *ws, const WsLayout &L, hipStream_t s, bool with_state) {
   const size_t base = lds_bytes_lex(P, 1), staged = base + stage_bytes(P);
   const int stage = stage_fits(staged) ? 1 : 0;
   CertRec *rec = (CertRec *)(ws + L.crec);
@@ -6358,21 +6382,22 @@ hipError_t launch_certify_lex(const DevProblem &P, const float *cap_lo, const fl
   return hipGetLastError();
 }
 
-hipError_t launch_certify(const DevProblem &P, const float *cap_lo, const float *cap_hi,
-                          const float *tail_lo, const float *tail_hi, const uint8_t *measured,
-                          int32_t O, float eps, int32_t *state, AllocOut cons, AllocOut opt,
-                          double *gap, uint8_t *ws, const WsLayout &L, hipStream_t s) {
-  if (O == 0) return hipSuccess;
-  if (reg_solver_supported(P)) {
-    const PrepLevels LV = prep_levels(P);
-    const size_t lds = reg_lds(P, 2);
-#define FS_CERTIFY_REG(KP, NTP)                                                                                  \
-  k_certify_reg<KP, NTP><<<O, kCertThreads, lds, s>>>(P, cap_lo, cap_hi, tail_lo, tail_hi, measured, eps, state, \
-                                                      cons, opt, gap, LV);
-    FS_REG_DISPATCH(FS_CERTIFY_REG)
-#undef FS_CERTIFY_REG
-    return hipGetLastError();
-  }
+hipError_t launch_certify_lex(const DevProblem &P, const float *cap_lo, const float *cap_hi, const float *tail_lo,
+                              const float *tail_hi, const uint8_t *measured, int32_t O, float eps, int32_t *state,
+                              AllocOut cons, AllocOut opt, double *gap_mm, double *gap_gp, uint8_t *ws,
+                              const WsLayout &L, int64_t rec_orders, hipStream_t s, bool with_state) {
+  return by_record_orders(O, rec_orders, [&](int32_t o, int32_t n) {
+    const size_t c = (size_t)o * P.N;
+    return certify_lex_orders(P, cap_lo + c, cap_hi + c, tail_lo + c, tail_hi + c, measured + c, n, eps,
+                              state ? state + o : nullptr, alloc_from(cons, o, P.K), alloc_from(opt, o, P.K),
+                              gap_mm ? gap_mm + o : nullptr, gap_gp ? gap_gp + o : nullptr, ws, L, s, with_state);
+  });
+}
+
+static hipError_t certify_orders(const DevProblem &P, const float *cap_lo, const float *cap_hi, const float *tail_lo,
+                                 const float *tail_hi, const uint8_t *measured, int32_t O, float eps, int32_t *state,
+                                 AllocOut cons, AllocOut opt, double *gap, uint8_t *ws, const WsLayout &L,
+                                 hipStream_t s) {
   const size_t base = lds_bytes_solver(P, 1), staged = base + stage_bytes(P);
   const int stage = stage_fits(staged) ? 1 : 0;
   CertRec *rec = (CertRec *)(ws + L.crec);
@@ -6393,6 +6418,28 @@ hipError_t launch_certify(const DevProblem &P, const float *cap_lo, const float 
   if (e != hipSuccess) return e;
   k_certify_state<<<O, 64, 0, s>>>(P, tail_hi, measured, eps, rec, 0, state, gap, nullptr);
   return hipGetLastError();
+}
+
+hipError_t launch_certify(const DevProblem &P, const float *cap_lo, const float *cap_hi,
+                          const float *tail_lo, const float *tail_hi, const uint8_t *measured,
+                          int32_t O, float eps, int32_t *state, AllocOut cons, AllocOut opt,
+                          double *gap, uint8_t *ws, const WsLayout &L, int64_t rec_orders, hipStream_t s) {
+  if (O == 0) return hipSuccess;
+  if (reg_solver_supported(P)) {  // (keeps no records)
+    const PrepLevels LV = prep_levels(P);
+    const size_t lds = reg_lds(P, 2);
+#define FS_CERTIFY_REG(KP, NTP)                                                                                  \
+  k_certify_reg<KP, NTP><<<O, kCertThreads, lds, s>>>(P, cap_lo, cap_hi, tail_lo, tail_hi, measured, eps, state, \
+                                                      cons, opt, gap, LV);
+    FS_REG_DISPATCH(FS_CERTIFY_REG)
+#undef FS_CERTIFY_REG
+    return hipGetLastError();
+  }
+  return by_record_orders(O, rec_orders, [&](int32_t o, int32_t n) {
+    const size_t c = (size_t)o * P.N;
+    return certify_orders(P, cap_lo + c, cap_hi + c, tail_lo + c, tail_hi + c, measured + c, n, eps, state + o,
+                          alloc_from(cons, o, P.K), alloc_from(opt, o, P.K), gap ? gap + o : nullptr, ws, L, s);
+  });
 }
 
 LoopLayout loop_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S) {
@@ -6647,7 +6694,7 @@ hipError_t launch_score_lex(const DevProblem &P, const float *cap_lo, const floa
   }
   if (!reg) {
     e = launch_certify_lex(P, cap_lo, cap_hi, tail_lo, tail_hi, measured, O, 0.0f, nullptr, none,
-                           none, gmm, ggp, ws, L.score, cs, false);
+                           none, gmm, ggp, ws, L.score, O, cs, false);
     if (e != hipSuccess) return e;
   }
   if (par) {

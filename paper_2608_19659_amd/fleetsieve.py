@@ -409,7 +409,7 @@ def certify(ctx: Context, problem, iv: DeviceIntervals, eps: float = 0.05, strea
     gap = torch.empty(O, dtype=torch.float64, device=dev)
     cons = _alloc_tensors(O, ref.K, dev)
     opt = _alloc_tensors(O, ref.K, dev)
-    ws_bytes = workspace_size(problem)
+    ws_bytes = workspace_size(problem, O)
     ws = workspace if workspace is not None else ctx.workspace(ws_bytes)
     _check(load_library().fs_certify(ctx.handle, ref.ptr, ivs, O, float(eps), state.data_ptr(),
                                      _alloc_struct(cons), _alloc_struct(opt), gap.data_ptr(), ws.data_ptr(),
@@ -440,7 +440,7 @@ def certify_lex(ctx: Context, problem, iv: DeviceIntervals, eps: float = 0.05, s
     ggp = torch.empty(O, dtype=torch.float64, device=dev)
     cons = _alloc_tensors(O, ref.K, dev)
     opt = _alloc_tensors(O, ref.K, dev)
-    ws_bytes = workspace_size(problem)
+    ws_bytes = workspace_size(problem, O)
     ws = workspace if workspace is not None else ctx.workspace(ws_bytes)
     _check(load_library().fs_certify_lex(ctx.handle, ref.ptr, ivs, O, float(eps), state.data_ptr(),
                                          _alloc_struct(cons), _alloc_struct(opt), gmm.data_ptr(), ggp.data_ptr(),
