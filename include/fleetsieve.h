@@ -269,7 +269,8 @@ fs_status fs_certify(fs_context *ctx, const fs_problem *p, fs_intervals iv, int3
  * min(lambda, fl32(r c)) when the cell's tail is within the SLO, else 0;
  * level (3) compares their binary64 sum taken from the last class to the
  * first (exact while the nonzero served rates lie within a factor 2^23 of
- * each other).  fs_solve_batch and fs_certify use levels (1)-(2) with the
+ * each other; further apart, every class and budget takes the largest rounded
+ * total, then the fewest GPUs).  fs_solve_batch and fs_certify use levels (1)-(2) with the
  * tie-breaks fewer GPUs, then smaller TP degrees.
  *
  * Supported while the solve's LDS fits 64 KiB: about (28 + 2K)(G + 1) +

@@ -91,6 +91,7 @@ fs_status make_problem(const fs_problem *p, fs::DevProblem *P) {
       return fail(FS_ERR_INVALID_ARGUMENT, "levels must be strictly ascending");
     P->levels[b] = v;
   }
+  float most = 0.0f, least = INFINITY;
   for (int i = 0; i < p->n_classes; ++i) {
     const float d = p->demand[i];
     if (!(d >= 0x1p-32f && d <= 0x1p32f)) return fail(FS_ERR_INVALID_ARGUMENT, "demand must be in [2^-32, 2^32]");
@@ -98,6 +99,8 @@ fs_status make_problem(const fs_problem *p, fs::DevProblem *P) {
     P->demand[i] = d;
     P->slo[i] = p->slo[i];
     P->rcp_demand[i] = 1.0 / (double)d;
+    most = d > most ? d : most;
+    least = d < least ? d : least;
     if (p->floor_rps) {
       const float f = p->floor_rps[i];
       if (!(f >= 0.0f) || !std::isfinite(f))
@@ -106,6 +109,8 @@ fs_status make_problem(const fs_problem *p, fs::DevProblem *P) {
       if (f > 0.0f) P->has_floor = 1;
     }
   }
+  P->small_rate = most * 0x1p-23f;
+  if (least < P->small_rate) P->small_rate = INFINITY;
   return FS_OK;
 }
 

@@ -30,6 +30,11 @@ struct DevProblem {
   // 2^-52 relative, is below the distance from any binary32 rounding
   // midpoint, at least 2^-50 relative).
   double rcp_demand[kMaxClasses];
+  // Whole objective: a usable capacity above 0 but below this may serve a rate
+  // more than 2^23 times smaller than another class's (a class serves at most
+  // its demand, at least one replica's capacity or its demand): the largest
+  // demand x 2^-23, +inf when the demands alone lie that far apart.
+  float small_rate;
   // First option of each TP degree among one class's options, which are
   // ordered by TP, then replicas: optoff[t] = sum over t' < t of G / tp[t'];
   // optoff[NT] is the number of options per class.

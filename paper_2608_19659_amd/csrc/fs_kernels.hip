@@ -184,6 +184,14 @@ __device__ __forceinline__ int cell_of(const DevProblem &P, int k, int ti, int b
 // ---------------------------------------------------------------------------
 // Set-up: load level of every (class, replica count), and candidate info.
 // ---------------------------------------------------------------------------
+// Whether usable capacities put served rates so far apart that their binary64
+// sums may round (the whole objective then keeps every cost): the smallest key
+// of theirs against that of small_rate.  A capacity of 0 has the largest key.
+__device__ __forceinline__ unsigned rate_key(float cap) { return __float_as_uint(cap) - 1u; }
+__device__ __forceinline__ bool spread_lanes(const DevProblem &P, unsigned key) {
+  return __builtin_amdgcn_ballot_w64(key < rate_key(P.small_rate)) != 0;
+}
+
 // Load level of r replicas of class k: the offered load per replica is
 // lambda_k / r in binary32, and the replica runs in the smallest level that
 // is at least that load; -1 when no level is large enough.  level_from takes
@@ -886,6 +894,7 @@ struct RegBatch {
   float *cells;
   RegShared X;
   int lane, c0, c1;
+  bool spread;  // of the realisation in LDS (spread_lanes)
   float a0, a1, l0, l1, slo0, slo1;
 
   // mem: the wavefronts' cells, then what they share
@@ -903,11 +912,12 @@ struct RegBatch {
     l1 = gt[c1];
   }
 
-  // The first request, then what the block shares (with its barrier).
-  __device__ __forceinline__ void begin(const DevProblem &P, const PrepLevels &LV) {
+  // The first request, then what the block shares (with its barrier).  none:
+  // the capacity of options that do not exist.
+  __device__ __forceinline__ void begin(const DevProblem &P, const PrepLevels &LV, float none) {
     if (SMALL && j < n) request(P, j);
     reg_stage(P, LV, X, threadIdx.x, blockDim.x);
-    if (lane == 0) cells[P.N] = 0.0f;
+    if (lane == 0) cells[P.N] = none;
     __syncthreads();
     slo0 = X.slo[c0];
     slo1 = X.slo[c1];
@@ -917,16 +927,22 @@ struct RegBatch {
   __device__ __forceinline__ void load(const DevProblem &P) {
     if constexpr (SMALL) {
       // lanes past the last cell hold copies of it
-      cells[c0] = l0 <= slo0 ? a0 : 0.0f;
-      cells[c1] = l1 <= slo1 ? a1 : 0.0f;
+      const float u0 = l0 <= slo0 ? a0 : 0.0f, u1 = l1 <= slo1 ? a1 : 0.0f;
+      cells[c0] = u0;
+      cells[c1] = u1;
+      spread = spread_lanes(P, min(rate_key(u0), rate_key(u1)));
       request(P, j + step < n ? j + step : j);
     } else {
       const float *gc = cap + j * P.N, *gt = tail + j * P.N;
+      unsigned key = ~0u;
 #pragma unroll 4
       for (int c = lane; c < P.N; c += kWave) {
         const float a = gc[c], l = gt[c];
-        cells[c] = l <= X.slo[c] ? a : 0.0f;
+        const float u = l <= X.slo[c] ? a : 0.0f;
+        cells[c] = u;
+        key = min(key, rate_key(u));
       }
+      spread = spread_lanes(P, key);
     }
     wave_lds_fence();
   }
@@ -940,7 +956,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_reg(DevProblem P, const
   RegBatch<SMALL> D(P, cap, tail, n, reg_mem, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), blockDim.x >> 6);
   RegSolver<KP, NTP> S;
   S.begin(P);
-  D.begin(P, LV);
+  D.begin(P, LV, 0.0f);
   S.init(P, D.X);
   for (; D.j < n; D.j += D.step) {
     D.load(P);
@@ -3611,15 +3627,21 @@ __global__ __launch_bounds__(kCertThreads) void k_certify_reg(DevProblem P, cons
 // best = larger goodput, then fewer GPUs, then the earlier option.  One
 // wavefront.  Options of one cost reach the same budgets with the same
 // completion, so each class first merges its allowed options per cost c into
-// the largest served rate (the earliest option among equal ones) -- no other
-// option of that cost can be the best at any budget -- and the layer update
-// runs over the costs that serve more than every cheaper one, lanes over the
-// budgets g:
+// the largest served rate (the earliest option among equal ones), and the
+// layer update runs over the costs that serve more than every cheaper one,
+// lanes over the budgets g:
 //   V_k[g] = best of (V_{k+1}[g] if empty allowed) and, for c = 1..g,
 //            (A_k[c] + V_{k+1}[g - c], c + GPUs of it),
 // equal (goodput, GPUs) going to the earlier option (the empty one first).
 // The choice of every (class, budget) is kept, and the allocation is read
 // in class order from the full budget.
+// A cost that serves no more than a cheaper one is left out because the
+// cheaper one is at least as good at every budget: its goodput is no smaller,
+// and where the totals are equal its GPUs are fewer -- as long as the sums are
+// exact (nonzero rates within a factor 2^23 of each other).  A rounded sum may
+// hide what a completion of the larger budget serves more, and the GPUs it
+// takes for that, so a realisation whose rates lie further apart (`spread`)
+// keeps every allowed cost.  The goodput totals are the same either way.
 // Bound by instruction issue, costs times budgets.  Listing only the costs
 // that serve more than every cheaper one, dense batches: 4 classes at G = 96
 // 365 -> 171 us (20,000 realisations), 8 at G = 256 484 -> 131 (2,048), 12 at
@@ -3674,7 +3696,7 @@ __device__ __forceinline__ void option_of(const DevProblem &P, int q, int *ti, i
 // with -inf (written as "none").  A term whose cost exceeds the budget reads
 // V[-1] (-inf) through a clamped offset, so no term needs a mask.
 __device__ void wave_lex_stage(const DevProblem &P, const int8_t *__restrict__ bmap, const Realisation &R,
-                               int tau, int floors_met, const LexLds &X, const WaveAlloc &alloc,
+                               int tau, int floors_met, bool spread, const LexLds &X, const WaveAlloc &alloc,
                                float *goodput, double *goodput64) {
   const int lane = threadIdx.x & (kWave - 1);
   const int K = P.K, G = P.G, NT = P.NT;
@@ -3689,8 +3711,8 @@ __device__ void wave_lex_stage(const DevProblem &P, const int8_t *__restrict__ b
     const double rcp = P.rcp_demand[k];
     // per cost the best allowed option (served rate, then the first in
     // (TP, replicas) order), listed for the costs that serve more than every
-    // cheaper one (a ballot per 64 costs): any other is beaten by that cheaper
-    // option at every budget (at least the goodput, fewer GPUs), and with the
+    // cheaper one (a ballot per 64 costs; with spread rates every one): any
+    // other is beaten by that cheaper option at every budget, and with the
     // empty option allowed one that serves nothing is.  (Without it the rates
     // are above 0, so their bits order them.)
     int n_c = 0, carry = empty_ok ? 0 : -1;
@@ -3716,7 +3738,8 @@ __device__ void wave_lex_stage(const DevProblem &P, const int8_t *__restrict__ b
       }
       const int ab = bq >= 0 ? __float_as_int(best) : -1;
       const int upto = wave_scan_max_dpp(ab);
-      const bool keep = ab > max(__builtin_amdgcn_update_dpp(-1, upto, 0x138, 0xF, 0xF, false), carry);  // wave_shr:1
+      const int before = spread ? -1 : max(__builtin_amdgcn_update_dpp(-1, upto, 0x138, 0xF, 0xF, false), carry);  // wave_shr:1
+      const bool keep = ab > before;
       carry = max(carry, __builtin_amdgcn_readlane(upto, kWave - 1));
       const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
       if (keep) {
@@ -3827,6 +3850,15 @@ __device__ __host__ inline size_t lex_work_bytes(int K, int G) {
   return 16 + (b > solver ? b : solver);  // 16: aligning the start
 }
 
+// Whether a realisation's rates are spread: cells whose tail breaks the SLO
+// count too (every cost is then kept needlessly, which changes nothing).
+__device__ __forceinline__ bool spread_rates(const DevProblem &P, const Realisation &R) {
+  unsigned key = ~0u;
+#pragma unroll 2
+  for (int c = threadIdx.x & (kWave - 1); c < P.N; c += kWave) key = min(key, rate_key(R.c(c)));
+  return spread_lanes(P, key);
+}
+
 // Max-min objective of one wavefront's realisation in a whole-objective work
 // area: by the tables and the rank selection where they fit it, otherwise
 // class after class (wave_solve).  Whole dense solves: 8 classes at G = 256
@@ -3865,15 +3897,18 @@ __device__ __forceinline__ LexLds lex_lds(const DevProblem &P, void *start) {
 // K <= 16, no floors): lane g - 1 holds budget g, and the layer sits in LDS
 // between -inf entries for the budgets below 0.  Per class the options of
 // the lane's cost are merged as above, then only the costs that serve more
-// than every cheaper one are kept: any other is beaten by that cheaper
-// option at every budget (at least the goodput, fewer GPUs), and with the
-// empty option allowed one that serves nothing is.  The last class's layer is
-// the best kept cost up to each budget; the first class's is needed at the
-// full budget only, one lane per cost; the middle classes take their kept
-// costs four at a time.  Bound by instruction issue: 65,536 realisations of 4
-// classes at G = 64 take 92 us, 36 of them the max-min solve, against 458 us
-// with every allowed cost at every budget of every class (wave_lex_stage).
-// Option codes are TP index << 8 | replicas (the option order), 0 empty.
+// than every cheaper one are kept, unless the rates are spread (both as above;
+// the last class's sums have one term, so it never needs the others).  The
+// last class's layer is the best kept cost up to each budget; the first
+// class's is needed at the full budget only, one lane per cost; the middle
+// classes take their kept costs four at a time.  Bound by instruction issue:
+// 65,536 realisations of 4 classes at G = 64 take 91 us (1.4 of them to find
+// out that the rates are not spread), 35 of them the max-min solve, against
+// 458 us with every allowed cost at every budget of every class
+// (wave_lex_stage).
+// Option codes are TP index << 8 | replicas (the option order), 0 empty.  An
+// option that does not exist reads a capacity of -1, a ratio below any tau*.
+constexpr float kRegLexNone = -1.0f;
 constexpr int kRegLexCells = 2 * kWave + 1;  // budgets -64 .. 64
 
 __device__ __forceinline__ void reg_lex_init(LexCell *V, int lane) {  // V: budget 0
@@ -3883,11 +3918,15 @@ __device__ __forceinline__ void reg_lex_init(LexCell *V, int lane) {  // V: budg
 template <int KP, int NTP>
 __device__ __forceinline__ RegAlloc reg_lex_stage(const DevProblem &P, const RegSolver<KP, NTP> &S,
                                                   const float *cells, const RegShared &X, LexCell *V, int tau,
-                                                  double *goodput64) {
+                                                  bool spread, double *goodput64) {
   const int lane = S.lane, g = lane + 1, K = P.K, G = P.G;
   const double NEG = -__builtin_inf();
   const bool empty_ok = tau <= 0;
-  const int none_bits = __float_as_int(-1.0f);
+  // A kept cost serves more than every cheaper one and than `below`: 0 with the
+  // empty option allowed, else any rate; with spread rates any rate, whatever
+  // the cheaper ones serve.
+  const int none_bits = __float_as_int(-1.0f), below = spread || !empty_ok ? none_bits : 0;
+  const int cap_before = spread ? -1 : INT_MAX;
   const char *base = reinterpret_cast<const char *>(cells);
   const char *vbase = reinterpret_cast<const char *>(V);
   int choice[KP];
@@ -3902,7 +3941,7 @@ __device__ __forceinline__ RegAlloc reg_lex_stage(const DevProblem &P, const Reg
       for (int ti = 0; ti < NTP; ++ti) c[ti] = *reinterpret_cast<const float *>(base + S.at[k][ti]);
       const double rcp = P.rcp_demand[k];
       const float dm = P.demand[k];
-      float a = -1.0f;
+      float a = __int_as_float(below);
       int code = 0;
 #pragma unroll
       for (int ti = 0; ti < NTP; ++ti) {
@@ -3914,9 +3953,9 @@ __device__ __forceinline__ RegAlloc reg_lex_stage(const DevProblem &P, const Reg
       }
       const int ab = __float_as_int(a);
       const int upto = wave_scan_max_dpp(ab);
-      const int before = __builtin_amdgcn_update_dpp(none_bits, upto, 0x138, 0xF, 0xF, false);  // wave_shr:1
-      const bool keep = ab > max(before, empty_ok ? 0 : none_bits);
+      const int before = __builtin_amdgcn_update_dpp(below, upto, 0x138, 0xF, 0xF, false);  // wave_shr:1
       if (k == K - 1 && k > 0) {
+        const bool keep = ab > max(before, empty_ok ? 0 : none_bits);
         const int cost = wave_scan_max_dpp(keep ? g : 0), src = 4 * max(cost - 1, 0);
         const float ra = __int_as_float(__builtin_amdgcn_ds_bpermute(src, ab));
         const int rc = __builtin_amdgcn_ds_bpermute(src, code);
@@ -3924,6 +3963,7 @@ __device__ __forceinline__ RegAlloc reg_lex_stage(const DevProblem &P, const Reg
         V[g] = LexCell{cost > 0 ? (double)ra : empty_ok ? 0.0 : NEG, cost << 16, 0};
         if (lane == 0) V[0] = LexCell{empty_ok ? 0.0 : NEG, 0, 0};
       } else if (k > 0) {
+        const bool keep = ab > min(before, cap_before);
         const LexCell e0 = V[g];
         double bgp = empty_ok ? e0.gp : NEG;
         int bkey = empty_ok ? e0.key : INT_MAX;
@@ -3961,6 +4001,7 @@ __device__ __forceinline__ RegAlloc reg_lex_stage(const DevProblem &P, const Reg
           if (lane == 0) V[0] = LexCell{0.0, 0, 0};
           wave_lds_fence();
         }
+        const bool keep = ab > min(before, cap_before);
         const LexCell vv = V[G - g];
         const double v = keep ? (double)a + vv.gp : NEG;
         const double best = wave_max_f64(v);
@@ -4019,7 +4060,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lex_reg(DevProblem P, c
   RegBatch<SMALL> D(P, cap, tail, n, reg_mem + nw * 4 * kRegLexCells, wave, nw);
   RegSolver<KP, NTP> S;
   S.begin(P);
-  D.begin(P, LV);
+  D.begin(P, LV, kRegLexNone);
   reg_lex_init(V, lane);
   S.init(P, D.X);
   for (; D.j < n; D.j += D.step) {
@@ -4027,7 +4068,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lex_reg(DevProblem P, c
     int E[KP];
     const int tau = S.solve(P, D.cells, E);
     double g64;
-    const RegAlloc A = reg_lex_stage<KP, NTP>(P, S, D.cells, D.X, V, tau, &g64);
+    const RegAlloc A = reg_lex_stage<KP, NTP>(P, S, D.cells, D.X, V, tau, D.spread, &g64);
     write_reg_alloc(out, D.j, P.K, tau, S.goodput(A), A, lane);
     if (gp64_out && lane == 0) gp64_out[D.j] = g64;
     wave_lds_fence();
@@ -4065,7 +4106,7 @@ __global__ __launch_bounds__(64) void k_solve_dense_lex(DevProblem P, const int8
   float gp;
   double gp64;
   const int tau = wave_tau(P, bmap, R, work, &fm);
-  wave_lex_stage(P, bmap, R, tau, fm, X, wa, &gp, &gp64);
+  wave_lex_stage(P, bmap, R, tau, fm, spread_rates(P, R), X, wa, &gp, &gp64);
   write_alloc(out, j, P.K, tau, fm, gp, wa);
   if (gp64_out && threadIdx.x == 0) gp64_out[j] = gp64;
 }
@@ -4092,16 +4133,22 @@ __device__ __forceinline__ void reg_certify_lex(const DevProblem &P, int o, cons
   if (R >= 2) return;
   LexCell *V = reinterpret_cast<LexCell *>(mem) + R * kRegLexCells + kWave;
   const float *gc = (R == 0 ? cap_lo : cap_hi) + off, *gt = (R == 0 ? tail_hi : tail_lo) + off;
+  unsigned key = ~0u;
 #pragma unroll 2
-  for (int c = lane; c < P.N; c += kWave) cells[c] = gt[c] <= X.slo[c] ? gc[c] : 0.0f;
-  if (lane == 0) cells[P.N] = 0.0f;
+  for (int c = lane; c < P.N; c += kWave) {
+    const float u = gt[c] <= X.slo[c] ? gc[c] : 0.0f;
+    cells[c] = u;
+    key = min(key, rate_key(u));
+  }
+  const bool spread = spread_lanes(P, key);
+  if (lane == 0) cells[P.N] = kRegLexNone;
   reg_lex_init(V, lane);
   S.init(P, X);
   wave_lds_fence();
   int E[KP];
   const int tau = S.solve(P, cells, E);
   double g64;
-  const RegAlloc A = reg_lex_stage<KP, NTP>(P, S, cells, X, V, tau, &g64);
+  const RegAlloc A = reg_lex_stage<KP, NTP>(P, S, cells, X, V, tau, spread, &g64);
   const float gp = S.goodput(A);
   write_reg_alloc(R == 0 ? cons : opt, o, P.K, tau, gp, A, lane);
   CertRec *me = rec + (size_t)o * 2 + R;
@@ -4167,7 +4214,7 @@ __global__ __launch_bounds__(64) void k_certify_lex(DevProblem P, const int8_t *
   float gp;
   double g64;
   const int tau = wave_tau(P, bm, rz, work, &fm);
-  wave_lex_stage(P, bm, rz, tau, fm, X, wa, &gp, &g64);
+  wave_lex_stage(P, bm, rz, tau, fm, spread_rates(P, rz), X, wa, &gp, &g64);
   write_alloc(R == 0 ? cons : opt, o, P.K, tau, fm, gp, wa);
   write_cert_rec(rec + (size_t)o * 2 + R, P.K, tau, fm, gp, g64, wa);
 }
@@ -4238,7 +4285,7 @@ __global__ __launch_bounds__(64) void k_score_lex_wave(DevProblem P, const int8_
   double mine_mm = 0.0, mine_gp = 0.0;
   const int s0 = chunk * kWave;
   const int ns = min(kWave, S - s0);
-  for (int j = 0; j < ns; ++j) {
+  for (int j = 0; j < ns; ++j) {  // (of the stage only the totals are used: spread rates or not)
     const float cs = cap_s[tile * S + s0 + j];
     const float ts = tail_s[tile * S + s0 + j];
     int fm;
@@ -4246,10 +4293,10 @@ __global__ __launch_bounds__(64) void k_score_lex_wave(DevProblem P, const int8_
     double gm, gp;
     Realisation rm{cm, lm, ci.cell, cs, ts};
     const int tm = wave_tau(P, bm, rm, work, &fm);
-    wave_lex_stage(P, bm, rm, tm, fm, X, wa, &g32, &gm);
+    wave_lex_stage(P, bm, rm, tm, fm, false, X, wa, &g32, &gm);
     Realisation rp{cp, lp, ci.cell, cs, ts};
     const int tp = wave_tau(P, bm, rp, work, &fm);
-    wave_lex_stage(P, bm, rp, tp, fm, X, wa, &g32, &gp);
+    wave_lex_stage(P, bm, rp, tp, fm, false, X, wa, &g32, &gp);
     // the binary64 totals are in lane 0
     gm = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(gm)),
                           __builtin_amdgcn_readfirstlane(__double2loint(gm)));
