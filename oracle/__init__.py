@@ -402,8 +402,8 @@ def profile_loop(problem, intervals, truth_cap, truth_tail, cand, cap_s, tail_s,
     candidate left ends undecided (the certificate of its final intervals is
     evaluated first, so a last reveal can still certify) and returns the best
     measured feasible allocation (Algorithm 1's last line): the optimum of its
-    table with every unmeasured cell infeasible (tail +inf) and every measured
-    cell at its measured values; so does a trajectory stopped by the round
+    table with every unmeasured cell infeasible and every measured cell at its
+    measured values; so does a trajectory stopped by the round
     limit.  With
     objective="lex" the certificate and the score are the stage-wise ones
     under the whole objective (certify_lex, score_lex) and A- is that
@@ -499,11 +499,12 @@ def profile_loop(problem, intervals, truth_cap, truth_tail, cand, cap_s, tail_s,
     # A trajectory that ends without a certificate (no unmeasured candidate
     # left, or the round limit) returns Algorithm 1's "best measured feasible
     # allocation": the optimum of the table in which every unmeasured cell is
-    # infeasible and every measured cell takes its measured values.
+    # infeasible (it serves nothing: a tail of +inf would be within an SLO of
+    # +inf) and every measured cell takes its measured values.
     for o in range(O):
         if state[o] == UNDECIDED:
-            masked_tail = np.where(ms[o] != 0, th[o], np.float32(np.inf)).astype(np.float32)
-            final[o] = solve(problem, cl[o], masked_tail, "dp" if objective == "maxmin" else "lex")
+            masked_cap = np.where(ms[o] != 0, cl[o], np.float32(0)).astype(np.float32)
+            final[o] = solve(problem, masked_cap, th[o], "dp" if objective == "maxmin" else "lex")
     tau_truth = np.zeros(O, np.float32)
     tau_oracle = np.zeros(O, np.float32)
     for o in range(O):

@@ -285,8 +285,9 @@ hipError_t launch_loop_count(const LoopDev &L, int32_t O, hipStream_t s);
 hipError_t launch_loop_reveal(const DevProblem &P, const LoopDev &L, const float *truth_cap,
                               const float *truth_tail, const int32_t *cand, int32_t E, int32_t O,
                               int32_t policy, const int32_t *order, hipStream_t s);
-// Overwrites the working tail_lo with the measured-only table (unmeasured
-// cells +inf, measured cells their point tails) for the final solve.
+// Overwrites the working cap_lo and tail_lo with the measured-only table
+// (unmeasured cells serve nothing, measured cells have their point values) for
+// the final solve.
 hipError_t launch_loop_measured_table(const DevProblem &P, const LoopDev &L, int32_t O, hipStream_t s);
 // Copies the returned allocations out (A- of a certified trajectory, meas of
 // one that ended undecided) and evaluates them on the true table.

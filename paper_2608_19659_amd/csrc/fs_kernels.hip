@@ -5332,14 +5332,16 @@ __global__ __launch_bounds__(64) void k_loop_reveal(DevProblem P, LoopDev L, con
 }
 
 // Algorithm 1's last line, the best measured feasible allocation: the
-// table of every trajectory with each unmeasured cell made infeasible (tail
-// +inf, written over the working tail_lo, which the loop no longer needs);
-// measured cells keep their point values.  The solve of (cap_lo, tail_lo)
-// then serves only measured cells.
+// table of every trajectory with each unmeasured cell made infeasible (it
+// serves nothing: no tail is out of bounds for an SLO of +inf), written over
+// the working cap_lo and tail_lo, which the loop no longer needs; measured
+// cells keep their point values.  The solve of (cap_lo, tail_lo) then serves
+// only measured cells.
 __global__ void k_loop_measured_table(LoopDev L, int64_t n) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
-  L.tail_lo[j] = L.measured[j] ? L.tail_hi[j] : __builtin_inff();
+  L.tail_lo[j] = L.tail_hi[j];
+  if (!L.measured[j]) L.cap_lo[j] = 0.0f;
 }
 
 // The returned allocation: A- of a certified trajectory, the best measured

@@ -98,6 +98,25 @@ def test_order_policy_follows_the_order():
         assert list(r.reveals[o][: r.rounds[o]]) == todo[: r.rounds[o]]
 
 
+@pytest.mark.parametrize("objective", ["maxmin", "lex"])
+def test_undecided_allocation_uses_measured_cells_only(objective):
+    """Also where a class has no limit on its tail (an SLO of +inf), which an
+    unmeasured cell's tail of +inf would meet."""
+    w, tc, tt, cs, ts = _loop_inputs("paper-shaped-2class-G16", [0, 1, 2, 3], 8)
+    p = w.problem
+    p = Problem(p.tp, p.levels, p.demand, np.full(2, np.inf, np.float32), p.budget)
+    r = oracle.profile_loop(p, w.intervals, tc, tt, w.cand, cs, ts, eps=-1.0, max_rounds=1, objective=objective)
+    served = 0
+    for o in range(4):
+        assert r.state[o] == oracle.UNDECIDED and r.rounds[o] == 1
+        seen = set(np.nonzero(w.intervals.measured[o])[0]) | {int(w.cand[r.reveals[o][0]])}
+        for i, (t, n) in enumerate(zip(r.final[o].tp_index, r.final[o].replicas)):
+            if n > 0:
+                served += 1
+                assert p.cell(i, t, oracle.bucket(p, i, n)) in seen, (o, i)
+    assert served > 0
+
+
 def test_negative_eps_reveals_everything():
     w, tc, tt, cs, ts = _loop_inputs("paper-shaped-2class-G16", [0, 1], 16)
     r = oracle.profile_loop(w.problem, w.intervals, tc, tt, w.cand, cs, ts, eps=-1.0, n_threads=THREADS)
