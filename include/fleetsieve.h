@@ -423,14 +423,16 @@ typedef struct fs_loop_out {
   float *tau_oracle;    /* [O] optimum of the true table (fs_solve_batch); or NULL           */
 } fs_loop_out;
 
-/* Workspace bytes for fs_profile_loop with these sizes. */
-/* Workspace of fs_profile_loop with FS_OPT_LOOP_REFIT = 1 (the loop's plus
- * the refitted intervals and two clamped copies of the samples). */
-fs_status fs_loop_refit_workspace_size(const fs_problem *p, int32_t n_orders, int32_t n_cand, int32_t n_samples,
-                                       size_t *bytes);
-
+/* Workspace bytes for fs_profile_loop with these sizes, sufficient for either
+ * objective.  With critical floors they include the scorer's tables, which
+ * come last: a workspace without them is accepted and scores by full solves. */
 fs_status fs_loop_workspace_size(const fs_problem *p, int32_t n_orders, int32_t n_cand,
                                  int32_t n_samples, size_t *bytes);
+
+/* The same with FS_OPT_LOOP_REFIT = 1 (the refitted intervals and two clamped
+ * copies of the samples more). */
+fs_status fs_loop_refit_workspace_size(const fs_problem *p, int32_t n_orders, int32_t n_cand, int32_t n_samples,
+                                       size_t *bytes);
 
 /* The profiling loop (Algorithm 1) for n_orders independent trajectories.
  * Trajectory o starts from row o of iv (its initial design; iv is read only,

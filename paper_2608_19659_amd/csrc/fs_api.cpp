@@ -532,7 +532,8 @@ fs_status fs_loop_workspace_size(const fs_problem *p, int32_t n_orders, int32_t 
   fs::DevProblem P;
   fs_status st = make_problem(p, &P);
   if (st != FS_OK) return st;
-  *bytes = fs::loop_layout(P, n_orders, n_cand, n_cand > 0 ? n_samples : 0).total;
+  fs::LoopLayout L = fs::loop_layout(P, n_orders, n_cand, n_cand > 0 ? n_samples : 0);
+  *bytes = fs::place_floor_tables(P, n_orders, n_cand, L.total, &L.score);
   return FS_OK;
 }
 
@@ -544,8 +545,9 @@ fs_status fs_loop_refit_workspace_size(const fs_problem *p, int32_t n_orders, in
   fs_status st = make_problem(p, &P);
   if (st != FS_OK) return st;
   const int32_t S = n_cand > 0 ? n_samples : 0;
-  const size_t base = fs::loop_layout(P, n_orders, n_cand, S).total;
-  *bytes = fs::refit_layout(P, n_orders, n_cand, S, base).total;
+  fs::LoopLayout L = fs::loop_layout(P, n_orders, n_cand, S);
+  const size_t end = fs::refit_layout(P, n_orders, n_cand, S, L.total).total;
+  *bytes = fs::place_floor_tables(P, n_orders, n_cand, end, &L.score);
   return FS_OK;
 }
 
@@ -641,11 +643,14 @@ fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv,
     if (st != FS_OK) return st;
   }
   const int32_t S = (n_cand > 0 && policy == FS_POLICY_SCORE) ? n_samples : 0;
-  const fs::LoopLayout LL = fs::loop_layout(P, n_orders, n_cand, S);
-  if (ctx->score_kernel == 0 && LL.score.floors) kernel = fs::kScoreFloors;
+  fs::LoopLayout LL = fs::loop_layout(P, n_orders, n_cand, S);
   const bool refit = ctx->loop_refit != 0;
   const fs::RefitLayout RL = fs::refit_layout(P, n_orders, n_cand, S, LL.total);
   const size_t need = refit ? RL.total : LL.total;
+  // the exclusion scorer with critical floors where the workspace holds its
+  // tables; a smaller one still scores by full solves
+  const size_t with_floors = fs::place_floor_tables(P, n_orders, n_cand, need, &LL.score);
+  if (ctx->score_kernel == 0 && LL.score.floors && workspace_bytes >= with_floors) kernel = fs::kScoreFloors;
   if (!d_workspace) return fail(FS_ERR_INVALID_ARGUMENT, "workspace is NULL");
   if (workspace_bytes < need)
     return fail(FS_ERR_WORKSPACE_TOO_SMALL, "workspace needs " + std::to_string(need) + " bytes" +
@@ -683,7 +688,7 @@ fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv,
     fs::RefitArgs R{};
     if (refit)
       R = fs::RefitArgs{(float *)(ws + RL.cap_lo), (float *)(ws + RL.tail_lo), (float *)(ws + RL.tail_hi),
-                        (float4 *)(ws + RL.bounds)};
+                        (float4 *)(ws + LL.scores_gp)};
     fs::ScoreArgs iv_args{};
     iv_args.cap_lo = iv.cap_lo; iv_args.cap_hi = iv.cap_hi; iv_args.tail_lo = iv.tail_lo;
     iv_args.tail_hi = iv.tail_hi; iv_args.measured = iv.measured;

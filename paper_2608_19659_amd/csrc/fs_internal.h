@@ -93,6 +93,10 @@ struct WsLayout {
 };
 
 WsLayout ws_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S);
+// Places the exclusion scorer's tables for critical floors in L from offset
+// `at` on, where the problem has them, and returns the end.  They come last in
+// every workspace, so that one without them still serves, by full solves.
+size_t place_floor_tables(const DevProblem &P, int64_t O, int64_t E, size_t at, WsLayout *L);
 
 // Static device scratch of fs_score_candidates_noalloc (FS_NOALLOC_SCRATCH_BYTES
 // in the public header), and its address on the current device.
@@ -206,12 +210,16 @@ struct LexExclRegions {
 LexExclRegions lex_excl_regions(const DevProblem &P, int64_t O, size_t *at);
 
 // Workspace of fs_profile_loop: the scorer's layout, then the loop's own
-// regions (offsets from the workspace start).
+// regions (offsets from the workspace start), without the scorer's tables for
+// critical floors, which come after the refit's regions, if any.
 struct LoopLayout {
   WsLayout score;
   size_t cap_lo, cap_hi, tail_lo, tail_hi, measured, cert_state, cons_obj, cons_tp, cons_rep, cons_fm,
       cons_gp, fin_obj, fin_tp, fin_rep, fin_fm, fin_gp, scores, gap_now, best, running, n_running;
-  size_t scores_gp, part_gp, gap_mm, gap_gp;  // the stage-wise score (whole objective)
+  // the stage-wise score (whole objective).  Rounds of three launches, which
+  // have no such score, keep the candidates' refitted intervals, float4 [O][E],
+  // from scores_gp on (double [O][E], and as much or more in part_gp behind it).
+  size_t scores_gp, part_gp, gap_mm, gap_gp;
   LexExclRegions lex_fast;
   size_t total;
 };
@@ -248,10 +256,10 @@ hipError_t launch_clamp_samples(const DevProblem &P, const int32_t *cand, int32_
                                 const float *tail_s, int32_t O, int32_t S, float *cs_out, float *ts_out,
                                 hipStream_t s);
 // Extra workspace of a loop with the fit step, after LoopLayout::total:
-// refitted cap_lo, tail_lo, tail_hi [O][N], clamped samples [O][E][S] x 2 and
-// the candidates' refitted intervals float4 [O][E].
+// refitted cap_lo, tail_lo, tail_hi [O][N], clamped samples [O][E][S] x 2 (which
+// rounds of three launches leave untouched).
 struct RefitLayout {
-  size_t cap_lo, tail_lo, tail_hi, cap_s, tail_s, bounds, total;
+  size_t cap_lo, tail_lo, tail_hi, cap_s, tail_s, total;
 };
 RefitLayout refit_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S, size_t start);
 LoopDev loop_dev(const LoopLayout &L, uint8_t *ws, int64_t O);

@@ -5920,26 +5920,29 @@ WsLayout ws_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S) {
   L.btab = at; at = align256(at + (excl ? sizeof(int32_t) * (size_t)O * 2 * P.K * P.G : 0));
   L.crec = at; at = align256(at + sizeof(CertRec) * 2 * (size_t)(O > 0 ? O : 1));
   L.total_min = at;
-  // the exclusion scorer with critical floors: both variants' tables
-  L.floors = floor_scorer_supported(P) && E > 0;
-  if (L.floors) {
-    const size_t O2 = (size_t)O * 2, n_thr = (size_t)excl_thresholds(P);
-    auto take = [&](size_t bytes) {
-      const size_t here = at;
-      at = align256(at + bytes);
-      return here;
-    };
-    L.f_btab = take(sizeof(int32_t) * O2 * P.K * P.G);
-    L.f_btab_r = take(sizeof(int32_t) * O2 * P.K * P.G);
-    L.f_cheap = take(sizeof(int32_t) * O2 * P.K);
-    L.f_mopt = take(sizeof(int32_t) * O2 * n_thr);
-    L.f_mopt_r = take(sizeof(int32_t) * O2 * n_thr);
-    L.f_ur = take(sizeof(int2) * (size_t)O * (size_t)E);
-    L.f_base_u = take(sizeof(int32_t) * O2);
-    L.f_base_r = take(sizeof(int32_t) * O2);
-  }
-  L.total = at;
+  L.total = place_floor_tables(P, O, E, at, &L);
   return L;
+}
+
+size_t place_floor_tables(const DevProblem &P, int64_t O, int64_t E, size_t at, WsLayout *L) {
+  L->floors = floor_scorer_supported(P) && E > 0;
+  if (!L->floors) return at;
+  // both variants' tables
+  const size_t O2 = (size_t)O * 2, n_thr = (size_t)excl_thresholds(P);
+  auto take = [&](size_t bytes) {
+    const size_t here = at;
+    at = align256(at + bytes);
+    return here;
+  };
+  L->f_btab = take(sizeof(int32_t) * O2 * P.K * P.G);
+  L->f_btab_r = take(sizeof(int32_t) * O2 * P.K * P.G);
+  L->f_cheap = take(sizeof(int32_t) * O2 * P.K);
+  L->f_mopt = take(sizeof(int32_t) * O2 * n_thr);
+  L->f_mopt_r = take(sizeof(int32_t) * O2 * n_thr);
+  L->f_ur = take(sizeof(int2) * (size_t)O * (size_t)E);
+  L->f_base_u = take(sizeof(int32_t) * O2);
+  L->f_base_r = take(sizeof(int32_t) * O2);
+  return at;
 }
 
 // Blocks of k_setup for the bucket map and for E candidate records.
@@ -6494,7 +6497,7 @@ hipError_t launch_certify(const DevProblem &P, const float *cap_lo, const float 
 LoopLayout loop_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S) {
   LoopLayout L{};
   L.score = ws_layout(P, O, E, S);
-  size_t at = L.score.total;
+  size_t at = L.score.total_min;
   const size_t ON = (size_t)O * P.N, OK = (size_t)O * P.K;
   auto take = [&](size_t bytes) {
     const size_t here = at;
@@ -6545,7 +6548,6 @@ RefitLayout refit_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S, s
   L.tail_hi = take(4 * ON);
   L.cap_s = take(4 * OES);
   L.tail_s = take(4 * OES);
-  L.bounds = take(sizeof(float4) * (size_t)O * (size_t)E);
   L.total = at;
   return L;
 }
@@ -6617,7 +6619,7 @@ LexExclRegions lex_excl_regions(const DevProblem &P, int64_t O, size_t *at) {
 LexScoreLayout lex_score_layout(const DevProblem &P, int64_t O, int64_t E, int64_t S) {
   LexScoreLayout L{};
   L.score = ws_layout(P, O, E, S);
-  size_t at = L.score.total;
+  size_t at = L.score.total_min;  // (no stage of it uses the tables for critical floors)
   auto take = [&](size_t bytes) {
     const size_t here = at;
     at = align256(at + (bytes > 0 ? bytes : 1));
