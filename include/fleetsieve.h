@@ -457,10 +457,12 @@ fs_status fs_loop_refit_workspace_size(const fs_problem *p, int32_t n_orders, in
  * refitted between rounds: the samples d_cap_s, d_tail_s
  * ([n_orders][n_cand][n_samples], drawn inside the initial intervals) stay
  * valid, since a candidate's intervals change only when it is revealed.
- * check_every > 0: every check_every rounds the call waits for the stream
- * and returns early once no trajectory is running (the call then returns
- * with the stream idle); check_every = 0: exactly max_rounds rounds are
- * enqueued without waiting.  Limits as fs_score_candidates; max_rounds in
+ * check_every > 0: every check_every rounds the call waits until the device
+ * has come that far and makes no further rounds once no trajectory is running
+ * (refused with FS_ERR_DEVICE on a stream under capture); check_every = 0:
+ * exactly max_rounds rounds are enqueued without waiting.  Either way the
+ * outputs are valid once the stream reaches the end of the call's work: it may
+ * return with a round and the output kernels still to run.  Limits as fs_score_candidates; max_rounds in
  * [0, 65535]; critical floors are supported. */
 fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv, int32_t n_orders,
                           const float *d_truth_cap, const float *d_truth_tail,

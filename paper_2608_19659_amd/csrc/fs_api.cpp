@@ -660,6 +660,15 @@ fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv,
   if (dg.err != hipSuccess) return hip_fail(dg.err, "hipSetDevice");
   uint8_t *ws = (uint8_t *)d_workspace;
   hipError_t e;
+  // the progress checks (the first after check_every rounds) wait, which a
+  // capture cannot: refused while nothing is enqueued
+  if (check_every > 0 && max_rounds > check_every) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    e = hipStreamIsCapturing(stream, &cap);
+    if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
+    if (cap != hipStreamCaptureStatusNone)
+      return fail(FS_ERR_DEVICE, "check_every > 0 waits for the stream, which is being captured");
+  }
   if (env_validate()) {
     int32_t *flag = (int32_t *)(ws + LL.score.flag);
     const int64_t cells = (int64_t)n_orders * P.N;

@@ -39,3 +39,36 @@ def test_a_class_without_a_tail_limit(env, budget, floors, kernel, lex):  # noqa
         ctx.set_score_kernel(0)
         ctx.set_option(fs.OPT_LOOP_OBJECTIVE, 0)
     assert_loop_equal(g, o, f"G={budget} floors={floors} kernel={kernel} lex={lex}")
+
+
+@pytest.mark.parametrize("floors", [None, [1.0, 0.0]])
+def test_progress_checks_are_refused_under_capture(env, floors):  # noqa: F811
+    """check_every > 0 waits for the stream, which a capture cannot: refused
+    before anything is enqueued, so the capture goes on; check_every = 0, and
+    checks that no round reaches, are captured.  Afterwards the context's loops
+    are what they were."""
+    torch, fs, ctx = env
+    w, p, tc, tt, cs, ts = _inputs("paper-shaped-2class-G16", [0, 1, 2], 16, floors=floors)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    args = (fs.DeviceIntervals.from_host(w.intervals, "cuda:0"), t(tc), t(tt), t(w.cand), t(cs), t(ts))
+    call = lambda n: fs.profile_loop(ctx, p, *args, eps=0.05, max_rounds=8, check_every=n)  # noqa: E731
+    want = call(1)
+    torch.cuda.synchronize()
+    note(f"loop under capture floors={floors}")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        with pytest.raises(fs.FleetSieveError) as e:
+            call(1)
+        got = call(0)
+        late = call(8)
+    assert e.value.status == fs.FS_ERR_DEVICE
+    for _ in range(3):
+        for x in (got.state, got.rounds, got.reveals, got.tau_truth):
+            x.zero_()
+        graph.replay()
+        eager = call(1)
+        torch.cuda.synchronize()
+        for k in ("state", "rounds", "reveals", "tau_truth", "gpu_seconds"):
+            assert torch.equal(getattr(got, k), getattr(want, k)), k
+            assert torch.equal(getattr(late, k), getattr(want, k)), k
+            assert torch.equal(getattr(eager, k), getattr(want, k)), k
