@@ -2599,8 +2599,11 @@ constexpr int kScorerWaves = 4096, kExclMaxWaves = 8, kExclBlocks = 512;
 // of a lane lies wholly below S or wholly past it; every group is fetched by
 // one 16-byte load at an in-bounds address (a group past S reads the tile's
 // last 4 samples, values that are never used), so the loads are unconditional
-// and the compiler's wait counts stay exact.  Otherwise single loads,
-// predicated per sample.
+// and the compiler's wait counts stay exact.  The caller's arrays may start at
+// any float: the load's type says so, and is still one instruction.  Otherwise
+// single loads, predicated per sample.
+typedef float SampleQuad __attribute__((ext_vector_type(4), aligned(4)));
+
 template <int SPL, bool VEC>
 __device__ __forceinline__ void load_chunk(const float *__restrict__ cap_s, const float *__restrict__ tail_s,
                                            size_t tbase, int s_first, int S, bool live, float (&cs)[SPL],
@@ -2609,8 +2612,8 @@ __device__ __forceinline__ void load_chunk(const float *__restrict__ cap_s, cons
 #pragma unroll
     for (int v4 = 0; v4 < SPL / 4; ++v4) {
       const size_t at = tbase + (size_t)min(s_first + 4 * v4, S - 4);
-      const float4 c4 = *reinterpret_cast<const float4 *>(cap_s + at);
-      const float4 l4 = *reinterpret_cast<const float4 *>(tail_s + at);
+      const SampleQuad c4 = *reinterpret_cast<const SampleQuad *>(cap_s + at);
+      const SampleQuad l4 = *reinterpret_cast<const SampleQuad *>(tail_s + at);
       cs[4 * v4 + 0] = c4.x; cs[4 * v4 + 1] = c4.y; cs[4 * v4 + 2] = c4.z; cs[4 * v4 + 3] = c4.w;
       ls[4 * v4 + 0] = l4.x; ls[4 * v4 + 1] = l4.y; ls[4 * v4 + 2] = l4.z; ls[4 * v4 + 3] = l4.w;
     }

@@ -72,3 +72,32 @@ def test_progress_checks_are_refused_under_capture(env, floors):  # noqa: F811
             assert torch.equal(getattr(got, k), getattr(want, k)), k
             assert torch.equal(getattr(late, k), getattr(want, k)), k
             assert torch.equal(getattr(eager, k), getattr(want, k)), k
+
+
+@pytest.mark.parametrize("offset", [1, 2, 3])
+def test_samples_at_any_float(env, offset):  # noqa: F811
+    """Sample arrays that start 4, 8 or 12 bytes past a 16-byte boundary (a
+    multiple of 4 samples, read four at a time), in the score and in loops
+    that clamp them as they are read."""
+    torch, fs, ctx = env
+    w, p, tc, tt, cs, ts = _inputs("paper-shaped-2class-G16", [0, 1, 2, 3], 32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+
+    def shifted(a):
+        buf = torch.empty(a.size + offset, dtype=torch.float32, device="cuda")
+        v = buf[offset:].view(a.shape)
+        v.copy_(t(a))
+        assert v.data_ptr() % 16 == 4 * offset
+        return v
+
+    d, dc, dtc, dtt = fs.DeviceIntervals.from_host(w.intervals, "cuda:0"), t(w.cand), t(tc), t(tt)
+    note(f"samples {4 * offset} bytes past a boundary")
+    a, b = (fs.score_candidates(ctx, p, d, dc, x, y) for x, y in ((t(cs), t(ts)), (shifted(cs), shifted(ts))))
+    torch.cuda.synchronize()
+    assert torch.equal(a.score, b.score) and torch.equal(a.best, b.best)
+    for refit in (False, True):
+        a, b = (fs.profile_loop(ctx, p, d, dtc, dtt, dc, x, y, eps=0.05, max_rounds=6, refit=refit)
+                for x, y in ((t(cs), t(ts)), (shifted(cs), shifted(ts))))
+        torch.cuda.synchronize()
+        for k in ("state", "rounds", "reveals", "tau_truth"):
+            assert torch.equal(getattr(a, k), getattr(b, k)), (refit, k)
