@@ -5848,7 +5848,7 @@ static size_t prep_lds_tables(const DevProblem &P) {
 }
 
 // LDS of the general set-up's work-list block from staged inputs: counters,
-// level ranges, candidates, revealed flags.
+// level ranges, candidates, revealed flags (of the O orders of a run).
 static size_t prep_list_lds(const DevProblem &P, int64_t O, int64_t E) {
   return 4 * (68 + 2 * (size_t)P.K * P.B + 2 * (size_t)E) + (size_t)O * P.N;
 }
@@ -5859,16 +5859,12 @@ constexpr size_t kPrepGeneralLdsLimit = 156 * 1024;
 
 // LDS of the one-block-per-order set-up: the larger of a class block's and
 // the work-list block's.
-static size_t prep_order_lds(const DevProblem &P, int64_t O, int64_t E) {  // O: of the longest list run
+static size_t prep_order_lds(const DevProblem &P, int64_t O, int64_t E) {  // O: of a list run
   const size_t K = P.K, G = P.G, N = P.N, pc = (size_t)P.NT * P.B;
   const size_t nw = 2 * K <= 16 ? 2 * K : K;  // wavefronts with a per-wavefront area
   const size_t cls = 4 * (2 * N + 2 * K * G + (size_t)E + nw * 3 * pc) + ((N + 3) & ~(size_t)3) + K * G;
   const size_t lst = 4 * (68 + 2 * K * (size_t)P.B + 2 * (size_t)E) + (size_t)O * N;
   return cls > lst ? cls : lst;
-}
-
-static bool prep_order_fits(const DevProblem &P, int64_t O, int64_t E) {
-  return P.G <= kPrepOrderMaxG && P.K <= kPrepOrderMaxK && prep_order_lds(P, O, E) <= kPrepLdsLimit;
 }
 
 // Runs of the work list: one block builds about 1,200 entries while a class
@@ -5877,13 +5873,31 @@ static bool prep_order_fits(const DevProblem &P, int64_t O, int64_t E) {
 // 17.4); at most 8, no more than there are orders (every run has at least one)
 // or wavefronts of the scorer's grid.
 constexpr int kListRuns = 8, kListRunTiles = 1200;
-static ListRuns list_runs(const DevProblem &P, const ScoreArgs &a) {
-  // the unstaged list block of the general set-up takes every order
-  const bool staged = (a.setup == 0 && prep_order_fits(P, a.O, a.E)) || prep_list_lds(P, a.O, a.E) <= kPrepGeneralLdsLimit;
-  int64_t n = staged ? ((int64_t)a.O * a.E + kListRunTiles - 1) / kListRunTiles : 1;
-  if (n > kListRuns) n = kListRuns;
-  if (a.waves > 0 && n > a.waves) n = a.waves;
-  return list_runs_of(a.O, n);
+
+// The set-up of a call and the runs of its list: the one-block-per-order
+// set-up where the problem and the LDS of its blocks allow it, else the general
+// one, whose list blocks stage their run where that fits; otherwise one block
+// builds the whole list from global memory.  The LDS of a list block is that
+// of the longest run.  Sized by all orders instead, 600 orders of 128 cells (4
+// classes, G = 64, 64 candidates of 64 samples) gave up the per-order set-up
+// and 1,400 the staging: 96 and 312 us a call, now 27 and 55; 200 orders of 960
+// cells (16 classes, G = 1024) 516, now 497.
+struct ListPlan {
+  ListRuns runs;
+  bool per_order, staged;
+};
+static ListPlan list_plan(const DevProblem &P, const ScoreArgs &a) {
+  const int64_t most = a.waves > 0 && a.waves < kListRuns ? a.waves : kListRuns;
+  int64_t want = ((int64_t)a.O * a.E + kListRunTiles - 1) / kListRunTiles;
+  if (want > most) want = most;
+  ListRuns runs{};
+  if (a.setup == 0 && P.G <= kPrepOrderMaxG && P.K <= kPrepOrderMaxK &&
+      list_runs_staged(a.O, want, most, [&](int per) { return prep_order_lds(P, per, a.E) <= kPrepLdsLimit; }, &runs))
+    return ListPlan{runs, true, true};
+  if (list_runs_staged(a.O, want, most, [&](int per) { return prep_list_lds(P, per, a.E) <= kPrepGeneralLdsLimit; },
+                       &runs))
+    return ListPlan{runs, false, true};
+  return ListPlan{list_runs_of(a.O, 1), false, false};
 }
 
 // Options per (order, realisation): one per (class, TP, r).
@@ -6043,11 +6057,12 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
   int32_t *mopt = (int32_t *)(a.ws + a.L.mopt);
   float *thr = (float *)(a.ws + a.L.thr);
   int4 *list = (int4 *)(a.ws + a.L.list);
-  const ListRuns runs = list_runs(P, a);
+  const ListPlan plan = list_plan(P, a);
+  const ListRuns runs = plan.runs;
   const int32_t n_thr = excl_thresholds(P);
   const int dump = a.tau_dump != nullptr;
   const size_t small = prep_lds_small(P), big = small + prep_lds_tables(P);
-  if (a.setup == 0 && prep_order_fits(P, a.O, a.E)) {
+  if (plan.per_order) {
     const PrepLevels LV = prep_levels(P);
     // compiled for the rank step's table count rounded up to 4, 8 or 16
     // and for at most 4 or 8 TP degrees (loops over them are unrolled)
@@ -6068,10 +6083,10 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
 #undef FS_PREP_ORDER_K
 #undef FS_PREP_ORDER
   } else {
-    // the work-list block reads staged inputs when they fit; tables in
+    // the work-list blocks read staged inputs when they fit; tables in
     // LDS when they fit, else in the workspace
-    const size_t lst = prep_list_lds(P, a.O, a.E);
-    const int staged = lst <= kPrepGeneralLdsLimit;
+    const size_t lst = prep_list_lds(P, runs.per, a.E);
+    const int staged = plan.staged;
     const bool in_lds = big <= kPrepGeneralLdsLimit;
     size_t lds = in_lds ? big : small;
     if (staged && lst > lds) lds = lst;
@@ -6159,7 +6174,7 @@ hipError_t launch_score(const DevProblem &P, const ScoreArgs &a, hipStream_t s) 
     float *thr = (float *)(a.ws + a.L.thr);
     int4 *list = (int4 *)(a.ws + a.L.list);
     const int32_t n_thr = excl_thresholds(P);
-    ListRuns runs = list_runs(P, a);
+    const ListRuns runs = list_plan(P, a).runs;
     hipError_t es = launch_excl_setup(P, a, s);
     if (es != hipSuccess) return es;
     if (a.E == 0) {

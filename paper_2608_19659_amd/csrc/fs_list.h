@@ -24,4 +24,13 @@ constexpr ListRuns list_runs_of(int O, int64_t most) {
   return ListRuns{log, 1 << log, O, (int)((O + (1 << log) - 1) >> log)};
 }
 
+// `want` runs, or more (up to `most`) until a block can stage the longest one:
+// fits(orders).  False where no run fits.
+template <class F>
+constexpr bool list_runs_staged(int O, int64_t want, int64_t most, F fits, ListRuns *runs) {
+  for (*runs = list_runs_of(O, want); !fits(runs->per); *runs = list_runs_of(O, 2 * runs->n))
+    if (2 * runs->n > most || 2 * runs->n > O) return false;
+  return true;
+}
+
 }  // namespace fs

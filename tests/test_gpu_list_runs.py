@@ -6,7 +6,7 @@ import sys
 import numpy as np
 import pytest
 
-from paper_2608_19659_amd.synth import make_workload
+from paper_2608_19659_amd.synth import Intervals, make_workload
 from test_gpu_parity import env, gpu_score  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -15,7 +15,9 @@ pytestmark = pytest.mark.gpu
 def _agree(env, O, E, setup, waves, S=20):  # noqa: F811
     """E candidates: the workload's 48 cells, repeated."""
     torch, fs, ctx = env
-    w = make_workload("paper-shaped-2class-G16", orders=list(range(O)), with_samples=False)
+    w = make_workload("paper-shaped-2class-G16", orders=list(range(min(O, 200))), with_samples=False)
+    if O > 200:  # the orders repeat
+        w.intervals = Intervals(*(np.resize(a, (O, a.shape[1])) for a in vars(w.intervals).values()))
     cand = np.resize(w.cand, E)
     rng = np.random.default_rng(O)
     lo, hi = w.intervals.cap_lo[:, cand, None], w.intervals.cap_hi[:, cand, None]
@@ -46,3 +48,12 @@ def test_list_runs_agree_with_full_solves(env, O, setup, waves):  # noqa: F811
 @pytest.mark.parametrize("setup,waves", [(0, 0), (0, 5), (1, 0)])
 def test_few_orders_with_many_candidates(env, O, E, setup, waves):  # noqa: F811
     _agree(env, O, E, setup, waves)
+
+
+@pytest.mark.parametrize("O,E", [(1300, 48), (1300, 3), (3400, 48), (3400, 2), (28000, 2)])
+@pytest.mark.parametrize("setup", [0, 1])
+def test_many_orders(env, O, E, setup):  # noqa: F811
+    """Revealed flags of all orders past what a list block stages (60 KB beside
+    the per-order set-up, 156 KB beside the general one): more runs than the
+    tiles ask for, and at 28,000 orders the list from global memory."""
+    _agree(env, O, E, setup, 0, S=4)
