@@ -695,9 +695,9 @@ fs_status fs_profile_loop(fs_context *ctx, const fs_problem *p, fs_intervals iv,
   const bool score = policy == FS_POLICY_SCORE && n_cand > 0;
   if (!lex && (kernel == 3 || !score) && ctx->score_kernel != 1 && fs::loop_fast_supported(P)) {
     fs::RefitArgs R{};
-    if (refit)
+    if (refit)  // (the candidates' intervals are the scorer's; without samples there is no room for them)
       R = fs::RefitArgs{(float *)(ws + RL.cap_lo), (float *)(ws + RL.tail_lo), (float *)(ws + RL.tail_hi),
-                        (float4 *)(ws + LL.scores_gp)};
+                        score ? (float4 *)(ws + LL.scores_gp) : nullptr};
     fs::ScoreArgs iv_args{};
     iv_args.cap_lo = iv.cap_lo; iv_args.cap_hi = iv.cap_hi; iv_args.tail_lo = iv.tail_lo;
     iv_args.tail_hi = iv.tail_hi; iv_args.measured = iv.measured;

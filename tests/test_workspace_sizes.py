@@ -85,3 +85,36 @@ def test_calls_with_the_former_sizes(env, case, lex):  # noqa: F811
                 np.testing.assert_array_equal(got[k], want[k], err_msg=f"{name} {k}")
     finally:
         ctx.set_option(fs.OPT_LOOP_OBJECTIVE, 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("E", [24, 5000, 16384])
+def test_fixed_order_loops_keep_no_candidate_intervals(env, E):  # noqa: F811
+    """A refitting loop with a fixed reveal order has no samples, so its
+    workspace has no room for the scorer's copy of the candidates' intervals
+    (16 bytes each; the candidates repeat): nothing is written past it, and the
+    loop is the general path's."""
+    _, _, ctx = env
+    p = _problem(2, 16, [1, 2, 4, 8], 3, 0)
+    iv, cells, cs, ts = _random_intervals_and_samples(p, 2, 1, seed=5)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    rng = np.random.default_rng(E)
+    order = t(np.stack([rng.permutation(E) for _ in range(2)]).astype(np.int32))
+    d, cand = fs.DeviceIntervals.from_host(iv, "cuda:0"), t(np.resize(cells, E))
+    tc, tt = t((iv.cap_lo + iv.cap_hi) * np.float32(0.5)), t((iv.tail_lo + iv.tail_hi) * np.float32(0.5))
+    call = lambda ws: _host(fs.profile_loop(  # noqa: E731
+        ctx, p, d, tc, tt, cand, t(cs), t(ts), eps=-1.0, policy=fs.POLICY_ORDER, order=order, max_rounds=30, workspace=ws,
+        refit=True))
+    size = fs.loop_refit_workspace_size(p, 2, E, 0)
+    print(f"[gpu] fixed-order refit loop E={E} workspace={size}", file=sys.stderr, flush=True)
+    buf = torch.full((size + (1 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+    got = call(buf[:size])
+    torch.cuda.synchronize()
+    assert bool((buf[size:] == 0xA5).all()), "written past the workspace"
+    ctx.set_score_kernel(1)
+    try:
+        want = call(None)
+    finally:
+        ctx.set_score_kernel(0)
+    for k in want:
+        np.testing.assert_array_equal(got[k], want[k], err_msg=k)
