@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import oracle
-from paper_2608_19659_amd.synth import Problem
+from paper_2608_19659_amd.synth import Intervals, Problem
 from test_gpu_loop import _inputs, assert_loop_equal, env, gpu_loop  # noqa: F401 (env is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -101,3 +101,60 @@ def test_samples_at_any_float(env, offset):  # noqa: F811
         torch.cuda.synchronize()
         for k in ("state", "rounds", "reveals", "tau_truth"):
             assert torch.equal(getattr(a, k), getattr(b, k)), (refit, k)
+
+
+TP4, TP5, TP8 = [1, 2, 4, 8], [1, 2, 3, 4, 6], [1, 2, 3, 4, 5, 6, 7, 8]
+
+# K, G, TP degrees, levels, candidates, samples, rounds, refit
+ROUNDS = [
+    # more than 16 partials a tile: the pick is the finalize's
+    (2, 16, TP4, 3, 5, 8196, 2, False), (2, 16, TP4, 3, 5, 8193, 2, True),
+    # one, two, five and six scoring wavefronts, the last with a second turn
+    (2, 16, TP4, 3, 128, 4, 6, False), (2, 16, TP4, 3, 129, 4, 6, True), (2, 16, TP4, 3, 600, 3, 6, False),
+    (2, 16, TP4, 3, 900, 3, 6, True),
+    # samples clamped as they are read, one at a time and four at a time
+    (4, 64, TP4, 4, 64, 33, 8, True), (4, 64, TP4, 4, 64, 36, 8, True),
+    # the class and TP counts the kernels are compiled for, at their limits
+    (4, 30, TP5, 3, 60, 6, 8, True), (4, 30, TP8, 3, 96, 6, 8, False), (5, 31, TP4, 3, 60, 6, 8, True),
+    (8, 64, TP4, 3, 96, 6, 8, False), (8, 40, TP8, 2, 128, 5, 6, True), (9, 37, TP4, 3, 108, 6, 6, True),
+    (16, 64, TP4, 2, 128, 5, 6, True), (12, 64, TP5, 2, 120, 5, 6, False), (16, 64, TP8, 2, 256, 4, 4, True),
+]
+
+
+def rounds_case(K, G, tp, levels, E, S, seed):
+    """Six trajectories (a third of the cells measured) of a problem whose
+    classes want about half of what G / K GPUs serve each, E candidates (cells,
+    repeated if there are fewer), samples and a truth inside the intervals."""
+    rng = np.random.default_rng(seed)
+    O, n_tp = 6, len(tp)
+    demand = (0.5 * G / K * rng.uniform(0.6, 1.4, K)).astype(np.float32)
+    p = Problem(tp=tp, levels=demand.max() * np.float32(0.5) ** np.arange(levels - 1, -1, -1, dtype=np.float32),
+                demand=demand, slo=np.full(K, 30.0, np.float32), budget=G)
+    shape = (O, K, n_tp, levels)
+    mid = rng.uniform(0.5, 1.1, shape) * np.asarray(tp)[:, None]
+    tail = rng.uniform(10.0, 32.0, shape)
+    meas = (rng.random((O, p.n_cells)) < 0.33).astype(np.uint8)
+    width = np.where(meas.reshape(shape) != 0, 0.0, rng.uniform(0.05, 0.6, shape))
+    flat = lambda a: np.ascontiguousarray(a.reshape(O, -1).astype(np.float32))  # noqa: E731
+    iv = Intervals(flat(mid * (1 - width)), flat(mid * (1 + width)), flat(tail * (1 - 0.5 * width)),
+                   flat(tail * (1 + 0.5 * width)), meas)
+    cand = np.resize(rng.permutation(p.n_cells), E).astype(np.int32)
+    inside = lambda lo, hi, u: (lo + (hi - lo) * u.astype(np.float32)).astype(np.float32)  # noqa: E731
+    u, v = rng.random((2, O, E, S)), rng.random((2, O, p.n_cells))
+    cs = inside(iv.cap_lo[:, cand, None], iv.cap_hi[:, cand, None], u[0])
+    ts = inside(iv.tail_lo[:, cand, None], iv.tail_hi[:, cand, None], u[1])
+    return p, iv, cand, cs, ts, inside(iv.cap_lo, iv.cap_hi, v[0]), inside(iv.tail_lo, iv.tail_hi, v[1])
+
+
+@pytest.mark.parametrize("case", ROUNDS, ids=lambda c: f"{c[0]}x{c[1]}-tp{len(c[2])}-E{c[4]}-S{c[5]}-refit{int(c[7])}")
+def test_rounds_of_three_launches(env, case, monkeypatch):  # noqa: F811
+    """Every way a round picks, clamps and is compiled, against the oracle."""
+    torch, fs, ctx = env
+    K, G, tp, levels, E, S, rounds, refit = case
+    p, iv, cand, cs, ts, tc, tt = rounds_case(K, G, tp, levels, E, S, seed=100 + K * G + E)
+    note(f"loop rounds K={K} G={G} tp={tp} E={E} S={S} refit={refit}")
+    o = oracle.profile_loop(p, iv, tc, tt, cand, cs, ts, eps=0.0, max_rounds=rounds, n_threads=8, refit=refit)
+    assert (o.rounds > 1).any()  # picks that follow a reveal
+    loop = fs.profile_loop
+    monkeypatch.setattr(fs, "profile_loop", lambda *a, **k: loop(*a, refit=refit, **k))
+    assert_loop_equal(gpu_loop(env, p, iv, tc, tt, cand, cs, ts, 0.0, 0, max_rounds=rounds), o, str(case))
