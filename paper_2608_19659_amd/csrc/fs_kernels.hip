@@ -1892,8 +1892,6 @@ __global__ __launch_bounds__(kThreads) void k_prep(DevProblem P, const float *__
   const size_t off = (size_t)o * N;
   const float *gcap = (R == 0 ? cap_lo : cap_hi) + off;
   const float *gtail = (R == 0 ? tail_hi : tail_lo) + off;
-  int top = 1;
-  while (2 * top <= G) top <<= 1;  // 2 * top > G >= g + 1
 
   // --- stage the cells; each thread's first candidate is read now
   for (int c = tid; c < N; c += nth) {
@@ -4390,56 +4388,6 @@ __host__ __device__ inline size_t lex_score_lds(int nbmax, int rmax) {
   return sizeof(int) * (2 * (size_t)nbmax + 2 * (size_t)rmax);
 }
 
-// Bitonic sort of n2 = M x kLexPrepThreads keys (M = 1 or 2) held in
-// registers: thread t holds positions M t .. M t + M - 1.  A stage pairs
-// position p with p ^ stride; the lower one keeps the minimum when the run
-// of length size it lies in ascends ((p & size) == 0), else the maximum.
-// Within a wavefront (stride / M < 64) the partner's key comes by a lane
-// shuffle, one round trip per stage with no LDS write or barrier (DPP row
-// moves for the short distances measured slower); the stages across
-// wavefronts go through keys (LDS) between block barriers.
-// On return keys holds the sorted keys (block-synchronised).
-template <int M>
-__device__ __forceinline__ void bitonic_regs(int *keys, int n2, int tid) {
-  int v[M];
-#pragma unroll
-  for (int j = 0; j < M; ++j) v[j] = keys[M * tid + j];
-  for (int size = 2; size <= n2; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      if (stride < M) {  // M = 2, stride 1: both positions in this thread
-        const bool up = ((M * tid) & size) == 0;
-        const int a = v[0], b = v[M - 1];
-        v[0] = up ? min(a, b) : max(a, b);
-        v[M - 1] = up ? max(a, b) : min(a, b);
-      } else if (stride / M < kWave) {
-#pragma unroll
-        for (int j = 0; j < M; ++j) {
-          const int p = M * tid + j;
-          const int w = __shfl_xor(v[j], stride / M, kWave);
-          const bool keep_min = ((p & stride) == 0) == ((p & size) == 0);
-          v[j] = keep_min ? min(v[j], w) : max(v[j], w);
-        }
-      } else {
-        __syncthreads();  // earlier reads of keys are done
-#pragma unroll
-        for (int j = 0; j < M; ++j) keys[M * tid + j] = v[j];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < M; ++j) {
-          const int p = M * tid + j;
-          const int w = keys[p ^ stride];
-          const bool keep_min = ((p & stride) == 0) == ((p & size) == 0);
-          v[j] = keep_min ? min(v[j], w) : max(v[j], w);
-        }
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < M; ++j) keys[M * tid + j] = v[j];
-  __syncthreads();
-}
-
 // Per (realisation R, order o), one block of kLexPrepThreads threads: every
 // option of every class (ratio bits, -1 when no load level holds it; served
 // rate) to opt_out, and the sorted distinct ratios, 0 always among them, to
@@ -4557,35 +4505,29 @@ __device__ void lex_breaks_block(const DevProblem &P, int R, int o, const float 
   } else {
     for (int q = m + tid; q < ns; q += kLexPrepThreads) lex_keys[q] = q == m ? 0 : q == m + 1 && ones ? one : INT_MAX;
     __syncthreads();
-    if (ns == kLexPrepThreads) {
-      bitonic_regs<1>(lex_keys, ns, tid);
-    } else if (ns == 2 * kLexPrepThreads) {
-      bitonic_regs<2>(lex_keys, ns, tid);
-    } else {
-      // Bitonic sort in LDS.  A stage of stride at most 64 pairs keys inside
-      // aligned runs of 128, and one wavefront handles every pair of a run (the
-      // 64 pair indices of a wavefront map to one run), so such a stage only
-      // waits for its own wavefront's writes, unless the stage before it
-      // crossed runs.
-      int prev = ns;
-      for (int size = 2; size <= ns; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-          if (stride > kWave || prev > kWave) __syncthreads();
-          else wave_lds_fence();
-          prev = stride;
-          for (int idx = tid; idx < (ns >> 1); idx += kLexPrepThreads) {
-            const int lo = ((idx & ~(stride - 1)) << 1) | (idx & (stride - 1)), hi = lo + stride;
-            const int a = lex_keys[lo], c = lex_keys[hi];
-            const bool up = (lo & size) == 0;
-            if ((a > c) == up) {
-              lex_keys[lo] = c;
-              lex_keys[hi] = a;
-            }
+    // Bitonic sort in LDS (of 1,024 keys or more).  A stage of stride at most
+    // 64 pairs keys inside aligned runs of 128, and one wavefront handles every
+    // pair of a run (the 64 pair indices of a wavefront map to one run), so such
+    // a stage only waits for its own wavefront's writes, unless the stage before
+    // it crossed runs.
+    int prev = ns;
+    for (int size = 2; size <= ns; size <<= 1) {
+      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+        if (stride > kWave || prev > kWave) __syncthreads();
+        else wave_lds_fence();
+        prev = stride;
+        for (int idx = tid; idx < (ns >> 1); idx += kLexPrepThreads) {
+          const int lo = ((idx & ~(stride - 1)) << 1) | (idx & (stride - 1)), hi = lo + stride;
+          const int a = lex_keys[lo], c = lex_keys[hi];
+          const bool up = (lo & size) == 0;
+          if ((a > c) == up) {
+            lex_keys[lo] = c;
+            lex_keys[hi] = a;
           }
         }
       }
-      __syncthreads();
     }
+    __syncthreads();
   }
   // thread t owns keys [t seg, (t + 1) seg): count its first occurrences,
   // then an exclusive count over the threads places them
