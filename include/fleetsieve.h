@@ -143,8 +143,8 @@ typedef enum fs_option {
    * levels 1-2, the max-min gap and score, as fs_certify and
    * fs_score_candidates) or FS_OBJECTIVE_LEXICOGRAPHIC (the whole objective:
    * the stage-wise certificate of fs_certify_lex and the stage-wise score of
-   * fs_score_candidates_lex, which solves every scenario in full;
-   * FS_ERR_UNSUPPORTED where that does not fit). */
+   * fs_score_candidates_lex; FS_ERR_UNSUPPORTED where the whole objective
+   * does not fit, see fs_solve_batch_lex). */
   FS_OPT_LOOP_OBJECTIVE = 7,
   /* 1: fs_profile_loop starts every round with Algorithm 1's fit step,
    * fs_refit_intervals of each trajectory's initial intervals with its
@@ -165,7 +165,8 @@ typedef enum fs_option {
 typedef enum fs_objective { FS_OBJECTIVE_MAXMIN = 0, FS_OBJECTIVE_LEXICOGRAPHIC = 1 } fs_objective;
 
 /* Creates a context bound to HIP device `hip_device` (with a stream and two
- * events of its own, used inside fs_score_candidates_lex).  One context per
+ * events of its own: fs_score_candidates_lex forks and joins by them, and
+ * fs_profile_loop waits on one for its progress count).  One context per
  * host thread; a context is not thread-safe. */
 fs_status fs_context_create(int hip_device, fs_context **out);
 void fs_context_destroy(fs_context *ctx);

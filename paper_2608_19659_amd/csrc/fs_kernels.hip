@@ -5330,8 +5330,10 @@ __global__ void k_loop_output(DevProblem P, LoopDev L, AllocOut meas, const int8
 // All of it is latency: staging 2.9 us (the scores beside it), reveal 0.8,
 // refit 2.0, solver tables 0.9, solve 0.8, allocation and state 0.8 on 4
 // classes at G = 64 with the fit step, 11.1 us traced; 7.5 us on 2 classes
-// without.  Refit loop of 16 trajectories, 36 rounds: 3,456 -> 1,156 us;
-// 200 trajectories of 2 classes, 16 rounds: 614 -> 310 us.
+// without.  Loop calls against nine or ten launches a round: 16 trajectories
+// of 4 classes with the fit step, the longest of 36 reveals (37 rounds
+// enqueued): 2,985 -> 988 us, 26.7 a round, 24 of it in the three kernels; 200
+// trajectories of 2 classes, the longest of 15 (17 enqueued): 816 -> 403 us.
 // ---------------------------------------------------------------------------
 // Where a round's reveal comes from: nothing scored yet; the scores of this
 // block's tiles (at most 16 partials each); best, already found; the fixed
@@ -5812,8 +5814,10 @@ static size_t prep_order_lds(const DevProblem &P, int64_t O, int64_t E) {  // O:
 // Runs of the work list: one block builds about 1,200 entries while a class
 // block of the set-up runs (2 classes at G = 16 over 200 orders and 48
 // candidates: the call took 17.4 us, with 2,400 entries a block 18.4, with 600
-// 17.4); at most 8, no more than there are orders (every run has at least one)
-// or wavefronts of the scorer's grid.
+// 17.4; 3 classes at G = 32 over 100 orders and 60 candidates 15.8, with 600
+// 15.9, with 2,400 16.5; from 4 classes on, where the class blocks take longer,
+// 600 to 2,400 are level); at most 8, no more than there are orders (every run
+// has at least one) or wavefronts of the scorer's grid.
 constexpr int kListRuns = 8, kListRunTiles = 1200;
 
 // The set-up of a call and the runs of its list: the one-block-per-order
@@ -6073,7 +6077,9 @@ static hipError_t launch_excl_setup(const DevProblem &P, const ScoreArgs &a, hip
 // Samples per lane of the exclusion scorer: a chunk of 512 samples, or of 256
 // where that holds a tile's samples (16 classes over 4 orders with 256
 // samples: the call took 38.2 us with half of each wavefront idle, 36.1 with
-// 256).  Chunks of 1024 leave a block fewer items to share out: with 8 classes
+// 256; 4 classes over 16 orders with 128 16.5 and 15.8; 2 classes over 200
+// orders with 256 17.0 and 16.0; 8 classes at G = 256 over 64 31.7 and 30.0).
+// Chunks of 1024 leave a block fewer items to share out: with 8 classes
 // at G = 256 (64 orders, 256 candidates, 4096 samples) the call took 50.8 us
 // with 512 and 52.6 with 1024, which allow three wavefronts per SIMD only.
 static int excl_spl(const ScoreArgs &a) {
@@ -6259,8 +6265,14 @@ static unsigned reg_solve_grid(int64_t n, int threads) {
 // The table solver for budgets past the register solver's.  Four wavefronts
 // of a block solve apart while that leaves three blocks a CU (8 classes at G =
 // 256: 80 us, together 96; 4 at G = 96: 134 and 266); 12 classes at G = 500
-// take 67 us together and 149 apart.  Where a CU holds a single block, it has
-// eight wavefronts.
+// take 67 us together and 149 apart.  Either side of that line the two are
+// close (8 classes: 89 apart and 87 together at 47 KB of LDS for four, 76 and 91
+// at 50; 4 classes: 75 and 76 at 47, 81 and 62 at 53; 12 classes: 104 and 106
+// at 47, 104 and 102 at 51; 16 classes: 124 and 119 at 44, 129 and 134 at 49).
+// Where a CU holds a single block, it has eight wavefronts (16 classes at G =
+// 1024, 84 KB: 96 us, with four 144); with one realisation in 16 KB or less eight
+// lose (8 classes at G = 384: 115 and 72), in 44 KB and more they win already (16
+// classes at G = 512: 63 and 83).
 constexpr size_t kWideAlone = 48 * 1024;
 constexpr size_t kWideLarge = 72 * 1024;
 
